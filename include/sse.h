@@ -136,8 +136,12 @@ int sse_abi_version(void);
 const char* sse_last_error(void);
 
 /*
- * Bytes of workspace a call needs.  op = 0 for sse_forward with the given
- * precision, 1 for sse_backward and sse_backward_signed with every gradient
+ * Bytes of workspace for a call.  op = 0 for sse_forward with the given
+ * precision (at most 256 bytes are required; the rest, for SSE_FP64, holds the
+ * momentum transform of G, up to 4 GiB of it at a time or the energies that one
+ * tile meets, whichever is larger: with a smaller workspace the call transforms G
+ * in slabs of energies that fit, or as it reads it, slower and with the same
+ * results bit for bit), 1 for sse_backward and sse_backward_signed with every gradient
  * (enough for either; a call without ddH needs less, see sse_backward), 2 for
  * sse_combine_d (precision ignored for 1 and 2).
  */
@@ -159,8 +163,12 @@ int sse_effective_flops(const sse_dims* dims, double* f_eff);
  * over (qz, w, +/-) in fp64.  Sigma is fully overwritten.  The matrix-core
  * shapes (norb, nkz = nqz, nw, nb) are (10, 7, 10, 4), (10, 7, 10, 3) and
  * (4, 3, 2, 4) for every precision, and (12, 7, 10, 4) for SSE_FP64 and
- * SSE_FP32; other shapes take SSE_FP64 only, on a direct vector-ALU kernel
- * (any other precision: SSE_ERR_PRECISION).
+ * SSE_FP32; other shapes take SSE_FP64 only (any other precision:
+ * SSE_ERR_PRECISION).  SSE_FP64 sums over the momenta in their discrete Fourier
+ * transform on every shape, except for problems of at most 1024 output blocks
+ * (nkz * ne * na) and nkz = 1, which sum the terms as they stand (integer-valued
+ * inputs then give exact integers), and for shapes whose window of 2 nw energies
+ * does not fit the LDS, which take a slow direct kernel.
  */
 int sse_forward(const sse_dims* dims, const double* G, const double* D, const double* dH,
                 const int32_t* nbr, double alpha_re, double alpha_im, int precision,
@@ -178,9 +186,9 @@ int sse_forward(const sse_dims* dims, const double* G, const double* D, const do
  * -w_m (G at E + w), both in D's layout [nqz][nw][na][nb][3][3]; how Dm is
  * obtained (for instance from a lesser/greater symmetry of D) is the caller's.
  * With Dm == Dp (the same pointer) this is sse_forward, in one pass.
- * Otherwise the matrix-core shapes run one pass per table (the E - w terms
- * write Sigma, the E + w terms add to it: twice the work of sse_forward); the
- * other shapes take both tables in one fp64 pass.  Other arguments, layouts,
+ * SSE_FP64 takes both tables in one pass; the other precisions, and SSE_FP64 for
+ * small problems on the matrix-core shapes, run one pass per table (the E - w terms
+ * write Sigma, the E + w terms add to it: twice the work of sse_forward).  Other arguments, layouts,
  * precisions, workspace and errors as for sse_forward; Sigma must not overlap
  * an input.
  */
@@ -201,9 +209,8 @@ int sse_forward_signed(const sse_dims* dims, const double* G, const double* Dp, 
  * dHba [na][nb][3][norb][norb] complex holds grad_j H_ba for the pair (a, b =
  * nbr[a,n]) (the layout of dH); NULL means the Hermitian reading dHba[a,n,j] =
  * dH[a,n,j]^H, which makes this call sse_forward_signed.  Every precision runs
- * on the matrix-core shapes with norb 10 or 4 (the fp64 kernel then works on
- * energy blocks of four, whose LDS holds the second table); at norb 12 and on
- * other shapes a stored dHba takes fp64 only, on the direct kernel.  Other
+ * on the matrix-core shapes with norb 10 or 4; at norb 12 and on other shapes a
+ * stored dHba takes fp64 only.  Other
  * arguments, layouts, workspace and errors as for sse_forward_signed.
  */
 int sse_forward_ex(const sse_dims* dims, const double* G, const double* Dp, const double* Dm, const double* dH,

@@ -54,6 +54,7 @@ bool count_ok(std::initializer_list<int64_t> xs) {
 }
 
 constexpr int64_t kMaxNorb = 32;
+constexpr size_t kMinWorkspace = 256;  // what every op takes; sse_check_nbr's status word
 
 int check_dims(const sse_dims* d) {
     if (!d) return fail(SSE_ERR_NULL, "dims is NULL");
@@ -106,7 +107,11 @@ int sse_workspace_bytes(const sse_dims* dims, int precision, int backward, size_
     if (!bytes) return fail(SSE_ERR_NULL, "bytes is NULL");
     if (backward == 0 && !precision_known(precision)) return fail(SSE_ERR_PRECISION, "unknown precision %d", precision);
     if (backward < 0 || backward > 2) return fail(SSE_ERR_DIMS, "op must be 0 (forward), 1 (backward) or 2 (combine_d)");
-    size_t ws = 256;  // status flag of sse_check_nbr
+    size_t ws = kMinWorkspace;
+    if (backward == 0 && precision == SSE_FP64) {
+        const size_t b = sse::fwd_kspace_workspace(sse::to_dims(*dims));
+        if (b > ws) ws = b;
+    }
     if (backward == 1) {
         const size_t b = sse::bwd_workspace_bytes(sse::to_dims(*dims));
         if (b > ws) ws = b;
@@ -146,15 +151,18 @@ int forward_impl(const sse_dims* dims, const double* G, const double* Dp, const 
     if ((precision == SSE_FP16 || precision == SSE_FP16_UNSCALED) && Dm != Dp)
         return fail(SSE_ERR_PRECISION, "precision %d (single-term fp16) is built for one coefficient table (Dm == Dp) only",
                     precision);
-    size_t need = 0;
-    sse_workspace_bytes(dims, precision, 0, &need);
-    if (need > 0 && (workspace == nullptr || workspace_bytes < need))
-        return fail(SSE_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+    if (workspace == nullptr || workspace_bytes < kMinWorkspace)
+        return fail(SSE_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", kMinWorkspace, workspace_bytes);
     const sse::Dims d = sse::to_dims(*dims);
     const sse::cd alpha{alpha_re, alpha_im};
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipError_t e;
-    if (sse::fwd_mfma_supports(d, precision, dHba != nullptr)) {
+    const bool small = d.nkz * d.ne * d.na <= sse::kDirectBlocks;
+    const bool mfma = sse::fwd_mfma_supports(d, precision, dHba != nullptr);
+    if (precision == SSE_FP64 && !(small && mfma) && sse::fwd_kspace_supported(d, Dm != Dp)) {
+        e = sse::launch_fwd_kspace(d, G, Dp, Dm, dH, dHba, nbr, alpha, Sigma, !small && d.nkz > 1, workspace,
+                                   workspace_bytes, s);
+    } else if (mfma) {
         if (Dm == Dp) {
             e = sse::launch_fwd_mfma(d, precision, G, Dp, dH, dHba, nbr, alpha, Sigma, s);
         } else {

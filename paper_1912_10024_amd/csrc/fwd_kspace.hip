@@ -1,0 +1,322 @@
+// fp64 Sigma (Eq. 3) in the momentum transform (kspace.h), any shape.
+//
+// transform_kernel writes hat G, atom by atom, into the workspace (a slab of
+// energies at a time where the workspace is smaller than G), then one workgroup per
+// (atom, transformed momentum, tile of eb energies) sums hat Sigma.  Per edge and
+// per chunk of rc rows of the neighbour's blocks:
+//   load   rows r0 .. r0+rc of hat G[E, b] for the eb + 2 nw energies the tile meets;
+//   for j in 0..2:
+//     right  H_j = rows . grad_j H^H            (lane = a row, grad H in scalar registers)
+//     filter U_i += sum_w D_ij[w] (H_j[E-w] + H_j[E+w])   (lane = an entry, 4 energies)
+//   left   Sigma[E] += sum_i A_i[:, rows] . U_i  (lane = (energy, column), sums in registers)
+// The rows of a block do not meet before the last step, so a chunk of them is all
+// that LDS holds; U_i stays in registers through the three directions and takes
+// the place of the rows in LDS for the last step.  inverse_kernel transforms the
+// output back in place.
+//
+// SRC = kTrans transforms while it loads (Nkz loads per entry, the same sums): for a
+// workspace without room.  DIRECT takes the sum over source momenta as it stands
+// (a loop over k' around the steps, Nkz times the work): every product and sum
+// is then one of Eq. 3's own, so integer-valued inputs give exact results.
+// Small problems and Nkz = 1 run it.
+#include <algorithm>
+
+#include "kspace.h"
+#include "sse_kernels.h"
+
+namespace sse {
+
+namespace {
+
+constexpr int kThreads = 256, kWaves = kThreads / 64;
+constexpr size_t kLdsMax = 160 * 1024;
+
+struct Tile {
+    int eb, rc;  // energies and rows of a workgroup's tile
+    int ncb;     // passes of the products over norb columns
+    ks::Div by_n, by_ncb, by_row[2];  // norb, ncb, entries of a chunk of rows (the last one may be shorter)
+    int rows;    // complex entries of one row buffer
+    int body;    // of both, or of U_i
+    size_t lds;
+};
+
+Tile make_tile(const Dims& d, int eb, int rc, int cb, bool two) {
+    const int n = (int)d.norb, tail = n % rc ? n % rc : rc;
+    Tile t{eb, rc, (n + cb - 1) / cb, ks::Div(n), ks::Div((n + cb - 1) / cb), {ks::Div(rc * n), ks::Div(tail * n)}, 0, 0, 0};
+    const int64_t rows = (eb + 2 * d.nw) * rc * ks::row_len(n);
+    const int64_t body = std::max(2 * rows, (int64_t)eb * 3 * rc * n);
+    const int64_t all = body + (two ? 18 : 9) * d.nw + d.nkz + 1;
+    t.lds = all < (1 << 20) ? sizeof(cd) * (size_t)all : (size_t)1 << 30;
+    t.rows = (int)std::min<int64_t>(rows, 1 << 28);
+    t.body = (int)std::min<int64_t>(body, 1 << 28);
+    return t;
+}
+
+}  // namespace
+
+// CB columns per pass of the products, MT passes of the left product per wave
+template <int SRC, bool DIRECT, bool TWO, bool HBA, int CB, int MT>
+__global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const double* __restrict__ G, int64_t g_atom,
+                                                                 int64_t g_kst, int64_t g_est, int slab,
+                                                                 const double* __restrict__ Dp,
+                                                                 const double* __restrict__ Dm,
+                                                                 const double* __restrict__ A,
+                                                                 const double* __restrict__ B,
+                                                                 const int32_t* __restrict__ nbr, cd alpha, Tile tile,
+                                                                 int e_lo, int e_hi, int64_t a0, double* __restrict__ S) {
+    extern __shared__ __align__(16) double smem[];
+    const int n = (int)d.norb, nkz = (int)d.nkz, nw = (int)d.nw, ne = (int)d.ne, nb = (int)d.nb;
+    const int np = ks::row_len(n), eb = tile.eb;
+    cd* sG = reinterpret_cast<cd*>(smem);  // rows of G [ew][r][np]
+    cd* sX = sG + tile.rows;               // H_j, same layout
+    cd* sU = sG;                           // U_i [e][i][r][c], after the last filter
+    cd* sD = sG + tile.body;               // [j][w][i]
+    cd* sDm = sD + 9 * nw;                 // (TWO)
+    cd* tw = sD + (TWO ? 18 : 9) * nw;
+    int* bad = reinterpret_cast<int*>(tw + nkz);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the workgroups of an atom get ids on one XCD, the tiles of a momentum next to
+    // each other: their windows of energies overlap
+    const int ntile = (e_hi - e_lo + eb - 1) / eb;
+    const int per = nkz * ntile, s = blockIdx.x >> 3;
+    const int64_t a = a0 + s / per * 8 + (blockIdx.x & 7);
+    if (a >= d.na) return;  // uniform, before any barrier
+    const int rem = s % per, kt = rem / ntile, e0 = e_lo + (rem - kt * ntile) * eb;
+    const int e_n = e_hi - e0 < eb ? e_hi - e0 : eb;  // energies of this tile
+    const int ewin = eb + 2 * nw;
+    const int nn = n * n;
+    const int64_t edges = d.na * d.nb;
+
+    if constexpr (!DIRECT) ks::stage_twiddles(tw, nkz, tid, kThreads);
+    // this thread's entries of the output tile: columns (e, c) number l and l + 64 of
+    // pass t's 128, rows rr .. rr + CB - 1
+    const int ncol = e_n * n, nrb = tile.ncb;
+    const int tasks = (ncol + 127) / 128 * nrb;
+    cd sum[MT][2][CB];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int r = 0; r < CB; ++r) sum[t][0][r] = sum[t][1][r] = cd{0.0, 0.0};
+    for (int m = 0; m < nb; ++m) {
+        const int64_t edge = a * nb + m;
+        const int32_t b = __builtin_amdgcn_readfirstlane(nbr[edge]);
+        if (b < 0 || b >= d.na) continue;
+        const ks::Source src{G + 2 * b * g_atom, g_kst, g_est};
+        const ks::uptr Ar = ks::uniform_ptr((HBA ? B : A) + 6 * edge * nn);
+        const ks::uptr Al = ks::uniform_ptr(A + 6 * edge * nn);
+        for (int r0 = 0; r0 < n; r0 += tile.rc) {
+            const int rc = n - r0 < tile.rc ? n - r0 : tile.rc;
+            // filter lanes: entry el = (r, c) of the chunk, energies 4 eq .. 4 eq + 3
+            const ks::Div by_row = tile.by_row[rc < tile.rc];
+            const int nel = rc * n, eq = by_row.quot(tid), el = tid - eq * nel;
+            const bool f_lane = eq * ks::kEBlk < eb;
+            const int f_r = tile.by_n.quot(el);
+            const int f_off = f_lane ? (eq * ks::kEBlk * rc + f_r) * np + el - f_r * n : 0;
+            cd acc[3][ks::kEBlk];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int e = 0; e < ks::kEBlk; ++e) acc[i][e] = cd{0.0, 0.0};
+            for (int kp = 0; kp < (DIRECT ? nkz : 1); ++kp) {
+                const int kg = DIRECT ? kp : kt;                                      // momentum of the blocks
+                const int kd = DIRECT ? (kt - kp < 0 ? kt - kp + nkz : kt - kp) : kt;  // of the coefficients
+                const bool coeff = DIRECT || r0 == 0;  // this step's coefficients are new ones
+                __syncthreads();                       // the buffers of the step before are read
+                if (coeff && tid == 0) *bad = 0;
+                ks::load_rows<kThreads, SRC, false>(src, tw, nkz, kg, e0 - nw - slab, ewin, ne - slab, r0, rc, n,
+                                                      by_row, tile.by_n, sG, tid);
+                if (coeff) {
+                    __syncthreads();  // *bad is cleared
+                    ks::stage_coeff<kThreads, !DIRECT, false>(Dp, tw, nkz, kd, nw, ne, edges, edge, sD, bad, tid);
+                    if constexpr (TWO)
+                        ks::stage_coeff<kThreads, !DIRECT, false>(Dm, tw, nkz, kd, nw, ne, edges, edge, sDm, bad, tid);
+                }
+                __syncthreads();
+                const bool finite = *bad == 0;
+                for (int j = 0; j < 3; ++j) {
+                    ks::right_product<kWaves, 2, CB, !HBA>(sG, Ar + 2 * j * nn, ewin * rc, n, tile.ncb, tile.by_ncb,
+                                                              (wave + j) % kWaves, lane, [&](int row) { return sX + row * np; });
+                    __syncthreads();
+                    if (f_lane) {
+                        const cd* Dl = sD + 3 * j * nw;
+                        const cd* Dh = (TWO ? sDm : sD) + 3 * j * nw;
+                        if (finite)
+                            ks::filter<TWO>(acc, sX + f_off, rc * np, nw, Dl, Dh);
+                        else
+                            ks::filter_masked<TWO>(acc, sX + f_off, rc * np, nw, Dl, Dh, e0 + eq * ks::kEBlk, ne);
+                    }
+                    __syncthreads();
+                }
+            }
+            if (f_lane) {
+#pragma unroll
+                for (int e = 0; e < ks::kEBlk; ++e)
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) ks::st(sU + ((eq * ks::kEBlk + e) * 3 + i) * nel + el, acc[i][e]);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int ti = 0; ti < MT; ++ti) {
+                const int t = wave + ti * kWaves;
+                if (t >= tasks) continue;
+                const int tc = tile.by_ncb.quot(t), col = tc * 128 + lane, rr = (t - tc * nrb) * CB;
+                const int x0 = col < ncol ? col : 0, x1 = col + 64 < ncol ? col + 64 : 0;
+                const int ea = tile.by_n.quot(x0), eb_ = tile.by_n.quot(x1);
+                int off[CB];
+#pragma unroll
+                for (int r = 0; r < CB; ++r) off[r] = 2 * ((rr + r < n ? rr + r : n - 1) * n + r0);
+                const cd* ua = sU + ea * 3 * nel + x0 - ea * n;
+                const cd* ub = sU + eb_ * 3 * nel + x1 - eb_ * n;
+                ks::uniform_product<2, CB, false>(sum[ti], 3 * rc, off, [&](int k, const cd* (&p)[2], ks::uptr& f) {
+                    const int i = k >= 2 * rc ? 2 : k >= rc ? 1 : 0;
+                    p[0] = ua + k * n;
+                    p[1] = ub + k * n;
+                    f = Al + 2 * (i * nn + k - i * rc);
+                });
+            }
+        }
+    }
+    double* So = S + 2 * (((int64_t)kt * ne + e0) * d.na + a) * nn;
+#pragma unroll
+    for (int ti = 0; ti < MT; ++ti) {
+        const int t = wave + ti * kWaves;
+        if (t >= tasks) continue;
+        const int tc = tile.by_ncb.quot(t), rr = (t - tc * nrb) * CB;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int col = tc * 128 + 64 * h + lane;
+            if (col >= ncol) continue;
+            const int e = tile.by_n.quot(col), c = col - e * n;
+            double* o = So + 2 * (e * d.na * nn + c);
+#pragma unroll
+            for (int r = 0; r < CB; ++r)
+                if (rr + r < n) cstore(o, (rr + r) * n, DIRECT ? cmul(alpha, sum[ti][h][r]) : sum[ti][h][r]);
+        }
+    }
+}
+
+// The tile with the least time per energy under the quantisation of each step:
+// cycles of the busiest wave, 16 per complex multiply-add, and the number of
+// rounds of workgroups on the chip.
+static bool pick_tile(const Dims& d, bool two, int cb, int mt, int cus, Tile* best, double* best_cost) {
+    const int n = (int)d.norb;
+    bool found = false;
+    auto up = [](double a, double b) { return (double)(int64_t)((a + b - 1) / b); };
+    for (int rc = 1; rc <= n; ++rc)
+        for (int eb = ks::kEBlk; eb <= 128 && eb / ks::kEBlk * rc * n <= kThreads; eb += ks::kEBlk) {
+            if (eb > ks::kEBlk && eb - ks::kEBlk >= d.ne) break;
+            const Tile t = make_tile(d, eb, rc, cb, two);
+            if (t.lds > kLdsMax) break;
+            const double win = eb + 2.0 * d.nw, lanes = (double)(eb / ks::kEBlk * rc * n);
+            const double passes = up((double)eb * n, 128) * t.ncb;
+            if (passes > mt * kWaves) break;
+            const int occ = t.lds <= kLdsMax / 2 ? 2 : 1;
+            // vector instructions of a workgroup per chunk of rows
+            const double right = 3 * up(win * rc, 128) * t.ncb * (n * cb * 8.4 + 60);
+            const double filt = up(lanes, 64) * 3.0 * d.nw * ks::kEBlk * (two ? 24 : 14);
+            const double left = passes * (3 * rc * cb * 8.4 + 70);
+            const double chunk = right + filt + left + kWaves * (2000 + 25 * up(win * rc * n, kThreads));
+            const double groups = up(up((double)d.ne, eb) * (double)(d.nkz * d.na), cus * occ);
+            const double cost = groups * up(n, rc) * chunk * (occ == 2 ? 2 : 1.5);
+            if (!found || cost < *best_cost) {
+                *best_cost = cost;
+                *best = t;
+                found = true;
+            }
+        }
+    return found;
+}
+
+// columns per pass: the number that divides norb with the least left over
+static void passes_of(int n, int* cb, int* mt) {
+    const int c6 = (n + 5) / 6 * 6, c5 = (n + 4) / 5 * 5, c4 = (n + 3) / 4 * 4;
+    *cb = c4 <= c5 && c4 <= c6 ? 4 : c5 <= c6 ? 5 : 6;
+    *mt = 2;
+}
+
+bool fwd_kspace_supported(const Dims& d, bool two) {
+    if (d.norb > 32 || d.nkz > 128 || d.ne >= (int64_t(1) << 28) || d.nw >= (1 << 14) || d.nb >= (1 << 28)) return false;
+    return make_tile(d, ks::kEBlk, 1, 5, two).lds <= kLdsMax;
+}
+
+// bytes of workspace that hold hat G: all of it, or a slab of energies of at most
+// kSlabBytes (at least the energies one tile meets)
+static int64_t hat_energy_bytes(const Dims& d) { return 16 * d.nkz * d.na * d.norb * d.norb; }
+size_t fwd_kspace_workspace(const Dims& d) {
+    constexpr int64_t kSlabBytes = int64_t(4) << 30;
+    if (d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks || !fwd_kspace_supported(d, true)) return 0;
+    const int64_t per = hat_energy_bytes(d), want = std::max(kSlabBytes / per, 64 + 4 * d.nw);
+    return (size_t)(per * std::min(d.ne, want));
+}
+
+template <int SRC, bool DIRECT, bool TWO, bool HBA, int CB, int MT>
+static hipError_t launch_cb(const Dims& d, const double* G, int64_t g_atom, int64_t g_kst, int64_t g_est, int slab,
+                            const double* Dp, const double* Dm, const double* A, const double* B, const int32_t* nbr,
+                            cd alpha, const Tile& t, int e_lo, int e_hi, double* S, hipStream_t stream) {
+    auto kern = fwd_kspace_kernel<SRC, DIRECT, TWO, HBA, CB, MT>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds);
+    if (e != hipSuccess) return e;
+    const int64_t per = d.nkz * ((e_hi - e_lo + t.eb - 1) / t.eb);
+    if (per > (int64_t(1) << 26)) return hipErrorInvalidValue;
+    const int64_t na8 = (d.na + 7) / 8 * 8, step = std::max<int64_t>(8, ((int64_t)1 << 30) / per / 8 * 8);
+    for (int64_t a0 = 0; a0 < na8; a0 += step)
+        hipLaunchKernelGGL(kern, dim3((unsigned)(std::min(step, na8 - a0) * per)), dim3(kThreads), t.lds, stream, d, G, g_atom,
+                           g_kst, g_est, slab, Dp, Dm, A, B, nbr, alpha, t, e_lo, e_hi, a0, S);
+    return hipGetLastError();
+}
+
+template <int SRC, bool DIRECT, bool TWO, bool HBA, class... Args>
+static hipError_t launch_shape(int cb, Args... args) {
+    if (cb == 4) return launch_cb<SRC, DIRECT, TWO, HBA, 4, 2>(args...);
+    if (cb == 5) return launch_cb<SRC, DIRECT, TWO, HBA, 5, 2>(args...);
+    return launch_cb<SRC, DIRECT, TWO, HBA, 6, 2>(args...);
+}
+
+template <int SRC, bool DIRECT, class... Args>
+static hipError_t launch_tables(bool two, bool hba, int cb, Args... args) {
+    if (two) return hba ? launch_shape<SRC, DIRECT, true, true>(cb, args...) : launch_shape<SRC, DIRECT, true, false>(cb, args...);
+    return hba ? launch_shape<SRC, DIRECT, false, true>(cb, args...) : launch_shape<SRC, DIRECT, false, false>(cb, args...);
+}
+
+hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
+                             const double* B, const int32_t* nbr, cd alpha, double* S, bool transform, void* ws,
+                             size_t ws_bytes, hipStream_t stream) {
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    const bool two = Dm != Dp, hba = B != nullptr;
+    const int64_t nn = d.norb * d.norb, ne = d.ne;
+    int cb, mt;
+    passes_of((int)d.norb, &cb, &mt);
+    Tile t{};
+    double cost = 0.0;
+    if (!pick_tile(d, two, cb, mt, cus, &t, &cost)) return hipErrorInvalidValue;
+    const int64_t g_atom = d.gs * nn, g_est = d.na * g_atom, g_kst = ne * g_est;
+    if (!transform)
+        return launch_tables<ks::kDirect, true>(two, hba, cb, d, G, g_atom, g_kst, g_est, 0, Dp, Dm, A, B, nbr, alpha, t, 0,
+                                                (int)ne, S, stream);
+    const int64_t room = (int64_t)(ws_bytes / (size_t)hat_energy_bytes(d));  // energies
+    if (room >= std::min(ne, (int64_t)t.eb + 2 * d.nw)) {
+        // slabs of whole tiles; a slab's transform takes the 2 nw energies around it
+        const int64_t step = room >= ne ? ne : (room - 2 * d.nw) / t.eb * t.eb;
+        double* hat = static_cast<double*>(ws);
+        for (int64_t lo = 0; lo < ne; lo += step) {
+            const int64_t hi = std::min(ne, lo + step);
+            const int64_t first = std::max<int64_t>(0, lo - d.nw), n_e = std::min(ne, hi + d.nw) - first;
+            e = launch_transform((int)d.nkz, first, n_e, d.na, nn, g_atom, g_est, g_kst, G, hat, stream);
+            if (e != hipSuccess) return e;
+            e = launch_tables<ks::kDirect, false>(two, hba, cb, d, hat, n_e * nn, d.na * n_e * nn, nn, (int)first, Dp, Dm, A,
+                                                  B, nbr, alpha, t, (int)lo, (int)hi, S, stream);
+            if (e != hipSuccess) return e;
+        }
+    } else {
+        e = launch_tables<ks::kTrans, false>(two, hba, cb, d, G, g_atom, g_kst, g_est, 0, Dp, Dm, A, B, nbr, alpha, t, 0,
+                                             (int)ne, S, stream);
+        if (e != hipSuccess) return e;
+    }
+    return launch_inverse((int)d.nkz, ne * d.na, nn, nn, cd{alpha.re / (double)d.nkz, alpha.im / (double)d.nkz}, S, stream);
+}
+
+}  // namespace sse

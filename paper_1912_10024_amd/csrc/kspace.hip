@@ -1,0 +1,132 @@
+// The momentum transforms around the kernels of kspace.h.  Both are bound by
+// memory: one read and one write of the array.
+#include "kspace.h"
+#include "sse_kernels.h"
+
+namespace sse {
+
+// hat[m][x][e - first][nn] = sum_k src[k][e][x][nn] exp(-2 pi i k m / nkz) for e in
+// [first, first + n_e), x < na: a block's entries stay together, its momenta and
+// energies come next to each other.  The sum runs over k as in ks::load_rows, bit
+// for bit.  NK = 0: any nkz, the thread's inputs in LDS.
+template <int NK>
+__global__ __launch_bounds__(256) void transform_kernel(int nkz, int64_t first, int64_t n_e, int64_t na, int64_t nn,
+                                                        int64_t atom, int64_t est, int64_t kst,
+                                                        const double* __restrict__ src, double* __restrict__ hat) {
+    extern __shared__ __align__(16) double smem[];
+    cd* tw = reinterpret_cast<cd*>(smem);
+    const int tid = threadIdx.x, threads = blockDim.x;
+    ks::stage_twiddles(tw, nkz, tid, threads);
+    __syncthreads();
+    cd* col = tw + nkz + tid;
+    const int64_t total = n_e * na * nn, out_kst = na * n_e * nn;
+    for (int64_t x = blockIdx.x * (int64_t)threads + tid; x < total; x += (int64_t)gridDim.x * threads) {
+        const int64_t blk = x / nn, rc = x - blk * nn, e = blk / na, a = blk - e * na;
+        const double* p = src + 2 * ((first + e) * est + a * atom + rc);
+        double* o = hat + 2 * ((a * n_e + e) * nn + rc);
+        if constexpr (NK > 0) {
+            cd v[NK > 0 ? NK : 1];
+#pragma unroll
+            for (int k = 0; k < NK; ++k) v[k] = cload(p, k * kst);
+#pragma unroll
+            for (int m = 0; m < NK; ++m) {
+                cd s{0.0, 0.0};
+#pragma unroll
+                for (int k = 0; k < NK; ++k) cfma(s, v[k], ks::ld(tw + k * m % NK));
+                cstore(o, m * out_kst, s);
+            }
+        } else {
+            for (int k = 0; k < nkz; ++k) ks::st(col + k * threads, cload(p, k * kst));
+            for (int m = 0; m < nkz; ++m) {
+                cd s{0.0, 0.0};
+                int j = 0;
+                for (int k = 0; k < nkz; ++k) {
+                    cfma(s, ks::ld(col + k * threads), ks::ld(tw + j));
+                    j += m;
+                    j -= j >= nkz ? nkz : 0;
+                }
+                cstore(o, m * out_kst, s);
+            }
+        }
+    }
+}
+
+// X[k] = scale * sum_m X[m] exp(+2 pi i k m / nkz), in place over the leading axis of
+// [nkz][blocks][bs] (the first nn entries of every block of bs)
+template <int NK>
+__global__ __launch_bounds__(256) void inverse_kernel(int nkz, int64_t blocks, int64_t nn, int64_t bs, cd scale,
+                                                      double* __restrict__ X) {
+    extern __shared__ __align__(16) double smem[];
+    cd* tw = reinterpret_cast<cd*>(smem);
+    const int tid = threadIdx.x, threads = blockDim.x;
+    ks::stage_twiddles(tw, nkz, tid, threads);
+    __syncthreads();
+    cd* col = tw + nkz + tid;
+    const int64_t total = blocks * nn, kst = blocks * bs;
+    for (int64_t x = blockIdx.x * (int64_t)threads + tid; x < total; x += (int64_t)gridDim.x * threads) {
+        const int64_t blk = x / nn;
+        double* p = X + 2 * (blk * bs + x - blk * nn);
+        if constexpr (NK > 0) {
+            cd v[NK > 0 ? NK : 1];
+#pragma unroll
+            for (int m = 0; m < NK; ++m) v[m] = cload(p, m * kst);
+#pragma unroll
+            for (int k = 0; k < NK; ++k) {
+                cd s = v[0];
+#pragma unroll
+                for (int m = 1; m < NK; ++m) cfma_conj(s, v[m], ks::ld(tw + k * m % NK));
+                cstore(p, k * kst, cmul(scale, s));
+            }
+        } else {
+            for (int m = 0; m < nkz; ++m) ks::st(col + m * threads, cload(p, m * kst));
+            for (int k = 0; k < nkz; ++k) {
+                cd s{0.0, 0.0};
+                int j = 0;
+                for (int m = 0; m < nkz; ++m) {
+                    cfma_conj(s, ks::ld(col + m * threads), ks::ld(tw + j));
+                    j += k;
+                    j -= j >= nkz ? nkz : 0;
+                }
+                cstore(p, k * kst, cmul(scale, s));
+            }
+        }
+    }
+}
+
+template <class K, class... Args>
+static hipError_t launch_transform_kernel(K kern, bool any, int nkz, int64_t total, hipStream_t stream, Args... args) {
+    const int threads = any ? 64 : 256;
+    const size_t lds = sizeof(cd) * (size_t)(nkz + (any ? nkz * threads : 0));
+    if (any) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    const int64_t want = (total + threads - 1) / threads;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(want < 65536 ? want : 65536)), dim3(threads), lds, stream, nkz, args...);
+    return hipGetLastError();
+}
+
+#define SSE_BY_NKZ(KERN, TOTAL, ...)                                                                  \
+    switch (nkz) {                                                                                    \
+        case 2: return launch_transform_kernel(KERN<2>, false, nkz, TOTAL, stream, __VA_ARGS__);      \
+        case 3: return launch_transform_kernel(KERN<3>, false, nkz, TOTAL, stream, __VA_ARGS__);      \
+        case 4: return launch_transform_kernel(KERN<4>, false, nkz, TOTAL, stream, __VA_ARGS__);      \
+        case 5: return launch_transform_kernel(KERN<5>, false, nkz, TOTAL, stream, __VA_ARGS__);      \
+        case 6: return launch_transform_kernel(KERN<6>, false, nkz, TOTAL, stream, __VA_ARGS__);      \
+        case 7: return launch_transform_kernel(KERN<7>, false, nkz, TOTAL, stream, __VA_ARGS__);      \
+        default: return launch_transform_kernel(KERN<0>, true, nkz, TOTAL, stream, __VA_ARGS__);      \
+    }
+
+hipError_t launch_transform(int nkz, int64_t first, int64_t n_e, int64_t na, int64_t nn, int64_t atom, int64_t est,
+                            int64_t kst, const double* src, double* hat, hipStream_t stream) {
+    SSE_BY_NKZ(transform_kernel, n_e * na * nn, first, n_e, na, nn, atom, est, kst, src, hat)
+}
+
+hipError_t launch_inverse(int nkz, int64_t blocks, int64_t nn, int64_t bs, cd scale, double* X, hipStream_t stream) {
+    SSE_BY_NKZ(inverse_kernel, blocks * nn, blocks, nn, bs, scale, X)
+}
+
+#undef SSE_BY_NKZ
+
+}  // namespace sse

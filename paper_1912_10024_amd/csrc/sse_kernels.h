@@ -19,6 +19,27 @@ bool generic_supported(const Dims& d);
 hipError_t launch_fwd_generic(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
                               const double* B, const int32_t* nbr, cd alpha, double* S, hipStream_t stream);
 
+// the momentum transform of a block array into hat[m][atom][energy][nn] for the
+// energies [first, first + n_e) (atom, est, kst: complex elements of src between
+// atoms, energies and momenta), and its inverse in place over the leading axis of
+// [nkz][blocks][bs] (the first nn entries of every block), times scale
+hipError_t launch_transform(int nkz, int64_t first, int64_t n_e, int64_t na, int64_t nn, int64_t atom, int64_t est,
+                            int64_t kst, const double* src, double* hat, hipStream_t stream);
+hipError_t launch_inverse(int nkz, int64_t blocks, int64_t nn, int64_t bs, cd scale, double* X, hipStream_t stream);
+
+// fp64 forward in the momentum transform (kspace.h), any shape whose tile fits the
+// LDS; transform = false sums over the source momenta as they stand.  Problems of
+// at most kDirectBlocks output blocks (four per compute unit) keep the direct sum:
+// their time is latency, and sums of integer-valued inputs stay exact.  ws holds the
+// transform of G, or a slab of it, where ws_bytes has room (fwd_kspace_workspace);
+// otherwise every workgroup transforms what it loads
+constexpr int64_t kDirectBlocks = 1024;
+bool fwd_kspace_supported(const Dims& d, bool two);
+size_t fwd_kspace_workspace(const Dims& d);
+hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
+                             const double* B, const int32_t* nbr, cd alpha, double* S, bool transform, void* ws,
+                             size_t ws_bytes, hipStream_t stream);
+
 // matrix-core forward (fp64 or fp32 operands; the split 16-bit forms go to
 // launch_fwd_h16) for the shapes it is
 // instantiated for; flags selects the energy branches (kBranchMinus,
