@@ -170,8 +170,8 @@ def kernel_source_hash(sources) -> str:
 
 FWD_SOURCES = ("fwd_mfma.hip", "fwd_common.h", "sse_common.h")
 H16_SOURCES = ("fwd_h16.hip", "fwd_common.h", "sse_common.h")
-PSE_SOURCES = ("pse.hip", "sse_common.h")
-BWD_SOURCES = ("bwd_mfma.hip", "sse_common.h")
+PSE_SOURCES = ("pse_kspace.hip", "kspace.h", "sse_common.h")
+BWD_SOURCES = ("bwd_kspace.hip", "fwd_kspace.hip", "kspace.h", "sse_common.h")
 
 
 def recorded_traffic(record, sources):

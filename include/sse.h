@@ -148,6 +148,14 @@ const char* sse_last_error(void);
 int sse_workspace_bytes(const sse_dims* dims, int precision, int op, size_t* bytes);
 
 /*
+ * Bytes of workspace with which a call is fastest, beyond what it requires: op = 1
+ * for sse_backward and sse_backward_signed (at least sse_workspace_bytes(dims, 0, 1)),
+ * 3 for sse_phonon_forward_ws (0: none is used).  The space holds the momentum
+ * transforms of the call's inputs.
+ */
+int sse_fast_workspace_bytes(const sse_dims* dims, int op, size_t* bytes);
+
+/*
  * Effective flops of one sse_forward call (one component), the paper's
  * computation-model count for the regrouped form: one left product
  * grad_i H . G per (kz', E', a, n, i) plus one product per
@@ -234,14 +242,13 @@ int sse_forward_ex(const sse_dims* dims, const double* G, const double* Dp, cons
  * 256) and, if ddH is wanted, S shares of every edge's dL/d(dH)
  * (16 * S * na * nb * 3 * norb^2 bytes, rounded up to 256), added in share
  * order, so results are bitwise reproducible: S = ceil(ne / 32) (one per range
- * of 32 energies) on the matrix-core shape (norb = 10, nkz = nqz = 7, nw = 10),
- * S = nkz (one per momentum) otherwise and in sse_backward_signed.  If dD is
- * wanted on the shapes of the matrix-core phonon kernel (norb = 10, nkz = nqz
- * = 7, nw = 10, nb = 4 or 3), it also holds a copy of dSigma with the atom
- * axis first (16 * na * nkz * ne * norb^2 bytes, the size of dSigma), from
- * which the dD kernel reads its shifted blocks of both energy branches (the
- * same sums in the same order as from dSigma itself; sse_backward_signed
- * reads one branch per launch from dSigma in place and needs no copy).  A smaller workspace than this call uses is
+ * of 32 energies) on the shape (norb = 10, nkz = nqz = 7, nw = 10), S = nkz (one
+ * per momentum) otherwise and in sse_backward_signed.  Room beyond these holds the
+ * momentum transforms of dSigma and of G (16 * na * nkz * ne * norb^2 bytes each),
+ * whichever fit (sse_fast_workspace_bytes); without them every kernel transforms what it
+ * reads, slower and with the same results bit for bit.  On the shapes (norb = 10,
+ * nkz = nqz = 7, nw = 10, nb = 4 or 3) a call of sse_backward that wants dD requires
+ * room for the transform of dSigma.  A smaller workspace than this call requires is
  * refused with SSE_ERR_WORKSPACE.  An entry of nbr outside [0, na) has no
  * terms: its ddH block is zero.
  */
@@ -275,8 +282,8 @@ int sse_backward_signed(const sse_dims* dims, const double* G, const double* Dp,
  * shares 16 * S * Na * Nb * 3 * Norb^2 more, S = ceil(NE / 32)
  * on the matrix-core shape (Norb = 10, Nkz = Nqz = 7, Nw = 10), S = Nkz otherwise
  * (at Nkz = 7, Norb = 10, Nb = 4, NE <= 224: about 500 atoms with ddH, about
- * 2.1 million without it).  dD reads dSigma in place (no atom-major copy:
- * slower than sse_backward's, the same sums).  Every call on one GPU uses that GPU's
+ * 2.1 million without it).  The momentum transforms of dSigma and G are kept in the array
+ * where they fit, else taken as they are read (slower, the same sums).  Every call on one GPU uses that GPU's
  * array (the current device's): calls that overlap on one GPU race.  The
  * kernels rewrite every part of the array they read, so no clearing is needed
  * between calls.  Other arguments and errors as for sse_backward.
@@ -333,12 +340,22 @@ int sse_combine_d(const sse_dims* dims, const double* Dfull, const int32_t* nbr,
  * phonon frequency w sits on the electron energy grid, w = 1..Nw; the momentum
  * grids coincide (Nqz = Nkz) and kz + qz wraps around.
  * Output Pi [nqz][nw][na][nb][3][3] complex (the layout of D), fully
- * overwritten.  fp64 throughout; no workspace.  Gs and Go may alias.
+ * overwritten.  fp64 throughout; no workspace (sse_phonon_forward_ws with one is faster).  Gs and Go may alias.
  * Errors as for sse_forward (SSE_ERR_DIMS also when no kernel covers the
  * shape: norb^2 > 640 or nqz * nw > 512 outside the matrix-core shape).
  */
 int sse_phonon_forward(const sse_dims* dims, const double* Gs, const double* Go, const double* dH,
                        const int32_t* nbr, double beta_re, double beta_im, double* Pi, void* stream);
+
+/*
+ * sse_phonon_forward with a workspace (NULL: none) of any size, used for the
+ * momentum transforms of Gs and Go: all of them with
+ * sse_fast_workspace_bytes(dims, 3) bytes, slabs of energies with less (whose sums
+ * are added in order: equal to the other sizes' up to rounding).
+ */
+int sse_phonon_forward_ws(const sse_dims* dims, const double* Gs, const double* Go, const double* dH,
+                          const int32_t* nbr, double beta_re, double beta_im, double* Pi, void* workspace,
+                          size_t workspace_bytes, void* stream);
 
 /*
  * Synchronous check of a neighbour table: returns SSE_OK if every entry lies

@@ -124,6 +124,16 @@ int sse_workspace_bytes(const sse_dims* dims, int precision, int backward, size_
     return ok();
 }
 
+int sse_fast_workspace_bytes(const sse_dims* dims, int op, size_t* bytes) {
+    int rc = check_dims(dims);
+    if (rc) return rc;
+    if (!bytes) return fail(SSE_ERR_NULL, "bytes is NULL");
+    if (op != 1 && op != 3) return fail(SSE_ERR_DIMS, "op must be 1 (backward) or 3 (phonon)");
+    const sse::Dims d = sse::to_dims(*dims);
+    *bytes = op == 3 ? sse::corr_kspace_workspace(d) : sse::bwd_fast_workspace_bytes(d);
+    return ok();
+}
+
 int sse_effective_flops(const sse_dims* dims, double* f_eff) {
     int rc = check_dims(dims);
     if (rc) return rc;
@@ -214,19 +224,19 @@ namespace {
 int backward_impl(const sse_dims* dims, const double* G, const double* Dp, const double* Dm, const double* dH,
                   const int32_t* nbr, double alpha_re, double alpha_im, const double* dSigma, double* dG,
                   double* dDp, double* dDm, double* ddH, void* workspace, size_t workspace_bytes, void* stream,
-                  bool signed_form, bool copy_g) {
+                  bool signed_form, bool with_hat) {
     int rc = check_dims(dims);
     if (rc) return rc;
     if (!G || !Dp || !Dm || !dH || !nbr || !dSigma) return fail(SSE_ERR_NULL, "an input pointer is NULL");
     const sse::Dims d = sse::to_dims(*dims);
     if (!sse::bwd_supported(d)) return fail(SSE_ERR_DIMS, "no adjoint kernel for these dims");
     // what this call uses (sse_workspace_bytes covers every gradient of either form)
-    const size_t need = sse::bwd_workspace_bytes_for(d, signed_form, ddH != nullptr, dDp || dDm, copy_g);
+    const size_t need = sse::bwd_workspace_bytes_for(d, signed_form, ddH != nullptr, with_hat && (dDp || dDm));
     if (workspace == nullptr || workspace_bytes < need)
         return fail(SSE_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
     if (!dG && !dDp && !dDm && !ddH) return ok();
     hipError_t e = sse::launch_bwd(d, G, Dp, Dm, dH, nbr, sse::cd{alpha_re, alpha_im}, dSigma, dG, dDp, dDm, ddH,
-                                   workspace, reinterpret_cast<hipStream_t>(stream), signed_form, copy_g);
+                                   workspace, workspace_bytes, reinterpret_cast<hipStream_t>(stream), signed_form);
     if (e != hipSuccess) return hip_fail(e, "backward launch");
     return ok();
 }
@@ -236,9 +246,9 @@ int backward_impl(const sse_dims* dims, const double* G, const double* Dp, const
 namespace sse {
 int backward_one_table(const sse_dims* dims, const double* G, const double* D, const double* dH, const int32_t* nbr,
                        double alpha_re, double alpha_im, const double* dSigma, double* dG, double* dD, double* ddH,
-                       void* workspace, size_t workspace_bytes, void* stream, bool copy_g) {
+                       void* workspace, size_t workspace_bytes, void* stream, bool with_hat) {
     return backward_impl(dims, G, D, D, dH, nbr, alpha_re, alpha_im, dSigma, dG, dD, nullptr, ddH, workspace,
-                         workspace_bytes, stream, false, copy_g);
+                         workspace_bytes, stream, false, with_hat);
 }
 }  // namespace sse
 
@@ -299,13 +309,26 @@ int sse_combine_d(const sse_dims* dims, const double* Dfull, const int32_t* nbr,
 
 int sse_phonon_forward(const sse_dims* dims, const double* Gs, const double* Go, const double* dH, const int32_t* nbr,
                        double beta_re, double beta_im, double* Pi, void* stream) {
+    return sse_phonon_forward_ws(dims, Gs, Go, dH, nbr, beta_re, beta_im, Pi, nullptr, 0, stream);
+}
+
+int sse_phonon_forward_ws(const sse_dims* dims, const double* Gs, const double* Go, const double* dH, const int32_t* nbr,
+                          double beta_re, double beta_im, double* Pi, void* workspace, size_t workspace_bytes,
+                          void* stream) {
     int rc = check_dims(dims);
     if (rc) return rc;
     if (!Gs || !Go || !dH || !nbr || !Pi) return fail(SSE_ERR_NULL, "a tensor pointer is NULL");
     const sse::Dims d = sse::to_dims(*dims);
-    if (!sse::pse_mfma_specialised(d) && !sse::pse_generic_supported(d))
-        return fail(SSE_ERR_DIMS, "no phonon self-energy kernel for these dims");
-    hipError_t e = sse::launch_pse(d, Gs, Go, dH, nbr, sse::cd{beta_re, beta_im}, Pi, reinterpret_cast<hipStream_t>(stream));
+    const bool mfma = sse::pse_mfma_specialised(d), small = d.nkz * d.ne * d.na <= sse::kDirectBlocks;
+    if (!mfma && !sse::pse_generic_supported(d)) return fail(SSE_ERR_DIMS, "no phonon self-energy kernel for these dims");
+    const sse::cd beta{beta_re, beta_im};
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    hipError_t e;
+    if (!(small && mfma) && sse::corr_kspace_supported(d, false))
+        e = sse::launch_pi_kspace(d, Gs, Go, dH, nbr, beta, Pi, !small && d.nkz > 1, workspace, workspace ? workspace_bytes : 0,
+                                  s);
+    else
+        e = sse::launch_pse(d, Gs, Go, dH, nbr, beta, Pi, s);
     if (e != hipSuccess) return hip_fail(e, "phonon forward launch");
     return ok();
 }

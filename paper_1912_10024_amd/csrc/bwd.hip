@@ -1,4 +1,6 @@
-// Adjoint of the scattering self-energy (fp64, vector ALUs).
+// Adjoint of the scattering self-energy (fp64): the workspace and the dispatch, and the
+// kernels for shapes whose window of 2 nw energies does not fit the LDS of those in
+// fwd_kspace.hip (dG), bwd_kspace.hip (d gradH) and pse_kspace.hip (dD).
 //
 // With g = dL/dSigma (PyTorch's complex-gradient convention) define, for an
 // edge (a, n) with neighbour b = nbr[a,n] and a source point (k', E'):
@@ -14,11 +16,10 @@
 //   (over signed frequencies: dDp from the g at E'+w terms, dDm from E'-w)
 // Shifted blocks are re-gathered from G and g, nothing of the forward is stored.
 //
-// dG and d gradH are formed by one workgroup per neighbour atom b, which walks
+// Here dG and d gradH are formed by one workgroup per neighbour atom b, which walks
 // the edges that point at b (a reverse adjacency built in the workspace, in
 // edge order), so every output element has one owner: no atomics, bitwise
-// reproducible.  dD is formed by one workgroup per edge here, or by the
-// matrix-core phonon kernel in its adjoint mode for the shape it covers.
+// reproducible; dD by one workgroup per edge.
 #include <algorithm>
 
 #include "sse_kernels.h"
@@ -120,33 +121,46 @@ __global__ void zero_i32_kernel(int64_t n, int32_t* p) {
     for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) p[x] = 0;
 }
 
-// ws layout after the reverse adjacency (256-byte aligned): the d gradH sums of
-// every edge, one set per momentum k' (complex [nkz][na*nb][3][norb][norb]),
-// added in k' order by bwd_dh_reduce_kernel (one per range of energies on the
-// matrix cores), if d gradH is asked for; then the atom-major copy of g that
-// the matrix-core D gradient reads, if dD is asked for with copy_g
+// ws layout after the reverse adjacency (256-byte aligned): the d gradH shares of
+// every edge (complex [share][na*nb][3][norb][norb]), added in order by
+// bwd_dh_reduce_kernel, if d gradH is asked for; then the momentum transforms of g
+// and of G, as far as there is room
 static size_t bwd_csr_bytes(const Dims& d) {  // count, offset, cursor, edges, order
     return (sizeof(int32_t) * (size_t)(4 * d.na + 1 + d.na * d.nb) + 255) / 256 * 256;
 }
-// the matrix-core kernel keeps one d gradH share per range of energies instead
-static bool bwd_use_mfma(const Dims& d, bool signed_form) {
-    return !signed_form && bwd_mfma_specialised(d) && d.ne < (int64_t(1) << 28) &&
-           d.na * bwd_mfma_shares(d) <= INT32_MAX;
+// one d gradH share per 32 energies on the shape of the matrix-core forward, whose Nkz
+// shares would take more room, else one per momentum
+static bool bwd_by_energy(const Dims& d, bool signed_form) {
+    return !signed_form && d.norb == 10 && d.nkz == 7 && d.nqz == 7 && d.nw == 10 && d.ne < (int64_t(1) << 28) &&
+           d.na * ((d.ne + 31) / 32) <= INT32_MAX;
 }
 static int64_t bwd_shares(const Dims& d, bool signed_form) {
-    return bwd_use_mfma(d, signed_form) ? bwd_mfma_shares(d) : d.nkz;
+    return bwd_by_energy(d, signed_form) ? (d.ne + 31) / 32 : d.nkz;
 }
 static size_t bwd_dh_bytes(const Dims& d, bool signed_form) {
     return (sizeof(cd) * (size_t)(bwd_shares(d, signed_form) * d.na * d.nb * 3 * d.norb * d.norb) + 255) / 256 * 256;
 }
-size_t bwd_workspace_bytes_for(const Dims& d, bool signed_form, bool with_dh, bool with_dd, bool copy_g) {
-    // only the one-table form reads both energy branches of g per GEMM row, whose
-    // window is the one that the atom-major copy keeps within a few pages
-    return bwd_csr_bytes(d) + (with_dh ? bwd_dh_bytes(d, signed_form) : 0) +
-           (with_dd && copy_g && !signed_form ? pse_atom_major_bytes(d) : 0);
+// the whole transform of g, or of slot 0 of G
+static size_t bwd_hat_bytes(const Dims& d) {
+    return (size_t)(16 * d.norb * d.norb * d.nkz * d.ne * d.na + 255) / 256 * 256;
+}
+size_t bwd_workspace_bytes_for(const Dims& d, bool signed_form, bool with_dh, bool with_hat) {
+    const bool hat = with_hat && !signed_form && d.norb == 10 && d.nkz == 7 && d.nw == 10 && (d.nb == 3 || d.nb == 4) &&
+                     d.ne < (int64_t(1) << 28);
+    return bwd_csr_bytes(d) + (with_dh ? bwd_dh_bytes(d, signed_form) : 0) + (hat ? bwd_hat_bytes(d) : 0);
 }
 size_t bwd_workspace_bytes(const Dims& d) {
-    return std::max(bwd_workspace_bytes_for(d, false, true, true, true), bwd_workspace_bytes_for(d, true, true, true, true));
+    return std::max(bwd_workspace_bytes_for(d, false, true, true), bwd_workspace_bytes_for(d, true, true, true));
+}
+static bool bwd_use_kspace(const Dims& d) {
+    return fwd_kspace_supported(d, true) && dh_kspace_supported(d) && corr_kspace_supported(d, true);
+}
+size_t bwd_fast_workspace_bytes(const Dims& d) {
+    constexpr size_t kHats = size_t(16) << 30;  // at most this for the transforms
+    const size_t least = bwd_workspace_bytes(d), hat = bwd_hat_bytes(d);
+    if (!bwd_use_kspace(d) || hat > kHats) return least;
+    const size_t base = bwd_csr_bytes(d) + std::max(bwd_dh_bytes(d, false), bwd_dh_bytes(d, true));
+    return std::max(least, base + (2 * hat <= kHats ? 2 * hat : hat));
 }
 
 // --------------------------------------------------------------- W and Y of one source point
@@ -459,43 +473,80 @@ bool bwd_supported(const Dims& d) {
            bwd_lds_dd(d) <= 160 * 1024 && d.na * d.nb <= INT32_MAX && (d.na + 7) / 8 * 8 * d.nkz <= INT32_MAX;
 }
 
-// dD (or dDp / dDm) for the given energy branches (gT: the atom-major copy of gS, or NULL)
-static hipError_t launch_dd(const Dims& d, const double* G, const double* A, const int32_t* nbr, const double* gS,
-                            const double* gT, cd calpha, double* dD, int branches, hipStream_t stream) {
-    if (pse_mfma_specialised(d)) return launch_dd_mfma(d, G, A, nbr, gS, gT, calpha, dD, stream, branches);
-    const size_t lds = bwd_lds_dd(d);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(bwd_dd_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bwd_dd_kernel, dim3((unsigned)(d.na * d.nb)), dim3(kBwdThreads), lds, stream, d, G, A, nbr, gS,
-                       calpha, branches, dD);
+// the kernels of kspace.h: every gradient from the transforms of g and G (room for
+// them, or for that of g, permitting)
+static hipError_t launch_bwd_kspace(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
+                                    const int32_t* nbr, cd alpha, const double* gS, double* dG, double* dDp, double* dDm,
+                                    double* dA, char* ws, size_t ws_bytes, const int32_t* offset, const int32_t* edges,
+                                    const int32_t* order, hipStream_t stream, bool signed_form) {
+    const cd calpha{alpha.re, -alpha.im};
+    const int nkz = (int)d.nkz;
+    const int64_t nn = d.norb * d.norb;
+    const size_t hat = bwd_hat_bytes(d), used = bwd_csr_bytes(d) + (dA ? bwd_dh_bytes(d, signed_form) : 0);
+    double *g_hat = nullptr, *G_hat = nullptr;
+    hipError_t e = hipSuccess;
+    if (d.nkz > 1 && ws_bytes >= used + hat) {
+        g_hat = reinterpret_cast<double*>(ws + used);
+        e = launch_transform(nkz, 0, d.ne, d.na, nn, nn, d.na * nn, d.ne * d.na * nn, gS, g_hat, stream);
+        if (e != hipSuccess) return e;
+        if ((dA || dDp || dDm) && ws_bytes >= used + 2 * hat) {
+            G_hat = reinterpret_cast<double*>(ws + used + hat);
+            e = launch_transform(nkz, 0, d.ne, d.na, nn, d.gs * nn, d.na * d.gs * nn, d.ne * d.na * d.gs * nn, G, G_hat, stream);
+            if (e != hipSuccess) return e;
+        }
+    }
+    if (dG) {
+        e = launch_dg_kspace(d, gS, g_hat, Dp, Dm, A, offset, edges, order, calpha, dG, stream);
+        if (e != hipSuccess) return e;
+    }
+    if (dA) {
+        double* shares = reinterpret_cast<double*>(ws + bwd_csr_bytes(d));
+        e = launch_dh_kspace(d, gS, g_hat, G, G_hat, Dp, Dm, A, nbr, alpha, bwd_by_energy(d, signed_form), shares, stream);
+        if (e != hipSuccess) return e;
+        const int64_t n = d.na * d.nb * 3 * nn;
+        hipLaunchKernelGGL(bwd_dh_reduce_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 65536)), dim3(256), 0, stream,
+                           d, nbr, shares, bwd_shares(d, signed_form), dA);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (dDp) {
+        e = launch_dd_kspace(d, signed_form ? 1 : 3, gS, g_hat, G, G_hat, A, nbr, calpha, dDp, stream);
+        if (e != hipSuccess) return e;
+    }
+    if (dDm) return launch_dd_kspace(d, 2, gS, g_hat, G, G_hat, A, nbr, calpha, dDm, stream);
+    return hipSuccess;
+}
+
+// dD (or dDp / dDm) for the given energy branches
+static hipError_t launch_dd(const Dims& d, const double* G, const double* A, const int32_t* nbr, const double* gS, cd calpha,
+                            double* dD, int branches, hipStream_t stream) {
+    hipLaunchKernelGGL(bwd_dd_kernel, dim3((unsigned)(d.na * d.nb)), dim3(kBwdThreads), bwd_lds_dd(d), stream, d, G, A, nbr,
+                       gS, calpha, branches, dD);
     return hipGetLastError();
 }
 
 hipError_t launch_bwd(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
                       const int32_t* nbr, cd alpha, const double* gS, double* dG, double* dDp, double* dDm, double* dA,
-                      void* ws, hipStream_t stream, bool signed_form, bool copy_g) {
+                      void* ws, size_t ws_bytes, hipStream_t stream, bool signed_form) {
     const cd calpha{alpha.re, -alpha.im};
-    const bool mfma = bwd_use_mfma(d, signed_form);
-    // every attribute is set before the first launch, so a failure leaves all outputs untouched
+    const bool kspace = bwd_use_kspace(d);
     const size_t lds = bwd_lds_dg(d, signed_form);
     auto kern = signed_form ? bwd_dg_dh_kernel<true> : bwd_dg_dh_kernel<false>;
-    if (dG || dA) {
-        hipError_t e = mfma ? bwd_mfma_prepare()
-                            : hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (!kspace) {
+        // every attribute is set before the first launch, so a failure leaves all outputs untouched
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)lds);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(bwd_dd_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)bwd_lds_dd(d));
         if (e != hipSuccess) return e;
     }
-    if ((dDp || dDm) && !pse_mfma_specialised(d)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(bwd_dd_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)bwd_lds_dd(d));
-        if (e != hipSuccess) return e;
-    }
-    if (dG || dA) {
-        int32_t* count = reinterpret_cast<int32_t*>(ws);
-        int32_t* offset = count + d.na;
-        int32_t* cursor = offset + d.na + 1;
-        int32_t* edges = cursor + d.na;
+    int32_t* count = reinterpret_cast<int32_t*>(ws);
+    int32_t* offset = count + d.na;
+    int32_t* cursor = offset + d.na + 1;
+    int32_t* edges = cursor + d.na;
+    int32_t* order = edges + d.na * d.nb;
+    if (dG || (dA && !kspace)) {
         const unsigned g1 = (unsigned)((d.na * d.nb + 255) / 256 < 4096 ? (d.na * d.nb + 255) / 256 : 4096);
         hipLaunchKernelGGL(zero_i32_kernel, dim3(g1), dim3(256), 0, stream, d.na, count);
         hipLaunchKernelGGL(rcsr_count_kernel, dim3(g1), dim3(256), 0, stream, d.na, d.nb, nbr, count);
@@ -503,43 +554,33 @@ hipError_t launch_bwd(const Dims& d, const double* G, const double* Dp, const do
         hipLaunchKernelGGL(rcsr_fill_kernel, dim3(g1), dim3(256), 0, stream, d.na, d.nb, nbr, cursor, edges);
         const unsigned g2 = (unsigned)((d.na + 255) / 256 < 4096 ? (d.na + 255) / 256 : 4096);
         hipLaunchKernelGGL(rcsr_sort_kernel, dim3(g2), dim3(256), 0, stream, d.na, offset, edges);
-        int32_t* order = edges + d.na * d.nb;
         hipLaunchKernelGGL(rcsr_order_kernel, dim3(1), dim3(1024), 0, stream, d.na, count, order);
-        double* dApart = dA ? reinterpret_cast<double*>(reinterpret_cast<char*>(ws) + bwd_csr_bytes(d)) : nullptr;
-        hipError_t e;
-        if (mfma) {
-            e = launch_bwd_mfma(d, G, Dp, A, gS, calpha, offset, edges, order, dG, dApart, stream);
-        } else {
-            const int64_t groups = (d.na + 7) / 8 * 8 * d.nkz;
-            hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kBwdThreads), lds, stream, d, G, Dp, Dm, A, gS,
-                               calpha, offset, edges, order, dG, dApart);
-            e = hipGetLastError();
-        }
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (kspace)
+        return launch_bwd_kspace(d, G, Dp, Dm, A, nbr, alpha, gS, dG, dDp, dDm, dA, static_cast<char*>(ws), ws_bytes, offset,
+                                 edges, order, stream, signed_form);
+    if (dG || dA) {
+        double* shares = dA ? reinterpret_cast<double*>(reinterpret_cast<char*>(ws) + bwd_csr_bytes(d)) : nullptr;
+        const int64_t groups = (d.na + 7) / 8 * 8 * d.nkz;
+        hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kBwdThreads), lds, stream, d, G, Dp, Dm, A, gS, calpha, offset,
+                           edges, order, dG, shares);
+        hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (dA) {
             const int64_t n = d.na * d.nb * 3 * d.norb * d.norb;
             const unsigned g3 = (unsigned)((n + 255) / 256 < 65536 ? (n + 255) / 256 : 65536);
-            hipLaunchKernelGGL(bwd_dh_reduce_kernel, dim3(g3), dim3(256), 0, stream, d, nbr, dApart,
-                               bwd_shares(d, signed_form), dA);
+            hipLaunchKernelGGL(bwd_dh_reduce_kernel, dim3(g3), dim3(256), 0, stream, d, nbr, shares, d.nkz, dA);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
     }
-    if (signed_form ? !dDp && !dDm : !dDp) return hipGetLastError();
-    // the matrix-core D gradient reads g from its atom-major copy when the workspace holds one
-    double* gT = nullptr;
-    if (copy_g && !signed_form && pse_atom_major_bytes(d) > 0) {
-        gT = reinterpret_cast<double*>(reinterpret_cast<char*>(ws) + bwd_csr_bytes(d) +
-                                       (dA ? bwd_dh_bytes(d, signed_form) : 0));
-        hipError_t e = pse_atom_major_g(d, gS, gT, stream);
-        if (e != hipSuccess) return e;
-    }
-    if (!signed_form) return launch_dd(d, G, A, nbr, gS, gT, calpha, dDp, 3, stream);
     if (dDp) {
-        hipError_t e = launch_dd(d, G, A, nbr, gS, gT, calpha, dDp, 1, stream);
+        hipError_t e = launch_dd(d, G, A, nbr, gS, calpha, dDp, signed_form ? 1 : 3, stream);
         if (e != hipSuccess) return e;
     }
-    if (dDm) return launch_dd(d, G, A, nbr, gS, gT, calpha, dDm, 2, stream);
+    if (dDm) return launch_dd(d, G, A, nbr, gS, calpha, dDm, 2, stream);
     return hipGetLastError();
 }
 

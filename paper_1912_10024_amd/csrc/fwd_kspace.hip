@@ -6,7 +6,7 @@
 // per chunk of rc rows of the neighbour's blocks:
 //   load   rows r0 .. r0+rc of hat G[E, b] for the eb + 2 nw energies the tile meets;
 //   for j in 0..2:
-//     right  H_j = rows . grad_j H^H            (lane = a row, grad H in scalar registers)
+//     right  H_j = rows . grad_j H^H            (lane = a row)
 //     filter U_i += sum_w D_ij[w] (H_j[E-w] + H_j[E+w])   (lane = an entry, 4 energies)
 //   left   Sigma[E] += sum_i A_i[:, rows] . U_i  (lane = (energy, column), sums in registers)
 // The rows of a block do not meet before the last step, so a chunk of them is all
@@ -54,16 +54,31 @@ Tile make_tile(const Dims& d, int eb, int rc, int cb, bool two) {
 
 }  // namespace
 
+// The dG part of the adjoint is the same operation on the edges into an atom b, with
+// g = dL/dSigma of the edge's own atom in place of G, the factors A_j on the right and
+// A_i^H on the left, and conj(D) (MODE = kAdjoint; with two tables the E - w terms take Dm)
+constexpr int kHermitian = 0;  // right factor grad_j H^H
+constexpr int kStored = 1;     // right factor given
+constexpr int kAdjoint = 2;
+
+// the edges of kAdjoint: in-edges of every atom in edge order, atoms in decreasing
+// in-degree (a workgroup's time grows with it, so the longest start first)
+struct InEdges {
+    const int32_t *offset, *edges, *order;
+};
+
 // CB columns per pass of the products, MT passes of the left product per wave
-template <int SRC, bool DIRECT, bool TWO, bool HBA, int CB, int MT>
+template <int SRC, bool DIRECT, bool TWO, int MODE, int CB, int MT>
 __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const double* __restrict__ G, int64_t g_atom,
                                                                  int64_t g_kst, int64_t g_est, int slab,
                                                                  const double* __restrict__ Dp,
                                                                  const double* __restrict__ Dm,
                                                                  const double* __restrict__ A,
                                                                  const double* __restrict__ B,
-                                                                 const int32_t* __restrict__ nbr, cd alpha, Tile tile,
-                                                                 int e_lo, int e_hi, int64_t a0, double* __restrict__ S) {
+                                                                 const int32_t* __restrict__ nbr, InEdges in, cd alpha,
+                                                                 Tile tile, int e_lo, int e_hi, int64_t a0, int s_slots,
+                                                                 double* __restrict__ S) {
+    constexpr bool ADJ = MODE == kAdjoint;
     extern __shared__ __align__(16) double smem[];
     const int n = (int)d.norb, nkz = (int)d.nkz, nw = (int)d.nw, ne = (int)d.ne, nb = (int)d.nb;
     const int np = ks::row_len(n), eb = tile.eb;
@@ -80,8 +95,9 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
     // each other: their windows of energies overlap
     const int ntile = (e_hi - e_lo + eb - 1) / eb;
     const int per = nkz * ntile, s = blockIdx.x >> 3;
-    const int64_t a = a0 + s / per * 8 + (blockIdx.x & 7);
-    if (a >= d.na) return;  // uniform, before any barrier
+    const int64_t pos = a0 + s / per * 8 + (blockIdx.x & 7);
+    if (pos >= d.na) return;  // uniform, before any barrier
+    const int64_t a = ADJ ? __builtin_amdgcn_readfirstlane(in.order[pos]) : pos;
     const int rem = s % per, kt = rem / ntile, e0 = e_lo + (rem - kt * ntile) * eb;
     const int e_n = e_hi - e0 < eb ? e_hi - e0 : eb;  // energies of this tile
     const int ewin = eb + 2 * nw;
@@ -98,13 +114,15 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
     for (int t = 0; t < MT; ++t)
 #pragma unroll
         for (int r = 0; r < CB; ++r) sum[t][0][r] = sum[t][1][r] = cd{0.0, 0.0};
-    for (int m = 0; m < nb; ++m) {
-        const int64_t edge = a * nb + m;
-        const int32_t b = __builtin_amdgcn_readfirstlane(nbr[edge]);
+    const int m_lo = ADJ ? __builtin_amdgcn_readfirstlane(in.offset[a]) : 0;
+    const int m_hi = ADJ ? __builtin_amdgcn_readfirstlane(in.offset[a + 1]) : nb;
+    for (int m = m_lo; m < m_hi; ++m) {
+        const int64_t edge = ADJ ? (int64_t)__builtin_amdgcn_readfirstlane(in.edges[m]) : a * nb + m;
+        const int64_t b = ADJ ? edge / nb : (int64_t)__builtin_amdgcn_readfirstlane(nbr[edge]);
         if (b < 0 || b >= d.na) continue;
         const ks::Source src{G + 2 * b * g_atom, g_kst, g_est};
-        const ks::uptr Ar = ks::uniform_ptr((HBA ? B : A) + 6 * edge * nn);
-        const ks::uptr Al = ks::uniform_ptr(A + 6 * edge * nn);
+        const double* Ar = (MODE == kStored ? B : A) + 6 * edge * nn;
+        const double* Al = A + 6 * edge * nn;
         for (int r0 = 0; r0 < n; r0 += tile.rc) {
             const int rc = n - r0 < tile.rc ? n - r0 : tile.rc;
             // filter lanes: entry el = (r, c) of the chunk, energies 4 eq .. 4 eq + 3
@@ -128,14 +146,14 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
                                                       by_row, tile.by_n, sG, tid);
                 if (coeff) {
                     __syncthreads();  // *bad is cleared
-                    ks::stage_coeff<kThreads, !DIRECT, false>(Dp, tw, nkz, kd, nw, ne, edges, edge, sD, bad, tid);
+                    ks::stage_coeff<kThreads, !DIRECT, ADJ>(Dp, tw, nkz, kd, nw, ne, edges, edge, sD, bad, tid);
                     if constexpr (TWO)
-                        ks::stage_coeff<kThreads, !DIRECT, false>(Dm, tw, nkz, kd, nw, ne, edges, edge, sDm, bad, tid);
+                        ks::stage_coeff<kThreads, !DIRECT, ADJ>(Dm, tw, nkz, kd, nw, ne, edges, edge, sDm, bad, tid);
                 }
                 __syncthreads();
                 const bool finite = *bad == 0;
                 for (int j = 0; j < 3; ++j) {
-                    ks::right_product<kWaves, 2, CB, !HBA>(sG, Ar + 2 * j * nn, ewin * rc, n, tile.ncb, tile.by_ncb,
+                    ks::right_product<kWaves, 2, CB, MODE == kHermitian>(sG, Ar + 2 * j * nn, ewin * rc, n, tile.ncb, tile.by_ncb,
                                                               (wave + j) % kWaves, lane, [&](int row) { return sX + row * np; });
                     __syncthreads();
                     if (f_lane) {
@@ -163,21 +181,31 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
                 const int tc = tile.by_ncb.quot(t), col = tc * 128 + lane, rr = (t - tc * nrb) * CB;
                 const int x0 = col < ncol ? col : 0, x1 = col + 64 < ncol ? col + 64 : 0;
                 const int ea = tile.by_n.quot(x0), eb_ = tile.by_n.quot(x1);
-                int off[CB];
-#pragma unroll
-                for (int r = 0; r < CB; ++r) off[r] = 2 * ((rr + r < n ? rr + r : n - 1) * n + r0);
+                const int fr = rr + ks::uniform_entry<CB>(lane);
+                const int fc = fr < n ? fr : n - 1, f_step = ADJ ? 2 * n : 2;
+                const double* f = Al + 2 * (ADJ ? r0 * n + fc : fc * n + r0) + (lane & 1);
                 const cd* ua = sU + ea * 3 * nel + x0 - ea * n;
                 const cd* ub = sU + eb_ * 3 * nel + x1 - eb_ * n;
-                ks::uniform_product<2, CB, false>(sum[ti], 3 * rc, off, [&](int k, const cd* (&p)[2], ks::uptr& f) {
-                    const int i = k >= 2 * rc ? 2 : k >= rc ? 1 : 0;
-                    p[0] = ua + k * n;
-                    p[1] = ub + k * n;
-                    f = Al + 2 * (i * nn + k - i * rc);
-                });
+                ks::uniform_product<2, CB, ADJ, false>(
+                    sum[ti], 3 * rc,
+                    [&](int k) {
+                        const int i = k >= 2 * rc ? 2 : k >= rc ? 1 : 0;
+                        return f[2 * i * nn + (k - i * rc) * f_step];
+                    },
+                    [&](int k, cd (&x)[2]) {
+                        x[0] = ks::ld(ua + k * n);
+                        x[1] = ks::ld(ub + k * n);
+                    });
             }
         }
     }
-    double* So = S + 2 * (((int64_t)kt * ne + e0) * d.na + a) * nn;
+    const int64_t s_est = d.na * s_slots * nn;
+    double* So = S + 2 * (((int64_t)kt * ne + e0) * s_est + a * s_slots * nn);
+    if (ADJ && s_slots > 1) {  // the slots that the forward map does not read
+        const int rest = (s_slots - 1) * nn;
+        for (int e = 0; e < e_n; ++e)
+            for (int x = tid; x < rest; x += kThreads) cstore(So, e * s_est + nn + x, cd{0.0, 0.0});
+    }
 #pragma unroll
     for (int ti = 0; ti < MT; ++ti) {
         const int t = wave + ti * kWaves;
@@ -188,7 +216,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
             const int col = tc * 128 + 64 * h + lane;
             if (col >= ncol) continue;
             const int e = tile.by_n.quot(col), c = col - e * n;
-            double* o = So + 2 * (e * d.na * nn + c);
+            double* o = So + 2 * (e * s_est + c);
 #pragma unroll
             for (int r = 0; r < CB; ++r)
                 if (rr + r < n) cstore(o, (rr + r) * n, DIRECT ? cmul(alpha, sum[ti][h][r]) : sum[ti][h][r]);
@@ -250,11 +278,12 @@ size_t fwd_kspace_workspace(const Dims& d) {
     return (size_t)(per * std::min(d.ne, want));
 }
 
-template <int SRC, bool DIRECT, bool TWO, bool HBA, int CB, int MT>
+template <int SRC, bool DIRECT, bool TWO, int MODE, int CB, int MT>
 static hipError_t launch_cb(const Dims& d, const double* G, int64_t g_atom, int64_t g_kst, int64_t g_est, int slab,
                             const double* Dp, const double* Dm, const double* A, const double* B, const int32_t* nbr,
-                            cd alpha, const Tile& t, int e_lo, int e_hi, double* S, hipStream_t stream) {
-    auto kern = fwd_kspace_kernel<SRC, DIRECT, TWO, HBA, CB, MT>;
+                            InEdges in, cd alpha, const Tile& t, int e_lo, int e_hi, int s_slots, double* S,
+                            hipStream_t stream) {
+    auto kern = fwd_kspace_kernel<SRC, DIRECT, TWO, MODE, CB, MT>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds);
     if (e != hipSuccess) return e;
     const int64_t per = d.nkz * ((e_hi - e_lo + t.eb - 1) / t.eb);
@@ -262,41 +291,80 @@ static hipError_t launch_cb(const Dims& d, const double* G, int64_t g_atom, int6
     const int64_t na8 = (d.na + 7) / 8 * 8, step = std::max<int64_t>(8, ((int64_t)1 << 30) / per / 8 * 8);
     for (int64_t a0 = 0; a0 < na8; a0 += step)
         hipLaunchKernelGGL(kern, dim3((unsigned)(std::min(step, na8 - a0) * per)), dim3(kThreads), t.lds, stream, d, G, g_atom,
-                           g_kst, g_est, slab, Dp, Dm, A, B, nbr, alpha, t, e_lo, e_hi, a0, S);
+                           g_kst, g_est, slab, Dp, Dm, A, B, nbr, in, alpha, t, e_lo, e_hi, a0, s_slots, S);
     return hipGetLastError();
 }
 
-template <int SRC, bool DIRECT, bool TWO, bool HBA, class... Args>
+template <int SRC, bool DIRECT, bool TWO, int MODE, class... Args>
 static hipError_t launch_shape(int cb, Args... args) {
-    if (cb == 4) return launch_cb<SRC, DIRECT, TWO, HBA, 4, 2>(args...);
-    if (cb == 5) return launch_cb<SRC, DIRECT, TWO, HBA, 5, 2>(args...);
-    return launch_cb<SRC, DIRECT, TWO, HBA, 6, 2>(args...);
+    if (cb == 4) return launch_cb<SRC, DIRECT, TWO, MODE, 4, 2>(args...);
+    if (cb == 5) return launch_cb<SRC, DIRECT, TWO, MODE, 5, 2>(args...);
+    return launch_cb<SRC, DIRECT, TWO, MODE, 6, 2>(args...);
 }
 
 template <int SRC, bool DIRECT, class... Args>
-static hipError_t launch_tables(bool two, bool hba, int cb, Args... args) {
-    if (two) return hba ? launch_shape<SRC, DIRECT, true, true>(cb, args...) : launch_shape<SRC, DIRECT, true, false>(cb, args...);
-    return hba ? launch_shape<SRC, DIRECT, false, true>(cb, args...) : launch_shape<SRC, DIRECT, false, false>(cb, args...);
+static hipError_t launch_tables(bool two, int mode, int cb, Args... args) {
+    if constexpr (!DIRECT) {
+        if (mode == kAdjoint)
+            return two ? launch_shape<SRC, DIRECT, true, kAdjoint>(cb, args...) : launch_shape<SRC, DIRECT, false, kAdjoint>(cb, args...);
+    }
+    if (two)
+        return mode == kStored ? launch_shape<SRC, DIRECT, true, kStored>(cb, args...)
+                               : launch_shape<SRC, DIRECT, true, kHermitian>(cb, args...);
+    return mode == kStored ? launch_shape<SRC, DIRECT, false, kStored>(cb, args...)
+                           : launch_shape<SRC, DIRECT, false, kHermitian>(cb, args...);
+}
+
+// the tile for these dims on the current device
+static hipError_t choose_tile(const Dims& d, bool two, int* cb, Tile* t) {
+    int dev = 0, cus = 0, mt = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    passes_of((int)d.norb, cb, &mt);
+    double cost = 0.0;
+    return pick_tile(d, two, *cb, mt, cus, t, &cost) ? hipSuccess : hipErrorInvalidValue;
+}
+
+hipError_t launch_dg_kspace(const Dims& d, const double* g, const double* g_hat, const double* Dp, const double* Dm,
+                            const double* A, const int32_t* offset, const int32_t* edges, const int32_t* order, cd calpha,
+                            double* dG, hipStream_t stream) {
+    const bool two = Dm != Dp;
+    const int64_t nn = d.norb * d.norb, ne = d.ne;
+    int cb;
+    Tile t{};
+    hipError_t e = choose_tile(d, two, &cb, &t);
+    if (e != hipSuccess) return e;
+    const InEdges in{offset, edges, order};
+    const int32_t* no_nbr = nullptr;
+    const double* no_b = nullptr;
+    // the E - w terms of this sum come from the table of the G at E + w
+    if (g_hat)
+        e = launch_tables<ks::kDirect, false>(two, kAdjoint, cb, d, g_hat, ne * nn, d.na * ne * nn, nn, 0, Dm, Dp, A, no_b, no_nbr,
+                                              in, calpha, t, 0, (int)ne, (int)d.gs, dG, stream);
+    else
+        e = launch_tables<ks::kTrans, false>(two, kAdjoint, cb, d, g, nn, ne * d.na * nn, d.na * nn, 0, Dm, Dp, A, no_b, no_nbr, in,
+                                             calpha, t, 0, (int)ne, (int)d.gs, dG, stream);
+    if (e != hipSuccess) return e;
+    return launch_inverse((int)d.nkz, ne * d.na, nn, d.gs * nn, cd{calpha.re / (double)d.nkz, calpha.im / (double)d.nkz}, dG,
+                          stream);
 }
 
 hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
                              const double* B, const int32_t* nbr, cd alpha, double* S, bool transform, void* ws,
                              size_t ws_bytes, hipStream_t stream) {
-    int dev = 0, cus = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    const bool two = Dm != Dp, hba = B != nullptr;
+    const bool two = Dm != Dp;
+    const int mode = B ? kStored : kHermitian;
     const int64_t nn = d.norb * d.norb, ne = d.ne;
-    int cb, mt;
-    passes_of((int)d.norb, &cb, &mt);
+    int cb;
     Tile t{};
-    double cost = 0.0;
-    if (!pick_tile(d, two, cb, mt, cus, &t, &cost)) return hipErrorInvalidValue;
+    hipError_t e = choose_tile(d, two, &cb, &t);
+    if (e != hipSuccess) return e;
+    const InEdges none{};
     const int64_t g_atom = d.gs * nn, g_est = d.na * g_atom, g_kst = ne * g_est;
     if (!transform)
-        return launch_tables<ks::kDirect, true>(two, hba, cb, d, G, g_atom, g_kst, g_est, 0, Dp, Dm, A, B, nbr, alpha, t, 0,
-                                                (int)ne, S, stream);
+        return launch_tables<ks::kDirect, true>(two, mode, cb, d, G, g_atom, g_kst, g_est, 0, Dp, Dm, A, B, nbr, none, alpha, t, 0,
+                                                (int)ne, 1, S, stream);
     const int64_t room = (int64_t)(ws_bytes / (size_t)hat_energy_bytes(d));  // energies
     if (room >= std::min(ne, (int64_t)t.eb + 2 * d.nw)) {
         // slabs of whole tiles; a slab's transform takes the 2 nw energies around it
@@ -307,13 +375,13 @@ hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, c
             const int64_t first = std::max<int64_t>(0, lo - d.nw), n_e = std::min(ne, hi + d.nw) - first;
             e = launch_transform((int)d.nkz, first, n_e, d.na, nn, g_atom, g_est, g_kst, G, hat, stream);
             if (e != hipSuccess) return e;
-            e = launch_tables<ks::kDirect, false>(two, hba, cb, d, hat, n_e * nn, d.na * n_e * nn, nn, (int)first, Dp, Dm, A,
-                                                  B, nbr, alpha, t, (int)lo, (int)hi, S, stream);
+            e = launch_tables<ks::kDirect, false>(two, mode, cb, d, hat, n_e * nn, d.na * n_e * nn, nn, (int)first, Dp, Dm, A,
+                                                  B, nbr, none, alpha, t, (int)lo, (int)hi, 1, S, stream);
             if (e != hipSuccess) return e;
         }
     } else {
-        e = launch_tables<ks::kTrans, false>(two, hba, cb, d, G, g_atom, g_kst, g_est, 0, Dp, Dm, A, B, nbr, alpha, t, 0,
-                                             (int)ne, S, stream);
+        e = launch_tables<ks::kTrans, false>(two, mode, cb, d, G, g_atom, g_kst, g_est, 0, Dp, Dm, A, B, nbr, none, alpha, t, 0,
+                                             (int)ne, 1, S, stream);
         if (e != hipSuccess) return e;
     }
     return launch_inverse((int)d.nkz, ne * d.na, nn, nn, cd{alpha.re / (double)d.nkz, alpha.im / (double)d.nkz}, S, stream);

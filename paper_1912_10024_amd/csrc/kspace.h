@@ -13,9 +13,9 @@
 //
 // All of it runs on the fp64 vector ALUs, whose peak on this chip is that of the
 // fp64 matrix cores: in each step one operand is the same for every lane (a
-// grad H entry, read through the scalar cache into scalar registers, or a
-// coefficient, broadcast from LDS), so a lane needs one LDS read for 12 to 24
-// multiply-adds, nothing is padded to a tile, and every size takes the same code.
+// grad H entry, broadcast from a register, or a coefficient, broadcast from LDS), so a lane needs one
+// LDS read for 12 to 24 multiply-adds, nothing is padded to a tile, and every size
+// takes the same code.
 #pragma once
 
 #include <type_traits>
@@ -26,12 +26,6 @@ namespace sse {
 namespace ks {
 
 constexpr int kEBlk = 4;  // energies of one lane in the filter
-constexpr int kWaitLgkm = 0xc07f;  // s_waitcnt lgkmcnt(0), the other counters as they are
-
-// memory that no kernel in flight writes, read at a uniform address: the constant
-// address space makes the compiler use the scalar cache
-typedef const double __attribute__((address_space(4)))* uptr;
-__device__ __forceinline__ uptr uniform_ptr(const double* p) { return (uptr)(uintptr_t)p; }
 
 // one complex entry of an LDS array (16-byte aligned)
 __device__ __forceinline__ cd ld(const cd* p) {
@@ -118,55 +112,156 @@ __device__ __forceinline__ void load_rows(const Source& s, const cd* tw, int nkz
     }
 }
 
-// acc[r][c] += x_r(k) * f_c(k) (CONJ: conj(f)) for k in [0, len): R operands per
-// lane from LDS, CB of them uniform from memory.  The operands of step k + 1 are on
-// their way while step k multiplies (4 R CB multiply-adds per lane): scalar loads
-// return out of order, so a wave can only wait for all of them, and without this
-// every step paid the scalar cache's latency.
-// at(k, x, f): addresses of step k's operands; off[c]: doubles between the uniform ones.
-template <int R, int CB, bool CONJ, class At>
-__device__ __forceinline__ void uniform_product(cd (&acc)[R][CB], int len, const int (&off)[CB], At at) {
-    cd x[2][R], f[2][CB];
-    auto fetch = [&](int buf, int k) {
-        const cd* p[R];
-        uptr u;
-        at(k < len ? k : len - 1, p, u);
-        __builtin_amdgcn_s_waitcnt(kWaitLgkm);  // the other buffer has arrived, before more is asked for
-#pragma unroll
-        for (int c = 0; c < CB; ++c) f[buf][c] = cd{u[off[c]], u[off[c] + 1]};
-#pragma unroll
-        for (int r = 0; r < R; ++r) x[buf][r] = ld(p[r]);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto mul = [&](int buf) {
-#pragma unroll
-        for (int c = 0; c < CB; ++c)
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                if constexpr (CONJ)
-                    cfma_conj(acc[r][c], x[buf][r], f[buf][c]);
-                else
-                    cfma(acc[r][c], x[buf][r], f[buf][c]);
-            }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    fetch(0, 0);
-    int k = 0;
-    for (; k + 2 <= len; k += 2) {
-        fetch(1, k + 1);
-        mul(0);
-        fetch(0, k + 2);
-        mul(1);
+// Products with a uniform operand.  The 2 CB doubles of a step's uniform operands
+// (CB complex entries of grad H) sit in one register, double l of them in lane l of
+// every row of 16 lanes, and the multiply-adds read them with the DPP row broadcast,
+// which costs nothing.  Through scalar registers they took a scalar load per entry, whose
+// results return out of order and from a cache that four workgroups share: the
+// products then ran at 40% of the rate they reach from the vector memory path.
+// All 64 lanes have to be active.  The wait states are those that a DPP read needs
+// after a vector write of its source.
+#define SSE_FMAC(D, S, X, K) "v_fmac_f64_dpp " D ", " S ", " X " row_newbcast:" K " row_mask:0xf bank_mask:0xf\n"
+// p0 += f[K0] x0, p1 += f[K0] x1, p2 += f[K1] x0, p3 += f[K1] x1 (CONJ: conj(f))
+template <bool CONJ, int K0, int K1>
+__device__ __forceinline__ void fma4(cd& p0, cd& p1, cd& p2, cd& p3, double f, cd x0, cd x1) {
+#define SSE_FMA4(SR, SI)                                                                                            \
+    asm("s_nop 1\n" SSE_FMAC("%0", "%8", "%9", "%13") SSE_FMAC("%1", "%8", "%10", "%13")                            \
+            SSE_FMAC("%2", "%8", "%11", "%13") SSE_FMAC("%3", "%8", "%12", "%13") SSE_FMAC("%4", "%8", "%9", "%15")  \
+                SSE_FMAC("%5", "%8", "%10", "%15") SSE_FMAC("%6", "%8", "%11", "%15")                                \
+                    SSE_FMAC("%7", "%8", "%12", "%15") SSE_FMAC("%0", SR, "%10", "%14")                              \
+                        SSE_FMAC("%1", SI, "%9", "%14") SSE_FMAC("%2", SR, "%12", "%14")                             \
+                            SSE_FMAC("%3", SI, "%11", "%14") SSE_FMAC("%4", SR, "%10", "%16")                        \
+                                SSE_FMAC("%5", SI, "%9", "%16") SSE_FMAC("%6", SR, "%12", "%16")                     \
+                                    SSE_FMAC("%7", SI, "%11", "%16")                                                 \
+        : "+&v"(p0.re), "+&v"(p0.im), "+&v"(p1.re), "+&v"(p1.im), "+&v"(p2.re), "+&v"(p2.im), "+&v"(p3.re),          \
+          "+&v"(p3.im)                                                                                               \
+        : "v"(f), "v"(x0.re), "v"(x0.im), "v"(x1.re), "v"(x1.im), "n"(2 * K0), "n"(2 * K0 + 1), "n"(2 * K1),         \
+          "n"(2 * K1 + 1))
+    if constexpr (CONJ)
+        SSE_FMA4("%8", "-%8");
+    else
+        SSE_FMA4("-%8", "%8");
+#undef SSE_FMA4
+}
+// p0 += f[K] x0, p1 += f[K] x1
+template <bool CONJ, int K>
+__device__ __forceinline__ void fma2(cd& p0, cd& p1, double f, cd x0, cd x1) {
+#define SSE_FMA2(SR, SI)                                                                                           \
+    asm("s_nop 1\n" SSE_FMAC("%0", "%4", "%5", "%9") SSE_FMAC("%1", "%4", "%6", "%9") SSE_FMAC("%2", "%4", "%7", "%9") \
+            SSE_FMAC("%3", "%4", "%8", "%9") SSE_FMAC("%0", SR, "%6", "%10") SSE_FMAC("%1", SI, "%5", "%10")       \
+                SSE_FMAC("%2", SR, "%8", "%10") SSE_FMAC("%3", SI, "%7", "%10")                                    \
+        : "+&v"(p0.re), "+&v"(p0.im), "+&v"(p1.re), "+&v"(p1.im)                                                   \
+        : "v"(f), "v"(x0.re), "v"(x0.im), "v"(x1.re), "v"(x1.im), "n"(2 * K), "n"(2 * K + 1))
+    if constexpr (CONJ)
+        SSE_FMA2("%4", "-%4");
+    else
+        SSE_FMA2("-%4", "%4");
+#undef SSE_FMA2
+}
+// p0 += f[K0] x, p1 += f[K1] x (K1 == K0: p0 only)
+template <bool CONJ, int K0, int K1>
+__device__ __forceinline__ void fma2r(cd& p0, cd& p1, double f, cd x) {
+#define SSE_FMA2R(SR, SI, TR, TI)                                                                                       \
+    if constexpr (K1 != K0)                                                                                     \
+        asm("s_nop 1\n" SSE_FMAC("%0", "%4", "%5", "%7") SSE_FMAC("%1", "%4", "%6", "%7")                       \
+                SSE_FMAC("%2", "%4", "%5", "%9") SSE_FMAC("%3", "%4", "%6", "%9")                               \
+                    SSE_FMAC("%0", SR, "%6", "%8") SSE_FMAC("%1", SI, "%5", "%8")                               \
+                        SSE_FMAC("%2", SR, "%6", "%10") SSE_FMAC("%3", SI, "%5", "%10")                         \
+            : "+&v"(p0.re), "+&v"(p0.im), "+&v"(p1.re), "+&v"(p1.im)                                            \
+            : "v"(f), "v"(x.re), "v"(x.im), "n"(2 * K0), "n"(2 * K0 + 1), "n"(2 * K1), "n"(2 * K1 + 1));        \
+    else                                                                                                        \
+        asm("s_nop 1\n" SSE_FMAC("%0", "%2", "%3", "%5") SSE_FMAC("%1", "%2", "%4", "%5")                       \
+                SSE_FMAC("%0", TR, "%4", "%6") SSE_FMAC("%1", TI, "%3", "%6")                                   \
+            : "+&v"(p0.re), "+&v"(p0.im)                                                                        \
+            : "v"(f), "v"(x.re), "v"(x.im), "n"(2 * K0), "n"(2 * K0 + 1))
+    if constexpr (CONJ) {
+        SSE_FMA2R("%4", "-%4", "%2", "-%2");
+    } else {
+        SSE_FMA2R("-%4", "%4", "-%2", "%2");
     }
-    if (k < len) mul(0);
+#undef SSE_FMA2R
+}
+#undef SSE_FMAC
+
+// acc[r][c] += f_c x_r (CONJ: conj(f_c)) for two operands x per lane
+template <int CB, bool CONJ, int C = 0>
+__device__ __forceinline__ void fma_block(cd (&acc)[2][CB], double f, const cd (&x)[2]) {
+    static_assert(CB <= 8, "16 doubles per row of lanes");
+    if constexpr (C + 2 <= CB) {
+        fma4<CONJ, C, C + 1>(acc[0][C], acc[1][C], acc[0][C + 1], acc[1][C + 1], f, x[0], x[1]);
+        fma_block<CB, CONJ, C + 2>(acc, f, x);
+    } else if constexpr (C < CB) {
+        fma2<CONJ, C>(acc[0][C], acc[1][C], f, x[0], x[1]);
+    }
+}
+// the same for one operand per lane
+template <int CB, bool CONJ, int C = 0>
+__device__ __forceinline__ void fma_block(cd (&acc)[1][CB], double f, const cd (&x)[1]) {
+    static_assert(CB <= 8, "16 doubles per row of lanes");
+    if constexpr (C < CB) {
+        cd none{0.0, 0.0};
+        constexpr int D = C + 1 < CB ? C + 1 : C;
+        fma2r<CONJ, C, D>(acc[0][C], C + 1 < CB ? acc[0][D] : none, f, x[0]);
+        fma_block<CB, CONJ, C + 2>(acc, f, x);
+    }
+}
+
+// double `comp` of the uniform operand this lane holds: entry min(l / 2, CB - 1), re or im
+template <int CB>
+__device__ __forceinline__ int uniform_entry(int lane) {
+    const int c = (lane & 15) >> 1;
+    return c < CB ? c : CB - 1;
+}
+
+// acc[r][c] += f_c(k) x_r(k) for k in [0, len).  factor(k): this lane's double of step k's
+// uniform operands, asked for TB steps ahead; operand(k, x): the lane's own, asked
+// for one step ahead from LDS, or (MEM) TB steps ahead from memory.
+template <int R, int CB, bool CONJ, bool MEM, class Factor, class Operand>
+__device__ __forceinline__ void uniform_product(cd (&acc)[R][CB], int len, Factor factor, Operand operand) {
+    constexpr int TB = 4;
+    double fa[TB], fb[TB];
+    cd xa[MEM ? TB : 2][R], xb[MEM ? TB : 1][R];
+    auto ask = [&](double (&f)[TB], auto& x, int k0) {
+#pragma unroll
+        for (int u = 0; u < TB; ++u) {
+            const int k = k0 + u < len ? k0 + u : len - 1;
+            f[u] = factor(k);
+            if constexpr (MEM) operand(k, x[u]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto mul = [&](const double (&f)[TB], auto& x, int k0) {
+#pragma unroll
+        for (int u = 0; u < TB; ++u) {
+            if (k0 + u < len) {
+                if constexpr (MEM) {
+                    fma_block<CB, CONJ>(acc, f[u], x[u]);
+                } else {
+                    operand(k0 + u + 1 < len ? k0 + u + 1 : len - 1, xa[(u + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    fma_block<CB, CONJ>(acc, f[u], xa[u & 1]);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    ask(fa, xa, 0);
+    if constexpr (!MEM) operand(0, xa[0]);
+    for (int k0 = 0; k0 < len; k0 += 2 * TB) {
+        ask(fb, xb, k0 + TB);
+        mul(fa, xa, k0);
+        if (k0 + TB >= len) break;
+        ask(fa, xa, k0 + 2 * TB);
+        mul(fb, xb, k0 + TB);
+    }
 }
 
 // out(row)[c] = sum_u sG[row][u] . f(u, c) for `rows` rows: a lane owns R rows, 64
 // apart, of a group of 64 R, CB columns at a time.  RT: f(u, c) = conj(M[c][u]) (the
 // right factor grad_j H^H), else f(u, c) = M[u][c].
 template <int WAVES, int R, int CB, bool RT, class Out>
-__device__ __forceinline__ void right_product(const cd* sG, uptr M, int rows, int n, int ncb, Div by_ncb, int first,
-                                              int lane, Out out) {
+__device__ __forceinline__ void right_product(const cd* sG, const double* __restrict__ M, int rows, int n, int ncb,
+                                              Div by_ncb, int first, int lane, Out out) {
     const int np = row_len(n);
     const int tasks = (rows + 64 * R - 1) / (64 * R) * ncb;
     for (int t = first; t < tasks; t += WAVES) {
@@ -174,22 +269,21 @@ __device__ __forceinline__ void right_product(const cd* sG, uptr M, int rows, in
         const int row = tr * 64 * R + lane;
         const cd* g[R];
         cd acc[R][CB];
-        int off[CB];
 #pragma unroll
         for (int r = 0; r < R; ++r) g[r] = sG + (row + 64 * r < rows ? row + 64 * r : 0) * np;
 #pragma unroll
-        for (int c = 0; c < CB; ++c) {
+        for (int c = 0; c < CB; ++c)
 #pragma unroll
             for (int r = 0; r < R; ++r) acc[r][c] = cd{0.0, 0.0};
-            const int cc = c0 + c < n ? c0 + c : n - 1;
-            off[c] = 2 * (RT ? cc * n : cc);
-        }
+        const int fc = c0 + uniform_entry<CB>(lane), cc = fc < n ? fc : n - 1;
+        const double* f = M + 2 * (RT ? cc * n : cc) + (lane & 1);
         const int step = RT ? 2 : 2 * n;
-        uniform_product<R, CB, RT>(acc, n, off, [&](int u, const cd* (&p)[R], uptr& f) {
+        uniform_product<R, CB, RT, false>(
+            acc, n, [&](int u) { return f[u * step]; },
+            [&](int u, cd (&x)[R]) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) p[r] = g[r] + u;
-            f = M + u * step;
-        });
+                for (int r = 0; r < R; ++r) x[r] = ld(g[r] + u);
+            });
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (row + 64 * r >= rows) continue;
@@ -301,8 +395,8 @@ __device__ __forceinline__ void filter_masked(cd (&acc)[3][kEBlk], const cd* X, 
 
 // Coefficients of one edge into LDS, [j][w][i] (nine per frequency): the transform
 // over the phonon momenta at kt (TRANS) or those of momentum kt.  CONJ: conjugated
-// (the adjoint).  Sets *bad where one is not finite.
-template <int THREADS, bool TRANS, bool CONJ>
+// (the adjoint).  SWAP: [i][w][j].  Sets *bad where one is not finite.
+template <int THREADS, bool TRANS, bool CONJ, bool SWAP = false>
 __device__ __forceinline__ void stage_coeff(const double* __restrict__ D, const cd* tw, int nkz, int kt, int nw, int ne,
                                             int64_t edges, int64_t edge, cd* sD, int* bad, int tid) {
     for (int x = tid; x < nw * 9; x += THREADS) {
@@ -323,7 +417,8 @@ __device__ __forceinline__ void stage_coeff(const double* __restrict__ D, const 
         if (w + 1 >= ne) v = cd{0.0, 0.0};  // a frequency that no pair of energies differs by has no term
         if constexpr (CONJ) v.im = -v.im;
         if (!(fabs(v.re) <= 1.7976931348623157e308 && fabs(v.im) <= 1.7976931348623157e308)) *bad = 1;
-        st(sD + ((ij % 3) * nw + w) * 3 + ij / 3, v);
+        const int in = SWAP ? ij / 3 : ij % 3, out = SWAP ? ij % 3 : ij / 3;
+        st(sD + (in * nw + w) * 3 + out, v);
     }
 }
 

@@ -56,14 +56,14 @@ int sse_backward_noalloc(const sse_dims* dims, const double* G, const double* D,
     int rc = sse_workspace_bytes(dims, SSE_FP64, 1, &full);
     if (rc) return rc;
     // the part of the workspace this call uses: without ddH, the reverse adjacency only
-    const size_t need = sse::bwd_workspace_bytes_for(sse::to_dims(*dims), false, ddH != nullptr);
+    const size_t need = sse::bwd_workspace_bytes_for(sse::to_dims(*dims), false, ddH != nullptr, false);
     if (need > kScratchBytes)
         return sse::set_error(SSE_ERR_WORKSPACE, "sse_backward_noalloc: these dims need %zu bytes of workspace, above its %zu",
                               need, kScratchBytes);
     void* ws = nullptr;
     hipError_t e = scratch_address(&ws);
     if (e != hipSuccess) return sse::set_error(SSE_ERR_HIP, "sse_backward_noalloc: scratch address: %s", hipGetErrorString(e));
-    // the D gradient reads g in the caller's layout: its atom-major copy would not fit the array
+    // the transforms of dSigma and G are kept where the array has room, else taken as they are read
     return sse::backward_one_table(dims, G, D, dH, nbr, alpha_re, alpha_im, dSigma, dG, dD, ddH, ws, kScratchBytes,
                                    stream, false);
 }

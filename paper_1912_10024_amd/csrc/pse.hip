@@ -116,29 +116,12 @@ __device__ __forceinline__ void pse_sum_row_tile(const Dims& d, const double* re
     }
 }
 
-// MODE = 0: Pi (Eq. 4) with Gs, Go as documented above.
-// MODE != 0: the D part of the adjoint of Eq. 3 for dL/dSigma = g,
-//   dD[q, w-1, a, n][i][j] = conj(alpha) sum_{k', E'} sum_{s in S} [0 <= E' + s w < NE]
-//                            sum_{r,c} conj((A_i G[k', E', b] A_j^H)[r][c]) g[k'+q, E'+s w, a][r][c],
-// which is the same contraction with Gs := g (no slot axis), the energy
-// branches of S summed into each A row, and T_ij = A_j . G^H . A_i^H (the Go
-// block is staged conjugate-transposed); beta = conj(alpha).  MODE is the set
-// S: bit 0 the branch s = +1 (g at E' + w: the terms whose G sits at E - w,
-// i.e. the coefficients at +w), bit 1 the branch s = -1 (coefficients at -w);
-// the one-table form of Eq. 3 takes both.
-// AM (adjoint only): g is read from its atom-major copy (pse_atom_major_g):
-// the GEMM rows of one workgroup then come from one contiguous region of the
-// atom (a few pages) instead of one (k, E) slab per block, 147 of them for the
-// 21 energies x 7 momenta a workgroup reads at a time.  Same arithmetic in the
-// same order as AM = false.
-template <int N, int NK, int NW, int NB, int MODE, bool AM>
+template <int N, int NK, int NW, int NB>
 __global__ __launch_bounds__(64 * (8 + NB)) void pse_mfma_kernel(
     Dims d, const double* __restrict__ Gs, const double* __restrict__ Go, const double* __restrict__ Ag,
     const int32_t* __restrict__ nbr, cd beta, double* __restrict__ Pi) {
     using C = PseCfg<N, NK, NW, NB>;
     static_assert(C::THREADS == 64 * (8 + NB), "launch bounds");
-    constexpr bool ADJ = MODE != 0, UP = !ADJ || (MODE & 1) != 0, LO = ADJ && (MODE & 2) != 0;
-    static_assert(!AM || ADJ, "the atom-major copy is the adjoint's");
     constexpr int NN = C::NN;
     extern __shared__ __align__(16) double smem[];
     double* sA = smem;           // [NB][3][N][N] complex
@@ -153,10 +136,6 @@ __global__ __launch_bounds__(64 * (8 + NB)) void pse_mfma_kernel(
     const int64_t slot = 2 * d.gs * NN;   // doubles between atoms at one (k, E)
     const int64_t e_step = slot * NA;      // doubles between energies
     const int64_t k_step = e_step * NE;    // doubles between momenta
-    // the shifted operand: Gs (laid out like G) or, for the adjoint, g (one block per
-    // atom), in its own layout or atom-major ([a][k][E] blocks)
-    const int64_t rs_slot = ADJ ? (AM ? 2 * NN * NE * (int64_t)NK : 2 * NN) : slot;
-    const int64_t rs_e = AM ? 2 * NN : rs_slot * NA, rs_k = AM ? 2 * NN * (int64_t)NE : rs_e * NE;
     const int nsrc = NK * NE;
 
     for (int x = tid; x < NB * 3 * NN; x += C::THREADS) {
@@ -195,10 +174,7 @@ __global__ __launch_bounds__(64 * (8 + NB)) void pse_mfma_kernel(
             for (int u = 0; u < C::GO_PER_LANE; ++u) {
                 const int x = lane + 64 * u;
                 if (x < NN) {
-                    if constexpr (ADJ)   // G^H: element (r, c) of G goes to (c, r), conjugated
-                        *reinterpret_cast<double2*>(myGo + 2 * ((x % N) * N + x / N)) = make_double2(gv[u].re, -gv[u].im);
-                    else
-                        *reinterpret_cast<double2*>(myGo + 2 * x) = make_double2(gv[u].re, gv[u].im);
+                    *reinterpret_cast<double2*>(myGo + 2 * x) = make_double2(gv[u].re, gv[u].im);
                 }
             }
             if (src + 1 < nsrc) load_go(src + 1);
@@ -319,10 +295,8 @@ __global__ __launch_bounds__(64 * (8 + NB)) void pse_mfma_kernel(
 #pragma unroll
         for (int s = 0; s < C::SL; ++s) acc[s] = pse_f64x4{0.0, 0.0, 0.0, 0.0};
 
-        // A rows of a source point: the wave's first k-step and the lane's K index folded
-        // in; the adjoint adds the row of the lower energy branch (ap2)
+        // A rows of a source point: the wave's first k-step and the lane's K index folded in
         const double* ap[C::ML];
-        const double* ap2[C::ML];
         auto a_rows = [&](int src) {
             const int E = src / NK, k = src % NK;
 #pragma unroll
@@ -331,22 +305,11 @@ __global__ __launch_bounds__(64 * (8 + NB)) void pse_mfma_kernel(
                 const int w = r % NW + 1, es = E + w;
                 const bool ok = r < C::MROWS && es < NE;
                 const int kq = (k + r / NW) % NK;
-                const double* base = Gs + kq * rs_k + rs_slot * a;
-                ap[ml] = (ok ? base + (int64_t)es * rs_e : pse_zero_block) + 4 * kg + kk;
-                if constexpr (LO) {
-                    const bool ok2 = r < C::MROWS && E - w >= 0;
-                    ap2[ml] = (ok2 ? base + (int64_t)(E - w) * rs_e : pse_zero_block) + 4 * kg + kk;
-                }
+                const double* base = Gs + kq * k_step + slot * a;
+                ap[ml] = (ok ? base + (int64_t)es * e_step : pse_zero_block) + 4 * kg + kk;
             }
         };
-        auto a_load = [&](int ml, int off) {
-            if constexpr (UP && LO)
-                return ap[ml][off] + ap2[ml][off];
-            else if constexpr (LO)
-                return ap2[ml][off];
-            else
-                return ap[ml][off];
-        };
+        auto a_load = [&](int ml, int off) { return ap[ml][off]; };
         double an[C::ML];
         a_rows(0);
 #pragma unroll
@@ -485,11 +448,11 @@ bool pse_mfma_specialised(const Dims& d) {
     return d.norb == 10 && d.nkz == 7 && d.nqz == 7 && d.nw == 10 && (d.nb == 4 || d.nb == 3) && d.ne < (1 << 28);
 }
 
-template <int NB, int MODE, bool AM = false>
+template <int NB>
 static hipError_t launch_pse_mfma(const Dims& d, const double* Rs, const double* Go, const double* A,
                                   const int32_t* nbr, cd beta, double* out, hipStream_t stream) {
     using C = PseCfg<10, 7, 10, NB>;
-    auto kern = pse_mfma_kernel<10, 7, 10, NB, MODE, AM>;
+    auto kern = pse_mfma_kernel<10, 7, 10, NB>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)C::LDS_BYTES);
     if (e != hipSuccess) return e;
@@ -504,61 +467,14 @@ bool pse_generic_supported(const Dims& d) {
 hipError_t launch_pse(const Dims& d, const double* Gs, const double* Go, const double* A, const int32_t* nbr, cd beta,
                       double* Pi, hipStream_t stream) {
     if (pse_mfma_specialised(d))
-        return d.nb == 4 ? launch_pse_mfma<4, 0, false>(d, Gs, Go, A, nbr, beta, Pi, stream)
-                         : launch_pse_mfma<3, 0, false>(d, Gs, Go, A, nbr, beta, Pi, stream);
+        return d.nb == 4 ? launch_pse_mfma<4>(d, Gs, Go, A, nbr, beta, Pi, stream)
+                         : launch_pse_mfma<3>(d, Gs, Go, A, nbr, beta, Pi, stream);
     const size_t lds = pse_generic_lds(d);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pse_generic_kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(pse_generic_kernel, dim3((unsigned)(d.na * d.nb)), dim3(kPseThreads), lds, stream, d, Gs, Go, A,
                        nbr, beta, Pi);
-    return hipGetLastError();
-}
-
-template <int MODE, bool AM>
-static hipError_t launch_dd_mode(const Dims& d, const double* G, const double* A, const int32_t* nbr, const double* gS,
-                                 cd calpha, double* dD, hipStream_t stream) {
-    return d.nb == 4 ? launch_pse_mfma<4, MODE, AM>(d, gS, G, A, nbr, calpha, dD, stream)
-                     : launch_pse_mfma<3, MODE, AM>(d, gS, G, A, nbr, calpha, dD, stream);
-}
-
-template <bool AM>
-static hipError_t launch_dd_layout(const Dims& d, const double* G, const double* A, const int32_t* nbr,
-                                   const double* g, cd calpha, double* dD, hipStream_t stream, int branches) {
-    if (branches == 3) return launch_dd_mode<3, AM>(d, G, A, nbr, g, calpha, dD, stream);
-    if (branches == 1) return launch_dd_mode<1, AM>(d, G, A, nbr, g, calpha, dD, stream);
-    if (branches == 2) return launch_dd_mode<2, AM>(d, G, A, nbr, g, calpha, dD, stream);
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_dd_mfma(const Dims& d, const double* G, const double* A, const int32_t* nbr, const double* gS,
-                          const double* gT, cd calpha, double* dD, hipStream_t stream, int branches) {
-    return gT ? launch_dd_layout<true>(d, G, A, nbr, gT, calpha, dD, stream, branches)
-              : launch_dd_layout<false>(d, G, A, nbr, gS, calpha, dD, stream, branches);
-}
-
-// ------------------------------------------------------------------ atom-major copy of g
-// gT[a][k][e][NN] (complex) = g[k][e][a][NN]: every entry written on every call
-__global__ void pse_atom_major_kernel(int64_t nkz, int64_t ne, int64_t na, int64_t nn, const double2* __restrict__ g,
-                                      double2* __restrict__ gT) {
-    const int64_t per_atom = nkz * ne * nn, total = na * per_atom;
-    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < total; x += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t a = x / per_atom, r = x % per_atom, blk = r / nn, rc = r % nn;
-        gT[x] = g[(blk * na + a) * nn + rc];
-    }
-}
-
-bool pse_atom_major_ok(const Dims& d) { return pse_mfma_specialised(d); }
-
-size_t pse_atom_major_bytes(const Dims& d) {
-    return pse_atom_major_ok(d) ? (size_t)(16 * d.norb * d.norb * d.nkz * d.ne * d.na + 255) / 256 * 256 : 0;
-}
-
-hipError_t pse_atom_major_g(const Dims& d, const double* g, double* gT, hipStream_t stream) {
-    const int64_t n = d.na * d.nkz * d.ne * d.norb * d.norb;
-    const unsigned grid = (unsigned)((n + 255) / 256 < 65536 ? (n + 255) / 256 : 65536);
-    hipLaunchKernelGGL(pse_atom_major_kernel, dim3(grid), dim3(256), 0, stream, d.nkz, d.ne, d.na, d.norb * d.norb,
-                       reinterpret_cast<const double2*>(g), reinterpret_cast<double2*>(gT));
     return hipGetLastError();
 }
 

@@ -1,0 +1,491 @@
+// fp64 correlations over energy in the momentum transform (kspace.h), any shape:
+// the phonon self-energy (Eq. 4) and the D gradient of Eq. 3.
+//
+//   dD_ij[q, w]  = conj(alpha) sum_{k, E, +-} sum_rc conj((A_i B[k, E] A_j^H)[r][c]) g[k+q, E +- w][r][c]
+//                = conj(alpha) sum_{k, E, +-} < X_i[k, E], Y_j[k+q, E +- w] >,   X_i = A_i B,  Y_j = g A_j
+// over the entries of a block, with B the neighbour's block of G; the sum over k is a
+// correlation, so in the transform hat dD[m, w] needs hat X[m] and hat Y[m] only:
+// Nkz times fewer products than the sum over (q, k), and 6 block products per (edge,
+// momentum, energy) instead of 12.  Pi_ij is the same sum over the upper branch with
+// g = Gs and B = Go^H: tr(A_i^H Gs A_j Go) = < A_i Go^H, Gs A_j >.
+//
+// One workgroup per (edge, transformed momentum), sweeping the energies in tiles of
+// eb, for one chunk of rc rows of the blocks after another:
+//   right  Y_j rows of the energies that enter the window  (lane = a row)
+//   left   X_i rows of the tile's energies                 (lane = (energy, column))
+//   sums   acc[i][w] += conj(X_i[E]) Y_j[E +- w]           (lane = an entry, one j, WB
+//          frequencies, a share of the energies)
+// A lane's window of WB energies per branch slides with E through registers, so a
+// step reads 3 + 1 (or 2) entries from LDS for 12 WB multiply-adds.  The planes
+// of Y that the next tile still needs move to the front of the buffer.  The lanes'
+// sums are added in LDS in a fixed order at the end.
+//
+// SRC = kTrans (for g) and x_trans (for B) transform while they load; DIRECT sums over k as it stands, one
+// workgroup per (edge, q) (exact for integer-valued inputs, Nkz times the work).
+#include <algorithm>
+
+#include "kspace.h"
+#include "sse_kernels.h"
+
+namespace sse {
+
+namespace {
+
+constexpr int kThreads = 256, kWaves = kThreads / 64;
+constexpr int kCB = 5, kXB = 6;  // columns per pass of Y, outputs (i, r) per pass of X
+constexpr size_t kLdsMax = 160 * 1024;
+
+struct CorrTile {
+    int eb, rc, es, nwb, nwg;  // energies, rows, shares of the energies, frequency blocks of a workgroup and groups of them
+    int halo_lo, halo_hi;      // planes of Y before and after the tile
+    int ncb;
+    ks::Div by_n, by_ncb, by_xb[2], by_rc[2], by_row[2];
+    int nel, y_entries, x_entries;
+    size_t lds;
+};
+
+struct CorrArgs {
+    const double *y, *x;                             // g (or Gs) and B (or Go), or their transforms
+    int64_t y_atom, y_kst, y_est, x_atom, x_kst, x_est;
+    int lo, hi, first, n_e;  // energies of X that are summed; the arrays hold first .. first + n_e - 1
+    bool add;                // add to the output instead of writing it
+    bool x_trans;            // x is the array itself: transformed as it is loaded
+};
+
+}  // namespace
+
+// HI, LO: the branches; CT: B is the conjugate transpose of the array's blocks
+template <int SRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
+__global__ __launch_bounds__(kThreads, 2) void corr_kspace_kernel(Dims d, CorrArgs g, const double* __restrict__ A,
+                                                                  const int32_t* __restrict__ nbr, cd scale, CorrTile t,
+                                                                  int64_t a0, double* __restrict__ out) {
+    extern __shared__ __align__(16) double smem[];
+    const int n = (int)d.norb, nkz = (int)d.nkz, nw = (int)d.nw, ne = (int)d.ne, nb = (int)d.nb;
+    const int nn = n * n, np = ks::row_len(n), eb = t.eb;
+    cd* sY = reinterpret_cast<cd*>(smem);  // [plane][j][r][c], plane 0 at energy e0 - halo_lo
+    cd* sX = sY + t.y_entries;             // [e][i][r][c]
+    cd* sG = sX + t.x_entries;             // rows of g [e][r][np]
+    cd* tw = sG + eb * t.rc * np;
+    int* bad = reinterpret_cast<int*>(tw + nkz);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the workgroups of an atom on one XCD: they read the same blocks of g
+    const int per = nb * nkz * t.nwg, s = blockIdx.x >> 3;
+    const int64_t a = a0 + s / per * 8 + (blockIdx.x & 7);
+    if (a >= d.na) return;  // uniform, before any barrier
+    int rem = s % per;
+    const int wg = rem % t.nwg;
+    rem /= t.nwg;
+    const int m = rem / nkz, kt = rem % nkz;
+    const int64_t edge = a * nb + m, edges = d.na * nb;
+    const int32_t b = __builtin_amdgcn_readfirstlane(nbr[edge]);
+    const bool valid = b >= 0 && b < d.na;
+
+    // this thread's sums: entry el, direction j, frequencies w0 + 1 .. w0 + WB, share es
+    const int el = tid % t.nel, rest = tid / t.nel;
+    const int wb = rest % t.nwb, j = rest / t.nwb % 3, es = rest / t.nwb / 3;
+    const int w0 = (wg * t.nwb + wb) * WB;
+    cd acc[3][WB];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int u = 0; u < WB; ++u) acc[i][u] = cd{0.0, 0.0};
+
+    if (valid) {
+        ks::stage_twiddles(tw, nkz, tid, kThreads);
+        if (tid == 0) *bad = 0;
+        const double* Af = A + 6 * edge * nn;
+        const ks::Source ys{g.y + 2 * a * g.y_atom, g.y_kst, g.y_est};
+        const double* xs = g.x + 2 * b * g.x_atom;
+        for (int kp = 0; kp < (DIRECT ? nkz : 1); ++kp) {
+            const int ky = DIRECT ? (kp + kt) % nkz : kt;
+            const int kx = DIRECT ? kp : CT ? (nkz - kt) % nkz : kt;
+            for (int r0 = 0; r0 < n; r0 += t.rc) {
+                const int rc = n - r0 < t.rc ? n - r0 : t.rc, last = rc < t.rc;
+                const int nel = rc * n, ps = 3 * nel;  // entries of a plane
+                // rows of `count` energies from `energy` on into the planes from `plane` on
+                auto fill = [&](int plane, int energy, int count) {
+                    __syncthreads();
+                    ks::load_rows<kThreads, SRC, false>(ys, tw, nkz, ky, energy - g.first, count, g.n_e, r0, rc, n, t.by_row[last],
+                                                        t.by_n, sG, tid);
+                    __syncthreads();
+                    const int rows = count * rc;
+                    for (int jj = 0; jj < 3; ++jj) {
+                        auto dst = [&](int row) {
+                            const int ew = t.by_rc[last].quot(row);
+                            return sY + (plane + ew) * ps + jj * nel + (row - ew * rc) * n;
+                        };
+                        const int w = (wave + 2 * jj) % kWaves;
+                        if (rows <= 64)
+                            ks::right_product<kWaves, 1, kCB, false>(sG, Af + 2 * jj * nn, rows, n, t.ncb, t.by_ncb, w, lane, dst);
+                        else
+                            ks::right_product<kWaves, 2, kCB, false>(sG, Af + 2 * jj * nn, rows, n, t.ncb, t.by_ncb, w, lane, dst);
+                    }
+                };
+                for (int p = 0; p < t.halo_lo + t.halo_hi; p += eb) {
+                    const int left = t.halo_lo + t.halo_hi - p;
+                    fill(p, g.lo - t.halo_lo + p, left < eb ? left : eb);
+                }
+                for (int e0 = g.lo; e0 < g.hi; e0 += eb) {
+                    const int e_n = g.hi - e0 < eb ? g.hi - e0 : eb;
+                    fill(t.halo_lo + t.halo_hi, e0 + t.halo_hi, eb);
+                    // X_i[e][r][c] = sum_t A_i[r0 + r][t] B[e][t][c]; two columns (e, c) per lane, B from memory
+                    const int ncol = e_n * n, nout = 3 * rc, nob = (nout + kXB - 1) / kXB;
+                    const int tasks = (ncol + 127) / 128 * nob;
+                    for (int task = wave; task < tasks; task += kWaves) {
+                        const int tc = t.by_xb[last].quot(task), o0 = (task - tc * nob) * kXB;
+                        const double* p[2];
+                        int col[2], e[2];
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            col[h] = tc * 128 + 64 * h + lane;
+                            const int x = col[h] < ncol ? col[h] : 0;
+                            e[h] = t.by_n.quot(x);
+                            const int c = x - e[h] * n;
+                            p[h] = xs + 2 * ((g.x_trans ? 0 : kx * g.x_kst) + (int64_t)(e0 - g.first + e[h]) * g.x_est + (CT ? c * n : c));
+                        }
+                        cd v[2][kXB];
+#pragma unroll
+                        for (int o = 0; o < kXB; ++o) v[0][o] = v[1][o] = cd{0.0, 0.0};
+                        const int fo = o0 + ks::uniform_entry<kXB>(lane), oo = fo < nout ? fo : nout - 1;
+                        const int fi = oo >= 2 * rc ? 2 : oo >= rc ? 1 : 0;
+                        const double* f = Af + 2 * (fi * nn + (r0 + oo - fi * rc) * n) + (lane & 1);
+                        ks::uniform_product<2, kXB, false, true>(v, n, [&](int q) { return f[2 * q]; }, [&](int q, cd (&x)[2]) {
+                            const int64_t at = CT ? q : q * n;
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) {
+                                if (g.x_trans) {
+                                    x[h] = cd{0.0, 0.0};
+                                    int mm = 0;
+                                    for (int k = 0; k < nkz; ++k) {
+                                        cfma(x[h], cload(p[h], k * g.x_kst + at), ks::ld(tw + mm));
+                                        mm += kx;
+                                        mm -= mm >= nkz ? nkz : 0;
+                                    }
+                                } else {
+                                    x[h] = cload(p[h], at);
+                                }
+                                if constexpr (CT) x[h].im = -x[h].im;
+                            }
+                        });
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            if (col[h] >= ncol) continue;
+                            cd* dst = sX + e[h] * ps + col[h] - e[h] * n;
+                            bool fin = true;
+#pragma unroll
+                            for (int o = 0; o < kXB; ++o) {
+                                if (o0 + o >= nout) continue;
+                                ks::st(dst + (o0 + o) * n, v[h][o]);
+                                fin = fin && fabs(v[h][o].re) <= 1.7976931348623157e308 && fabs(v[h][o].im) <= 1.7976931348623157e308;
+                            }
+                            if (!fin) *bad = 1;
+                        }
+                    }
+                    __syncthreads();
+                    const int share = eb / t.es, mine = e_n - es * share;
+                    const int cnt = es < t.es && el < nel ? (mine < share ? mine : share) : 0;
+                    const cd* X = sX + es * share * ps + el;
+                    const cd* Yc = sY + (es * share + t.halo_lo) * ps + j * nel + el;  // plane of the first energy
+                    if (*bad == 0) {
+                        const cd* ph = Yc + (w0 + 1) * ps;
+                        const cd* pl = Yc - (w0 + 1) * ps;
+                        cd hi[WB], lo[WB];
+                        if (cnt > 0) {
+                            if constexpr (HI) {
+#pragma unroll
+                                for (int u = 0; u + 1 < WB; ++u) hi[u] = ks::ld(ph + u * ps);
+                            }
+                            if constexpr (LO) {
+#pragma unroll
+                                for (int u = 1; u < WB; ++u) lo[(WB - u) % WB] = ks::ld(pl - u * ps);
+                            }
+                        }
+                        ph += (WB - 1) * ps;
+                        auto step = [&](auto S) {
+                            constexpr int st = decltype(S)::value;
+                            if constexpr (HI) hi[(st + WB - 1) % WB] = ks::ld(ph);
+                            if constexpr (LO) lo[st % WB] = ks::ld(pl);
+                            cd x[3];
+#pragma unroll
+                            for (int i = 0; i < 3; ++i) x[i] = ks::ld(X + i * nel);
+#pragma unroll
+                            for (int u = 0; u < WB; ++u) {
+                                cd y;
+                                if constexpr (HI && LO) {
+                                    const cd h = hi[(st + u) % WB], l = lo[(st + WB - u) % WB];
+                                    y = cd{h.re + l.re, h.im + l.im};
+                                } else if constexpr (HI) {
+                                    y = hi[(st + u) % WB];
+                                } else {
+                                    y = lo[(st + WB - u) % WB];
+                                }
+#pragma unroll
+                                for (int i = 0; i < 3; ++i) cfma_conja(acc[i][u], x[i], y);
+                            }
+                            X += ps;
+                            ph += ps;
+                            pl += ps;
+                        };
+                        int left = cnt;
+                        for (; left >= WB; left -= WB) {
+                            step(std::integral_constant<int, 0>{});
+                            if constexpr (WB > 1) step(std::integral_constant<int, 1>{});
+                            if constexpr (WB > 2) step(std::integral_constant<int, 2>{});
+                            if constexpr (WB > 3) step(std::integral_constant<int, 3>{});
+                            if constexpr (WB > 4) step(std::integral_constant<int, 4>{});
+                        }
+                        if (left > 0) step(std::integral_constant<int, 0>{});
+                        if constexpr (WB > 2)
+                            if (left > 1) step(std::integral_constant<int, 1>{});
+                        if constexpr (WB > 3)
+                            if (left > 2) step(std::integral_constant<int, 2>{});
+                        if constexpr (WB > 4)
+                            if (left > 3) step(std::integral_constant<int, 3>{});
+                    } else {
+                        // a term outside the grid is left out instead of multiplied by a zero block
+                        for (int e = 0; e < cnt; ++e) {
+                            const int E = e0 + es * share + e;
+#pragma unroll
+                            for (int u = 0; u < WB; ++u) {
+                                const int w = w0 + 1 + u;
+                                if (w > nw) continue;
+#pragma unroll
+                                for (int i = 0; i < 3; ++i) {
+                                    const cd x = ks::ld(X + e * ps + i * nel);
+                                    if (HI && E + w < ne) cfma_conja(acc[i][u], x, ks::ld(Yc + (e + w) * ps));
+                                    if (LO && E - w >= 0) cfma_conja(acc[i][u], x, ks::ld(Yc + (e - w) * ps));
+                                }
+                            }
+                        }
+                    }
+                    // the planes that the next tile's window keeps
+                    const int keep = (t.halo_lo + t.halo_hi) * ps, from = eb * ps;
+                    for (int x0 = 0; x0 < keep; x0 += 4 * kThreads) {
+                        cd v[4];
+                        __syncthreads();
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int x = x0 + u * kThreads + tid;
+                            if (x < keep) v[u] = ks::ld(sY + from + x);
+                        }
+                        __syncthreads();
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int x = x0 + u * kThreads + tid;
+                            if (x < keep) ks::st(sY + x, v[u]);
+                        }
+                    }
+                }
+            }
+        }
+    }
+    // the lanes' sums, one direction i at a time, in the order of (share, entry)
+    cd* red = sY;
+    const int outs = 3 * t.nwb * WB;
+    for (int i = 0; i < 3; ++i) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < WB; ++u) ks::st(red + u * kThreads + tid, i == 0 ? acc[0][u] : i == 1 ? acc[1][u] : acc[2][u]);
+        __syncthreads();
+        for (int o = tid; o < outs; o += kThreads) {
+            const int u = o % WB, wo = o / WB % t.nwb, jo = o / WB / t.nwb;
+            const int w = (wg * t.nwb + wo) * WB + u;
+            if (w >= nw) continue;
+            cd sum{0.0, 0.0};
+            for (int se = 0; se < t.es; ++se) {
+                const cd* p = red + u * kThreads + ((se * 3 + jo) * t.nwb + wo) * t.nel;
+                for (int x = 0; x < t.nel; ++x) {
+                    const cd v = ks::ld(p + x);
+                    sum.re += v.re;
+                    sum.im += v.im;
+                }
+            }
+            const int64_t at = (((int64_t)kt * nw + w) * edges + edge) * 9 + i * 3 + jo;
+            if (DIRECT) sum = cmul(scale, sum);
+            if (g.add) {
+                const cd old = cload(out, at);
+                sum = cd{old.re + sum.re, old.im + sum.im};
+            }
+            cstore(out, at, sum);
+        }
+    }
+}
+
+// frequencies per lane: the block that divides nw with the least left over, the larger one of equals
+static int freq_block(int64_t nw) {
+    int best = 2;
+    for (int wb = 3; wb <= 5; ++wb)
+        if ((nw + wb - 1) / wb * wb <= (nw + best - 1) / best * best) best = wb;
+    return best;
+}
+
+// the tile with the least time under the quantisation of each step
+static bool corr_tile(const Dims& d, bool hi, bool lo, CorrTile* best) {
+    const int n = (int)d.norb, wb = freq_block(d.nw), np = ks::row_len(n);
+    const int64_t nwb_all = (d.nw + wb - 1) / wb;
+    if (d.norb > 32 || d.nkz > 128 || d.nw > 4096 || d.ne >= (int64_t(1) << 28) || d.nb >= (1 << 20)) return false;
+    auto up = [](double a, double b) { return (double)(int64_t)((a + b - 1) / b); };
+    double best_cost = 0.0;
+    bool found = false;
+    for (int rc = 1; rc <= n && 3 * rc * n <= kThreads; ++rc) {
+        CorrTile t{};
+        const int nel = rc * n;
+        t.rc = rc;
+        t.nel = nel;
+        t.nwb = (int)std::min<int64_t>(nwb_all, kThreads / (3 * nel));
+        t.nwg = (int)((nwb_all + t.nwb - 1) / t.nwb);
+        const int max_es = kThreads / (3 * nel * t.nwb);
+        t.halo_lo = lo ? (int)nwb_all * wb : 0;
+        t.halo_hi = hi ? (int)nwb_all * wb : 0;
+        t.ncb = (n + kCB - 1) / kCB;
+        const int tail = n % rc ? n % rc : rc;
+        t.by_n = ks::Div(n);
+        t.by_ncb = ks::Div(t.ncb);
+        t.by_xb[0] = ks::Div((3 * rc + kXB - 1) / kXB);
+        t.by_xb[1] = ks::Div((3 * tail + kXB - 1) / kXB);
+        t.by_rc[0] = ks::Div(rc);
+        t.by_rc[1] = ks::Div(tail);
+        t.by_row[0] = ks::Div(nel);
+        t.by_row[1] = ks::Div(tail * n);
+        for (int es = 1; es <= max_es; ++es)
+            for (int eb = es; eb <= 128; eb += es) {
+                if (eb > es && eb - es >= d.ne) break;
+                const int64_t y = (int64_t)(eb + t.halo_lo + t.halo_hi) * 3 * nel, x = (int64_t)eb * 3 * nel;
+                const int64_t all = std::max<int64_t>(y + x + (int64_t)eb * rc * np, wb * kThreads) + d.nkz + 1;
+                if (all > (int64_t)(kLdsMax / sizeof(cd))) break;
+                t.eb = eb;
+                t.es = es;
+                t.y_entries = (int)y;
+                t.x_entries = (int)x;
+                t.lds = sizeof(cd) * (size_t)all;
+                const int occ = t.lds <= kLdsMax / 2 ? 2 : 1;
+                const int r = eb * rc <= 64 ? 1 : 2;
+                // vector instructions per tile and chunk, of the whole workgroup and of its busiest
+                // wave in each step, and those of the prologue of a chunk
+                const double halo = t.halo_lo + t.halo_hi;
+                const double s1 = (eb / es) * (wb * (hi && lo ? 14.0 : 12.0) + 10);
+                const double r1 = n * kCB * 4.4 * r + 80, rt = 3 * up((double)eb * rc, 64 * r) * t.ncb;
+                const double l1 = n * kXB * 8.8 + 150, lt = up((double)eb * n, 128) * up(3.0 * rc, kXB);
+                const double fixed = 400 + 25 * up((double)eb * nel, kThreads) + 4 * up(halo * 3 * nel, kThreads);
+                const double total = up(3.0 * nel * t.nwb * es, 64) * s1 + rt * r1 + lt * l1 + kWaves * fixed;
+                const double longest = s1 + up(rt, kWaves) * r1 + up(lt, kWaves) * l1 + fixed + 1500;
+                const double tile = total / kWaves + longest / occ;
+                const double fill = up(halo, eb) * (rt * r1 / kWaves + 1000);
+                const double cost = up(n, rc) * (up((double)d.ne, eb) * tile + fill) * t.nwg;
+                if (!found || cost < best_cost) {
+                    best_cost = cost;
+                    *best = t;
+                    found = true;
+                }
+            }
+    }
+    return found;
+}
+
+bool corr_kspace_supported(const Dims& d, bool both) {
+    CorrTile t;
+    return corr_tile(d, true, both, &t);
+}
+
+template <int SRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
+static hipError_t launch_corr_wb(const Dims& d, const CorrArgs& g, const double* A, const int32_t* nbr, cd scale,
+                                 const CorrTile& t, double* out, hipStream_t stream) {
+    auto kern = corr_kspace_kernel<SRC, DIRECT, HI, LO, CT, WB>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds);
+    if (e != hipSuccess) return e;
+    const int64_t per = d.nb * d.nkz * t.nwg;
+    if (per > (int64_t(1) << 26)) return hipErrorInvalidValue;
+    const int64_t na8 = (d.na + 7) / 8 * 8, step = std::max<int64_t>(8, ((int64_t)1 << 30) / per / 8 * 8);
+    for (int64_t a0 = 0; a0 < na8; a0 += step)
+        hipLaunchKernelGGL(kern, dim3((unsigned)(std::min(step, na8 - a0) * per)), dim3(kThreads), t.lds, stream, d, g, A, nbr,
+                           scale, t, a0, out);
+    return hipGetLastError();
+}
+
+template <int SRC, bool DIRECT, bool HI, bool LO, bool CT, class... Args>
+static hipError_t launch_corr_shape(int wb, Args... args) {
+    switch (wb) {
+        case 2: return launch_corr_wb<SRC, DIRECT, HI, LO, CT, 2>(args...);
+        case 3: return launch_corr_wb<SRC, DIRECT, HI, LO, CT, 3>(args...);
+        case 4: return launch_corr_wb<SRC, DIRECT, HI, LO, CT, 4>(args...);
+        default: return launch_corr_wb<SRC, DIRECT, HI, LO, CT, 5>(args...);
+    }
+}
+
+template <int SRC, bool DIRECT, class... Args>
+static hipError_t launch_corr(bool phonon, int branches, int wb, Args... args) {
+    if (phonon) return launch_corr_shape<SRC, DIRECT, true, false, true>(wb, args...);
+    if (branches == 3) return launch_corr_shape<SRC, DIRECT, true, true, false>(wb, args...);
+    if (branches == 1) return launch_corr_shape<SRC, DIRECT, true, false, false>(wb, args...);
+    return launch_corr_shape<SRC, DIRECT, false, true, false>(wb, args...);
+}
+
+hipError_t launch_dd_kspace(const Dims& d, int branches, const double* g, const double* g_hat, const double* G,
+                            const double* G_hat, const double* A, const int32_t* nbr, cd calpha, double* dD,
+                            hipStream_t stream) {
+    CorrTile t;
+    if (!corr_tile(d, (branches & 1) != 0, (branches & 2) != 0, &t)) return hipErrorInvalidValue;
+    const int wb = freq_block(d.nw);
+    const int64_t nn = d.norb * d.norb, ne = d.ne, na = d.na, x_atom = d.gs * nn;
+    CorrArgs a{g, G, nn, ne * na * nn, na * nn, x_atom, ne * na * x_atom, na * x_atom, 0, (int)ne, 0, (int)ne, false, !G_hat};
+    if (g_hat) {
+        a.y = g_hat;
+        a.y_atom = ne * nn;
+        a.y_kst = na * ne * nn;
+        a.y_est = nn;
+    }
+    if (G_hat) {
+        a.x = G_hat;
+        a.x_atom = ne * nn;
+        a.x_kst = na * ne * nn;
+        a.x_est = nn;
+    }
+    hipError_t e = g_hat ? launch_corr<ks::kDirect, false>(false, branches, wb, d, a, A, nbr, calpha, t, dD, stream)
+                         : launch_corr<ks::kTrans, false>(false, branches, wb, d, a, A, nbr, calpha, t, dD, stream);
+    if (e != hipSuccess) return e;
+    return launch_inverse((int)d.nkz, d.nw * na * d.nb, 9, 9, cd{calpha.re / (double)d.nkz, calpha.im / (double)d.nkz}, dD, stream);
+}
+
+hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, const double* A, const int32_t* nbr, cd beta,
+                            double* Pi, bool transform, void* ws, size_t ws_bytes, hipStream_t stream) {
+    CorrTile t;
+    if (!corr_tile(d, true, false, &t)) return hipErrorInvalidValue;
+    const int wb = freq_block(d.nw), nkz = (int)d.nkz;
+    const int64_t nn = d.norb * d.norb, ne = d.ne, na = d.na, atom = d.gs * nn, est = na * atom;
+    CorrArgs g{Gs, Go, atom, ne * est, est, atom, ne * est, est, 0, (int)ne, 0, (int)ne, false, false};
+    if (!transform) return launch_corr<ks::kDirect, true>(true, 1, wb, d, g, A, nbr, beta, t, Pi, stream);
+    // room for energies of a transform: both arrays whole, or slabs of whole tiles of
+    // energies of both (with the nw energies above for Gs), or neither
+    hipError_t e = hipSuccess;
+    const int64_t per = 16 * d.nkz * na * nn, room = (int64_t)(ws_bytes / (size_t)per);
+    const int64_t step = room >= 2 * ne ? ne : (room - d.nw) / 2 / t.eb * t.eb;
+    if (step >= std::min<int64_t>(ne, t.eb)) {
+        double* hy = static_cast<double*>(ws);
+        for (int64_t lo = 0; lo < ne && e == hipSuccess; lo += step) {
+            const int64_t hi = std::min(ne, lo + step), n_y = std::min(ne, hi + d.nw) - lo, n_x = hi - lo;
+            double* hx = hy + per / 8 * n_y;
+            e = launch_transform(nkz, lo, n_y, na, nn, atom, est, ne * est, Gs, hy, stream);
+            if (e == hipSuccess) e = launch_transform(nkz, lo, n_x, na, nn, atom, est, ne * est, Go, hx, stream);
+            if (e != hipSuccess) return e;
+            g = CorrArgs{hy, hx, n_y * nn, na * n_y * nn, nn, n_x * nn, na * n_x * nn, nn,
+                         (int)lo, (int)hi, (int)lo, (int)n_y, lo > 0, false};
+            e = launch_corr<ks::kDirect, false>(true, 1, wb, d, g, A, nbr, beta, t, Pi, stream);
+        }
+    } else {
+        g.x_trans = true;
+        e = launch_corr<ks::kTrans, false>(true, 1, wb, d, g, A, nbr, beta, t, Pi, stream);
+    }
+    if (e != hipSuccess) return e;
+    return launch_inverse(nkz, d.nw * na * d.nb, 9, 9, cd{beta.re / (double)d.nkz, beta.im / (double)d.nkz}, Pi, stream);
+}
+
+// both transforms, or (Pi) slabs of at most 8 GiB of them
+size_t corr_kspace_workspace(const Dims& d) {
+    constexpr int64_t kSlabBytes = int64_t(8) << 30;
+    if (d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks || !corr_kspace_supported(d, true)) return 0;
+    const int64_t per = 16 * d.nkz * d.na * d.norb * d.norb;
+    return (size_t)(per * std::min(2 * d.ne, std::max(kSlabBytes / per, 256 + 4 * d.nw)));
+}
+
+}  // namespace sse

@@ -40,6 +40,32 @@ hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, c
                              const double* B, const int32_t* nbr, cd alpha, double* S, bool transform, void* ws,
                              size_t ws_bytes, hipStream_t stream);
 
+// Pi in the momentum transform, any shape.  transform as for launch_fwd_kspace; ws holds
+// the transforms of Gs and Go, or slabs of energies of them, whose sums are added in
+// order (their last bits then depend on the room)
+bool corr_kspace_supported(const Dims& d, bool both);
+size_t corr_kspace_workspace(const Dims& d);
+hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, const double* A, const int32_t* nbr, cd beta,
+                            double* Pi, bool transform, void* ws, size_t ws_bytes, hipStream_t stream);
+
+// The adjoint in the momentum transform, any shape.  g_hat, G_hat: the whole transforms
+// of g = dL/dSigma and G (launch_transform), or NULL: every workgroup transforms what
+// it loads (the same sums, bit for bit).
+// dG from the in-edges of every atom; the one-table form passes Dm = Dp
+hipError_t launch_dg_kspace(const Dims& d, const double* g, const double* g_hat, const double* Dp, const double* Dm,
+                            const double* A, const int32_t* offset, const int32_t* edges, const int32_t* order, cd calpha,
+                            double* dG, hipStream_t stream);
+// d gradH: one share per edge and part of the (momenta, energies), added by the caller;
+// by_energy: a share holds all momenta of 32 energies, else all energies of a momentum
+bool dh_kspace_supported(const Dims& d);
+hipError_t launch_dh_kspace(const Dims& d, const double* g, const double* g_hat, const double* G, const double* G_hat,
+                            const double* Dp, const double* Dm, const double* A, const int32_t* nbr, cd alpha,
+                            bool by_energy, double* shares, hipStream_t stream);
+// dD; branches: 1 the terms with G at E - w (coefficients at +w), 2 those with G at E + w, 3 both
+hipError_t launch_dd_kspace(const Dims& d, int branches, const double* g, const double* g_hat, const double* G,
+                            const double* G_hat, const double* A, const int32_t* nbr, cd calpha, double* dD,
+                            hipStream_t stream);
+
 // matrix-core forward (fp64 or fp32 operands; the split 16-bit forms go to
 // launch_fwd_h16) for the shapes it is
 // instantiated for; flags selects the energy branches (kBranchMinus,
@@ -63,24 +89,15 @@ hipError_t launch_fwd_h16(const Dims& d, int precision, const double* G, const d
 // read Dm and feed dDm; otherwise Dp is the one table and dDp its gradient (Dm,
 // dDm unused).
 size_t bwd_workspace_bytes(const Dims& d);  // enough for either form, with every gradient
-// what one call uses: the reverse adjacency, plus the d gradH shares if that
-// gradient is asked for, plus the atom-major copy of g if the D gradient of the
-// one-table form is asked for with copy_g (on the dims that take it: pse_atom_major_ok)
-size_t bwd_workspace_bytes_for(const Dims& d, bool signed_form, bool with_dh, bool with_dd = false,
-                               bool copy_g = false);
+// what one call requires: the reverse adjacency, plus the d gradH shares if that
+// gradient is asked for, plus (with_hat) the transform of g on the shapes of the
+// matrix-core forward with 3 or 4 neighbours
+size_t bwd_workspace_bytes_for(const Dims& d, bool signed_form, bool with_dh, bool with_hat);
+size_t bwd_fast_workspace_bytes(const Dims& d);  // what a call is fastest with
 bool bwd_supported(const Dims& d);
-// dG and d gradH of the one-table form on the matrix cores (Norb = 10, Nkz = Nqz = 7,
-// Nw = 10): one workgroup per (neighbour atom, range of energies), one d gradH
-// share per range (bwd_mfma_shares of them) in dApart
-bool bwd_mfma_specialised(const Dims& d);
-int64_t bwd_mfma_shares(const Dims& d);
-hipError_t bwd_mfma_prepare();
-hipError_t launch_bwd_mfma(const Dims& d, const double* G, const double* D, const double* A, const double* gS, cd calpha,
-                           const int32_t* offset, const int32_t* edges, const int32_t* order, double* dG,
-                           double* dApart, hipStream_t stream);
 hipError_t launch_bwd(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
                       const int32_t* nbr, cd alpha, const double* gS, double* dG, double* dDp, double* dDm, double* dA,
-                      void* ws, hipStream_t stream, bool signed_form, bool copy_g);
+                      void* ws, size_t ws_bytes, hipStream_t stream, bool signed_form);
 
 // absorption-branch coefficients: Dm[q,w,a,n,i,j] = Dopp[(-q) mod nqz, w, a, n, j, i]
 hipError_t launch_absorption_d(const Dims& d, const double* Dopp, double* Dm, hipStream_t stream);
@@ -97,23 +114,11 @@ bool pse_mfma_specialised(const Dims& d);
 bool pse_generic_supported(const Dims& d);
 hipError_t launch_pse(const Dims& d, const double* Gs, const double* Go, const double* A, const int32_t* nbr, cd beta,
                       double* Pi, hipStream_t stream);
-// the D gradient of the adjoint on the same matrix-core kernel (shapes with
-// pse_mfma_specialised); branches: 1 the terms with G at E - w (coefficients at
-// +w), 2 those with G at E + w (at -w), 3 both (the one-table form).  gT: the
-// atom-major copy of gS written by pse_atom_major_g (read in its place), or NULL
-hipError_t launch_dd_mfma(const Dims& d, const double* G, const double* A, const int32_t* nbr, const double* gS,
-                          const double* gT, cd calpha, double* dD, hipStream_t stream, int branches = 3);
-// the atom-major copy of g for the D gradient: whether these dims take it, its
-// bytes (0 when they do not), and the copy itself (every byte written)
-bool pse_atom_major_ok(const Dims& d);
-size_t pse_atom_major_bytes(const Dims& d);
-hipError_t pse_atom_major_g(const Dims& d, const double* g, double* gT, hipStream_t stream);
-
-// sse_backward with copy_g = true; false: the D gradient reads g in the caller's
-// layout and the workspace holds no copy of it (sse_backward_noalloc)
+// sse_backward; with_hat = false: a workspace without the transform of g will do
+// (sse_backward_noalloc)
 int backward_one_table(const sse_dims* dims, const double* G, const double* D, const double* dH, const int32_t* nbr,
                        double alpha_re, double alpha_im, const double* dSigma, double* dG, double* dD, double* ddH,
-                       void* workspace, size_t workspace_bytes, void* stream, bool copy_g);
+                       void* workspace, size_t workspace_bytes, void* stream, bool with_hat);
 
 // sets the thread-local text that sse_last_error returns; returns code
 int set_error(int code, const char* fmt, ...);

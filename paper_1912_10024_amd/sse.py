@@ -69,9 +69,25 @@ def workspace(d: Dims, precision: str = "fp64", backward: bool = False, device="
     nbytes = ctypes.c_size_t(0)
     cd = _lib.SSEDims.of(d)
     op = int(backward) if op is None else op
+    if op == 1:
+        ws = _fast_workspace(cd, op, device)
+        if ws is not None:
+            return ws
     _raise(lib.sse_workspace_bytes(ctypes.byref(cd), PRECISIONS.get(precision, -1), op, ctypes.byref(nbytes)),
            "sse_workspace_bytes")
     return torch.empty(max(int(nbytes.value), 1), dtype=torch.uint8, device=device)
+
+
+def _fast_workspace(cd, op: int, device):
+    """The workspace a call is fastest with, or None where there is no room for it."""
+    nbytes = ctypes.c_size_t(0)
+    _raise(_lib.load().sse_fast_workspace_bytes(ctypes.byref(cd), op, ctypes.byref(nbytes)), "sse_fast_workspace_bytes")
+    if nbytes.value == 0:
+        return None
+    try:
+        return torch.empty(int(nbytes.value), dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
 
 
 def effective_flops(d: Dims) -> float:
@@ -229,8 +245,9 @@ def phonon_forward(Gs, Go, dH, nbr, nqz: int, nw: int, beta=-1j, out=None) -> to
     lib = _lib.load()
     cd = _lib.SSEDims.of(d)
     b = complex(beta)
-    rc = lib.sse_phonon_forward(ctypes.byref(cd), _ptr(Gs), _ptr(Go), _ptr(dH), _ptr(nbr), b.real, b.imag, _ptr(out),
-                                _stream(Gs.device))
+    ws = _fast_workspace(cd, 3, Gs.device)
+    rc = lib.sse_phonon_forward_ws(ctypes.byref(cd), _ptr(Gs), _ptr(Go), _ptr(dH), _ptr(nbr), b.real, b.imag, _ptr(out),
+                                   _ptr(ws), ws.numel() if ws is not None else 0, _stream(Gs.device))
     _raise(rc, "sse_phonon_forward")
     return out
 

@@ -138,3 +138,124 @@ def test_problems_of_a_thousand_blocks_keep_exact_sums():
     t = _gpu(x)
     S = sse.forward(t["G"], t["D"], t["dH"], t["nbr"], alpha=1.0).cpu().numpy()
     assert np.array_equal(S, oracle.sse_forward(d, x["G"], x["D"], x["dH"], x["nbr"], alpha=1.0))
+
+
+# ------------------------------------------------------------------ Pi
+PI_SHAPES = [s for i, s in enumerate(SHAPES) if i not in (6,)] + [
+    (Dims(nkz=2, ne=180, nqz=2, nw=3, na=3, nb=2, norb=25, g_slots=1), 7),   # the largest norb Pi takes
+    (Dims(nkz=7, ne=61, nqz=7, nw=10, na=4, nb=3, norb=10, g_slots=2), 13),
+    (Dims(nkz=3, ne=100, nqz=3, nw=7, na=4, nb=2, norb=9, g_slots=1), 14),   # blocks of 4 over 7 frequencies
+]
+
+
+@pytest.mark.parametrize("d,seed", PI_SHAPES, ids=["x".join(map(str, d.as_tuple())) for d, _ in PI_SHAPES])
+def test_pi_matches_the_oracle(d, seed):
+    print(f"[gpu] kspace pi dims={d.as_tuple()}", flush=True)
+    rng = np.random.default_rng(seed + 100)
+    x = _inputs(d, seed)
+    x["Go"] = _cn(rng, d.g_shape)
+    x["nbr"][1, 0] = d.na + 2
+    t = _gpu(x)
+    P = sse.phonon_forward(t["G"], t["Go"], t["dH"], t["nbr"], d.nqz, d.nw, beta=0.2 - 0.9j).cpu().numpy()
+    x["nbr"][1, 0] = 0
+    ref = oracle.pse_forward(d, x["G"], x["Go"], x["dH"], x["nbr"], beta=0.2 - 0.9j)
+    assert np.array_equal(P[:, :, 1, 0], np.zeros_like(P[:, :, 1, 0]))
+    ref[:, :, 1, 0] = 0
+    assert _rel(P, ref) <= TOL
+
+
+def _pi_ws(t, d, nbytes):
+    """Pi through the C entry with a workspace of nbytes."""
+    import ctypes
+
+    from paper_1912_10024_amd import _lib
+    out = torch.full(d.d_shape, complex(float("nan"), float("nan")), dtype=torch.complex128, device="cuda")
+    ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device="cuda")
+    P = lambda v: ctypes.c_void_p(v.data_ptr())
+    rc = _lib.load().sse_phonon_forward_ws(ctypes.byref(_lib.SSEDims.of(d)), P(t["G"]), P(t["Go"]), P(t["dH"]), P(t["nbr"]),
+                                           0.0, -1.0, P(out), P(ws), nbytes, ctypes.c_void_p(0))
+    torch.cuda.synchronize()
+    assert rc == 0
+    return out.cpu().numpy()
+
+
+def test_pi_workspaces():
+    d = Dims(nkz=3, ne=140, nqz=3, nw=6, na=5, nb=2, norb=6, g_slots=1)
+    print(f"[gpu] kspace pi workspaces dims={d.as_tuple()}", flush=True)
+    x = _inputs(d, 3)
+    x["Go"] = _cn(np.random.default_rng(4), d.g_shape)
+    t = _gpu(x)
+    ref = oracle.pse_forward(d, x["G"], x["Go"], x["dH"], x["nbr"])
+    per = 16 * d.nkz * d.na * d.norb ** 2
+    whole = _pi_ws(t, d, per * 2 * d.ne)
+    assert _rel(whole, ref) <= TOL
+    assert np.array_equal(_pi_ws(t, d, 0), whole)
+    for energies in (279, 200, 120):
+        assert _rel(_pi_ws(t, d, per * energies), ref) <= TOL, energies
+
+
+def test_pi_block_that_is_not_finite_stays_with_its_terms():
+    """A non-finite block of Go at energy E reaches the frequencies with E + w on the grid."""
+    d = Dims(nkz=2, ne=150, nqz=2, nw=12, na=4, nb=1, norb=3, g_slots=1)
+    print(f"[gpu] kspace pi non-finite dims={d.as_tuple()}", flush=True)
+    x = _inputs(d, 5)
+    x["Go"] = _cn(np.random.default_rng(6), d.g_shape)
+    b = int(x["nbr"][2, 0])
+    x["Go"][1, d.ne - 4, b, 0, 1, 1] = np.inf
+    t = _gpu(x)
+    P = sse.phonon_forward(t["G"], t["Go"], t["dH"], t["nbr"], d.nqz, d.nw)
+    ok = torch.isfinite(torch.view_as_real(P)).all(-1).all(-1).all(-1).all(0).cpu()   # [nw, na, nb]
+    for a in range(d.na):
+        hit = int(x["nbr"][a, 0]) == b
+        assert ok[3:, a].all()
+        assert bool(ok[:3, a].any()) != hit
+
+
+# ------------------------------------------------------------------ the adjoint
+ADJ_SHAPES = [s for i, s in enumerate(SHAPES) if i not in (6,)] + [
+    (Dims(nkz=2, ne=130, nqz=2, nw=3, na=5, nb=2, norb=16, g_slots=2), 15),  # the largest norb the adjoint takes
+]
+
+
+def _grads(d, seed):
+    x = _inputs(d, seed)
+    x["gS"] = _cn(np.random.default_rng(seed + 77), d.sigma_shape)
+    return x
+
+
+@pytest.mark.parametrize("d,seed", ADJ_SHAPES, ids=["x".join(map(str, d.as_tuple())) for d, _ in ADJ_SHAPES])
+def test_adjoint_matches_the_oracle(d, seed):
+    print(f"[gpu] kspace adjoint dims={d.as_tuple()}", flush=True)
+    x = _grads(d, seed)
+    t = _gpu(x)
+    alpha = -0.4 + 0.8j
+    got = sse.backward(t["G"], t["D"], t["dH"], t["nbr"], t["gS"], alpha=alpha)
+    ref = oracle.sse_backward(d, x["G"], x["D"], x["dH"], x["nbr"], x["gS"], alpha=alpha)
+    for name, g, r in zip(("dG", "dD", "ddH"), got, ref):
+        assert _rel(g.cpu().numpy(), r) <= TOL, name
+    got = sse.backward_signed(t["G"], t["D"], t["Dm"], t["dH"], t["nbr"], t["gS"], alpha=alpha)
+    ref = oracle.sse_backward_signed(d, x["G"], x["D"], x["Dm"], x["dH"], x["nbr"], x["gS"], alpha=alpha)
+    for name, g, r in zip(("dG", "dDp", "dDm", "ddH"), got, ref):
+        assert _rel(g.cpu().numpy(), r) <= TOL, name
+
+
+@pytest.mark.parametrize("d,seed", [SHAPES[0], SHAPES[1]], ids=IDS[:2])
+def test_adjoint_with_every_workspace_gives_the_same_bits(d, seed):
+    """Both transforms in the workspace, that of dSigma alone, or neither."""
+    import ctypes
+
+    from paper_1912_10024_amd import _lib
+    print(f"[gpu] kspace adjoint workspaces dims={d.as_tuple()}", flush=True)
+    t = _gpu(_grads(d, seed))
+    full = sse.backward(t["G"], t["D"], t["dH"], t["nbr"], t["gS"])
+    need = ctypes.c_size_t(0)
+    assert _lib.load().sse_workspace_bytes(ctypes.byref(_lib.SSEDims.of(d)), 0, 1, ctypes.byref(need)) == 0
+    hat = 16 * d.nkz * d.ne * d.na * d.norb ** 2 + 256
+    for nbytes in (need.value, need.value + hat, need.value + 2 * hat):
+        ws = torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda")
+        for a, b in zip(sse.backward(t["G"], t["D"], t["dH"], t["nbr"], t["gS"], ws=ws), full):
+            assert torch.equal(a, b), nbytes
+    got = sse.backward_noalloc(t["G"], t["D"], t["dH"], t["nbr"], t["gS"], dG=torch.empty_like(full[0]),
+                               dD=torch.empty_like(full[1]), ddH=torch.empty_like(full[2]))
+    for a, b in zip(got, full):
+        assert torch.equal(a, b)
