@@ -168,7 +168,7 @@ def kernel_source_hash(sources) -> str:
     return h.hexdigest()
 
 
-FWD_SOURCES = ("fwd_mfma.hip", "fwd_common.h", "sse_common.h")
+FWD_SOURCES = ("fwd_kspace.hip", "kspace.hip", "kspace.h", "sse_common.h")
 H16_SOURCES = ("fwd_h16.hip", "fwd_common.h", "sse_common.h")
 PSE_SOURCES = ("pse_kspace.hip", "kspace.h", "sse_common.h")
 BWD_SOURCES = ("bwd_kspace.hip", "fwd_kspace.hip", "kspace.h", "sse_common.h")
@@ -187,7 +187,7 @@ def recorded_traffic(record, sources):
 
 
 def fwd_mfma_dispatches(d, dev) -> int:
-    """Kernel dispatches of one fp64 / fp32 forward call: the atoms go in batches
+    """Kernel dispatches of one fp32 forward call: the atoms go in batches
     of about twelve rounds of workgroups (12 * compute units / Norb, a multiple of
     8), as launch_fwd_flags in fwd_mfma.hip issues them."""
     import torch
@@ -244,7 +244,7 @@ def phonon_record(args, sse, flops, d, G, dH, nbr, dev):
     P = torch.empty(d.d_shape, dtype=torch.complex128, device=dev)
     wall, kern_ms = time_phonon(sse, G, Go, dH, nbr, d, P, args.steps, args.warmup, dev)
     ms = float(np.mean(kern_ms))
-    useful = flops.pse_flops(d)
+    useful = flops.kspace_flops(d)
     rec = {
         "workload": f"electron-phonon SSE Pi^< forward ({args.config}), Gs = G<, Go = G>",
         "value": round(useful / (ms * 1e-3) / 1e12, 3),
@@ -252,14 +252,13 @@ def phonon_record(args, sse, flops, d, G, dH, nbr, dev):
         "kernel_ms": round(ms, 3),
         "kernel_ms_all": [round(x, 3) for x in kern_ms],
         "ms_per_step": round(wall * 1e3 / args.steps, 3),
-        "roofline": {"bound": "mfma", "achieved": round(useful / (ms * 1e-3) / 1e12, 3),
+        "roofline": {"bound": "alu", "achieved": round(useful / (ms * 1e-3) / 1e12, 3),
                      "peak": FP64_MFMA_PEAK / 1e12, "unit": "TFLOP/s",
                      "frac": round(useful / (ms * 1e-3) / FP64_MFMA_PEAK, 4),
                      "traffic": (recorded_traffic("pse_mfma_device_traffic.txt", PSE_SOURCES)
                                  if args.config == "device" else None),
                      "flops_per_launch": useful,
-                     "what": "useful fp64 flops: the trace contraction on the matrix cores plus T = gradH.Go.gradH^H "
-                             "on the vector ALUs (same fp64 peak)"},
+                     "what": "useful fp64 flops in the momentum transform (flops.kspace_flops), on the vector ALUs"},
     }
     if not args.no_cpu:
         rec["rel_err_vs_oracle_sampled"] = phonon_sample_error(d, G, Go, dH, nbr, P)
@@ -299,14 +298,13 @@ def adjoint_record(args, sse, dev):
     S = torch.empty(d.sigma_shape, dtype=torch.complex128, device=dev)
     fwd = timed(lambda: sse.forward(G, D, dH, nbr, out=S))
     bwd = timed(lambda: sse.backward(G, D, dH, nbr, gS, ws=ws))
-    # dG and d gradH alone: the matrix-core dG / d gradH kernel (plus the reverse
-    # adjacency and the share reduction, together under 0.1% of it)
+    # dG and d gradH alone (with the transforms, the reverse adjacency and the share reduction)
     dgdh = timed(lambda: sse.backward(G, D, dH, nbr, gS, need=(True, False, True), ws=ws))
     del inp, G, D, dH, nbr, gS, S, ws
     torch.cuda.empty_cache()
-    from paper_1912_10024_amd.flops import adjoint_dgdh_flops
+    from paper_1912_10024_amd.flops import kspace_flops
 
-    flops = adjoint_dgdh_flops(d)
+    flops = kspace_flops(d) + kspace_flops(d, products=12, sums=2)
     ms = float(np.mean(dgdh))
     achieved = flops / (ms * 1e-3) / 1e12
     return {"workload": "adjoint dL/dG, dL/dD, dL/d gradH of L = Re sum tr(W Sigma<) (mid: Nkz=7, NE=256, "
@@ -315,12 +313,11 @@ def adjoint_record(args, sse, dev):
             "forward_ms": round(float(np.mean(fwd)), 3),
             "ratio_to_forward": round(float(np.mean(bwd)) / float(np.mean(fwd)), 2),
             "ms_dg_dgradh": round(ms, 3),
-            "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": FP64_MFMA_PEAK / 1e12,
+            "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": FP64_MFMA_PEAK / 1e12,
                          "unit": "TFLOP/s", "frac": round(achieved * 1e12 / FP64_MFMA_PEAK, 4),
                          "traffic": recorded_traffic("bwd_mfma_mid_traffic.txt", BWD_SOURCES),
                          "flops_per_launch": flops,
-                         "what": "useful fp64 flops of the dG / d gradH kernel: Y = conj(alpha D) . W on the matrix "
-                                 "cores and the 27 block products built on it (flops.adjoint_dgdh_flops)"}}
+                         "what": "useful fp64 flops of dG and d gradH in the momentum transform (flops.kspace_flops)"}}
 
 
 def main():
@@ -400,15 +397,15 @@ def main():
         cpu, cpu_pts, cpu_ref = cpu_baseline(d, G, D, dH, nbr, args.cpu_seconds, f_block)
     peaks = {"fp64": FP64_MFMA_PEAK, "fp32": FP32_MFMA_PEAK, "bf16x2": FP16_MFMA_PEAK, "fp16x2": FP16_MFMA_PEAK,
              "fp16": FP16_MFMA_PEAK, "fp16_unscaled": FP16_MFMA_PEAK}
-    # fp64: the useful flops of the regrouped form (GEMM and all twelve products
-    # that form P; vector ALUs and matrix cores share the fp64 peak); fp32: the
+    # fp64: the useful flops of the form in the momentum transform (vector ALUs, whose
+    # fp64 peak is the matrix cores'); fp32: the
     # fp32 matrix-core work (GEMM and the nine right products); 16-bit forms: the
     # four hi/lo partial products of both on the 16-bit matrix cores
-    mfma_flops = {"fp64": flops.pd_useful_flops(d), "fp32": flops.pd_mfma_flops(d),
+    mfma_flops = {"fp64": flops.kspace_flops(d), "fp32": flops.pd_mfma_flops(d),
                   "bf16x2": flops.split16_mfma_flops(d), "fp16x2": flops.split16_mfma_flops(d),
                   "fp16": flops.single16_mfma_flops(d), "fp16_unscaled": flops.single16_mfma_flops(d)}
-    whats = {"fp64": "useful fp64 flops: P.D GEMM + the 12 products forming P (X on the vector ALUs, X.gradH^H on "
-                     "the matrix cores; one shared fp64 peak)",
+    whats = {"fp64": "useful fp64 flops in the momentum transform: 6 products with grad H and the sum over frequencies "
+                     "and directions per (edge, momentum, energy), on the vector ALUs (flops.kspace_flops)",
              "fp32": "fp32 matrix-core flops: P.D GEMM + P = X.gradH^H products",
              "bf16x2": "16-bit matrix-core flops: 4 hi/lo products of the P.D GEMM and of P = X.gradH^H",
              "fp16x2": "16-bit matrix-core flops: 4 hi/lo products of the P.D GEMM and of P = X.gradH^H",
@@ -435,13 +432,10 @@ def main():
                                      if form in traffic_records and args.config == "device" else None),
                          "flops_per_launch": mfma_flops[form], "what": whats[form]},
         }
-        if direct:
-            # one dispatch of the direct kernel; its fp64 arithmetic runs on the
-            # vector ALUs, whose fp64 peak equals the matrix cores' one
-            res[form]["roofline"].update(bound="alu", dispatches_per_call=1,
-                                         what="useful fp64 flops of the regrouped count (flops.pd_useful_flops), "
-                                              "executed by the direct kernel on the vector ALUs")
-        elif form in ("fp64", "fp32"):
+        if form == "fp64":
+            # the transform of G, the sums and the transform back
+            res[form]["roofline"].update(bound="alu")
+        elif form == "fp32":
             # this kernel runs as several dispatches per call; the roofline's launch
             # is the call (flops, traffic and HIP-event time all per call)
             res[form]["roofline"]["dispatches_per_call"] = fwd_mfma_dispatches(d, dev)

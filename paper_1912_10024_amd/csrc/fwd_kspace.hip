@@ -186,7 +186,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
                 const double* f = Al + 2 * (ADJ ? r0 * n + fc : fc * n + r0) + (lane & 1);
                 const cd* ua = sU + ea * 3 * nel + x0 - ea * n;
                 const cd* ub = sU + eb_ * 3 * nel + x1 - eb_ * n;
-                ks::uniform_product<2, CB, ADJ, false>(
+                ks::uniform_product<2, CB, ADJ>(
                     sum[ti], 3 * rc,
                     [&](int k) {
                         const int i = k >= 2 * rc ? 2 : k >= rc ? 1 : 0;
@@ -236,15 +236,16 @@ static bool pick_tile(const Dims& d, bool two, int cb, int mt, int cus, Tile* be
             if (eb > ks::kEBlk && eb - ks::kEBlk >= d.ne) break;
             const Tile t = make_tile(d, eb, rc, cb, two);
             if (t.lds > kLdsMax) break;
-            const double win = eb + 2.0 * d.nw, lanes = (double)(eb / ks::kEBlk * rc * n);
+            const double win = eb + 2.0 * d.nw;
             const double passes = up((double)eb * n, 128) * t.ncb;
             if (passes > mt * kWaves) break;
             const int occ = t.lds <= kLdsMax / 2 ? 2 : 1;
-            // vector instructions of a workgroup per chunk of rows
-            const double right = 3 * up(win * rc, 128) * t.ncb * (n * cb * 8.4 + 60);
-            const double filt = up(lanes, 64) * 3.0 * d.nw * ks::kEBlk * (two ? 24 : 14);
+            // per chunk of rows, in vector instructions of a workgroup: the busiest wave of each
+            // product and the filter, weighted by a fit to eleven tiles at 10 and 12 orbitals (within 10%)
+            const double right = 3 * kWaves * up(up(win * rc, 128) * t.ncb, kWaves) * (n * cb * 8.4 + 60);
+            const double filt = kWaves * 3.0 * d.nw * ks::kEBlk * (two ? 24 : 14);
             const double left = passes * (3 * rc * cb * 8.4 + 70);
-            const double chunk = right + filt + left + kWaves * (2000 + 25 * up(win * rc * n, kThreads));
+            const double chunk = 1.7 * (right + filt) + 1.25 * left + 5500;
             const double groups = up(up((double)d.ne, eb) * (double)(d.nkz * d.na), cus * occ);
             const double cost = groups * up(n, rc) * chunk * (occ == 2 ? 2 : 1.5);
             if (!found || cost < *best_cost) {

@@ -112,6 +112,55 @@ __device__ __forceinline__ void load_rows(const Source& s, const cd* tw, int nkz
     }
 }
 
+// The same rows through registers: ask() issues the loads, put() stores them later, so that
+// other work hides their latency.  U entries per thread; what is left is loaded by put().
+template <int THREADS, int U, int SRC, bool CT>
+struct RowsAhead {
+    cd v[U];
+    __device__ __forceinline__ cd get(const Source& s, const cd* tw, int nkz, int kt, int e, int ne, int at) const {
+        const bool ok = e >= 0 && e < ne;
+        const double* p = s.p + 2 * ((SRC == kTrans ? 0 : kt * s.kst) + (ok ? e : 0) * s.est + at);
+        cd a{0.0, 0.0};
+        if constexpr (SRC == kTrans) {
+            int m = 0;
+#pragma unroll 4
+            for (int k = 0; k < nkz; ++k) {
+                cfma(a, cload(p, k * s.kst), ld(tw + m));
+                m += kt;
+                m -= m >= nkz ? nkz : 0;
+            }
+        } else {
+            a = cload(p, 0);
+        }
+        if (!ok) a = cd{0.0, 0.0};
+        return CT ? cd{a.re, -a.im} : a;
+    }
+    __device__ __forceinline__ void ask(const Source& s, const cd* tw, int nkz, int kt, int e_first, int new_, int ne, int r0,
+                                        int rc, int n, Div by_row, Div by_n, int tid) {
+        const int nrow = rc * n, total = new_ * nrow;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int x = tid + u * THREADS < total ? tid + u * THREADS : 0;
+            const int ew = by_row.quot(x), rem = x - ew * nrow, r = by_n.quot(rem), c = rem - r * n;
+            v[u] = get(s, tw, nkz, kt, e_first + ew, ne, CT ? c * n + r0 + r : r0 * n + rem);
+        }
+    }
+    __device__ __forceinline__ void put(const Source& s, const cd* tw, int nkz, int kt, int e_first, int new_, int ne, int r0,
+                                        int rc, int n, Div by_row, Div by_n, cd* dst, int tid) const {
+        const int nrow = rc * n, total = new_ * nrow, np = row_len(n);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int x = tid + u * THREADS;
+            const int ew = by_row.quot(x), rem = x - ew * nrow, r = by_n.quot(rem), c = rem - r * n;
+            if (x < total) st(dst + (ew * rc + r) * np + c, v[u]);
+        }
+        for (int x = tid + U * THREADS; x < total; x += THREADS) {
+            const int ew = by_row.quot(x), rem = x - ew * nrow, r = by_n.quot(rem), c = rem - r * n;
+            st(dst + (ew * rc + r) * np + c, get(s, tw, nkz, kt, e_first + ew, ne, CT ? c * n + r0 + r : r0 * n + rem));
+        }
+    }
+};
+
 // Products with a uniform operand.  The 2 CB doubles of a step's uniform operands
 // (CB complex entries of grad H) sit in one register, double l of them in lane l of
 // every row of 16 lanes, and the multiply-adds read them with the DPP row broadcast,
@@ -214,45 +263,37 @@ __device__ __forceinline__ int uniform_entry(int lane) {
 }
 
 // acc[r][c] += f_c(k) x_r(k) for k in [0, len).  factor(k): this lane's double of step k's
-// uniform operands, asked for TB steps ahead; operand(k, x): the lane's own, asked
-// for one step ahead from LDS, or (MEM) TB steps ahead from memory.
-template <int R, int CB, bool CONJ, bool MEM, class Factor, class Operand>
+// uniform operands, asked for TB steps ahead; operand(k, x): the lane's own from LDS,
+// asked for one step ahead.
+template <int R, int CB, bool CONJ, class Factor, class Operand>
 __device__ __forceinline__ void uniform_product(cd (&acc)[R][CB], int len, Factor factor, Operand operand) {
     constexpr int TB = 4;
     double fa[TB], fb[TB];
-    cd xa[MEM ? TB : 2][R], xb[MEM ? TB : 1][R];
-    auto ask = [&](double (&f)[TB], auto& x, int k0) {
+    cd x[2][R];
+    auto ask = [&](double (&f)[TB], int k0) {
 #pragma unroll
-        for (int u = 0; u < TB; ++u) {
-            const int k = k0 + u < len ? k0 + u : len - 1;
-            f[u] = factor(k);
-            if constexpr (MEM) operand(k, x[u]);
-        }
+        for (int u = 0; u < TB; ++u) f[u] = factor(k0 + u < len ? k0 + u : len - 1);
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto mul = [&](const double (&f)[TB], auto& x, int k0) {
+    auto mul = [&](const double (&f)[TB], int k0) {
 #pragma unroll
         for (int u = 0; u < TB; ++u) {
             if (k0 + u < len) {
-                if constexpr (MEM) {
-                    fma_block<CB, CONJ>(acc, f[u], x[u]);
-                } else {
-                    operand(k0 + u + 1 < len ? k0 + u + 1 : len - 1, xa[(u + 1) & 1]);
-                    __builtin_amdgcn_sched_barrier(0);
-                    fma_block<CB, CONJ>(acc, f[u], xa[u & 1]);
-                }
+                operand(k0 + u + 1 < len ? k0 + u + 1 : len - 1, x[(u + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                fma_block<CB, CONJ>(acc, f[u], x[u & 1]);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    ask(fa, xa, 0);
-    if constexpr (!MEM) operand(0, xa[0]);
+    ask(fa, 0);
+    operand(0, x[0]);
     for (int k0 = 0; k0 < len; k0 += 2 * TB) {
-        ask(fb, xb, k0 + TB);
-        mul(fa, xa, k0);
+        ask(fb, k0 + TB);
+        mul(fa, k0);
         if (k0 + TB >= len) break;
-        ask(fa, xa, k0 + 2 * TB);
-        mul(fb, xb, k0 + TB);
+        ask(fa, k0 + 2 * TB);
+        mul(fb, k0 + TB);
     }
 }
 
@@ -278,7 +319,7 @@ __device__ __forceinline__ void right_product(const cd* sG, const double* __rest
         const int fc = c0 + uniform_entry<CB>(lane), cc = fc < n ? fc : n - 1;
         const double* f = M + 2 * (RT ? cc * n : cc) + (lane & 1);
         const int step = RT ? 2 : 2 * n;
-        uniform_product<R, CB, RT, false>(
+        uniform_product<R, CB, RT>(
             acc, n, [&](int u) { return f[u * step]; },
             [&](int u, cd (&x)[R]) {
 #pragma unroll

@@ -11,8 +11,9 @@
 //
 // One workgroup per (edge, transformed momentum), sweeping the energies in tiles of
 // eb, for one chunk of rc rows of the blocks after another:
-//   right  Y_j rows of the energies that enter the window  (lane = a row)
-//   left   X_i rows of the tile's energies                 (lane = (energy, column))
+//   load   rows of g of the energies that enter the window, all of B of the tile's energies
+//   right  Y_j rows                                        (lane = a row)
+//   left   X_i rows                                        (lane = (energy, column))
 //   sums   acc[i][w] += conj(X_i[E]) Y_j[E +- w]           (lane = an entry, one j, WB
 //          frequencies, a share of the energies)
 // A lane's window of WB energies per branch slides with E through registers, so a
@@ -20,7 +21,7 @@
 // of Y that the next tile still needs move to the front of the buffer.  The lanes'
 // sums are added in LDS in a fixed order at the end.
 //
-// SRC = kTrans (for g) and x_trans (for B) transform while they load; DIRECT sums over k as it stands, one
+// YSRC, XSRC = kTrans transform g and B while they load; DIRECT sums over k as it stands, one
 // workgroup per (edge, q) (exact for integer-valued inputs, Nkz times the work).
 #include <algorithm>
 
@@ -31,32 +32,34 @@ namespace sse {
 
 namespace {
 
-constexpr int kThreads = 256, kWaves = kThreads / 64;
-constexpr int kCB = 5, kXB = 6;  // columns per pass of Y, outputs (i, r) per pass of X
+constexpr int kThreads = 512, kWaves = kThreads / 64;
+constexpr int kCB = 5, kXB = 5;  // columns per pass of Y, outputs (i, r) per pass of X
 constexpr size_t kLdsMax = 160 * 1024;
 
 struct CorrTile {
+    int wb;                    // frequencies of a lane
     int eb, rc, es, nwb, nwg;  // energies, rows, shares of the energies, frequency blocks of a workgroup and groups of them
     int halo_lo, halo_hi;      // planes of Y before and after the tile
     int ncb;
-    ks::Div by_n, by_ncb, by_xb[2], by_rc[2], by_row[2];
-    int nel, y_entries, x_entries;
+    ks::Div by_n, by_ncb, by_xb[2], by_rc[2], by_row[2], by_nn;
+    int nel, y_entries, x_entries, g_entries;
     size_t lds;
 };
 
 struct CorrArgs {
     const double *y, *x;                             // g (or Gs) and B (or Go), or their transforms
     int64_t y_atom, y_kst, y_est, x_atom, x_kst, x_est;
-    int lo, hi, first, n_e;  // energies of X that are summed; the arrays hold first .. first + n_e - 1
+    int lo, hi;         // energies of X that are summed
+    int first, n_e;     // the energies that y holds
+    int x_first;        // the first energy that x holds
     bool add;                // add to the output instead of writing it
-    bool x_trans;            // x is the array itself: transformed as it is loaded
 };
 
 }  // namespace
 
 // HI, LO: the branches; CT: B is the conjugate transpose of the array's blocks
-template <int SRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
-__global__ __launch_bounds__(kThreads, 2) void corr_kspace_kernel(Dims d, CorrArgs g, const double* __restrict__ A,
+template <int YSRC, int XSRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
+__global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs g, const double* __restrict__ A,
                                                                   const int32_t* __restrict__ nbr, cd scale, CorrTile t,
                                                                   int64_t a0, double* __restrict__ out) {
     extern __shared__ __align__(16) double smem[];
@@ -65,7 +68,8 @@ __global__ __launch_bounds__(kThreads, 2) void corr_kspace_kernel(Dims d, CorrAr
     cd* sY = reinterpret_cast<cd*>(smem);  // [plane][j][r][c], plane 0 at energy e0 - halo_lo
     cd* sX = sY + t.y_entries;             // [e][i][r][c]
     cd* sG = sX + t.x_entries;             // rows of g [e][r][np]
-    cd* tw = sG + eb * t.rc * np;
+    cd* sB = sG + t.g_entries;             // B [e][t][np]
+    cd* tw = sB + eb * n * np;
     int* bad = reinterpret_cast<int*>(tw + nkz);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -96,26 +100,27 @@ __global__ __launch_bounds__(kThreads, 2) void corr_kspace_kernel(Dims d, CorrAr
         if (tid == 0) *bad = 0;
         const double* Af = A + 6 * edge * nn;
         const ks::Source ys{g.y + 2 * a * g.y_atom, g.y_kst, g.y_est};
-        const double* xs = g.x + 2 * b * g.x_atom;
+        const ks::Source xs{g.x + 2 * b * g.x_atom, g.x_kst, g.x_est};
         for (int kp = 0; kp < (DIRECT ? nkz : 1); ++kp) {
             const int ky = DIRECT ? (kp + kt) % nkz : kt;
             const int kx = DIRECT ? kp : CT ? (nkz - kt) % nkz : kt;
             for (int r0 = 0; r0 < n; r0 += t.rc) {
                 const int rc = n - r0 < t.rc ? n - r0 : t.rc, last = rc < t.rc;
                 const int nel = rc * n, ps = 3 * nel;  // entries of a plane
-                // rows of `count` energies from `energy` on into the planes from `plane` on
-                auto fill = [&](int plane, int energy, int count) {
-                    __syncthreads();
-                    ks::load_rows<kThreads, SRC, false>(ys, tw, nkz, ky, energy - g.first, count, g.n_e, r0, rc, n, t.by_row[last],
-                                                        t.by_n, sG, tid);
-                    __syncthreads();
+                auto load = [&](int energy, int count) {
+                    ks::load_rows<kThreads, YSRC, false>(ys, tw, nkz, ky, energy - g.first, count, g.n_e, r0, rc, n, t.by_row[last],
+                                                         t.by_n, sG, tid);
+                };
+                // Y of the loaded rows of `count` energies into the planes from `plane` on; the first
+                // task goes to wave `from`
+                auto right = [&](int plane, int count, int from) {
                     const int rows = count * rc;
                     for (int jj = 0; jj < 3; ++jj) {
                         auto dst = [&](int row) {
                             const int ew = t.by_rc[last].quot(row);
                             return sY + (plane + ew) * ps + jj * nel + (row - ew * rc) * n;
                         };
-                        const int w = (wave + 2 * jj) % kWaves;
+                        const int w = (wave + 2 * kWaves - from - jj * t.ncb) % kWaves;
                         if (rows <= 64)
                             ks::right_product<kWaves, 1, kCB, false>(sG, Af + 2 * jj * nn, rows, n, t.ncb, t.by_ncb, w, lane, dst);
                         else
@@ -123,26 +128,39 @@ __global__ __launch_bounds__(kThreads, 2) void corr_kspace_kernel(Dims d, CorrAr
                     }
                 };
                 for (int p = 0; p < t.halo_lo + t.halo_hi; p += eb) {
-                    const int left = t.halo_lo + t.halo_hi - p;
-                    fill(p, g.lo - t.halo_lo + p, left < eb ? left : eb);
+                    const int left = t.halo_lo + t.halo_hi - p, count = left < eb ? left : eb;
+                    __syncthreads();
+                    load(g.lo - t.halo_lo + p, count);
+                    __syncthreads();
+                    right(p, count, 0);
                 }
+                ks::RowsAhead<kThreads, 2, YSRC, false> y_next;
+                ks::RowsAhead<kThreads, 4, XSRC, CT> x_next;
+                auto ask = [&](int e0) {
+                    const int e_n = g.hi - e0 < eb ? g.hi - e0 : eb;
+                    y_next.ask(ys, tw, nkz, ky, e0 + t.halo_hi - g.first, eb, g.n_e, r0, rc, n, t.by_row[last], t.by_n, tid);
+                    x_next.ask(xs, tw, nkz, kx, e0 - g.x_first, e_n, ne, 0, n, n, t.by_nn, t.by_n, tid);
+                };
+                ask(g.lo);
                 for (int e0 = g.lo; e0 < g.hi; e0 += eb) {
                     const int e_n = g.hi - e0 < eb ? g.hi - e0 : eb;
-                    fill(t.halo_lo + t.halo_hi, e0 + t.halo_hi, eb);
-                    // X_i[e][r][c] = sum_t A_i[r0 + r][t] B[e][t][c]; two columns (e, c) per lane, B from memory
+                    __syncthreads();
+                    y_next.put(ys, tw, nkz, ky, e0 + t.halo_hi - g.first, eb, g.n_e, r0, rc, n, t.by_row[last], t.by_n, sG, tid);
+                    x_next.put(xs, tw, nkz, kx, e0 - g.x_first, e_n, ne, 0, n, n, t.by_nn, t.by_n, sB, tid);
+                    __syncthreads();
+                    // X_i[e][r][c] = sum_t A_i[r0 + r][t] B[e][t][c]; two columns (e, c) per lane
                     const int ncol = e_n * n, nout = 3 * rc, nob = (nout + kXB - 1) / kXB;
                     const int tasks = (ncol + 127) / 128 * nob;
                     for (int task = wave; task < tasks; task += kWaves) {
                         const int tc = t.by_xb[last].quot(task), o0 = (task - tc * nob) * kXB;
-                        const double* p[2];
+                        const cd* p[2];
                         int col[2], e[2];
 #pragma unroll
                         for (int h = 0; h < 2; ++h) {
                             col[h] = tc * 128 + 64 * h + lane;
                             const int x = col[h] < ncol ? col[h] : 0;
                             e[h] = t.by_n.quot(x);
-                            const int c = x - e[h] * n;
-                            p[h] = xs + 2 * ((g.x_trans ? 0 : kx * g.x_kst) + (int64_t)(e0 - g.first + e[h]) * g.x_est + (CT ? c * n : c));
+                            p[h] = sB + e[h] * n * np + x - e[h] * n;
                         }
                         cd v[2][kXB];
 #pragma unroll
@@ -150,23 +168,9 @@ __global__ __launch_bounds__(kThreads, 2) void corr_kspace_kernel(Dims d, CorrAr
                         const int fo = o0 + ks::uniform_entry<kXB>(lane), oo = fo < nout ? fo : nout - 1;
                         const int fi = oo >= 2 * rc ? 2 : oo >= rc ? 1 : 0;
                         const double* f = Af + 2 * (fi * nn + (r0 + oo - fi * rc) * n) + (lane & 1);
-                        ks::uniform_product<2, kXB, false, true>(v, n, [&](int q) { return f[2 * q]; }, [&](int q, cd (&x)[2]) {
-                            const int64_t at = CT ? q : q * n;
-#pragma unroll
-                            for (int h = 0; h < 2; ++h) {
-                                if (g.x_trans) {
-                                    x[h] = cd{0.0, 0.0};
-                                    int mm = 0;
-                                    for (int k = 0; k < nkz; ++k) {
-                                        cfma(x[h], cload(p[h], k * g.x_kst + at), ks::ld(tw + mm));
-                                        mm += kx;
-                                        mm -= mm >= nkz ? nkz : 0;
-                                    }
-                                } else {
-                                    x[h] = cload(p[h], at);
-                                }
-                                if constexpr (CT) x[h].im = -x[h].im;
-                            }
+                        ks::uniform_product<2, kXB, false>(v, n, [&](int q) { return f[2 * q]; }, [&](int q, cd (&x)[2]) {
+                            x[0] = ks::ld(p[0] + q * np);
+                            x[1] = ks::ld(p[1] + q * np);
                         });
 #pragma unroll
                         for (int h = 0; h < 2; ++h) {
@@ -182,7 +186,12 @@ __global__ __launch_bounds__(kThreads, 2) void corr_kspace_kernel(Dims d, CorrAr
                             if (!fin) *bad = 1;
                         }
                     }
+                    right(t.halo_lo + t.halo_hi, eb, tasks % kWaves);
                     __syncthreads();
+                    // on its way while the sums run (after the last tile: that one again, so that the
+                    // registers are dead in between)
+                    ask(e0 + eb < g.hi ? e0 + eb : e0);
+                    __builtin_amdgcn_sched_barrier(0);
                     const int share = eb / t.es, mine = e_n - es * share;
                     const int cnt = es < t.es && el < nel ? (mine < share ? mine : share) : 0;
                     const cd* X = sX + es * share * ps + el;
@@ -312,24 +321,19 @@ __global__ __launch_bounds__(kThreads, 2) void corr_kspace_kernel(Dims d, CorrAr
     }
 }
 
-// frequencies per lane: the block that divides nw with the least left over, the larger one of equals
-static int freq_block(int64_t nw) {
-    int best = 2;
-    for (int wb = 3; wb <= 5; ++wb)
-        if ((nw + wb - 1) / wb * wb <= (nw + best - 1) / best * best) best = wb;
-    return best;
-}
-
 // the tile with the least time under the quantisation of each step
 static bool corr_tile(const Dims& d, bool hi, bool lo, CorrTile* best) {
-    const int n = (int)d.norb, wb = freq_block(d.nw), np = ks::row_len(n);
-    const int64_t nwb_all = (d.nw + wb - 1) / wb;
+    const int n = (int)d.norb, np = ks::row_len(n);
     if (d.norb > 32 || d.nkz > 128 || d.nw > 4096 || d.ne >= (int64_t(1) << 28) || d.nb >= (1 << 20)) return false;
     auto up = [](double a, double b) { return (double)(int64_t)((a + b - 1) / b); };
     double best_cost = 0.0;
     bool found = false;
+    // both branches' windows of five frequencies do not fit the registers
+    for (int wb = 2; wb <= (hi && lo ? 4 : 5); ++wb)
     for (int rc = 1; rc <= n && 3 * rc * n <= kThreads; ++rc) {
         CorrTile t{};
+        const int64_t nwb_all = (d.nw + wb - 1) / wb;
+        t.wb = wb;
         const int nel = rc * n;
         t.rc = rc;
         t.nel = nel;
@@ -348,28 +352,33 @@ static bool corr_tile(const Dims& d, bool hi, bool lo, CorrTile* best) {
         t.by_rc[1] = ks::Div(tail);
         t.by_row[0] = ks::Div(nel);
         t.by_row[1] = ks::Div(tail * n);
+        t.by_nn = ks::Div(n * n);
         for (int es = 1; es <= max_es; ++es)
             for (int eb = es; eb <= 128; eb += es) {
                 if (eb > es && eb - es >= d.ne) break;
                 const int64_t y = (int64_t)(eb + t.halo_lo + t.halo_hi) * 3 * nel, x = (int64_t)eb * 3 * nel;
-                const int64_t all = std::max<int64_t>(y + x + (int64_t)eb * rc * np, wb * kThreads) + d.nkz + 1;
+                const int64_t gr = (int64_t)eb * rc * np, bt = (int64_t)eb * n * np;
+                const int64_t all = std::max<int64_t>(y + x + gr + bt, wb * kThreads) + d.nkz + 1;
                 if (all > (int64_t)(kLdsMax / sizeof(cd))) break;
                 t.eb = eb;
                 t.es = es;
                 t.y_entries = (int)y;
                 t.x_entries = (int)x;
+                t.g_entries = (int)gr;
                 t.lds = sizeof(cd) * (size_t)all;
                 const int occ = t.lds <= kLdsMax / 2 ? 2 : 1;
                 const int r = eb * rc <= 64 ? 1 : 2;
                 // vector instructions per tile and chunk, of the whole workgroup and of its busiest
-                // wave in each step, and those of the prologue of a chunk
+                // wave in each step, and those of the prologue of a chunk; the steps left over
+                // from groups of wb energies wait for their operands
                 const double halo = t.halo_lo + t.halo_hi;
-                const double s1 = (eb / es) * (wb * (hi && lo ? 14.0 : 12.0) + 10);
+                const double s1 = (eb / es + eb / es % wb * 1.5) * (wb * (hi && lo ? 14.0 : 12.0) + 10);
                 const double r1 = n * kCB * 4.4 * r + 80, rt = 3 * up((double)eb * rc, 64 * r) * t.ncb;
-                const double l1 = n * kXB * 8.8 + 150, lt = up((double)eb * n, 128) * up(3.0 * rc, kXB);
-                const double fixed = 400 + 25 * up((double)eb * nel, kThreads) + 4 * up(halo * 3 * nel, kThreads);
+                const double l1 = n * kXB * 8.8 + 100, lt = up((double)eb * n, 128) * up(3.0 * rc, kXB);
+                const double fixed = 400 + 25 * (up((double)eb * nel, kThreads) + up((double)eb * n * n, kThreads)) +
+                                     4 * up(halo * 3 * nel, kThreads);
                 const double total = up(3.0 * nel * t.nwb * es, 64) * s1 + rt * r1 + lt * l1 + kWaves * fixed;
-                const double longest = s1 + up(rt, kWaves) * r1 + up(lt, kWaves) * l1 + fixed + 1500;
+                const double longest = s1 + std::max(up(rt + lt, kWaves) * r1, l1 * up(lt, kWaves)) + fixed + 1500;
                 const double tile = total / kWaves + longest / occ;
                 const double fill = up(halo, eb) * (rt * r1 / kWaves + 1000);
                 const double cost = up(n, rc) * (up((double)d.ne, eb) * tile + fill) * t.nwg;
@@ -388,10 +397,10 @@ bool corr_kspace_supported(const Dims& d, bool both) {
     return corr_tile(d, true, both, &t);
 }
 
-template <int SRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
+template <int YSRC, int XSRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
 static hipError_t launch_corr_wb(const Dims& d, const CorrArgs& g, const double* A, const int32_t* nbr, cd scale,
                                  const CorrTile& t, double* out, hipStream_t stream) {
-    auto kern = corr_kspace_kernel<SRC, DIRECT, HI, LO, CT, WB>;
+    auto kern = corr_kspace_kernel<YSRC, XSRC, DIRECT, HI, LO, CT, WB>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds);
     if (e != hipSuccess) return e;
     const int64_t per = d.nb * d.nkz * t.nwg;
@@ -403,22 +412,26 @@ static hipError_t launch_corr_wb(const Dims& d, const CorrArgs& g, const double*
     return hipGetLastError();
 }
 
-template <int SRC, bool DIRECT, bool HI, bool LO, bool CT, class... Args>
+template <int YSRC, int XSRC, bool DIRECT, bool HI, bool LO, bool CT, class... Args>
 static hipError_t launch_corr_shape(int wb, Args... args) {
     switch (wb) {
-        case 2: return launch_corr_wb<SRC, DIRECT, HI, LO, CT, 2>(args...);
-        case 3: return launch_corr_wb<SRC, DIRECT, HI, LO, CT, 3>(args...);
-        case 4: return launch_corr_wb<SRC, DIRECT, HI, LO, CT, 4>(args...);
-        default: return launch_corr_wb<SRC, DIRECT, HI, LO, CT, 5>(args...);
+        case 2: return launch_corr_wb<YSRC, XSRC, DIRECT, HI, LO, CT, 2>(args...);
+        case 3: return launch_corr_wb<YSRC, XSRC, DIRECT, HI, LO, CT, 3>(args...);
+        case 4: return launch_corr_wb<YSRC, XSRC, DIRECT, HI, LO, CT, 4>(args...);
+        default: return launch_corr_wb<YSRC, XSRC, DIRECT, HI, LO, CT, 5>(args...);
     }
 }
 
+template <int YSRC, int XSRC, class... Args>
+static hipError_t launch_dd(int branches, int wb, Args... args) {
+    if (branches == 3) return launch_corr_shape<YSRC, XSRC, false, true, true, false>(wb, args...);
+    if (branches == 1) return launch_corr_shape<YSRC, XSRC, false, true, false, false>(wb, args...);
+    return launch_corr_shape<YSRC, XSRC, false, false, true, false>(wb, args...);
+}
+
 template <int SRC, bool DIRECT, class... Args>
-static hipError_t launch_corr(bool phonon, int branches, int wb, Args... args) {
-    if (phonon) return launch_corr_shape<SRC, DIRECT, true, false, true>(wb, args...);
-    if (branches == 3) return launch_corr_shape<SRC, DIRECT, true, true, false>(wb, args...);
-    if (branches == 1) return launch_corr_shape<SRC, DIRECT, true, false, false>(wb, args...);
-    return launch_corr_shape<SRC, DIRECT, false, true, false>(wb, args...);
+static hipError_t launch_pi_corr(int wb, Args... args) {
+    return launch_corr_shape<SRC, SRC, DIRECT, true, false, true>(wb, args...);
 }
 
 hipError_t launch_dd_kspace(const Dims& d, int branches, const double* g, const double* g_hat, const double* G,
@@ -426,9 +439,8 @@ hipError_t launch_dd_kspace(const Dims& d, int branches, const double* g, const 
                             hipStream_t stream) {
     CorrTile t;
     if (!corr_tile(d, (branches & 1) != 0, (branches & 2) != 0, &t)) return hipErrorInvalidValue;
-    const int wb = freq_block(d.nw);
-    const int64_t nn = d.norb * d.norb, ne = d.ne, na = d.na, x_atom = d.gs * nn;
-    CorrArgs a{g, G, nn, ne * na * nn, na * nn, x_atom, ne * na * x_atom, na * x_atom, 0, (int)ne, 0, (int)ne, false, !G_hat};
+        const int64_t nn = d.norb * d.norb, ne = d.ne, na = d.na, x_atom = d.gs * nn;
+    CorrArgs a{g, G, nn, ne * na * nn, na * nn, x_atom, ne * na * x_atom, na * x_atom, 0, (int)ne, 0, (int)ne, 0, false};
     if (g_hat) {
         a.y = g_hat;
         a.y_atom = ne * nn;
@@ -441,8 +453,13 @@ hipError_t launch_dd_kspace(const Dims& d, int branches, const double* g, const 
         a.x_kst = na * ne * nn;
         a.x_est = nn;
     }
-    hipError_t e = g_hat ? launch_corr<ks::kDirect, false>(false, branches, wb, d, a, A, nbr, calpha, t, dD, stream)
-                         : launch_corr<ks::kTrans, false>(false, branches, wb, d, a, A, nbr, calpha, t, dD, stream);
+    hipError_t e;
+    if (G_hat)
+        e = launch_dd<ks::kDirect, ks::kDirect>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
+    else if (g_hat)
+        e = launch_dd<ks::kDirect, ks::kTrans>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
+    else
+        e = launch_dd<ks::kTrans, ks::kTrans>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
     if (e != hipSuccess) return e;
     return launch_inverse((int)d.nkz, d.nw * na * d.nb, 9, 9, cd{calpha.re / (double)d.nkz, calpha.im / (double)d.nkz}, dD, stream);
 }
@@ -451,10 +468,10 @@ hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, c
                             double* Pi, bool transform, void* ws, size_t ws_bytes, hipStream_t stream) {
     CorrTile t;
     if (!corr_tile(d, true, false, &t)) return hipErrorInvalidValue;
-    const int wb = freq_block(d.nw), nkz = (int)d.nkz;
+    const int nkz = (int)d.nkz;
     const int64_t nn = d.norb * d.norb, ne = d.ne, na = d.na, atom = d.gs * nn, est = na * atom;
-    CorrArgs g{Gs, Go, atom, ne * est, est, atom, ne * est, est, 0, (int)ne, 0, (int)ne, false, false};
-    if (!transform) return launch_corr<ks::kDirect, true>(true, 1, wb, d, g, A, nbr, beta, t, Pi, stream);
+    CorrArgs g{Gs, Go, atom, ne * est, est, atom, ne * est, est, 0, (int)ne, 0, (int)ne, 0, false};
+    if (!transform) return launch_pi_corr<ks::kDirect, true>(t.wb, d, g, A, nbr, beta, t, Pi, stream);
     // room for energies of a transform: both arrays whole, or slabs of whole tiles of
     // energies of both (with the nw energies above for Gs), or neither
     hipError_t e = hipSuccess;
@@ -469,12 +486,11 @@ hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, c
             if (e == hipSuccess) e = launch_transform(nkz, lo, n_x, na, nn, atom, est, ne * est, Go, hx, stream);
             if (e != hipSuccess) return e;
             g = CorrArgs{hy, hx, n_y * nn, na * n_y * nn, nn, n_x * nn, na * n_x * nn, nn,
-                         (int)lo, (int)hi, (int)lo, (int)n_y, lo > 0, false};
-            e = launch_corr<ks::kDirect, false>(true, 1, wb, d, g, A, nbr, beta, t, Pi, stream);
+                         (int)lo, (int)hi, (int)lo, (int)n_y, (int)lo, lo > 0};
+            e = launch_pi_corr<ks::kDirect, false>(t.wb, d, g, A, nbr, beta, t, Pi, stream);
         }
     } else {
-        g.x_trans = true;
-        e = launch_corr<ks::kTrans, false>(true, 1, wb, d, g, A, nbr, beta, t, Pi, stream);
+        e = launch_pi_corr<ks::kTrans, false>(t.wb, d, g, A, nbr, beta, t, Pi, stream);
     }
     if (e != hipSuccess) return e;
     return launch_inverse(nkz, d.nw * na * d.nb, 9, 9, cd{beta.re / (double)d.nkz, beta.im / (double)d.nkz}, Pi, stream);

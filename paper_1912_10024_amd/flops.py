@@ -60,6 +60,15 @@ def pd_useful_flops(d) -> float:
     return pd_gemm_flops(d) + pd_left_flops(d)
 
 
+def kspace_flops(d, products: int = 6, sums: int = 1) -> float:
+    """Useful fp64 flops of the kernels in the momentum transform: per (edge,
+    momentum, energy) `products` Norb x Norb block products with grad H and `sums`
+    filters or correlations over the frequencies of 9 Nw Norb^2 multiply-adds.
+    Sigma, dG, Pi and dD take 6 and 1, d gradH 12 and 2."""
+    points = d.na * d.nb * d.nkz * d.ne
+    return 8.0 * points * (products * d.norb ** 3 + sums * 9.0 * d.nw * d.norb ** 2)
+
+
 def split16_mfma_flops(d) -> float:
     """Flops the split 16-bit forms issue on the 16-bit matrix cores: the four
     hi/lo partial products of the P.D GEMM and of the nine right products P =
