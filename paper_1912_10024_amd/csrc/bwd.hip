@@ -117,6 +117,84 @@ __global__ __launch_bounds__(1024) void rcsr_order_kernel(int64_t na, const int3
     for (int64_t a = tid; a < na; a += 1024) order[atomicAdd(&cursor[bucket(a)], 1)] = (int32_t)a;
 }
 
+// The whole adjacency and order in one launch for small tables: six launches of a few
+// microseconds each, one of them a scan whose middle runs on one thread, were a tenth of the smallest
+// adjoint.  One workgroup, the counts in LDS.
+constexpr int kSmallAtoms = 4096, kSmallEdges = 1 << 16;
+
+// exclusive prefix sums of v over the 1024 threads (part: 1024 entries)
+__device__ __forceinline__ int32_t scan_1024(int32_t v, int32_t* part, int tid) {
+    part[tid] = v;
+    __syncthreads();
+    for (int step = 1; step < 1024; step <<= 1) {
+        const int32_t add = tid >= step ? part[tid - step] : 0;
+        __syncthreads();
+        part[tid] += add;
+        __syncthreads();
+    }
+    const int32_t r = part[tid] - v;
+    __syncthreads();
+    return r;
+}
+
+__global__ __launch_bounds__(1024) void rcsr_small_kernel(int na, int nb, const int32_t* __restrict__ nbr,
+                                                          int32_t* __restrict__ offset, int32_t* __restrict__ edges,
+                                                          int32_t* __restrict__ order) {
+    __shared__ int32_t cursor[kSmallAtoms];
+    __shared__ int32_t part[1024];
+    __shared__ int32_t bucket[256];
+    const int tid = threadIdx.x, total = na * nb;
+    for (int i = tid; i < na; i += 1024) cursor[i] = 0;
+    __syncthreads();
+    for (int x = tid; x < total; x += 1024) {
+        const int32_t b = nbr[x];
+        if (b >= 0 && b < na) atomicAdd(&cursor[b], 1);
+    }
+    __syncthreads();
+    constexpr int kPer = kSmallAtoms / 1024;
+    const int per = (na + 1023) / 1024, lo = tid * per;
+    int32_t cnt[kPer], sum = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        cnt[u] = u < per && lo + u < na ? cursor[lo + u] : 0;
+        sum += cnt[u];
+    }
+    int32_t run = scan_1024(sum, part, tid);
+    if (tid < 256) bucket[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        if (u >= per || lo + u >= na) continue;
+        cursor[lo + u] = run;
+        offset[lo + u] = run;
+        run += cnt[u];
+        if (lo + u == na - 1) offset[na] = run;
+        atomicAdd(&bucket[255 - (cnt[u] < 255 ? cnt[u] : 255)], 1);
+    }
+    __syncthreads();
+    const int32_t first = scan_1024(tid < 256 ? bucket[tid] : 0, part, tid);
+    if (tid < 256) bucket[tid] = first;
+    __syncthreads();
+    for (int x = tid; x < total; x += 1024) {
+        const int32_t b = nbr[x];
+        if (b >= 0 && b < na) edges[atomicAdd(&cursor[b], 1)] = x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        if (u >= per || lo + u >= na) continue;
+        order[atomicAdd(&bucket[255 - (cnt[u] < 255 ? cnt[u] : 255)], 1)] = lo + u;
+        // the fill order is arbitrary: sort the list so the walk is in edge order
+        int32_t* e = edges + cursor[lo + u] - cnt[u];
+        for (int i = 1; i < cnt[u]; ++i) {
+            const int32_t v = e[i];
+            int j = i - 1;
+            for (; j >= 0 && e[j] > v; --j) e[j + 1] = e[j];
+            e[j + 1] = v;
+        }
+    }
+}
+
 __global__ void zero_i32_kernel(int64_t n, int32_t* p) {
     for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x) p[x] = 0;
 }
@@ -547,14 +625,18 @@ hipError_t launch_bwd(const Dims& d, const double* G, const double* Dp, const do
     int32_t* edges = cursor + d.na;
     int32_t* order = edges + d.na * d.nb;
     if (dG || (dA && !kspace)) {
-        const unsigned g1 = (unsigned)((d.na * d.nb + 255) / 256 < 4096 ? (d.na * d.nb + 255) / 256 : 4096);
-        hipLaunchKernelGGL(zero_i32_kernel, dim3(g1), dim3(256), 0, stream, d.na, count);
-        hipLaunchKernelGGL(rcsr_count_kernel, dim3(g1), dim3(256), 0, stream, d.na, d.nb, nbr, count);
-        hipLaunchKernelGGL(rcsr_scan_kernel, dim3(1), dim3(1024), 0, stream, d.na, count, offset, cursor);
-        hipLaunchKernelGGL(rcsr_fill_kernel, dim3(g1), dim3(256), 0, stream, d.na, d.nb, nbr, cursor, edges);
-        const unsigned g2 = (unsigned)((d.na + 255) / 256 < 4096 ? (d.na + 255) / 256 : 4096);
-        hipLaunchKernelGGL(rcsr_sort_kernel, dim3(g2), dim3(256), 0, stream, d.na, offset, edges);
-        hipLaunchKernelGGL(rcsr_order_kernel, dim3(1), dim3(1024), 0, stream, d.na, count, order);
+        if (d.na <= kSmallAtoms && d.na * d.nb <= kSmallEdges) {
+            hipLaunchKernelGGL(rcsr_small_kernel, dim3(1), dim3(1024), 0, stream, (int)d.na, (int)d.nb, nbr, offset, edges, order);
+        } else {
+            const unsigned g1 = (unsigned)((d.na * d.nb + 255) / 256 < 4096 ? (d.na * d.nb + 255) / 256 : 4096);
+            hipLaunchKernelGGL(zero_i32_kernel, dim3(g1), dim3(256), 0, stream, d.na, count);
+            hipLaunchKernelGGL(rcsr_count_kernel, dim3(g1), dim3(256), 0, stream, d.na, d.nb, nbr, count);
+            hipLaunchKernelGGL(rcsr_scan_kernel, dim3(1), dim3(1024), 0, stream, d.na, count, offset, cursor);
+            hipLaunchKernelGGL(rcsr_fill_kernel, dim3(g1), dim3(256), 0, stream, d.na, d.nb, nbr, cursor, edges);
+            const unsigned g2 = (unsigned)((d.na + 255) / 256 < 4096 ? (d.na + 255) / 256 : 4096);
+            hipLaunchKernelGGL(rcsr_sort_kernel, dim3(g2), dim3(256), 0, stream, d.na, offset, edges);
+            hipLaunchKernelGGL(rcsr_order_kernel, dim3(1), dim3(1024), 0, stream, d.na, count, order);
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -57,7 +57,8 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
     cd* sD = sG + t.body;                  // [j][w][i]
     cd* sDm = sD + 9 * nw;                 // (TWO)
     cd* sO = sD + (TWO ? 18 : 9) * nw;     // the chunk's result
-    cd* tw = sO + 3 * t.rc * n;
+    cd* sA = sO + 3 * t.rc * n;            // grad H of the edge
+    cd* tw = sA + 3 * nn;
     int* bad = reinterpret_cast<int*>(tw + nkz);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
     const int m_lo = p.by_energy ? 0 : share, m_hi = p.by_energy ? nkz : share + 1;
     const int e_lo = p.by_energy ? 32 * share : 0, e_hi = p.by_energy ? (e_lo + 32 < ne ? e_lo + 32 : ne) : ne;
     ks::stage_twiddles(tw, nkz, tid, kThreads);
-    const double* Ar = A + 6 * edge * nn;
+    ks::stage_factor<kThreads>(A, edge, nn, sA, tid);
     const ks::Source gs{p.g + 2 * a * p.g_atom, p.g_kst, p.g_est}, bs{p.G + 2 * b * p.G_atom, p.G_kst, p.G_est};
     const int kk = lane >> 4, j16 = lane & 15;
     const int nt = (2 * n + 15) / 16;
@@ -109,7 +110,7 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
                     __syncthreads();
                     const bool finite = *bad == 0;
                     for (int j = 0; j < 3; ++j) {
-                        ks::right_product<kWaves, 2, kCB, false>(sG, Ar + 2 * j * nn, ewin * rc, n, t.ncb, t.by_ncb,
+                        ks::right_product<kWaves, 2, kCB, false>(sG, sA + j * nn, ewin * rc, n, t.ncb, t.by_ncb,
                                                                  (wave + j) % kWaves, lane, [&](int row) { return sX + row * np; });
                         __syncthreads();
                         if (f_lane) {
@@ -215,7 +216,7 @@ static bool dh_tile(const Dims& d, bool two, DhTile* best) {
             const int64_t rows = (eb + 2 * d.nw) * rc * np, u = (int64_t)eb * 3 * rc * n, bb = (int64_t)eb * n * np;
             const int64_t red = kWaves * 16 * 64 / 2;
             const int64_t body = std::max(std::max(2 * rows, u + bb), red);
-            const int64_t all = body + (two ? 18 : 9) * d.nw + 3 * rc * n + d.nkz + 1;
+            const int64_t all = body + (two ? 18 : 9) * d.nw + 3 * rc * n + 3 * n * n + d.nkz + 1;
             if (all > (int64_t)(kLdsMax / sizeof(cd))) break;
             t.rows = (int)rows;
             t.u_entries = (int)u;

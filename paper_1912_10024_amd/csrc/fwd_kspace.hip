@@ -40,12 +40,12 @@ struct Tile {
     size_t lds;
 };
 
-Tile make_tile(const Dims& d, int eb, int rc, int cb, bool two) {
+Tile make_tile(const Dims& d, int eb, int rc, int cb, bool two, bool stored) {
     const int n = (int)d.norb, tail = n % rc ? n % rc : rc;
     Tile t{eb, rc, (n + cb - 1) / cb, ks::Div(n), ks::Div((n + cb - 1) / cb), {ks::Div(rc * n), ks::Div(tail * n)}, 0, 0, 0};
     const int64_t rows = (eb + 2 * d.nw) * rc * ks::row_len(n);
     const int64_t body = std::max(2 * rows, (int64_t)eb * 3 * rc * n);
-    const int64_t all = body + (two ? 18 : 9) * d.nw + d.nkz + 1;
+    const int64_t all = body + (two ? 18 : 9) * d.nw + (stored ? 6 : 3) * n * n + d.nkz + 1;
     t.lds = all < (1 << 20) ? sizeof(cd) * (size_t)all : (size_t)1 << 30;
     t.rows = (int)std::min<int64_t>(rows, 1 << 28);
     t.body = (int)std::min<int64_t>(body, 1 << 28);
@@ -87,7 +87,9 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
     cd* sU = sG;                           // U_i [e][i][r][c], after the last filter
     cd* sD = sG + tile.body;               // [j][w][i]
     cd* sDm = sD + 9 * nw;                 // (TWO)
-    cd* tw = sD + (TWO ? 18 : 9) * nw;
+    cd* sA = sD + (TWO ? 18 : 9) * nw;     // grad H of the edge [i][r][c]
+    cd* sR = sA + (MODE == kStored ? 3 * n * n : 0);  // right factor
+    cd* tw = sR + 3 * n * n;
     int* bad = reinterpret_cast<int*>(tw + nkz);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -121,8 +123,6 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
         const int64_t b = ADJ ? edge / nb : (int64_t)__builtin_amdgcn_readfirstlane(nbr[edge]);
         if (b < 0 || b >= d.na) continue;
         const ks::Source src{G + 2 * b * g_atom, g_kst, g_est};
-        const double* Ar = (MODE == kStored ? B : A) + 6 * edge * nn;
-        const double* Al = A + 6 * edge * nn;
         for (int r0 = 0; r0 < n; r0 += tile.rc) {
             const int rc = n - r0 < tile.rc ? n - r0 : tile.rc;
             // filter lanes: entry el = (r, c) of the chunk, energies 4 eq .. 4 eq + 3
@@ -144,6 +144,10 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
                 if (coeff && tid == 0) *bad = 0;
                 ks::load_rows<kThreads, SRC, false>(src, tw, nkz, kg, e0 - nw - slab, ewin, ne - slab, r0, rc, n,
                                                       by_row, tile.by_n, sG, tid);
+                if (r0 == 0 && kp == 0) {
+                    ks::stage_factor<kThreads>(A, edge, nn, sA, tid);
+                    if constexpr (MODE == kStored) ks::stage_factor<kThreads>(B, edge, nn, sR, tid);
+                }
                 if (coeff) {
                     __syncthreads();  // *bad is cleared
                     ks::stage_coeff<kThreads, !DIRECT, ADJ>(Dp, tw, nkz, kd, nw, ne, edges, edge, sD, bad, tid);
@@ -153,7 +157,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
                 __syncthreads();
                 const bool finite = *bad == 0;
                 for (int j = 0; j < 3; ++j) {
-                    ks::right_product<kWaves, 2, CB, MODE == kHermitian>(sG, Ar + 2 * j * nn, ewin * rc, n, tile.ncb, tile.by_ncb,
+                    ks::right_product<kWaves, 2, CB, MODE == kHermitian>(sG, sR + j * nn, ewin * rc, n, tile.ncb, tile.by_ncb,
                                                               (wave + j) % kWaves, lane, [&](int row) { return sX + row * np; });
                     __syncthreads();
                     if (f_lane) {
@@ -183,7 +187,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
                 const int ea = tile.by_n.quot(x0), eb_ = tile.by_n.quot(x1);
                 const int fr = rr + ks::uniform_entry<CB>(lane);
                 const int fc = fr < n ? fr : n - 1, f_step = ADJ ? 2 * n : 2;
-                const double* f = Al + 2 * (ADJ ? r0 * n + fc : fc * n + r0) + (lane & 1);
+                const double* f = reinterpret_cast<const double*>(sA) + 2 * (ADJ ? r0 * n + fc : fc * n + r0) + (lane & 1);
                 const cd* ua = sU + ea * 3 * nel + x0 - ea * n;
                 const cd* ub = sU + eb_ * 3 * nel + x1 - eb_ * n;
                 ks::uniform_product<2, CB, ADJ>(
@@ -227,14 +231,14 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
 // The tile with the least time per energy under the quantisation of each step:
 // cycles of the busiest wave, 16 per complex multiply-add, and the number of
 // rounds of workgroups on the chip.
-static bool pick_tile(const Dims& d, bool two, int cb, int mt, int cus, Tile* best, double* best_cost) {
+static bool pick_tile(const Dims& d, bool two, bool stored, int cb, int mt, int cus, Tile* best, double* best_cost) {
     const int n = (int)d.norb;
     bool found = false;
     auto up = [](double a, double b) { return (double)(int64_t)((a + b - 1) / b); };
     for (int rc = 1; rc <= n; ++rc)
         for (int eb = ks::kEBlk; eb <= 128 && eb / ks::kEBlk * rc * n <= kThreads; eb += ks::kEBlk) {
             if (eb > ks::kEBlk && eb - ks::kEBlk >= d.ne) break;
-            const Tile t = make_tile(d, eb, rc, cb, two);
+            const Tile t = make_tile(d, eb, rc, cb, two, stored);
             if (t.lds > kLdsMax) break;
             const double win = eb + 2.0 * d.nw;
             const double passes = up((double)eb * n, 128) * t.ncb;
@@ -266,7 +270,7 @@ static void passes_of(int n, int* cb, int* mt) {
 
 bool fwd_kspace_supported(const Dims& d, bool two) {
     if (d.norb > 32 || d.nkz > 128 || d.ne >= (int64_t(1) << 28) || d.nw >= (1 << 14) || d.nb >= (1 << 28)) return false;
-    return make_tile(d, ks::kEBlk, 1, 5, two).lds <= kLdsMax;
+    return make_tile(d, ks::kEBlk, 1, 5, two, true).lds <= kLdsMax;
 }
 
 // bytes of workspace that hold hat G: all of it, or a slab of energies of at most
@@ -317,14 +321,14 @@ static hipError_t launch_tables(bool two, int mode, int cb, Args... args) {
 }
 
 // the tile for these dims on the current device
-static hipError_t choose_tile(const Dims& d, bool two, int* cb, Tile* t) {
+static hipError_t choose_tile(const Dims& d, bool two, bool stored, int* cb, Tile* t) {
     int dev = 0, cus = 0, mt = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     passes_of((int)d.norb, cb, &mt);
     double cost = 0.0;
-    return pick_tile(d, two, *cb, mt, cus, t, &cost) ? hipSuccess : hipErrorInvalidValue;
+    return pick_tile(d, two, stored, *cb, mt, cus, t, &cost) ? hipSuccess : hipErrorInvalidValue;
 }
 
 hipError_t launch_dg_kspace(const Dims& d, const double* g, const double* g_hat, const double* Dp, const double* Dm,
@@ -334,7 +338,7 @@ hipError_t launch_dg_kspace(const Dims& d, const double* g, const double* g_hat,
     const int64_t nn = d.norb * d.norb, ne = d.ne;
     int cb;
     Tile t{};
-    hipError_t e = choose_tile(d, two, &cb, &t);
+    hipError_t e = choose_tile(d, two, false, &cb, &t);
     if (e != hipSuccess) return e;
     const InEdges in{offset, edges, order};
     const int32_t* no_nbr = nullptr;
@@ -359,7 +363,7 @@ hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, c
     const int64_t nn = d.norb * d.norb, ne = d.ne;
     int cb;
     Tile t{};
-    hipError_t e = choose_tile(d, two, &cb, &t);
+    hipError_t e = choose_tile(d, two, B != nullptr, &cb, &t);
     if (e != hipSuccess) return e;
     const InEdges none{};
     const int64_t g_atom = d.gs * nn, g_est = d.na * g_atom, g_kst = ne * g_est;

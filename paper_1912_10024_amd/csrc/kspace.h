@@ -297,11 +297,18 @@ __device__ __forceinline__ void uniform_product(cd (&acc)[R][CB], int len, Facto
     }
 }
 
+// The three blocks of grad H of an edge into LDS (the uniform operands are read from
+// there: from memory every pass of a product began with the latency of a load)
+template <int THREADS>
+__device__ __forceinline__ void stage_factor(const double* __restrict__ A, int64_t edge, int nn, cd* sA, int tid) {
+    for (int x = tid; x < 3 * nn; x += THREADS) st(sA + x, cload(A, 3 * edge * nn + x));
+}
+
 // out(row)[c] = sum_u sG[row][u] . f(u, c) for `rows` rows: a lane owns R rows, 64
 // apart, of a group of 64 R, CB columns at a time.  RT: f(u, c) = conj(M[c][u]) (the
 // right factor grad_j H^H), else f(u, c) = M[u][c].
 template <int WAVES, int R, int CB, bool RT, class Out>
-__device__ __forceinline__ void right_product(const cd* sG, const double* __restrict__ M, int rows, int n, int ncb,
+__device__ __forceinline__ void right_product(const cd* sG, const cd* sM, int rows, int n, int ncb,
                                               Div by_ncb, int first, int lane, Out out) {
     const int np = row_len(n);
     const int tasks = (rows + 64 * R - 1) / (64 * R) * ncb;
@@ -317,7 +324,7 @@ __device__ __forceinline__ void right_product(const cd* sG, const double* __rest
 #pragma unroll
             for (int r = 0; r < R; ++r) acc[r][c] = cd{0.0, 0.0};
         const int fc = c0 + uniform_entry<CB>(lane), cc = fc < n ? fc : n - 1;
-        const double* f = M + 2 * (RT ? cc * n : cc) + (lane & 1);
+        const double* f = reinterpret_cast<const double*>(sM) + 2 * (RT ? cc * n : cc) + (lane & 1);
         const int step = RT ? 2 : 2 * n;
         uniform_product<R, CB, RT>(
             acc, n, [&](int u) { return f[u * step]; },

@@ -69,7 +69,8 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
     cd* sX = sY + t.y_entries;             // [e][i][r][c]
     cd* sG = sX + t.x_entries;             // rows of g [e][r][np]
     cd* sB = sG + t.g_entries;             // B [e][t][np]
-    cd* tw = sB + eb * n * np;
+    cd* sA = sB + eb * n * np;             // grad H of the edge
+    cd* tw = sA + 3 * nn;
     int* bad = reinterpret_cast<int*>(tw + nkz);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
     if (valid) {
         ks::stage_twiddles(tw, nkz, tid, kThreads);
         if (tid == 0) *bad = 0;
-        const double* Af = A + 6 * edge * nn;
+        ks::stage_factor<kThreads>(A, edge, nn, sA, tid);
         const ks::Source ys{g.y + 2 * a * g.y_atom, g.y_kst, g.y_est};
         const ks::Source xs{g.x + 2 * b * g.x_atom, g.x_kst, g.x_est};
         for (int kp = 0; kp < (DIRECT ? nkz : 1); ++kp) {
@@ -122,9 +123,9 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
                         };
                         const int w = (wave + 2 * kWaves - from - jj * t.ncb) % kWaves;
                         if (rows <= 64)
-                            ks::right_product<kWaves, 1, kCB, false>(sG, Af + 2 * jj * nn, rows, n, t.ncb, t.by_ncb, w, lane, dst);
+                            ks::right_product<kWaves, 1, kCB, false>(sG, sA + jj * nn, rows, n, t.ncb, t.by_ncb, w, lane, dst);
                         else
-                            ks::right_product<kWaves, 2, kCB, false>(sG, Af + 2 * jj * nn, rows, n, t.ncb, t.by_ncb, w, lane, dst);
+                            ks::right_product<kWaves, 2, kCB, false>(sG, sA + jj * nn, rows, n, t.ncb, t.by_ncb, w, lane, dst);
                     }
                 };
                 for (int p = 0; p < t.halo_lo + t.halo_hi; p += eb) {
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
                         for (int o = 0; o < kXB; ++o) v[0][o] = v[1][o] = cd{0.0, 0.0};
                         const int fo = o0 + ks::uniform_entry<kXB>(lane), oo = fo < nout ? fo : nout - 1;
                         const int fi = oo >= 2 * rc ? 2 : oo >= rc ? 1 : 0;
-                        const double* f = Af + 2 * (fi * nn + (r0 + oo - fi * rc) * n) + (lane & 1);
+                        const double* f = reinterpret_cast<const double*>(sA) + 2 * (fi * nn + (r0 + oo - fi * rc) * n) + (lane & 1);
                         ks::uniform_product<2, kXB, false>(v, n, [&](int q) { return f[2 * q]; }, [&](int q, cd (&x)[2]) {
                             x[0] = ks::ld(p[0] + q * np);
                             x[1] = ks::ld(p[1] + q * np);
@@ -358,7 +359,7 @@ static bool corr_tile(const Dims& d, bool hi, bool lo, CorrTile* best) {
                 if (eb > es && eb - es >= d.ne) break;
                 const int64_t y = (int64_t)(eb + t.halo_lo + t.halo_hi) * 3 * nel, x = (int64_t)eb * 3 * nel;
                 const int64_t gr = (int64_t)eb * rc * np, bt = (int64_t)eb * n * np;
-                const int64_t all = std::max<int64_t>(y + x + gr + bt, wb * kThreads) + d.nkz + 1;
+                const int64_t all = std::max<int64_t>(y + x + gr + bt + 3 * n * n, wb * kThreads) + d.nkz + 1;
                 if (all > (int64_t)(kLdsMax / sizeof(cd))) break;
                 t.eb = eb;
                 t.es = es;

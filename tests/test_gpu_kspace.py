@@ -259,3 +259,19 @@ def test_adjoint_with_every_workspace_gives_the_same_bits(d, seed):
                                dD=torch.empty_like(full[1]), ddH=torch.empty_like(full[2]))
     for a, b in zip(got, full):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("na,nb", [(2, 1), (1025, 3), (4096, 16), (4097, 2)], ids=["two", "odd", "largest_small", "large"])
+def test_adjoint_adjacency_at_the_edges_of_its_kernels(na, nb):
+    """The reverse adjacency in one launch (up to 4096 atoms and 65536 edges) and in
+    several, with atoms that no edge points at and one that many point at."""
+    d = Dims(nkz=2, ne=2, nqz=2, nw=1, na=na, nb=nb, norb=1, g_slots=1)
+    print(f"[gpu] kspace adjacency dims={d.as_tuple()}", flush=True)
+    x = _grads(d, 21)
+    if na > 2:
+        x["nbr"][: na // 4, 0] = na - 1
+    t = _gpu(x)
+    got = sse.backward(t["G"], t["D"], t["dH"], t["nbr"], t["gS"])
+    ref = oracle.sse_backward(d, x["G"], x["D"], x["dH"], x["nbr"], x["gS"])
+    for name, g, r in zip(("dG", "dD", "ddH"), got, ref):
+        assert _rel(g.cpu().numpy(), r) <= TOL, name
