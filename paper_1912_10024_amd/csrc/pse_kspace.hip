@@ -298,19 +298,26 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
 #pragma unroll
         for (int u = 0; u < WB; ++u) ks::st(red + u * kThreads + tid, i == 0 ? acc[0][u] : i == 1 ? acc[1][u] : acc[2][u]);
         __syncthreads();
-        for (int o = tid; o < outs; o += kThreads) {
-            const int u = o % WB, wo = o / WB % t.nwb, jo = o / WB / t.nwb;
+        // eight lanes per output: every eighth entry each, then a tree over the eight
+        for (int o0 = 0; o0 < outs; o0 += kThreads / 8) {
+            const int o = o0 + tid / 8, oo = o < outs ? o : 0;
+            const int u = oo % WB, wo = oo / WB % t.nwb, jo = oo / WB / t.nwb;
             const int w = (wg * t.nwb + wo) * WB + u;
-            if (w >= nw) continue;
             cd sum{0.0, 0.0};
             for (int se = 0; se < t.es; ++se) {
                 const cd* p = red + u * kThreads + ((se * 3 + jo) * t.nwb + wo) * t.nel;
-                for (int x = 0; x < t.nel; ++x) {
+                for (int x = tid & 7; x < t.nel; x += 8) {
                     const cd v = ks::ld(p + x);
                     sum.re += v.re;
                     sum.im += v.im;
                 }
             }
+#pragma unroll
+            for (int h = 4; h > 0; h >>= 1) {
+                sum.re += __shfl_down(sum.re, h, 8);
+                sum.im += __shfl_down(sum.im, h, 8);
+            }
+            if (o >= outs || w >= nw || (tid & 7)) continue;
             const int64_t at = (((int64_t)kt * nw + w) * edges + edge) * 9 + i * 3 + jo;
             if (DIRECT) sum = cmul(scale, sum);
             if (g.add) {
@@ -369,19 +376,18 @@ static bool corr_tile(const Dims& d, bool hi, bool lo, CorrTile* best) {
                 t.lds = sizeof(cd) * (size_t)all;
                 const int occ = t.lds <= kLdsMax / 2 ? 2 : 1;
                 const int r = eb * rc <= 64 ? 1 : 2;
-                // vector instructions per tile and chunk, of the whole workgroup and of its busiest
-                // wave in each step, and those of the prologue of a chunk; the steps left over
-                // from groups of wb energies wait for their operands
+                // vector instructions of the busiest SIMD (its share of the waves, rounded up) per
+                // tile and chunk, the waits of a step, and the prologue of a chunk; the steps left
+                // over from groups of wb energies wait for their operands
                 const double halo = t.halo_lo + t.halo_hi;
-                const double s1 = (eb / es + eb / es % wb * 1.5) * (wb * (hi && lo ? 14.0 : 12.0) + 10);
+                const double s1 = (eb / es + eb / es % wb * 5.0) * (wb * (hi && lo ? 14.0 : 12.0) + 10);
                 const double r1 = n * kCB * 4.4 * r + 80, rt = 3 * up((double)eb * rc, 64 * r) * t.ncb;
                 const double l1 = n * kXB * 8.8 + 100, lt = up((double)eb * n, 128) * up(3.0 * rc, kXB);
                 const double fixed = 400 + 25 * (up((double)eb * nel, kThreads) + up((double)eb * n * n, kThreads)) +
                                      4 * up(halo * 3 * nel, kThreads);
-                const double total = up(3.0 * nel * t.nwb * es, 64) * s1 + rt * r1 + lt * l1 + kWaves * fixed;
-                const double longest = s1 + std::max(up(rt + lt, kWaves) * r1, l1 * up(lt, kWaves)) + fixed + 1500;
-                const double tile = total / kWaves + longest / occ;
-                const double fill = up(halo, eb) * (rt * r1 / kWaves + 1000);
+                const double tile = up(up(3.0 * nel * t.nwb * es, 64), 4) * s1 + up(rt, 4) * r1 + up(lt, 4) * l1 +
+                                    kWaves / 4 * fixed + 3000.0 / occ;
+                const double fill = up(halo, eb) * (up(rt, 4) * r1 + 1000);
                 const double cost = up(n, rc) * (up((double)d.ne, eb) * tile + fill) * t.nwg;
                 if (!found || cost < best_cost) {
                     best_cost = cost;
@@ -497,9 +503,10 @@ hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, c
     return launch_inverse(nkz, d.nw * na * d.nb, 9, 9, cd{beta.re / (double)d.nkz, beta.im / (double)d.nkz}, Pi, stream);
 }
 
-// both transforms, or (Pi) slabs of at most 8 GiB of them
+// both transforms, or slabs of at most 32 GiB of them (a slab costs a prologue and a
+// reduction: at 4864 atoms and 1024 energies 16 slabs took 1603 ms)
 size_t corr_kspace_workspace(const Dims& d) {
-    constexpr int64_t kSlabBytes = int64_t(8) << 30;
+    constexpr int64_t kSlabBytes = int64_t(32) << 30;
     if (d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks || !corr_kspace_supported(d, true)) return 0;
     const int64_t per = 16 * d.nkz * d.na * d.norb * d.norb;
     return (size_t)(per * std::min(2 * d.ne, std::max(kSlabBytes / per, 256 + 4 * d.nw)));

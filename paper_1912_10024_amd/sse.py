@@ -69,25 +69,28 @@ def workspace(d: Dims, precision: str = "fp64", backward: bool = False, device="
     nbytes = ctypes.c_size_t(0)
     cd = _lib.SSEDims.of(d)
     op = int(backward) if op is None else op
-    if op == 1:
-        ws = _fast_workspace(cd, op, device)
-        if ws is not None:
-            return ws
     _raise(lib.sse_workspace_bytes(ctypes.byref(cd), PRECISIONS.get(precision, -1), op, ctypes.byref(nbytes)),
            "sse_workspace_bytes")
+    if op == 1:
+        ws = _fast_workspace(cd, op, device, least=int(nbytes.value))
+        if ws is not None:
+            return ws
     return torch.empty(max(int(nbytes.value), 1), dtype=torch.uint8, device=device)
 
 
-def _fast_workspace(cd, op: int, device):
-    """The workspace a call is fastest with, or None where there is no room for it."""
-    nbytes = ctypes.c_size_t(0)
-    _raise(_lib.load().sse_fast_workspace_bytes(ctypes.byref(cd), op, ctypes.byref(nbytes)), "sse_fast_workspace_bytes")
-    if nbytes.value == 0:
-        return None
-    try:
-        return torch.empty(int(nbytes.value), dtype=torch.uint8, device=device)
-    except torch.OutOfMemoryError:
-        return None
+def _fast_workspace(cd, op: int, device, least: int = 1 << 26):
+    """The workspace a call is fastest with, a smaller one where the device has no
+    room for it, or None below `least` bytes."""
+    out = ctypes.c_size_t(0)
+    _raise(_lib.load().sse_fast_workspace_bytes(ctypes.byref(cd), op, ctypes.byref(out)), "sse_fast_workspace_bytes")
+    nbytes = int(out.value)
+    least = min(least, nbytes)
+    while nbytes > 0 and nbytes >= least:
+        try:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            nbytes //= 2
+    return None
 
 
 def effective_flops(d: Dims) -> float:
