@@ -41,7 +41,7 @@ def parse():
     p.add_argument("--config", default="device", choices=["tiny", "mid", "device", "mid12", "direct5"],
                    help="workload; mid12: the mid workload with 12 orbitals (the paper's count), fp64 and fp32 "
                         "forms only, with --no-phonon --no-adjoint; direct5: 1024 atoms, NE 64 with 5 "
-                        "neighbours (no matrix-core instance: the direct fp64 kernel), fp64 only, with "
+                        "neighbours (no matrix-core instance), fp64 only, with "
                         "--no-phonon --no-adjoint")
     p.add_argument("--forms", default="fp64,fp32,bf16x2,fp16x2,fp16",
                    help="comma-separated operand precisions to time; the first is the headline value "
@@ -255,7 +255,7 @@ def phonon_record(args, sse, flops, d, G, dH, nbr, dev):
         "roofline": {"bound": "alu", "achieved": round(useful / (ms * 1e-3) / 1e12, 3),
                      "peak": FP64_MFMA_PEAK / 1e12, "unit": "TFLOP/s",
                      "frac": round(useful / (ms * 1e-3) / FP64_MFMA_PEAK, 4),
-                     "traffic": (recorded_traffic("pse_mfma_device_traffic.txt", PSE_SOURCES)
+                     "traffic": (recorded_traffic("pi_kspace_device_traffic.txt", PSE_SOURCES)
                                  if args.config == "device" else None),
                      "flops_per_launch": useful,
                      "what": "useful fp64 flops in the momentum transform (flops.kspace_flops), on the vector ALUs"},
@@ -315,7 +315,7 @@ def adjoint_record(args, sse, dev):
             "ms_dg_dgradh": round(ms, 3),
             "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": FP64_MFMA_PEAK / 1e12,
                          "unit": "TFLOP/s", "frac": round(achieved * 1e12 / FP64_MFMA_PEAK, 4),
-                         "traffic": recorded_traffic("bwd_mfma_mid_traffic.txt", BWD_SOURCES),
+                         "traffic": recorded_traffic("adjoint_kspace_mid_traffic.txt", BWD_SOURCES),
                          "flops_per_launch": flops,
                          "what": "useful fp64 flops of dG and d gradH in the momentum transform (flops.kspace_flops)"}}
 
@@ -353,15 +353,14 @@ def main():
                      "--no-phonon --no-adjoint")
     if args.config == "direct5":
         # a shape without a matrix-core instance (one neighbour more than the
-        # instances): the direct fp64 kernel on the vector ALUs
+        # instances)
         from paper_1912_10024_amd.inputs import Dims
 
         CONFIGS = dict(CONFIGS, direct5=Dims(nkz=7, ne=64, nqz=7, nw=10, na=1024, nb=5, norb=10, g_slots=1))
         CONFIG_INDEX = dict(CONFIG_INDEX, direct5=CONFIG_INDEX["mid"])
         if args.forms.strip() != "fp64" or not (args.no_phonon and args.no_adjoint):
-            sys.exit("--config direct5 takes --forms fp64 (the direct kernel is fp64 only) with "
+            sys.exit("--config direct5 takes --forms fp64 (fp64 only) with "
                      "--no-phonon --no-adjoint")
-    direct = args.config == "direct5"
     d = CONFIGS[args.config]
     dev = torch.device("cuda:0")
     if args.only_adjoint:
@@ -412,7 +411,7 @@ def main():
              "fp16": "16-bit matrix-core flops of the single-term form run on the split kernel: 2x the P.D GEMM, "
                      "4x P = X.gradH^H (flops.single16_mfma_flops)",
              "fp16_unscaled": "as fp16 (flops.single16_mfma_flops)"}
-    traffic_records = {"fp64": ("fwd_mfma_device_traffic.txt", FWD_SOURCES),
+    traffic_records = {"fp64": ("fwd_kspace_device_traffic.txt", FWD_SOURCES),
                        "fp16x2": ("fwd_h16_device_traffic.txt", H16_SOURCES)}
     res = {}
     for form in forms:
