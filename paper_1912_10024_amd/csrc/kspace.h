@@ -20,6 +20,7 @@
 
 #include <type_traits>
 
+#include "kspace_plan.h"
 #include "sse_common.h"
 
 namespace sse {
@@ -33,18 +34,6 @@ __device__ __forceinline__ cd ld(const cd* p) {
     return cd{v.x, v.y};
 }
 __device__ __forceinline__ void st(cd* p, cd v) { *reinterpret_cast<double2*>(p) = make_double2(v.re, v.im); }
-
-// x / d for 0 <= x < 2^16, 1 <= d < 2^16, with the reciprocal taken on the host
-struct Div {
-    uint32_t m, one;  // one: d == 1
-    __host__ __device__ Div() : m(0), one(0) {}
-    __host__ explicit Div(int d) : m(d == 1 ? 0u : (uint32_t)(0xffffffffu / (uint32_t)d) + 1u), one(d == 1 ? 0xffffffffu : 0u) {}
-    __device__ __forceinline__ int quot(int x) const { return (int)(__umulhi((uint32_t)x, m) | ((uint32_t)x & one)); }
-};
-
-// LDS row of norb complex entries: an odd number of 16-byte entries, so that
-// lanes that read down a column hit distinct banks
-__host__ __device__ __forceinline__ int row_len(int n) { return n | 1; }
 
 // exp(-2 pi i m / nkz), m = 0 .. nkz-1
 __device__ __forceinline__ void stage_twiddles(cd* tw, int nkz, int tid, int threads) {

@@ -32,19 +32,10 @@ namespace sse {
 
 namespace {
 
-constexpr int kThreads = 512, kWaves = kThreads / 64;
-constexpr int kCB = 5, kXB = 5;  // columns per pass of Y, outputs (i, r) per pass of X
-constexpr size_t kLdsMax = 160 * 1024;
-
-struct CorrTile {
-    int wb;                    // frequencies of a lane
-    int eb, rc, es, nwb, nwg;  // energies, rows, shares of the energies, frequency blocks of a workgroup and groups of them
-    int halo_lo, halo_hi;      // planes of Y before and after the tile
-    int ncb;
-    ks::Div by_n, by_ncb, by_xb[2], by_rc[2], by_row[2], by_nn;
-    int nel, y_entries, x_entries, g_entries;
-    size_t lds;
-};
+constexpr int kThreads = ks::kCorrThreads, kWaves = kThreads / 64;
+constexpr int kCB = ks::kCorrCB, kXB = ks::kCorrXB;
+using ks::corr_tile;
+using ks::CorrTile;
 
 struct CorrArgs {
     const double *y, *x;                             // g (or Gs) and B (or Go), or their transforms
@@ -121,7 +112,7 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
                             const int ew = t.by_rc[last].quot(row);
                             return sY + (plane + ew) * ps + jj * nel + (row - ew * rc) * n;
                         };
-                        const int w = (wave + 2 * kWaves - from - jj * t.ncb) % kWaves;
+                        const int w = ks::first_task<kWaves>(wave, from + jj * t.ncb);
                         if (rows <= 64)
                             ks::right_product<kWaves, 1, kCB, false>(sG, sA + jj * nn, rows, n, t.ncb, t.by_ncb, w, lane, dst);
                         else
@@ -327,76 +318,6 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
             cstore(out, at, sum);
         }
     }
-}
-
-// the tile with the least time under the quantisation of each step
-static bool corr_tile(const Dims& d, bool hi, bool lo, CorrTile* best) {
-    const int n = (int)d.norb, np = ks::row_len(n);
-    if (d.norb > 32 || d.nkz > 128 || d.nw > 4096 || d.ne >= (int64_t(1) << 28) || d.nb >= (1 << 20)) return false;
-    auto up = [](double a, double b) { return (double)(int64_t)((a + b - 1) / b); };
-    double best_cost = 0.0;
-    bool found = false;
-    // both branches' windows of five frequencies do not fit the registers
-    for (int wb = 2; wb <= (hi && lo ? 4 : 5); ++wb)
-    for (int rc = 1; rc <= n && 3 * rc * n <= kThreads; ++rc) {
-        CorrTile t{};
-        const int64_t nwb_all = (d.nw + wb - 1) / wb;
-        t.wb = wb;
-        const int nel = rc * n;
-        t.rc = rc;
-        t.nel = nel;
-        t.nwb = (int)std::min<int64_t>(nwb_all, kThreads / (3 * nel));
-        t.nwg = (int)((nwb_all + t.nwb - 1) / t.nwb);
-        const int max_es = kThreads / (3 * nel * t.nwb);
-        t.halo_lo = lo ? (int)nwb_all * wb : 0;
-        t.halo_hi = hi ? (int)nwb_all * wb : 0;
-        t.ncb = (n + kCB - 1) / kCB;
-        const int tail = n % rc ? n % rc : rc;
-        t.by_n = ks::Div(n);
-        t.by_ncb = ks::Div(t.ncb);
-        t.by_xb[0] = ks::Div((3 * rc + kXB - 1) / kXB);
-        t.by_xb[1] = ks::Div((3 * tail + kXB - 1) / kXB);
-        t.by_rc[0] = ks::Div(rc);
-        t.by_rc[1] = ks::Div(tail);
-        t.by_row[0] = ks::Div(nel);
-        t.by_row[1] = ks::Div(tail * n);
-        t.by_nn = ks::Div(n * n);
-        for (int es = 1; es <= max_es; ++es)
-            for (int eb = es; eb <= 128; eb += es) {
-                if (eb > es && eb - es >= d.ne) break;
-                const int64_t y = (int64_t)(eb + t.halo_lo + t.halo_hi) * 3 * nel, x = (int64_t)eb * 3 * nel;
-                const int64_t gr = (int64_t)eb * rc * np, bt = (int64_t)eb * n * np;
-                const int64_t all = std::max<int64_t>(y + x + gr + bt + 3 * n * n, wb * kThreads) + d.nkz + 1;
-                if (all > (int64_t)(kLdsMax / sizeof(cd))) break;
-                t.eb = eb;
-                t.es = es;
-                t.y_entries = (int)y;
-                t.x_entries = (int)x;
-                t.g_entries = (int)gr;
-                t.lds = sizeof(cd) * (size_t)all;
-                const int occ = t.lds <= kLdsMax / 2 ? 2 : 1;
-                const int r = eb * rc <= 64 ? 1 : 2;
-                // vector instructions of the busiest SIMD (its share of the waves, rounded up) per
-                // tile and chunk, the waits of a step, and the prologue of a chunk; the steps left
-                // over from groups of wb energies wait for their operands
-                const double halo = t.halo_lo + t.halo_hi;
-                const double s1 = (eb / es + eb / es % wb * 5.0) * (wb * (hi && lo ? 14.0 : 12.0) + 10);
-                const double r1 = n * kCB * 4.4 * r + 80, rt = 3 * up((double)eb * rc, 64 * r) * t.ncb;
-                const double l1 = n * kXB * 8.8 + 100, lt = up((double)eb * n, 128) * up(3.0 * rc, kXB);
-                const double fixed = 400 + 25 * (up((double)eb * nel, kThreads) + up((double)eb * n * n, kThreads)) +
-                                     4 * up(halo * 3 * nel, kThreads);
-                const double tile = up(up(3.0 * nel * t.nwb * es, 64), 4) * s1 + up(rt, 4) * r1 + up(lt, 4) * l1 +
-                                    kWaves / 4 * fixed + 3000.0 / occ;
-                const double fill = up(halo, eb) * (up(rt, 4) * r1 + 1000);
-                const double cost = up(n, rc) * (up((double)d.ne, eb) * tile + fill) * t.nwg;
-                if (!found || cost < best_cost) {
-                    best_cost = cost;
-                    *best = t;
-                    found = true;
-                }
-            }
-    }
-    return found;
 }
 
 bool corr_kspace_supported(const Dims& d, bool both) {
