@@ -50,6 +50,22 @@ struct CorrTile {
     size_t lds;
 };
 
+// What a thread sums: entry el, direction j, frequencies w0 + 1 .. w0 + wb, share es of the energies
+struct CorrLane {
+    int el, j, es, w0;
+};
+__host__ __device__ __forceinline__ CorrLane corr_lane(const CorrTile& t, int tid, int wg) {
+    const int rest = tid / t.nel;
+    return CorrLane{tid % t.nel, rest / t.nwb % 3, rest / t.nwb / 3, (wg * t.nwb + rest % t.nwb) * t.wb};
+}
+// Energies it sums of a tile with e_n of them, in a chunk with nel entries.  A lane whose
+// frequencies all lie beyond nw (the last group may have fewer blocks than the others) has
+// none: its window would leave the planes of Y.
+__host__ __device__ __forceinline__ int corr_energies(const CorrTile& t, const CorrLane& l, int nw, int nel, int e_n) {
+    const int share = t.eb / t.es, mine = e_n - l.es * share;
+    return l.es < t.es && l.el < nel && l.w0 < nw && mine > 0 ? (mine < share ? mine : share) : 0;
+}
+
 // the tile with the least time under the quantisation of each step
 inline bool corr_tile(const Dims& d, bool hi, bool lo, CorrTile* best) {
     const int n = (int)d.norb, np = row_len(n);

@@ -77,10 +77,8 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
     const int32_t b = __builtin_amdgcn_readfirstlane(nbr[edge]);
     const bool valid = b >= 0 && b < d.na;
 
-    // this thread's sums: entry el, direction j, frequencies w0 + 1 .. w0 + WB, share es
-    const int el = tid % t.nel, rest = tid / t.nel;
-    const int wb = rest % t.nwb, j = rest / t.nwb % 3, es = rest / t.nwb / 3;
-    const int w0 = (wg * t.nwb + wb) * WB;
+    const ks::CorrLane own = ks::corr_lane(t, tid, wg);
+    const int el = own.el, j = own.j, es = own.es, w0 = own.w0;
     cd acc[3][WB];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
@@ -184,8 +182,7 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
                     // registers are dead in between)
                     ask(e0 + eb < g.hi ? e0 + eb : e0);
                     __builtin_amdgcn_sched_barrier(0);
-                    const int share = eb / t.es, mine = e_n - es * share;
-                    const int cnt = es < t.es && el < nel ? (mine < share ? mine : share) : 0;
+                    const int share = eb / t.es, cnt = ks::corr_energies(t, own, nw, nel, e_n);
                     const cd* X = sX + es * share * ps + el;
                     const cd* Yc = sY + (es * share + t.halo_lo) * ps + j * nel + el;  // plane of the first energy
                     if (*bad == 0) {

@@ -38,11 +38,39 @@ static int first_task() {
     return 0;
 }
 
+// the planes of Y that a lane of corr_kspace_kernel reads: those of its energies shifted by
+// w0 + 1 .. w0 + wb up and down
+static int corr_window() {
+    for (int both = 0; both < 2; ++both)
+        for (int n = 1; n <= 25; n += n < 12 ? 1 : 4)
+            for (int nw = 1; nw <= 130; nw += nw < 50 ? 1 : 9)
+                for (int ne : {7, 64}) {
+                    ks::CorrTile t;
+                    if (!ks::corr_tile(dims(2, ne, nw, 4, 2, n), true, both, &t)) continue;
+                    const int planes = t.eb + t.halo_lo + t.halo_hi, tail = n % t.rc ? n % t.rc * n : t.nel;
+                    for (int wg = 0; wg < t.nwg; ++wg)
+                        for (int tid = 0; tid < ks::kCorrThreads; ++tid)
+                            for (int e_n : {t.eb, 1})
+                                for (int nel : {t.nel, tail}) {
+                                    const ks::CorrLane l = ks::corr_lane(t, tid, wg);
+                                    const int cnt = ks::corr_energies(t, l, nw, nel, e_n);
+                                    if (cnt <= 0) continue;
+                                    const int first = l.es * (t.eb / t.es) + t.halo_lo, last = first + cnt - 1;
+                                    if (last + l.w0 + t.wb >= planes || (both && first - l.w0 - t.wb < 0)) {
+                                        printf("norb %d nw %d ne %d both %d: group %d of %d, frequencies from %d, planes %d\n", n, nw,
+                                               ne, both, wg, t.nwg, l.w0, planes);
+                                        return 1;
+                                    }
+                                }
+                }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
         int (*run)();
-    } checks[] = {{"first_task", first_task}};
+    } checks[] = {{"first_task", first_task}, {"corr_window", corr_window}};
     for (const auto& c : checks)
         if (argc > 1 && !strcmp(argv[1], c.name)) return c.run();
     printf("no such check\n");

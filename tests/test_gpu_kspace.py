@@ -275,3 +275,23 @@ def test_adjoint_adjacency_at_the_edges_of_its_kernels(na, nb):
     ref = oracle.sse_backward(d, x["G"], x["D"], x["dH"], x["nbr"], x["gS"])
     for name, g, r in zip(("dG", "dD", "ddH"), got, ref):
         assert _rel(g.cpu().numpy(), r) <= TOL, name
+
+
+def test_pi_and_dd_with_a_ragged_last_group_of_frequencies():
+    """More frequency blocks than the lanes of a workgroup hold: several workgroups per
+    (edge, momentum), the last of them with fewer blocks."""
+    d = Dims(nkz=2, ne=44, nqz=2, nw=31, na=12, nb=2, norb=25, g_slots=1)
+    print(f"[gpu] kspace pi groups dims={d.as_tuple()}", flush=True)
+    x = _inputs(d, 31)
+    x["Go"] = _cn(np.random.default_rng(32), d.g_shape)
+    t = _gpu(x)
+    P = sse.phonon_forward(t["G"], t["Go"], t["dH"], t["nbr"], d.nqz, d.nw).cpu().numpy()
+    assert _rel(P, oracle.pse_forward(d, x["G"], x["Go"], x["dH"], x["nbr"])) <= TOL
+    d = Dims(nkz=2, ne=60, nqz=2, nw=41, na=9, nb=2, norb=16, g_slots=1)
+    print(f"[gpu] kspace adjoint groups dims={d.as_tuple()}", flush=True)
+    x = _grads(d, 33)
+    t = _gpu(x)
+    got = sse.backward(t["G"], t["D"], t["dH"], t["nbr"], t["gS"])
+    ref = oracle.sse_backward(d, x["G"], x["D"], x["dH"], x["nbr"], x["gS"])
+    for name, g, r in zip(("dG", "dD", "ddH"), got, ref):
+        assert _rel(g.cpu().numpy(), r) <= TOL, name
