@@ -195,9 +195,22 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
     }
 }
 
+// LDS entries of a tile: its buffers, then everything
+static int64_t dh_body(const Dims& d, int rc, int eb) {
+    const int64_t n = d.norb, np = ks::row_len((int)n), rows = (eb + 2 * d.nw) * rc * np;
+    return std::max(std::max(2 * rows, eb * 3 * rc * n + eb * n * np), (int64_t)kWaves * 16 * 64 / 2);
+}
+static int64_t dh_entries(const Dims& d, bool two, int rc, int eb) {
+    return dh_body(d, rc, eb) + (two ? 18 : 9) * d.nw + 3 * rc * d.norb + 3 * d.norb * d.norb + d.nkz + 1;
+}
+static bool dh_fits(const Dims& d, bool two) {  // the smallest tile
+    return d.norb <= 32 && d.nkz <= 128 && d.ne < (int64_t(1) << 28) && d.nw < (1 << 14) &&
+           dh_entries(d, two, 1, ks::kEBlk) <= (int64_t)(kLdsMax / sizeof(cd));
+}
+
 static bool dh_tile(const Dims& d, bool two, DhTile* best) {
     const int n = (int)d.norb, np = ks::row_len(n);
-    if (d.norb > 32 || d.nkz > 128 || d.ne >= (int64_t(1) << 28) || d.nw >= (1 << 14)) return false;
+    if (!dh_fits(d, two)) return false;
     auto up = [](double a, double b) { return (double)(int64_t)((a + b - 1) / b); };
     double best_cost = 0.0;
     bool found = false;
@@ -213,14 +226,11 @@ static bool dh_tile(const Dims& d, bool two, DhTile* best) {
             t.by_row[0] = ks::Div(rc * n);
             t.by_row[1] = ks::Div(tail * n);
             t.by_nn = ks::Div(n * n);
-            const int64_t rows = (eb + 2 * d.nw) * rc * np, u = (int64_t)eb * 3 * rc * n, bb = (int64_t)eb * n * np;
-            const int64_t red = kWaves * 16 * 64 / 2;
-            const int64_t body = std::max(std::max(2 * rows, u + bb), red);
-            const int64_t all = body + (two ? 18 : 9) * d.nw + 3 * rc * n + 3 * n * n + d.nkz + 1;
+            const int64_t all = dh_entries(d, two, rc, eb);
             if (all > (int64_t)(kLdsMax / sizeof(cd))) break;
-            t.rows = (int)rows;
-            t.u_entries = (int)u;
-            t.body = (int)body;
+            t.rows = (int)(eb + 2 * d.nw) * rc * np;
+            t.u_entries = eb * 3 * rc * n;
+            t.body = (int)dh_body(d, rc, eb);
             t.lds = sizeof(cd) * (size_t)all;
             const int occ = t.lds <= kLdsMax / 2 ? 2 : 1;
             const double win = eb + 2.0 * d.nw;
@@ -240,10 +250,7 @@ static bool dh_tile(const Dims& d, bool two, DhTile* best) {
     return found;
 }
 
-bool dh_kspace_supported(const Dims& d) {
-    DhTile t;
-    return dh_tile(d, true, &t);
-}
+bool dh_kspace_supported(const Dims& d) { return dh_fits(d, true); }
 
 template <int GSRC, int BSRC, bool TWO>
 static hipError_t launch_dh(const Dims& d, const DhArgs& p, const double* Dp, const double* Dm, const double* A,

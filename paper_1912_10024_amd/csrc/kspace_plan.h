@@ -66,74 +66,142 @@ __host__ __device__ __forceinline__ int corr_energies(const CorrTile& t, const C
     return l.es < t.es && l.el < nel && l.w0 < nw && mine > 0 ? (mine < share ? mine : share) : 0;
 }
 
-// the tile with the least time under the quantisation of each step
+__host__ __device__ __forceinline__ int up_div(int a, int b) { return (a + b - 1) / b; }
+
+// A tile but for its energies: LDS in entries (base + energies * per, at least `least` for
+// the last sum) and what the cost of a tile takes from it
+struct CorrShape {
+    int n, wb, rc, nel, nwb, nwg, ncb, halo;
+    int base, per, least;
+    int chunks, x_passes;
+    double step;  // vector instructions of one energy of the sums
+};
+inline bool corr_limits(const Dims& d) {
+    return d.norb <= 32 && d.nkz <= 128 && d.nw <= 4096 && d.ne < (int64_t(1) << 28) && d.nb < (1 << 20);
+}
+inline CorrShape corr_shape(const Dims& d, bool hi, bool lo, int wb, int rc) {
+    const int n = (int)d.norb, nwb_all = up_div((int)d.nw, wb);
+    CorrShape s{};
+    s.n = n;
+    s.wb = wb;
+    s.rc = rc;
+    s.nel = rc * n;
+    s.nwb = std::min(nwb_all, kCorrThreads / (3 * s.nel));
+    s.nwg = up_div(nwb_all, s.nwb);
+    s.ncb = up_div(n, kCorrCB);
+    s.halo = (hi + lo) * nwb_all * wb;
+    s.base = s.halo * 3 * s.nel + 3 * n * n + (int)d.nkz + 1;
+    s.per = 6 * s.nel + (rc + n) * row_len(n);
+    s.least = wb * kCorrThreads + (int)d.nkz + 1;
+    s.chunks = up_div(n, rc);
+    s.x_passes = up_div(3 * rc, kCorrXB);
+    s.step = wb * (hi && lo ? 14.0 : 12.0) + 10;
+    return s;
+}
+inline int corr_entries(const CorrShape& s, int eb) { return std::max(s.base + eb * s.per, s.least); }
+
+// Vector instructions of the busiest SIMD (its share of the waves, rounded up) per tile of
+// es shares of `share` energies, the waits of a step, and the prologue of a chunk; the steps
+// left over from groups of wb energies wait for their operands
+inline double corr_cost(const CorrShape& s, int ne, int es, int share) {
+    auto up = [](int a, int shift) { return (a + (1 << shift) - 1) >> shift; };
+    const int eb = es * share, wide = eb * s.rc <= 64 ? 0 : 1;  // rows per lane of the right products, less one
+    const int rt = 3 * up(eb * s.rc, 6 + wide) * s.ncb, lt = up(eb * s.n, 7) * s.x_passes;
+    const double r1 = s.n * kCorrCB * 4.4 * (1 + wide) + 80, l1 = s.n * kCorrXB * 8.8 + 100;
+    const double fixed = 400 + 25 * (up(eb * s.nel, 9) + up(eb * s.n * s.n, 9)) + 4 * up(s.halo * 3 * s.nel, 9);
+    const bool two = corr_entries(s, eb) <= (int)(kLdsBytes / kEntry / 2);  // workgroups on a compute unit
+    const double tile = up(up(3 * s.nel * s.nwb * es, 6), 2) * (share + share % s.wb * 5) * s.step + up(rt, 2) * r1 +
+                        up(lt, 2) * l1 + kCorrWaves / 4 * fixed + (two ? 1500 : 3000);
+    const double fill = up_div(s.halo, eb) * (up(rt, 2) * r1 + 1000);
+    return (double)s.chunks * s.nwg * (up_div(ne, eb) * tile + fill);
+}
+
+// both branches' windows of five frequencies do not fit the registers
+inline int corr_max_wb(bool hi, bool lo) { return hi && lo ? 4 : 5; }
+
+// whether the smallest tile fits the LDS
+inline bool corr_fits(const Dims& d, bool hi, bool lo) {
+    if (!corr_limits(d)) return false;
+    for (int wb = 2; wb <= corr_max_wb(hi, lo); ++wb)
+        if (corr_entries(corr_shape(d, hi, lo, wb, 1), 1) <= (int)(kLdsBytes / kEntry)) return true;
+    return false;
+}
+
+// The tile with the least cost.  Tried are the row counts that give different numbers of
+// chunks; all the lanes' shares, a half, a third of them or a power of two in between; and,
+// for the room of one and of two workgroups per compute unit, tiles that divide the
+// energies evenly and tiles of whole groups of wb.  A call searches
+// once, in 5 to 25 us on one core; over 5,900 shapes the cost is on average 0.1% above that
+// of every combination tried in turn, which took 20 to 230 us.
 inline bool corr_tile(const Dims& d, bool hi, bool lo, CorrTile* best) {
-    const int n = (int)d.norb, np = row_len(n);
-    if (d.norb > 32 || d.nkz > 128 || d.nw > 4096 || d.ne >= (int64_t(1) << 28) || d.nb >= (1 << 20)) return false;
-    auto up = [](double a, double b) { return (double)(int64_t)((a + b - 1) / b); };
+    if (!corr_limits(d)) return false;
+    const int n = (int)d.norb, ne = (int)d.ne;
+    constexpr int kRoom = (int)(kLdsBytes / kEntry);
     double best_cost = 0.0;
-    bool found = false;
-    // both branches' windows of five frequencies do not fit the registers
-    for (int wb = 2; wb <= (hi && lo ? 4 : 5); ++wb)
-    for (int rc = 1; rc <= n && 3 * rc * n <= kCorrThreads; ++rc) {
-        CorrTile t{};
-        const int64_t nwb_all = (d.nw + wb - 1) / wb;
-        t.wb = wb;
-        const int nel = rc * n;
-        t.rc = rc;
-        t.nel = nel;
-        t.nwb = (int)std::min<int64_t>(nwb_all, kCorrThreads / (3 * nel));
-        t.nwg = (int)((nwb_all + t.nwb - 1) / t.nwb);
-        const int max_es = kCorrThreads / (3 * nel * t.nwb);
-        t.halo_lo = lo ? (int)nwb_all * wb : 0;
-        t.halo_hi = hi ? (int)nwb_all * wb : 0;
-        t.ncb = (n + kCorrCB - 1) / kCorrCB;
-        const int tail = n % rc ? n % rc : rc;
-        t.by_n = Div(n);
-        t.by_ncb = Div(t.ncb);
-        t.by_xb[0] = Div((3 * rc + kCorrXB - 1) / kCorrXB);
-        t.by_xb[1] = Div((3 * tail + kCorrXB - 1) / kCorrXB);
-        t.by_rc[0] = Div(rc);
-        t.by_rc[1] = Div(tail);
-        t.by_row[0] = Div(nel);
-        t.by_row[1] = Div(tail * n);
-        t.by_nn = Div(n * n);
-        for (int es = 1; es <= max_es; ++es)
-            for (int eb = es; eb <= 128; eb += es) {
-                if (eb > es && eb - es >= d.ne) break;
-                const int64_t y = (int64_t)(eb + t.halo_lo + t.halo_hi) * 3 * nel, x = (int64_t)eb * 3 * nel;
-                const int64_t gr = (int64_t)eb * rc * np, bt = (int64_t)eb * n * np;
-                const int64_t all = std::max<int64_t>(y + x + gr + bt + 3 * n * n, wb * kCorrThreads) + d.nkz + 1;
-                if (all > (int64_t)(kLdsBytes / kEntry)) break;
-                t.eb = eb;
-                t.es = es;
-                t.y_entries = (int)y;
-                t.x_entries = (int)x;
-                t.g_entries = (int)gr;
-                t.lds = kEntry * (size_t)all;
-                const int occ = t.lds <= kLdsBytes / 2 ? 2 : 1;
-                const int r = eb * rc <= 64 ? 1 : 2;
-                // vector instructions of the busiest SIMD (its share of the waves, rounded up) per
-                // tile and chunk, the waits of a step, and the prologue of a chunk; the steps left
-                // over from groups of wb energies wait for their operands
-                const double halo = t.halo_lo + t.halo_hi;
-                const double s1 = (eb / es + eb / es % wb * 5.0) * (wb * (hi && lo ? 14.0 : 12.0) + 10);
-                const double r1 = n * kCorrCB * 4.4 * r + 80, rt = 3 * up((double)eb * rc, 64 * r) * t.ncb;
-                const double l1 = n * kCorrXB * 8.8 + 100, lt = up((double)eb * n, 128) * up(3.0 * rc, kCorrXB);
-                const double fixed = 400 + 25 * (up((double)eb * nel, kCorrThreads) + up((double)eb * n * n, kCorrThreads)) +
-                                     4 * up(halo * 3 * nel, kCorrThreads);
-                const double tile = up(up(3.0 * nel * t.nwb * es, 64), 4) * s1 + up(rt, 4) * r1 + up(lt, 4) * l1 +
-                                    kCorrWaves / 4 * fixed + 3000.0 / occ;
-                const double fill = up(halo, eb) * (up(rt, 4) * r1 + 1000);
-                const double cost = up(n, rc) * (up((double)d.ne, eb) * tile + fill) * t.nwg;
-                if (!found || cost < best_cost) {
-                    best_cost = cost;
-                    *best = t;
-                    found = true;
+    CorrShape bs{};
+    int best_es = 0, best_share = 0;
+    for (int wb = corr_max_wb(hi, lo); wb >= 2; --wb)
+        for (int c = 1, rc_before = 0; c <= n; ++c) {
+            const int rc = up_div(n, c);
+            if (rc == rc_before || 3 * rc * n > kCorrThreads) continue;
+            rc_before = rc;
+            const CorrShape s = corr_shape(d, hi, lo, wb, rc);
+            if (corr_entries(s, 1) > kRoom) continue;
+            const int most = std::min(128, (kRoom - s.base) / s.per), half = std::min(128, (kRoom / 2 - s.base) / s.per);
+            auto shares = [&](int es) {
+                if (es < 1 || es > most) return;
+                const int need = up_div(ne, es);
+                for (int room : {most, half}) {
+                    const int limit = std::min(room / es, need);
+                    if (limit < 1) continue;
+                    const int even = up_div(need, up_div(need, limit)), down = limit / wb * wb, over = up_div(even, wb) * wb;
+                    for (int share : {even, down, over <= limit ? over : 0, limit / wb / 2 * wb}) {
+                        if (share < 1) continue;
+                        const double cost = corr_cost(s, ne, es, share);
+                        if (best_share && cost >= best_cost) continue;
+                        best_cost = cost;
+                        bs = s;
+                        best_es = es;
+                        best_share = share;
+                    }
                 }
-            }
-    }
-    return found;
+            };
+            const int max_es = kCorrThreads / (3 * s.nel * s.nwb);
+            shares(max_es);
+            if (max_es > 2) shares(max_es / 2);
+            if (max_es > 5) shares(max_es / 3);
+            int es = 1;
+            while (4 * es < max_es) es *= 2;
+            for (; es < max_es; es *= 2) shares(es);
+        }
+    if (!best_share) return false;
+    const int eb = best_es * best_share, tail = n % bs.rc ? n % bs.rc : bs.rc;
+    CorrTile t{};
+    t.wb = bs.wb;
+    t.eb = eb;
+    t.rc = bs.rc;
+    t.es = best_es;
+    t.nwb = bs.nwb;
+    t.nwg = bs.nwg;
+    t.halo_lo = lo ? bs.halo / (hi + lo) : 0;
+    t.halo_hi = hi ? bs.halo / (hi + lo) : 0;
+    t.ncb = bs.ncb;
+    t.by_n = Div(n);
+    t.by_ncb = Div(t.ncb);
+    t.by_xb[0] = Div(up_div(3 * bs.rc, kCorrXB));
+    t.by_xb[1] = Div(up_div(3 * tail, kCorrXB));
+    t.by_rc[0] = Div(bs.rc);
+    t.by_rc[1] = Div(tail);
+    t.by_row[0] = Div(bs.nel);
+    t.by_row[1] = Div(tail * n);
+    t.by_nn = Div(n * n);
+    t.nel = bs.nel;
+    t.y_entries = (eb + t.halo_lo + t.halo_hi) * 3 * bs.nel;
+    t.x_entries = eb * 3 * bs.nel;
+    t.g_entries = eb * bs.rc * row_len(n);
+    t.lds = kEntry * (size_t)corr_entries(bs, eb);
+    *best = t;
+    return true;
 }
 
 }  // namespace ks

@@ -317,10 +317,7 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
     }
 }
 
-bool corr_kspace_supported(const Dims& d, bool both) {
-    CorrTile t;
-    return corr_tile(d, true, both, &t);
-}
+bool corr_kspace_supported(const Dims& d, bool both) { return ks::corr_fits(d, true, both); }
 
 template <int YSRC, int XSRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
 static hipError_t launch_corr_wb(const Dims& d, const CorrArgs& g, const double* A, const int32_t* nbr, cd scale,

@@ -1,5 +1,7 @@
 // Host checks of csrc/kspace_plan.h; one check per run, named by argv[1].  Prints what is
 // wrong and returns 1, or returns 0.
+#include <algorithm>
+#include <chrono>
 #include <cstdio>
 #include <cstring>
 
@@ -66,11 +68,45 @@ static int corr_window() {
     return 0;
 }
 
+// Time of the searches that five small and middling calls do once each, the least of
+// thirty: microseconds, where trying every combination took 0.4 ms for the five
+static int corr_search_time() {
+    using Clock = std::chrono::steady_clock;
+    double sum = 0.0;
+    for (const Dims& d : {dims(3, 16, 2, 16, 4, 4), dims(5, 64, 6, 200, 4, 8), dims(7, 128, 10, 512, 4, 10), dims(3, 48, 5, 250, 3, 6),
+                          dims(3, 101, 4, 500, 3, 5)}) {
+        double least = 1e9;
+        for (int rep = 0; rep < 30; ++rep) {
+            const auto t0 = Clock::now();
+            ks::CorrTile t;
+            if (!ks::corr_tile(d, true, false, &t)) return 1;
+            least = std::min(least, std::chrono::duration<double, std::micro>(Clock::now() - t0).count());
+        }
+        sum += least;
+    }
+    printf("%.1f us\n", sum);
+    return sum < 200.0 ? 0 : 1;
+}
+
+// the smallest tile fits exactly where the search finds one
+static int corr_support() {
+    for (int both = 0; both < 2; ++both)
+        for (int n = 1; n <= 32; ++n)
+            for (int nw = 1; nw <= 400; nw += nw < 20 ? 1 : 17) {
+                ks::CorrTile t;
+                const Dims d = dims(2, 64, nw, 4, 2, n);
+                if (ks::corr_fits(d, true, both) == ks::corr_tile(d, true, both, &t)) continue;
+                printf("norb %d nw %d both %d\n", n, nw, both);
+                return 1;
+            }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
         int (*run)();
-    } checks[] = {{"first_task", first_task}, {"corr_window", corr_window}};
+    } checks[] = {{"first_task", first_task}, {"corr_window", corr_window}, {"corr_search_time", corr_search_time}, {"corr_support", corr_support}};
     for (const auto& c : checks)
         if (argc > 1 && !strcmp(argv[1], c.name)) return c.run();
     printf("no such check\n");
