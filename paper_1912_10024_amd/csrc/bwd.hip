@@ -206,10 +206,13 @@ __global__ void zero_i32_kernel(int64_t n, int32_t* p) {
 static size_t bwd_csr_bytes(const Dims& d) {  // count, offset, cursor, edges, order
     return (sizeof(int32_t) * (size_t)(4 * d.na + 1 + d.na * d.nb) + 255) / 256 * 256;
 }
+static bool bwd_use_kspace(const Dims& d) {
+    return fwd_kspace_supported(d, true) && dh_kspace_supported(d) && corr_kspace_supported(d, true);
+}
 // one d gradH share per 32 energies on the shape of the matrix-core forward, whose Nkz
-// shares would take more room, else one per momentum
+// shares would take more room, else one per momentum, as the kernels of this file always write
 static bool bwd_by_energy(const Dims& d, bool signed_form) {
-    return !signed_form && d.norb == 10 && d.nkz == 7 && d.nqz == 7 && d.nw == 10 && d.ne < (int64_t(1) << 28) &&
+    return !signed_form && d.norb == 10 && d.nkz == 7 && d.nqz == 7 && d.nw == 10 && bwd_use_kspace(d) &&
            d.na * ((d.ne + 31) / 32) <= INT32_MAX;
 }
 static int64_t bwd_shares(const Dims& d, bool signed_form) {
@@ -229,9 +232,6 @@ size_t bwd_workspace_bytes_for(const Dims& d, bool signed_form, bool with_dh, bo
 }
 size_t bwd_workspace_bytes(const Dims& d) {
     return std::max(bwd_workspace_bytes_for(d, false, true, true), bwd_workspace_bytes_for(d, true, true, true));
-}
-static bool bwd_use_kspace(const Dims& d) {
-    return fwd_kspace_supported(d, true) && dh_kspace_supported(d) && corr_kspace_supported(d, true);
 }
 size_t bwd_fast_workspace_bytes(const Dims& d) {
     constexpr size_t kHats = size_t(16) << 30;  // at most this for the transforms
@@ -653,7 +653,7 @@ hipError_t launch_bwd(const Dims& d, const double* G, const double* Dp, const do
         if (dA) {
             const int64_t n = d.na * d.nb * 3 * d.norb * d.norb;
             const unsigned g3 = (unsigned)((n + 255) / 256 < 65536 ? (n + 255) / 256 : 65536);
-            hipLaunchKernelGGL(bwd_dh_reduce_kernel, dim3(g3), dim3(256), 0, stream, d, nbr, shares, d.nkz, dA);
+            hipLaunchKernelGGL(bwd_dh_reduce_kernel, dim3(g3), dim3(256), 0, stream, d, nbr, shares, bwd_shares(d, signed_form), dA);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }

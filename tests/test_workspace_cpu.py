@@ -1,0 +1,31 @@
+"""Workspace sizes of the C entries against what the kernels write (runs without a GPU)."""
+import ctypes
+
+import pytest
+
+from paper_1912_10024_amd import _lib
+from paper_1912_10024_amd.inputs import Dims
+
+
+def _bytes(d, op):
+    out = ctypes.c_size_t(0)
+    assert _lib.load().sse_workspace_bytes(ctypes.byref(_lib.SSEDims.of(d)), 0, op, ctypes.byref(out)) == _lib.SSE_OK
+    return out.value
+
+
+def _backward_rejects(d, nbytes):
+    """Whether sse_backward (ddH alone) refuses a workspace of nbytes; it looks at no pointer before."""
+    P = ctypes.c_void_p
+    rc = _lib.load().sse_backward(ctypes.byref(_lib.SSEDims.of(d)), *([P(256)] * 4), 0.0, 1.0, P(256), None, None, P(256),
+                                  P(256), nbytes, None)
+    return rc == _lib.SSE_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("ne", [1, 32, 192])
+def test_shares_of_a_neighbour_count_beyond_the_transform_kernels(ne):
+    """2^20 neighbours are more than the kernels in the momentum transform index, so the
+    adjoint runs its direct kernels, which write one share of dL/d(dH) per momentum."""
+    d = Dims(nkz=7, ne=ne, nqz=7, nw=10, na=1, nb=1 << 20, norb=10, g_slots=1)
+    shares = 16 * d.nkz * d.na * d.nb * 3 * d.norb ** 2
+    assert _bytes(d, 1) >= shares + 4 * (4 * d.na + 1 + d.na * d.nb)
+    assert _backward_rejects(d, shares)
