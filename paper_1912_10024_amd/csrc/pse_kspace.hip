@@ -422,7 +422,7 @@ hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, c
 // reduction: at 4864 atoms and 1024 energies 16 slabs took 1603 ms)
 size_t corr_kspace_workspace(const Dims& d) {
     constexpr int64_t kSlabBytes = int64_t(32) << 30;
-    if (d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks || !corr_kspace_supported(d, true)) return 0;
+    if (d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks || !corr_kspace_supported(d, false)) return 0;
     const int64_t per = 16 * d.nkz * d.na * d.norb * d.norb;
     return (size_t)(per * std::min(2 * d.ne, std::max(kSlabBytes / per, 256 + 4 * d.nw)));
 }

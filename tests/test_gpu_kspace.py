@@ -295,3 +295,16 @@ def test_pi_and_dd_with_a_ragged_last_group_of_frequencies():
     ref = oracle.sse_backward(d, x["G"], x["D"], x["dH"], x["nbr"], x["gS"])
     for name, g, r in zip(("dG", "dD", "ddH"), got, ref):
         assert _rel(g.cpu().numpy(), r) <= TOL, name
+
+
+def test_pi_where_only_one_window_fits():
+    """A shape whose window to both sides does not fit the LDS: Pi, with the workspace it
+    asks for and without one."""
+    d = Dims(nkz=2, ne=130, nqz=2, nw=60, na=5, nb=1, norb=25, g_slots=1)
+    print(f"[gpu] kspace pi wide dims={d.as_tuple()}", flush=True)
+    x = _inputs(d, 41)
+    x["Go"] = _cn(np.random.default_rng(42), d.g_shape)
+    t = _gpu(x)
+    ref = oracle.pse_forward(d, x["G"], x["Go"], x["dH"], x["nbr"])
+    assert _rel(sse.phonon_forward(t["G"], t["Go"], t["dH"], t["nbr"], d.nqz, d.nw).cpu().numpy(), ref) <= TOL
+    assert _rel(_pi_ws(t, d, 0), ref) <= TOL

@@ -29,3 +29,17 @@ def test_shares_of_a_neighbour_count_beyond_the_transform_kernels(ne):
     shares = 16 * d.nkz * d.na * d.nb * 3 * d.norb ** 2
     assert _bytes(d, 1) >= shares + 4 * (4 * d.na + 1 + d.na * d.nb)
     assert _backward_rejects(d, shares)
+
+
+def _fast(d, op):
+    out = ctypes.c_size_t(0)
+    assert _lib.load().sse_fast_workspace_bytes(ctypes.byref(_lib.SSEDims.of(d)), op, ctypes.byref(out)) == _lib.SSE_OK
+    return out.value
+
+
+@pytest.mark.parametrize("norb,nw", [(25, 60), (12, 140)])
+def test_pi_asks_for_a_workspace_wherever_its_one_window_fits(norb, nw):
+    """Pi reads the energies above only; shapes where a window to both sides would not fit
+    the LDS still run in the transform."""
+    d = Dims(nkz=2, ne=130, nqz=2, nw=nw, na=5, nb=2, norb=norb, g_slots=1)
+    assert _fast(d, 3) >= 16 * d.nkz * d.na * norb ** 2 * (2 * d.ne - 1)
