@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_dg_dh_kernel(Dims d, const do
                                                                 const double* __restrict__ gS, cd calpha,
                                                                 const int32_t* __restrict__ offset,
                                                                 const int32_t* __restrict__ edges,
-                                                                const int32_t* __restrict__ order,
+                                                                const int32_t* __restrict__ order, int64_t first,
                                                                 double* __restrict__ dG, double* __restrict__ dApart) {
     extern __shared__ double smem[];
     const int N = (int)d.norb, NN = N * N;
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_dg_dh_kernel(Dims d, const do
     // XCD (they read the same D, grad H and g blocks); the atoms come in
     // decreasing in-degree (a workgroup walks the edges into its atom), so the
     // longest workgroups start first.
-    const int64_t bid = blockIdx.x, span = 8 * d.nkz;
+    const int64_t bid = first + blockIdx.x, span = 8 * d.nkz;
     const int64_t pos = (bid / span) * 8 + bid % 8;
     const int64_t kp = (bid % span) / 8;
     if (pos >= d.na) return;  // uniform for the workgroup, before any barrier
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_dd_kernel(Dims d, const doubl
                                                              const double* __restrict__ Ag,
                                                              const int32_t* __restrict__ nbr,
                                                              const double* __restrict__ gS, cd calpha, int branches,
-                                                             double* __restrict__ dD) {
+                                                             int64_t first, double* __restrict__ dD) {
     extern __shared__ double smem[];
     const int N = (int)d.norb, NN = N * N;
     const int nqw = (int)(d.nqz * d.nw);
@@ -467,7 +467,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_dd_kernel(Dims d, const doubl
     cd* sE = sB + NN;                      // [3][N][N]  A_i B
     cd* sP = sE + 3 * NN;                  // [9][N][N]  A_i B A_j^H
     const int tid = threadIdx.x;
-    const int64_t edge = blockIdx.x;
+    const int64_t edge = first + blockIdx.x;
     if (edge >= d.na * d.nb) return;
     const int64_t a = edge / d.nb, n = edge % d.nb;
     const int32_t b = nbr[edge];
@@ -598,8 +598,10 @@ static hipError_t launch_bwd_kspace(const Dims& d, const double* G, const double
 // dD (or dDp / dDm) for the given energy branches
 static hipError_t launch_dd(const Dims& d, const double* G, const double* A, const int32_t* nbr, const double* gS, cd calpha,
                             double* dD, int branches, hipStream_t stream) {
-    hipLaunchKernelGGL(bwd_dd_kernel, dim3((unsigned)(d.na * d.nb)), dim3(kBwdThreads), bwd_lds_dd(d), stream, d, G, A, nbr,
-                       gS, calpha, branches, dD);
+    const int64_t all = d.na * d.nb, step = launch_groups(kBwdThreads);
+    for (int64_t first = 0; first < all; first += step)
+        hipLaunchKernelGGL(bwd_dd_kernel, dim3((unsigned)std::min(step, all - first)), dim3(kBwdThreads), bwd_lds_dd(d), stream, d,
+                           G, A, nbr, gS, calpha, branches, first, dD);
     return hipGetLastError();
 }
 
@@ -646,8 +648,10 @@ hipError_t launch_bwd(const Dims& d, const double* G, const double* Dp, const do
     if (dG || dA) {
         double* shares = dA ? reinterpret_cast<double*>(reinterpret_cast<char*>(ws) + bwd_csr_bytes(d)) : nullptr;
         const int64_t groups = (d.na + 7) / 8 * 8 * d.nkz;
-        hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kBwdThreads), lds, stream, d, G, Dp, Dm, A, gS, calpha, offset,
-                           edges, order, dG, shares);
+        const int64_t step = launch_groups(kBwdThreads) / 8 * 8;
+        for (int64_t first = 0; first < groups; first += step)
+            hipLaunchKernelGGL(kern, dim3((unsigned)std::min(step, groups - first)), dim3(kBwdThreads), lds, stream, d, G, Dp, Dm,
+                               A, gS, calpha, offset, edges, order, first, dG, shares);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (dA) {

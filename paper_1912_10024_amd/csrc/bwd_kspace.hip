@@ -46,7 +46,7 @@ template <int GSRC, int BSRC, bool TWO>
 __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p, const double* __restrict__ Dp,
                                                                 const double* __restrict__ Dm, const double* __restrict__ A,
                                                                 const int32_t* __restrict__ nbr, cd alpha, DhTile t,
-                                                                int nshare, double* __restrict__ out) {
+                                                                int nshare, ks::LaunchPart part, double* __restrict__ out) {
     extern __shared__ __align__(16) double smem[];
     const int n = (int)d.norb, nkz = (int)d.nkz, nw = (int)d.nw, ne = (int)d.ne, nb = (int)d.nb;
     const int nn = n * n, np = ks::row_len(n), eb = t.eb;
@@ -63,10 +63,10 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the workgroups of an atom on one XCD
-    const int per = nb * nshare, s = blockIdx.x >> 3;
-    const int64_t a = (int64_t)(s / per) * 8 + (blockIdx.x & 7);
+    const int s = blockIdx.x >> 3;
+    const int64_t a = part.a0 + s / part.n * 8 + (blockIdx.x & 7);
     if (a >= d.na) return;  // uniform, before any barrier
-    const int rem = s % per, share = rem % nshare;
+    const int rem = part.first + s % part.n, share = rem % nshare;
     const int64_t edge = a * nb + rem / nshare, edges = d.na * nb;
     const int32_t b = __builtin_amdgcn_readfirstlane(nbr[edge]);
     if (b < 0 || b >= d.na) return;  // the reduction writes zero
@@ -259,10 +259,11 @@ static hipError_t launch_dh(const Dims& d, const DhArgs& p, const double* Dp, co
     auto kern = dh_kspace_kernel<GSRC, BSRC, TWO>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds);
     if (e != hipSuccess) return e;
-    const int64_t groups = (d.na + 7) / 8 * 8 * d.nb * nshare;
-    if (groups > INT32_MAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kThreads), t.lds, stream, d, p, Dp, Dm, A, nbr, alpha, t, (int)nshare,
-                       shares);
+    if (d.nb * nshare > INT32_MAX) return hipErrorInvalidValue;
+    ks::launch_parts(d.na, d.nb * nshare, kThreads, [&](ks::LaunchPart part) {
+        hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, p, Dp, Dm, A, nbr, alpha, t, (int)nshare,
+                           part, shares);
+    });
     return hipGetLastError();
 }
 

@@ -11,6 +11,8 @@
 // (two LDS buffers), so a term costs two barriers.  When Norb^2 is small, the
 // sum over (i, u) of an output element is split over `parts` threads and
 // reduced in LDS once per output block.
+#include <algorithm>
+
 #include "sse_kernels.h"
 
 namespace sse {
@@ -171,7 +173,7 @@ __global__ __launch_bounds__(kGenThreads) void fwd_generic_kernel(Dims d, const 
 hipError_t launch_fwd_generic(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
                               const double* B, const int32_t* nbr, cd alpha, double* S, hipStream_t stream) {
     const int64_t nblk = d.nkz * d.ne * d.na;
-    const unsigned grid = (unsigned)(nblk < (int64_t)(1 << 30) ? nblk : (1 << 30));
+    const unsigned grid = (unsigned)std::min(nblk, launch_groups(kGenThreads));
     const int64_t nn = d.norb * d.norb;
     const int parts = gen_parts(nn);
     const bool stage = nn <= kGenStageMaxNN;

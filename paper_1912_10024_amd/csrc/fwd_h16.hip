@@ -47,6 +47,8 @@
 // work.  Each chunk's fp32 sums are unscaled
 // and added to fp64 accumulators; the (w, +/-) stencil adds them into an fp64
 // output ring in LDS in conflict-free phases (bitwise reproducible).
+#include <algorithm>
+
 #include "fwd_common.h"
 #include "sse_kernels.h"
 
@@ -219,7 +221,7 @@ template <int NORB, int NKZ, int NW, int NB, int EB, int PREC, int FLAGS>
 __global__ __launch_bounds__(512) void fwd_h16_kernel(Dims d, const double* __restrict__ G,
                                                       const double* __restrict__ Dg, const double* __restrict__ Ag,
                                                       const double* __restrict__ Bg, const int32_t* __restrict__ nbr,
-                                                      cd alpha, double* __restrict__ S) {
+                                                      cd alpha, double* __restrict__ S, int64_t first) {
     using C = H16Cfg<NORB, NKZ, NW, NB, EB>;
     using O = Split16<PREC>;
     constexpr bool NORM = O::NORM;
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(512) void fwd_h16_kernel(Dims d, const double* __re
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // XCD-aware mapping: the Norb workgroups of one atom share its D, grad H and
     // neighbour G blocks, so they get block ids that land on the same XCD.
-    const int64_t bid = blockIdx.x;
+    const int64_t bid = first + blockIdx.x;
     const int r = (int)((bid >> 3) % NORB);
     const int64_t a = ((bid >> 3) / NORB) * 8 + (bid & 7);
     if (a >= d.na) return;  // uniform for the whole workgroup, before any barrier
@@ -655,8 +657,10 @@ static hipError_t launch_h16_flags(const Dims& d, const double* G, const double*
                                        (int)C::LDS_BYTES);
     if (e != hipSuccess) return e;
     const int64_t groups = ((d.na + 7) / 8) * 8 * NORB;
-    hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(C::THREADS), C::LDS_BYTES, stream, d, G, D, A, B, nbr, alpha,
-                       S);
+    const int64_t step = launch_groups(C::THREADS) / 8 * 8;
+    for (int64_t first = 0; first < groups; first += step)
+        hipLaunchKernelGGL(kern, dim3((unsigned)std::min(step, groups - first)), dim3(C::THREADS), C::LDS_BYTES, stream, d, G, D,
+                           A, B, nbr, alpha, S, first);
     return hipGetLastError();
 }
 

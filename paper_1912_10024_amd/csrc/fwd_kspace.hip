@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
                                                                  const double* __restrict__ A,
                                                                  const double* __restrict__ B,
                                                                  const int32_t* __restrict__ nbr, InEdges in, cd alpha,
-                                                                 Tile tile, int e_lo, int e_hi, int64_t a0, int s_slots,
+                                                                 Tile tile, int e_lo, int e_hi, ks::LaunchPart part, int s_slots,
                                                                  double* __restrict__ S) {
     constexpr bool ADJ = MODE == kAdjoint;
     extern __shared__ __align__(16) double smem[];
@@ -96,11 +96,11 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
     // the workgroups of an atom get ids on one XCD, the tiles of a momentum next to
     // each other: their windows of energies overlap
     const int ntile = (e_hi - e_lo + eb - 1) / eb;
-    const int per = nkz * ntile, s = blockIdx.x >> 3;
-    const int64_t pos = a0 + s / per * 8 + (blockIdx.x & 7);
+    const int s = blockIdx.x >> 3;
+    const int64_t pos = part.a0 + s / part.n * 8 + (blockIdx.x & 7);
     if (pos >= d.na) return;  // uniform, before any barrier
     const int64_t a = ADJ ? __builtin_amdgcn_readfirstlane(in.order[pos]) : pos;
-    const int rem = s % per, kt = rem / ntile, e0 = e_lo + (rem - kt * ntile) * eb;
+    const int rem = part.first + s % part.n, kt = rem / ntile, e0 = e_lo + (rem - kt * ntile) * eb;
     const int e_n = e_hi - e0 < eb ? e_hi - e0 : eb;  // energies of this tile
     const int ewin = eb + 2 * nw;
     const int nn = n * n;
@@ -292,11 +292,11 @@ static hipError_t launch_cb(const Dims& d, const double* G, int64_t g_atom, int6
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds);
     if (e != hipSuccess) return e;
     const int64_t per = d.nkz * ((e_hi - e_lo + t.eb - 1) / t.eb);
-    if (per > (int64_t(1) << 26)) return hipErrorInvalidValue;
-    const int64_t na8 = (d.na + 7) / 8 * 8, step = std::max<int64_t>(8, ((int64_t)1 << 30) / per / 8 * 8);
-    for (int64_t a0 = 0; a0 < na8; a0 += step)
-        hipLaunchKernelGGL(kern, dim3((unsigned)(std::min(step, na8 - a0) * per)), dim3(kThreads), t.lds, stream, d, G, g_atom,
-                           g_kst, g_est, slab, Dp, Dm, A, B, nbr, in, alpha, t, e_lo, e_hi, a0, s_slots, S);
+    if (per > INT32_MAX) return hipErrorInvalidValue;
+    ks::launch_parts(d.na, per, kThreads, [&](ks::LaunchPart part) {
+        hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, G, g_atom, g_kst, g_est, slab, Dp, Dm, A,
+                           B, nbr, in, alpha, t, e_lo, e_hi, part, s_slots, S);
+    });
     return hipGetLastError();
 }
 

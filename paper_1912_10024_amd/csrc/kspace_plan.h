@@ -27,6 +27,25 @@ struct Div {
 // lanes that read down a column hit distinct banks
 __host__ __device__ __forceinline__ int row_len(int n) { return n | 1; }
 
+// A launch of `per` workgroups for each of na atoms, dealt over the eight XCDs by atom
+// (workgroup x: atom x mod 8 of its eight), in parts of as many workgroups as a launch may
+// have: whole groups of eight atoms, or, where eight atoms are too many, a range of `per`.
+struct LaunchPart {
+    int64_t a0;    // first atom
+    int first, n;  // the range of `per`
+    unsigned groups;
+};
+template <class Launch>
+inline void launch_parts(int64_t na, int64_t per, int threads, Launch launch) {
+    const int64_t most = launch_groups(threads), na8 = (na + 7) / 8 * 8;
+    const int64_t atoms = std::max<int64_t>(8, most / per / 8 * 8), range = std::min(per, most / 8);
+    for (int64_t a0 = 0; a0 < na8; a0 += atoms)
+        for (int64_t first = 0; first < per; first += range) {
+            const int64_t n = std::min(range, per - first);
+            launch(LaunchPart{a0, (int)first, (int)n, (unsigned)(std::min(atoms, na8 - a0) * n)});
+        }
+}
+
 // The first task of a wave when the tasks from `shift` on go to waves 0, 1, ...: the
 // tasks of one step are dealt on from where the last step's ended.  A mask, since
 // wave - shift is negative as soon as the steps before had more tasks than waves.

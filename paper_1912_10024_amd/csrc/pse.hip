@@ -31,6 +31,8 @@
 //
 // pse_generic_kernel (any other shape): one workgroup per neighbour slot, the
 // same three steps on the vector ALUs with one thread per (q, w).
+#include <algorithm>
+
 #include "sse_kernels.h"
 
 namespace sse {
@@ -374,7 +376,7 @@ __global__ __launch_bounds__(kPseThreads) void pse_generic_kernel(Dims d, const 
                                                                   const double* __restrict__ Go,
                                                                   const double* __restrict__ Ag,
                                                                   const int32_t* __restrict__ nbr, cd beta,
-                                                                  double* __restrict__ Pi) {
+                                                                  int64_t first, double* __restrict__ Pi) {
     extern __shared__ __align__(16) double smem[];
     const int N = (int)d.norb, NN = N * N;
     const int nqw = (int)(d.nqz * d.nw);
@@ -383,7 +385,7 @@ __global__ __launch_bounds__(kPseThreads) void pse_generic_kernel(Dims d, const 
     cd* sV = sG + NN;                      // [3][N][N] V_j = A_j Go
     cd* sT = sV + 3 * NN;                  // [9][NN]  entry (ij, s*N + t) = T_ij[t][s]
     const int tid = threadIdx.x;
-    const int64_t edge = blockIdx.x;
+    const int64_t edge = first + blockIdx.x;
     const int64_t a = edge / d.nb, n = edge % d.nb;
     const int32_t b = nbr[edge];
     const bool valid_b = b >= 0 && b < d.na;
@@ -473,8 +475,10 @@ hipError_t launch_pse(const Dims& d, const double* Gs, const double* Go, const d
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pse_generic_kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(pse_generic_kernel, dim3((unsigned)(d.na * d.nb)), dim3(kPseThreads), lds, stream, d, Gs, Go, A,
-                       nbr, beta, Pi);
+    const int64_t edges = d.na * d.nb, step = launch_groups(kPseThreads);
+    for (int64_t first = 0; first < edges; first += step)
+        hipLaunchKernelGGL(pse_generic_kernel, dim3((unsigned)std::min(step, edges - first)), dim3(kPseThreads), lds, stream, d,
+                           Gs, Go, A, nbr, beta, first, Pi);
     return hipGetLastError();
 }
 

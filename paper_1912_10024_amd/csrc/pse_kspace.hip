@@ -52,7 +52,7 @@ struct CorrArgs {
 template <int YSRC, int XSRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
 __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs g, const double* __restrict__ A,
                                                                   const int32_t* __restrict__ nbr, cd scale, CorrTile t,
-                                                                  int64_t a0, double* __restrict__ out) {
+                                                                  ks::LaunchPart part, double* __restrict__ out) {
     extern __shared__ __align__(16) double smem[];
     const int n = (int)d.norb, nkz = (int)d.nkz, nw = (int)d.nw, ne = (int)d.ne, nb = (int)d.nb;
     const int nn = n * n, np = ks::row_len(n), eb = t.eb;
@@ -66,10 +66,10 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the workgroups of an atom on one XCD: they read the same blocks of g
-    const int per = nb * nkz * t.nwg, s = blockIdx.x >> 3;
-    const int64_t a = a0 + s / per * 8 + (blockIdx.x & 7);
+    const int s = blockIdx.x >> 3;
+    const int64_t a = part.a0 + s / part.n * 8 + (blockIdx.x & 7);
     if (a >= d.na) return;  // uniform, before any barrier
-    int rem = s % per;
+    int rem = part.first + s % part.n;
     const int wg = rem % t.nwg;
     rem /= t.nwg;
     const int m = rem / nkz, kt = rem % nkz;
@@ -326,11 +326,10 @@ static hipError_t launch_corr_wb(const Dims& d, const CorrArgs& g, const double*
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds);
     if (e != hipSuccess) return e;
     const int64_t per = d.nb * d.nkz * t.nwg;
-    if (per > (int64_t(1) << 26)) return hipErrorInvalidValue;
-    const int64_t na8 = (d.na + 7) / 8 * 8, step = std::max<int64_t>(8, ((int64_t)1 << 30) / per / 8 * 8);
-    for (int64_t a0 = 0; a0 < na8; a0 += step)
-        hipLaunchKernelGGL(kern, dim3((unsigned)(std::min(step, na8 - a0) * per)), dim3(kThreads), t.lds, stream, d, g, A, nbr,
-                           scale, t, a0, out);
+    if (per > INT32_MAX) return hipErrorInvalidValue;
+    ks::launch_parts(d.na, per, kThreads, [&](ks::LaunchPart part) {
+        hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, g, A, nbr, scale, t, part, out);
+    });
     return hipGetLastError();
 }
 

@@ -50,6 +50,10 @@ struct Dims {
     int64_t nkz, ne, nqz, nw, na, nb, norb, gs;
 };
 
+// Workgroups that one launch may have: HIP takes the number of work-items modulo 2^32
+// without an error, and the rest would never run.
+inline int64_t launch_groups(int threads) { return ((int64_t(1) << 32) - 1) / threads; }
+
 inline Dims to_dims(const sse_dims& d) {
     return Dims{d.nkz, d.ne, d.nqz, d.nw, d.na, d.nb, d.norb, d.g_slots};
 }

@@ -102,11 +102,34 @@ static int corr_support() {
     return 0;
 }
 
+// the parts of a launch hold every (atom, workgroup of an atom) once, in at most 2^32 - 1
+// work-items each
+static int launch_parts() {
+    for (int threads : {256, 512})
+        for (int64_t na : {1LL, 9LL, 4864LL, 1100000LL, 300000000LL})
+            for (int64_t per : {1LL, 28LL, 1000LL, 3000000LL, 2000000000LL}) {
+                if (na > 10000 && per > 10000) continue;  // beyond any card's memory, and many parts
+                int64_t next_a = 0, next = 0;
+                bool ok = true;
+                ks::launch_parts(na, per, threads, [&](ks::LaunchPart p) {
+                    const int64_t atoms = (int64_t)p.groups / p.n;
+                    ok = ok && p.a0 == next_a && p.first == next && (int64_t)p.groups == atoms * p.n && atoms % 8 == 0 && atoms > 0 &&
+                         (int64_t)p.groups * threads < (int64_t(1) << 32);
+                    next += p.n;
+                    if (next == per) next_a += atoms, next = 0;
+                });
+                if (ok && next == 0 && next_a >= na) continue;
+                printf("%lld atoms of %lld workgroups of %d\n", (long long)na, (long long)per, threads);
+                return 1;
+            }
+    return 0;
+}
+
 int main(int argc, char** argv) {
     const struct {
         const char* name;
         int (*run)();
-    } checks[] = {{"first_task", first_task}, {"corr_window", corr_window}, {"corr_search_time", corr_search_time}, {"corr_support", corr_support}};
+    } checks[] = {{"first_task", first_task}, {"corr_window", corr_window}, {"corr_search_time", corr_search_time}, {"corr_support", corr_support}, {"launch_parts", launch_parts}};
     for (const auto& c : checks)
         if (argc > 1 && !strcmp(argv[1], c.name)) return c.run();
     printf("no such check\n");

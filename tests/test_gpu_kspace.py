@@ -308,3 +308,56 @@ def test_pi_where_only_one_window_fits():
     ref = oracle.pse_forward(d, x["G"], x["Go"], x["dH"], x["nbr"])
     assert _rel(sse.phonon_forward(t["G"], t["Go"], t["dH"], t["nbr"], d.nqz, d.nw).cpu().numpy(), ref) <= TOL
     assert _rel(_pi_ws(t, d, 0), ref) <= TOL
+
+
+def test_more_workgroups_than_one_launch_takes():
+    """A launch holds at most 2^32 work-items.  Over a million atoms with four neighbours
+    need more for Pi and dD (2^23 workgroups of 512) and for d gradH (2^24 of 256); sampled
+    atoms against the oracle on their own neighbourhood."""
+    d = Dims(nkz=2, ne=2, nqz=2, nw=1, na=1100000, nb=8, norb=1, g_slots=1)
+    print(f"[gpu] kspace many atoms dims={d.as_tuple()}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    cn = lambda shape: torch.view_as_complex(torch.randn((*shape, 2), generator=gen, dtype=torch.float64, device="cuda"))
+    t = dict(G=cn(d.g_shape), Go=cn(d.g_shape), D=cn(d.d_shape), dH=cn(d.dh_shape), gS=cn(d.sigma_shape))
+    step = torch.tensor([1, 2, 5, 17, 1000, 40001, 333333, 700001], device="cuda")
+    t["nbr"] = ((torch.arange(d.na, device="cuda")[:, None] + step[None]) % d.na).to(torch.int32).contiguous()
+    P = sse.phonon_forward(t["G"], t["Go"], t["dH"], t["nbr"], d.nqz, d.nw)
+    grads = sse.backward(t["G"], t["D"], t["dH"], t["nbr"], t["gS"])
+    for a in (0, 7, d.na // 2, d.na - 1):
+        # the atom and its neighbours as a structure of their own: its edges alone have terms
+        atoms = [a] + t["nbr"][a].tolist()
+        own = {k: t[k][:, :, atoms].cpu().numpy().copy() for k in ("G", "Go", "D", "gS")}
+        own["dH"] = t["dH"][atoms].cpu().numpy().copy()
+        own["gS"][:, :, 1:] = 0
+        e = d.replace(na=len(atoms))
+        nbr = np.tile(np.arange(1, d.nb + 1, dtype=np.int32), (len(atoms), 1))
+        ref = oracle.pse_forward(e, own["G"], own["Go"], own["dH"], nbr)
+        assert _rel(P[:, :, a].cpu().numpy(), ref[:, :, 0]) <= TOL
+        _, rD, rH = oracle.sse_backward(e, own["G"], own["D"], own["dH"], nbr, own["gS"])
+        assert _rel(grads[1][:, :, a].cpu().numpy(), rD[:, :, 0]) <= TOL
+        assert _rel(grads[2][a].cpu().numpy(), rH[0]) <= TOL
+
+
+def test_more_workgroups_than_one_launch_takes_in_half_precision():
+    """The same for the 16-bit forward, whose workgroups (norb per atom, of 512) pass 2^32
+    work-items at two million atoms of four orbitals; against the fp64 form there."""
+    d = Dims(nkz=3, ne=3, nqz=3, nw=2, na=2110000, nb=4, norb=4, g_slots=1)
+    print(f"[gpu] 16-bit many atoms dims={d.as_tuple()}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(6)
+
+    def cn(shape):
+        x = torch.empty(shape, dtype=torch.complex128, device="cuda")
+        torch.view_as_real(x).normal_(generator=gen)
+        return x
+
+    G, D, dH = cn(d.g_shape), cn(d.d_shape), cn(d.dh_shape)
+    step = torch.tensor([1, 2, 1000, 700001], device="cuda")
+    nbr = ((torch.arange(d.na, device="cuda")[:, None] + step[None]) % d.na).to(torch.int32).contiguous()
+    out = torch.full(d.sigma_shape, complex(float("nan"), float("nan")), dtype=torch.complex128, device="cuda")
+    S = sse.forward(G, D, dH, nbr, precision="fp16x2", out=out)
+    ref = sse.forward(G, D, dH, nbr)
+    for a in (0, 1055000, 2097151, 2097152, d.na - 1):
+        err = (S[:, :, a] - ref[:, :, a]).abs().norm() / ref[:, :, a].abs().norm()
+        assert float(err) <= 1e-5, (a, float(err))   # fp16x2 carries about 22 bits; unwritten is NaN

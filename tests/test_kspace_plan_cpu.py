@@ -18,7 +18,7 @@ def checker(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["first_task", "corr_window", "corr_search_time", "corr_support"])
+@pytest.mark.parametrize("check", ["first_task", "corr_window", "corr_search_time", "corr_support", "launch_parts"])
 def test_plan(checker, check):
     res = subprocess.run([checker, check], capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stdout
