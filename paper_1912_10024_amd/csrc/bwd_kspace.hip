@@ -46,7 +46,8 @@ template <int GSRC, int BSRC, bool TWO>
 __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p, const double* __restrict__ Dp,
                                                                 const double* __restrict__ Dm, const double* __restrict__ A,
                                                                 const int32_t* __restrict__ nbr, cd alpha, DhTile t,
-                                                                int nshare, ks::LaunchPart part, double* __restrict__ out) {
+                                                                int nshare, ks::LaunchPart part, ks::Twiddles table,
+                                                                double* __restrict__ out) {
     extern __shared__ __align__(16) double smem[];
     const int n = (int)d.norb, nkz = (int)d.nkz, nw = (int)d.nw, ne = (int)d.ne, nb = (int)d.nb;
     const int nn = n * n, np = ks::row_len(n), eb = t.eb;
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
     cd* sO = sD + (TWO ? 18 : 9) * nw;     // the chunk's result
     cd* sA = sO + 3 * t.rc * n;            // grad H of the edge
     cd* tw = sA + 3 * nn;
-    int* bad = reinterpret_cast<int*>(tw + nkz);
+    int* bad = reinterpret_cast<int*>(tw + 2 * nkz);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the workgroups of an atom on one XCD
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
     if (b < 0 || b >= d.na) return;  // the reduction writes zero
     const int m_lo = p.by_energy ? 0 : share, m_hi = p.by_energy ? nkz : share + 1;
     const int e_lo = p.by_energy ? 32 * share : 0, e_hi = p.by_energy ? (e_lo + 32 < ne ? e_lo + 32 : ne) : ne;
-    ks::stage_twiddles(tw, nkz, tid, kThreads);
+    ks::stage_twiddles(tw, table, nkz, tid, kThreads);
     ks::stage_factor<kThreads>(A, edge, nn, sA, tid);
     const ks::Source gs{p.g + 2 * a * p.g_atom, p.g_kst, p.g_est}, bs{p.G + 2 * b * p.G_atom, p.G_kst, p.G_est};
     const int kk = lane >> 4, j16 = lane & 15;
@@ -201,7 +202,7 @@ static int64_t dh_body(const Dims& d, int rc, int eb) {
     return std::max(std::max(2 * rows, eb * 3 * rc * n + eb * n * np), (int64_t)kWaves * 16 * 64 / 2);
 }
 static int64_t dh_entries(const Dims& d, bool two, int rc, int eb) {
-    return dh_body(d, rc, eb) + (two ? 18 : 9) * d.nw + 3 * rc * d.norb + 3 * d.norb * d.norb + d.nkz + 1;
+    return dh_body(d, rc, eb) + (two ? 18 : 9) * d.nw + 3 * rc * d.norb + 3 * d.norb * d.norb + 2 * d.nkz + 1;
 }
 static bool dh_fits(const Dims& d, bool two) {  // the smallest tile
     return d.norb <= 32 && d.nkz <= 128 && d.ne < (int64_t(1) << 28) && d.nw < (1 << 14) &&
@@ -262,7 +263,7 @@ static hipError_t launch_dh(const Dims& d, const DhArgs& p, const double* Dp, co
     if (d.nb * nshare > INT32_MAX) return hipErrorInvalidValue;
     ks::launch_parts(d.na, d.nb * nshare, kThreads, [&](ks::LaunchPart part) {
         hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, p, Dp, Dm, A, nbr, alpha, t, (int)nshare,
-                           part, shares);
+                           part, ks::twiddles(d.nkz), shares);
     });
     return hipGetLastError();
 }

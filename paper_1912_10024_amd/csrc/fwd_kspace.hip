@@ -45,7 +45,7 @@ Tile make_tile(const Dims& d, int eb, int rc, int cb, bool two, bool stored) {
     Tile t{eb, rc, (n + cb - 1) / cb, ks::Div(n), ks::Div((n + cb - 1) / cb), {ks::Div(rc * n), ks::Div(tail * n)}, 0, 0, 0};
     const int64_t rows = (eb + 2 * d.nw) * rc * ks::row_len(n);
     const int64_t body = std::max(2 * rows, (int64_t)eb * 3 * rc * n);
-    const int64_t all = body + (two ? 18 : 9) * d.nw + (stored ? 6 : 3) * n * n + d.nkz + 1;
+    const int64_t all = body + (two ? 18 : 9) * d.nw + (stored ? 6 : 3) * n * n + 2 * d.nkz + 1;
     t.lds = all < (1 << 20) ? sizeof(cd) * (size_t)all : (size_t)1 << 30;
     t.rows = (int)std::min<int64_t>(rows, 1 << 28);
     t.body = (int)std::min<int64_t>(body, 1 << 28);
@@ -76,7 +76,8 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
                                                                  const double* __restrict__ A,
                                                                  const double* __restrict__ B,
                                                                  const int32_t* __restrict__ nbr, InEdges in, cd alpha,
-                                                                 Tile tile, int e_lo, int e_hi, ks::LaunchPart part, int s_slots,
+                                                                 Tile tile, int e_lo, int e_hi, ks::LaunchPart part,
+                                                                 ks::Twiddles table, int s_slots,
                                                                  double* __restrict__ S) {
     constexpr bool ADJ = MODE == kAdjoint;
     extern __shared__ __align__(16) double smem[];
@@ -90,7 +91,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
     cd* sA = sD + (TWO ? 18 : 9) * nw;     // grad H of the edge [i][r][c]
     cd* sR = sA + (MODE == kStored ? 3 * n * n : 0);  // right factor
     cd* tw = sR + 3 * n * n;
-    int* bad = reinterpret_cast<int*>(tw + nkz);
+    int* bad = reinterpret_cast<int*>(tw + 2 * nkz);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the workgroups of an atom get ids on one XCD, the tiles of a momentum next to
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
     const int nn = n * n;
     const int64_t edges = d.na * d.nb;
 
-    if constexpr (!DIRECT) ks::stage_twiddles(tw, nkz, tid, kThreads);
+    if constexpr (!DIRECT) ks::stage_twiddles(tw, table, nkz, tid, kThreads);
     // this thread's entries of the output tile: columns (e, c) number l and l + 64 of
     // pass t's 128, rows rr .. rr + CB - 1
     const int ncol = e_n * n, nrb = tile.ncb;
@@ -190,16 +191,38 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
                 const double* f = reinterpret_cast<const double*>(sA) + 2 * (ADJ ? r0 * n + fc : fc * n + r0) + (lane & 1);
                 const cd* ua = sU + ea * 3 * nel + x0 - ea * n;
                 const cd* ub = sU + eb_ * 3 * nel + x1 - eb_ * n;
-                ks::uniform_product<2, CB, ADJ>(
-                    sum[ti], 3 * rc,
-                    [&](int k) {
-                        const int i = k >= 2 * rc ? 2 : k >= rc ? 1 : 0;
-                        return f[2 * i * nn + (k - i * rc) * f_step];
-                    },
-                    [&](int k, cd (&x)[2]) {
-                        x[0] = ks::ld(ua + k * n);
-                        x[1] = ks::ld(ub + k * n);
-                    });
+                auto operand = [&](int k, cd (&x)[2]) {
+                    x[0] = ks::ld(ua + k * n);
+                    x[1] = ks::ld(ub + k * n);
+                };
+                if constexpr (ADJ) {
+                    // each direction's sum by itself: one chain over an atom's whole in-degree rounds
+                    // more than the terms it adds
+                    for (int i = 0; i < 3; ++i) {
+                        cd part[2][CB];
+#pragma unroll
+                        for (int r = 0; r < CB; ++r) part[0][r] = part[1][r] = cd{0.0, 0.0};
+                        const double* fi = f + 2 * i * nn;
+                        ks::uniform_product<2, CB, ADJ>(
+                            part, rc, [&](int k) { return fi[k * f_step]; },
+                            [&](int k, cd (&x)[2]) { operand(i * rc + k, x); });
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+#pragma unroll
+                            for (int r = 0; r < CB; ++r) {
+                                sum[ti][h][r].re += part[h][r].re;
+                                sum[ti][h][r].im += part[h][r].im;
+                            }
+                    }
+                } else {
+                    ks::uniform_product<2, CB, ADJ>(
+                        sum[ti], 3 * rc,
+                        [&](int k) {
+                            const int i = k >= 2 * rc ? 2 : k >= rc ? 1 : 0;
+                            return f[2 * i * nn + (k - i * rc) * f_step];
+                        },
+                        operand);
+                }
             }
         }
     }
@@ -295,7 +318,7 @@ static hipError_t launch_cb(const Dims& d, const double* G, int64_t g_atom, int6
     if (per > INT32_MAX) return hipErrorInvalidValue;
     ks::launch_parts(d.na, per, kThreads, [&](ks::LaunchPart part) {
         hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, G, g_atom, g_kst, g_est, slab, Dp, Dm, A,
-                           B, nbr, in, alpha, t, e_lo, e_hi, part, s_slots, S);
+                           B, nbr, in, alpha, t, e_lo, e_hi, part, ks::twiddles(d.nkz), s_slots, S);
     });
     return hipGetLastError();
 }
@@ -351,7 +374,7 @@ hipError_t launch_dg_kspace(const Dims& d, const double* g, const double* g_hat,
         e = launch_tables<ks::kTrans, false>(two, kAdjoint, cb, d, g, nn, ne * d.na * nn, d.na * nn, 0, Dm, Dp, A, no_b, no_nbr, in,
                                              calpha, t, 0, (int)ne, (int)d.gs, dG, stream);
     if (e != hipSuccess) return e;
-    return launch_inverse((int)d.nkz, ne * d.na, nn, d.gs * nn, cd{calpha.re / (double)d.nkz, calpha.im / (double)d.nkz}, dG,
+    return launch_inverse((int)d.nkz, ne * d.na, nn, d.gs * nn, calpha, dG,
                           stream);
 }
 
@@ -389,7 +412,7 @@ hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, c
                                              (int)ne, 1, S, stream);
         if (e != hipSuccess) return e;
     }
-    return launch_inverse((int)d.nkz, ne * d.na, nn, nn, cd{alpha.re / (double)d.nkz, alpha.im / (double)d.nkz}, S, stream);
+    return launch_inverse((int)d.nkz, ne * d.na, nn, nn, alpha, S, stream);
 }
 
 }  // namespace sse

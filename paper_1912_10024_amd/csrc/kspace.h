@@ -35,13 +35,59 @@ __device__ __forceinline__ cd ld(const cd* p) {
 }
 __device__ __forceinline__ void st(cd* p, cd v) { *reinterpret_cast<double2*>(p) = make_double2(v.re, v.im); }
 
-// exp(-2 pi i m / nkz), m = 0 .. nkz-1
-__device__ __forceinline__ void stage_twiddles(cd* tw, int nkz, int tid, int threads) {
+// exp(-2 pi i m / nkz), m = 0 .. nkz-1, each as a rounded value and what rounding took off.
+// The same twiddle enters the transform of G, that of D and the inverse: with few momenta
+// its rounding would be one error with one sign in all terms (at three momenta it made dG
+// 1.1 times further off than the direct sum).  From kTableNkz on there are enough different
+// ones for that not to matter, and the second parts are zero.
+__device__ __forceinline__ void stage_twiddles(cd* tw, const Twiddles& table, int nkz, int tid, int threads) {
     for (int m = tid; m < nkz; m += threads) {
-        double s, c;
-        sincospi(2.0 * (double)m / (double)nkz, &s, &c);
-        st(tw + m, cd{c, -s});
+        if (nkz < kTableNkz) {
+            st(tw + 2 * m, cd{table.t[m][0], table.t[m][1]});
+            st(tw + 2 * m + 1, cd{table.t[m][2], table.t[m][3]});
+        } else {
+            double s, c;
+            sincospi(2.0 * (double)m / (double)nkz, &s, &c);
+            st(tw + 2 * m, cd{c, -s});
+            st(tw + 2 * m + 1, cd{0.0, 0.0});
+        }
     }
+}
+
+// One pair of terms, k and nkz - k, of a sum over the momenta: the twiddle tw[0] + tw[1] and
+// its conjugate times a and b, as Re (a + b) + i Im (a - b).  Half the products of the two terms
+// by themselves, and a chain half as long to round.  CONJ: with the conjugate twiddles.
+template <bool CONJ = false>
+__device__ __forceinline__ void pair_fma(cd& s, cd a, cd b, cd hi, cd lo) {
+    const cd p{a.re + b.re, a.im + b.im}, q{a.re - b.re, a.im - b.im};
+    if (CONJ) hi.im = -hi.im, lo.im = -lo.im;
+    s.re = fma(lo.re, p.re, s.re);
+    s.im = fma(lo.re, p.im, s.im);
+    s.re = fma(-lo.im, q.im, s.re);
+    s.im = fma(lo.im, q.re, s.im);
+    s.re = fma(hi.re, p.re, s.re);
+    s.im = fma(hi.re, p.im, s.im);
+    s.re = fma(-hi.im, q.im, s.re);
+    s.im = fma(hi.im, q.re, s.im);
+}
+// the term at nkz / 2 (even nkz), whose twiddle is (-1)^m
+__device__ __forceinline__ void middle_add(cd& s, cd a, int m) {
+    s.re += m & 1 ? -a.re : a.re;
+    s.im += m & 1 ? -a.im : a.im;
+}
+// sum_k load(k) tw[k m mod nkz]
+template <bool CONJ = false, class Load>
+__device__ __forceinline__ cd momentum_sum(int nkz, int m, const cd* tw, Load load) {
+    cd s = load(0);
+    int j = m;
+#pragma unroll 2
+    for (int k = 1; 2 * k < nkz; ++k) {
+        pair_fma<CONJ>(s, load(k), load(nkz - k), ld(tw + 2 * j), ld(tw + 2 * j + 1));
+        j += m;
+        j -= j >= nkz ? nkz : 0;
+    }
+    if (!(nkz & 1)) middle_add(s, load(nkz / 2), m);
+    return s;
 }
 
 // Where a tile of energies x rows of a source block array is loaded from
@@ -80,14 +126,21 @@ __device__ __forceinline__ void load_rows(const Source& s, const cd* tw, int nkz
             acc[u] = cd{0.0, 0.0};
         }
         if constexpr (SRC == kTrans) {
-            int m = 0;  // k * kt mod nkz
-#pragma unroll 4
-            for (int k = 0; k < nkz; ++k) {
-                const cd t = ld(tw + m);
+            // momentum_sum of U entries at a time
 #pragma unroll
-                for (int u = 0; u < U; ++u) cfma(acc[u], cload(p[u], k * s.kst), t);
+            for (int u = 0; u < U; ++u) acc[u] = cload(p[u], 0);
+            int m = kt;  // k * kt mod nkz
+#pragma unroll 2
+            for (int k = 1; 2 * k < nkz; ++k) {
+                const cd hi = ld(tw + 2 * m), lo = ld(tw + 2 * m + 1);
+#pragma unroll
+                for (int u = 0; u < U; ++u) pair_fma(acc[u], cload(p[u], k * s.kst), cload(p[u], (nkz - k) * s.kst), hi, lo);
                 m += kt;
                 m -= m >= nkz ? nkz : 0;
+            }
+            if (!(nkz & 1)) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) middle_add(acc[u], cload(p[u], nkz / 2 * s.kst), kt);
             }
         } else {
 #pragma unroll
@@ -110,17 +163,10 @@ struct RowsAhead {
         const bool ok = e >= 0 && e < ne;
         const double* p = s.p + 2 * ((SRC == kTrans ? 0 : kt * s.kst) + (ok ? e : 0) * s.est + at);
         cd a{0.0, 0.0};
-        if constexpr (SRC == kTrans) {
-            int m = 0;
-#pragma unroll 4
-            for (int k = 0; k < nkz; ++k) {
-                cfma(a, cload(p, k * s.kst), ld(tw + m));
-                m += kt;
-                m -= m >= nkz ? nkz : 0;
-            }
-        } else {
+        if constexpr (SRC == kTrans)
+            a = momentum_sum(nkz, kt, tw, [&](int k) { return cload(p, k * s.kst); });
+        else
             a = cload(p, 0);
-        }
         if (!ok) a = cd{0.0, 0.0};
         return CT ? cd{a.re, -a.im} : a;
     }
@@ -438,16 +484,10 @@ __device__ __forceinline__ void stage_coeff(const double* __restrict__ D, const 
                                             int64_t edges, int64_t edge, cd* sD, int* bad, int tid) {
     for (int x = tid; x < nw * 9; x += THREADS) {
         const int w = x / 9, ij = x % 9;
-        cd v{0.0, 0.0};
+        cd v;
         const int64_t o = ((int64_t)w * edges + edge) * 9 + ij, qst = (int64_t)nw * edges * 9;
         if constexpr (TRANS) {
-            int m = 0;
-#pragma unroll 4
-            for (int q = 0; q < nkz; ++q) {
-                cfma(v, cload(D, o + q * qst), ld(tw + m));
-                m += kt;
-                m -= m >= nkz ? nkz : 0;
-            }
+            v = momentum_sum(nkz, kt, tw, [&](int q) { return cload(D, o + q * qst); });
         } else {
             v = cload(D, o + kt * qst);
         }

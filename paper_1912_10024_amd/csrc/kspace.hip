@@ -5,20 +5,30 @@
 
 namespace sse {
 
+// ks::momentum_sum of NK values in registers
+template <int NK, bool CONJ>
+__device__ __forceinline__ cd momentum_sum(const cd (&v)[NK > 0 ? NK : 1], const cd* tw, int m) {
+    cd s = v[0];
+#pragma unroll
+    for (int k = 1; 2 * k < NK; ++k) ks::pair_fma<CONJ>(s, v[k], v[NK - k], ks::ld(tw + 2 * (k * m % NK)), ks::ld(tw + 2 * (k * m % NK) + 1));
+    if constexpr (NK % 2 == 0) ks::middle_add(s, v[NK / 2], m);
+    return s;
+}
+
 // hat[m][x][e - first][nn] = sum_k src[k][e][x][nn] exp(-2 pi i k m / nkz) for e in
 // [first, first + n_e), x < na: a block's entries stay together, its momenta and
-// energies come next to each other.  The sum runs over k as in ks::load_rows, bit
-// for bit.  NK = 0: any nkz, the thread's inputs in LDS.
+// energies come next to each other.  The sum runs over pairs of k as in ks::load_rows,
+// bit for bit.  NK = 0: any nkz, the thread's inputs in LDS.
 template <int NK>
-__global__ __launch_bounds__(256) void transform_kernel(int nkz, int64_t first, int64_t n_e, int64_t na, int64_t nn,
-                                                        int64_t atom, int64_t est, int64_t kst,
+__global__ __launch_bounds__(256) void transform_kernel(int nkz, ks::Twiddles table, int64_t first, int64_t n_e, int64_t na,
+                                                        int64_t nn, int64_t atom, int64_t est, int64_t kst,
                                                         const double* __restrict__ src, double* __restrict__ hat) {
     extern __shared__ __align__(16) double smem[];
     cd* tw = reinterpret_cast<cd*>(smem);
     const int tid = threadIdx.x, threads = blockDim.x;
-    ks::stage_twiddles(tw, nkz, tid, threads);
+    ks::stage_twiddles(tw, table, nkz, tid, threads);
     __syncthreads();
-    cd* col = tw + nkz + tid;
+    cd* col = tw + 2 * nkz + tid;
     const int64_t total = n_e * na * nn, out_kst = na * n_e * nn;
     for (int64_t x = blockIdx.x * (int64_t)threads + tid; x < total; x += (int64_t)gridDim.x * threads) {
         const int64_t blk = x / nn, rc = x - blk * nn, e = blk / na, a = blk - e * na;
@@ -29,39 +39,32 @@ __global__ __launch_bounds__(256) void transform_kernel(int nkz, int64_t first, 
 #pragma unroll
             for (int k = 0; k < NK; ++k) v[k] = cload(p, k * kst);
 #pragma unroll
-            for (int m = 0; m < NK; ++m) {
-                cd s{0.0, 0.0};
-#pragma unroll
-                for (int k = 0; k < NK; ++k) cfma(s, v[k], ks::ld(tw + k * m % NK));
-                cstore(o, m * out_kst, s);
-            }
+            for (int m = 0; m < NK; ++m) cstore(o, m * out_kst, momentum_sum<NK, false>(v, tw, m));
         } else {
             for (int k = 0; k < nkz; ++k) ks::st(col + k * threads, cload(p, k * kst));
-            for (int m = 0; m < nkz; ++m) {
-                cd s{0.0, 0.0};
-                int j = 0;
-                for (int k = 0; k < nkz; ++k) {
-                    cfma(s, ks::ld(col + k * threads), ks::ld(tw + j));
-                    j += m;
-                    j -= j >= nkz ? nkz : 0;
-                }
-                cstore(o, m * out_kst, s);
-            }
+            for (int m = 0; m < nkz; ++m)
+                cstore(o, m * out_kst, ks::momentum_sum(nkz, m, tw, [&](int k) { return ks::ld(col + k * threads); }));
         }
     }
 }
 
-// X[k] = scale * sum_m X[m] exp(+2 pi i k m / nkz), in place over the leading axis of
+// X[k] = scale / nkz * sum_m X[m] exp(+2 pi i k m / nkz), in place over the leading axis of
 // [nkz][blocks][bs] (the first nn entries of every block of bs)
 template <int NK>
-__global__ __launch_bounds__(256) void inverse_kernel(int nkz, int64_t blocks, int64_t nn, int64_t bs, cd scale,
-                                                      double* __restrict__ X) {
+__global__ __launch_bounds__(256) void inverse_kernel(int nkz, ks::Twiddles table, int64_t blocks, int64_t nn, int64_t bs,
+                                                      cd scale, double* __restrict__ X) {
     extern __shared__ __align__(16) double smem[];
     cd* tw = reinterpret_cast<cd*>(smem);
     const int tid = threadIdx.x, threads = blockDim.x;
-    ks::stage_twiddles(tw, nkz, tid, threads);
+    ks::stage_twiddles(tw, table, nkz, tid, threads);
     __syncthreads();
-    cd* col = tw + nkz + tid;
+    cd* col = tw + 2 * nkz + tid;
+    // 1 / nkz in two terms: the quotient of every sum is rounded like a division
+    const double inv = 1.0 / (double)nkz, inv_low = fma(-inv, (double)nkz, 1.0) * inv;
+    auto scaled = [&](cd s) {
+        const cd v = cmul(scale, s);
+        return cd{fma(v.re, inv, v.re * inv_low), fma(v.im, inv, v.im * inv_low)};
+    };
     const int64_t total = blocks * nn, kst = blocks * bs;
     for (int64_t x = blockIdx.x * (int64_t)threads + tid; x < total; x += (int64_t)gridDim.x * threads) {
         const int64_t blk = x / nn;
@@ -71,24 +74,12 @@ __global__ __launch_bounds__(256) void inverse_kernel(int nkz, int64_t blocks, i
 #pragma unroll
             for (int m = 0; m < NK; ++m) v[m] = cload(p, m * kst);
 #pragma unroll
-            for (int k = 0; k < NK; ++k) {
-                cd s = v[0];
-#pragma unroll
-                for (int m = 1; m < NK; ++m) cfma_conj(s, v[m], ks::ld(tw + k * m % NK));
-                cstore(p, k * kst, cmul(scale, s));
-            }
+            for (int k = 0; k < NK; ++k) cstore(p, k * kst, scaled(momentum_sum<NK, true>(v, tw, k)));
         } else {
             for (int m = 0; m < nkz; ++m) ks::st(col + m * threads, cload(p, m * kst));
-            for (int k = 0; k < nkz; ++k) {
-                cd s{0.0, 0.0};
-                int j = 0;
-                for (int m = 0; m < nkz; ++m) {
-                    cfma_conj(s, ks::ld(col + m * threads), ks::ld(tw + j));
-                    j += k;
-                    j -= j >= nkz ? nkz : 0;
-                }
-                cstore(p, k * kst, cmul(scale, s));
-            }
+            for (int k = 0; k < nkz; ++k)
+                cstore(p, k * kst,
+                       scaled(ks::momentum_sum<true>(nkz, k, tw, [&](int m) { return ks::ld(col + m * threads); })));
         }
     }
 }
@@ -96,14 +87,15 @@ __global__ __launch_bounds__(256) void inverse_kernel(int nkz, int64_t blocks, i
 template <class K, class... Args>
 static hipError_t launch_transform_kernel(K kern, bool any, int nkz, int64_t total, hipStream_t stream, Args... args) {
     const int threads = any ? 64 : 256;
-    const size_t lds = sizeof(cd) * (size_t)(nkz + (any ? nkz * threads : 0));
+    const size_t lds = sizeof(cd) * (size_t)(2 * nkz + (any ? nkz * threads : 0));
     if (any) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)lds);
         if (e != hipSuccess) return e;
     }
     const int64_t want = (total + threads - 1) / threads;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(want < 65536 ? want : 65536)), dim3(threads), lds, stream, nkz, args...);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(want < 65536 ? want : 65536)), dim3(threads), lds, stream, nkz,
+                       ks::twiddles(nkz), args...);
     return hipGetLastError();
 }
 

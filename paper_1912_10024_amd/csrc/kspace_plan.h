@@ -3,6 +3,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 #include <cstddef>
 
 #include "sse_common.h"
@@ -44,6 +45,35 @@ inline void launch_parts(int64_t na, int64_t per, int threads, Launch launch) {
             const int64_t n = std::min(range, per - first);
             launch(LaunchPart{a0, (int)first, (int)n, (unsigned)(std::min(atoms, na8 - a0) * n)});
         }
+}
+
+// Twiddles of up to kTableNkz - 1 momenta, cos and -sin of 2 pi m / nkz rounded, then what
+// the rounding took off (from 64-bit mantissas: about eleven bits of it)
+constexpr int kTableNkz = 17;
+struct Twiddles {
+    double t[kTableNkz - 1][4];
+};
+inline const Twiddles& twiddles(int64_t nkz) {
+    struct All {
+        Twiddles of[kTableNkz];
+        All() {
+            for (int n = 1; n < kTableNkz; ++n)
+                for (int m = 0; m < kTableNkz - 1; ++m) {
+                    const int p = m % n, r = std::min(p, n - p);  // the angle 2 pi r / n in [0, pi]
+                    const long double x = 2.0L * 3.14159265358979323846264338327950288L * r / n;
+                    long double c = cosl(x), s = sinl(x);
+                    if (4 * r % n == 0) c = 4 * r == n ? 0 : r ? -1 : 1, s = 4 * r == n ? 1 : 0;
+                    if (p != r) s = -s;
+                    double* t = of[n].t[m];
+                    t[0] = (double)c;
+                    t[1] = -(double)s;
+                    t[2] = (double)(c - t[0]);
+                    t[3] = (double)(-s - t[1]);
+                }
+        }
+    };
+    static const All all;
+    return all.of[nkz < kTableNkz ? nkz : 0];
 }
 
 // The first task of a wave when the tasks from `shift` on go to waves 0, 1, ...: the
@@ -109,9 +139,9 @@ inline CorrShape corr_shape(const Dims& d, bool hi, bool lo, int wb, int rc) {
     s.nwg = up_div(nwb_all, s.nwb);
     s.ncb = up_div(n, kCorrCB);
     s.halo = (hi + lo) * nwb_all * wb;
-    s.base = s.halo * 3 * s.nel + 3 * n * n + (int)d.nkz + 1;
+    s.base = s.halo * 3 * s.nel + 3 * n * n + 2 * (int)d.nkz + 1;
     s.per = 6 * s.nel + (rc + n) * row_len(n);
-    s.least = wb * kCorrThreads + (int)d.nkz + 1;
+    s.least = wb * kCorrThreads + 2 * (int)d.nkz + 1;
     s.chunks = up_div(n, rc);
     s.x_passes = up_div(3 * rc, kCorrXB);
     s.step = wb * (hi && lo ? 14.0 : 12.0) + 10;

@@ -52,7 +52,7 @@ struct CorrArgs {
 template <int YSRC, int XSRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
 __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs g, const double* __restrict__ A,
                                                                   const int32_t* __restrict__ nbr, cd scale, CorrTile t,
-                                                                  ks::LaunchPart part, double* __restrict__ out) {
+                                                                  ks::LaunchPart part, ks::Twiddles table, double* __restrict__ out) {
     extern __shared__ __align__(16) double smem[];
     const int n = (int)d.norb, nkz = (int)d.nkz, nw = (int)d.nw, ne = (int)d.ne, nb = (int)d.nb;
     const int nn = n * n, np = ks::row_len(n), eb = t.eb;
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
     cd* sB = sG + t.g_entries;             // B [e][t][np]
     cd* sA = sB + eb * n * np;             // grad H of the edge
     cd* tw = sA + 3 * nn;
-    int* bad = reinterpret_cast<int*>(tw + nkz);
+    int* bad = reinterpret_cast<int*>(tw + 2 * nkz);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the workgroups of an atom on one XCD: they read the same blocks of g
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
         for (int u = 0; u < WB; ++u) acc[i][u] = cd{0.0, 0.0};
 
     if (valid) {
-        ks::stage_twiddles(tw, nkz, tid, kThreads);
+        ks::stage_twiddles(tw, table, nkz, tid, kThreads);
         if (tid == 0) *bad = 0;
         ks::stage_factor<kThreads>(A, edge, nn, sA, tid);
         const ks::Source ys{g.y + 2 * a * g.y_atom, g.y_kst, g.y_est};
@@ -328,7 +328,8 @@ static hipError_t launch_corr_wb(const Dims& d, const CorrArgs& g, const double*
     const int64_t per = d.nb * d.nkz * t.nwg;
     if (per > INT32_MAX) return hipErrorInvalidValue;
     ks::launch_parts(d.na, per, kThreads, [&](ks::LaunchPart part) {
-        hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, g, A, nbr, scale, t, part, out);
+        hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, g, A, nbr, scale, t, part,
+                           ks::twiddles(d.nkz), out);
     });
     return hipGetLastError();
 }
@@ -382,7 +383,7 @@ hipError_t launch_dd_kspace(const Dims& d, int branches, const double* g, const 
     else
         e = launch_dd<ks::kTrans, ks::kTrans>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
     if (e != hipSuccess) return e;
-    return launch_inverse((int)d.nkz, d.nw * na * d.nb, 9, 9, cd{calpha.re / (double)d.nkz, calpha.im / (double)d.nkz}, dD, stream);
+    return launch_inverse((int)d.nkz, d.nw * na * d.nb, 9, 9, calpha, dD, stream);
 }
 
 hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, const double* A, const int32_t* nbr, cd beta,
@@ -414,7 +415,7 @@ hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, c
         e = launch_pi_corr<ks::kTrans, false>(t.wb, d, g, A, nbr, beta, t, Pi, stream);
     }
     if (e != hipSuccess) return e;
-    return launch_inverse(nkz, d.nw * na * d.nb, 9, 9, cd{beta.re / (double)d.nkz, beta.im / (double)d.nkz}, Pi, stream);
+    return launch_inverse(nkz, d.nw * na * d.nb, 9, 9, beta, Pi, stream);
 }
 
 // both transforms, or slabs of at most 32 GiB of them (a slab costs a prologue and a

@@ -22,7 +22,7 @@ hipError_t launch_fwd_generic(const Dims& d, const double* G, const double* Dp, 
 // the momentum transform of a block array into hat[m][atom][energy][nn] for the
 // energies [first, first + n_e) (atom, est, kst: complex elements of src between
 // atoms, energies and momenta), and its inverse in place over the leading axis of
-// [nkz][blocks][bs] (the first nn entries of every block), times scale
+// [nkz][blocks][bs] (the first nn entries of every block), times scale / nkz
 hipError_t launch_transform(int nkz, int64_t first, int64_t n_e, int64_t na, int64_t nn, int64_t atom, int64_t est,
                             int64_t kst, const double* src, double* hat, hipStream_t stream);
 hipError_t launch_inverse(int nkz, int64_t blocks, int64_t nn, int64_t bs, cd scale, double* X, hipStream_t stream);
