@@ -22,6 +22,7 @@
 // reproducible; dD by one workgroup per edge.
 #include <algorithm>
 
+#include "kspace.h"
 #include "sse_kernels.h"
 
 namespace sse {
@@ -558,28 +559,29 @@ static hipError_t launch_bwd_kspace(const Dims& d, const double* G, const double
                                     double* dA, char* ws, size_t ws_bytes, const int32_t* offset, const int32_t* edges,
                                     const int32_t* order, hipStream_t stream, bool signed_form) {
     const cd calpha{alpha.re, -alpha.im};
-    const int nkz = (int)d.nkz;
     const int64_t nn = d.norb * d.norb;
+    // the sum over the momenta as it stands under the same line as the forward
+    const bool direct = d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks;
     const size_t hat = bwd_hat_bytes(d), used = bwd_csr_bytes(d) + (dA ? bwd_dh_bytes(d, signed_form) : 0);
     double *g_hat = nullptr, *G_hat = nullptr;
     hipError_t e = hipSuccess;
-    if (d.nkz > 1 && ws_bytes >= used + hat) {
+    if (!direct && ws_bytes >= used + hat) {
         g_hat = reinterpret_cast<double*>(ws + used);
-        e = launch_transform(nkz, 0, d.ne, d.na, nn, nn, d.na * nn, d.ne * d.na * nn, gS, g_hat, stream);
+        e = launch_transform(d, 0, d.ne, ks::array_blocks(gS, d, 1), g_hat, stream);
         if (e != hipSuccess) return e;
         if ((dA || dDp || dDm) && ws_bytes >= used + 2 * hat) {
             G_hat = reinterpret_cast<double*>(ws + used + hat);
-            e = launch_transform(nkz, 0, d.ne, d.na, nn, d.gs * nn, d.na * d.gs * nn, d.ne * d.na * d.gs * nn, G, G_hat, stream);
+            e = launch_transform(d, 0, d.ne, ks::array_blocks(G, d, d.gs), G_hat, stream);
             if (e != hipSuccess) return e;
         }
     }
     if (dG) {
-        e = launch_dg_kspace(d, gS, g_hat, Dp, Dm, A, offset, edges, order, calpha, dG, stream);
+        e = launch_dg_kspace(d, direct, gS, g_hat, Dp, Dm, A, offset, edges, order, calpha, dG, stream);
         if (e != hipSuccess) return e;
     }
     if (dA) {
         double* shares = reinterpret_cast<double*>(ws + bwd_csr_bytes(d));
-        e = launch_dh_kspace(d, gS, g_hat, G, G_hat, Dp, Dm, A, nbr, alpha, bwd_by_energy(d, signed_form), shares, stream);
+        e = launch_dh_kspace(d, direct, gS, g_hat, G, G_hat, Dp, Dm, A, nbr, alpha, bwd_by_energy(d, signed_form), shares, stream);
         if (e != hipSuccess) return e;
         const int64_t n = d.na * d.nb * 3 * nn;
         hipLaunchKernelGGL(bwd_dh_reduce_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 65536)), dim3(256), 0, stream,
@@ -588,10 +590,10 @@ static hipError_t launch_bwd_kspace(const Dims& d, const double* G, const double
         if (e != hipSuccess) return e;
     }
     if (dDp) {
-        e = launch_dd_kspace(d, signed_form ? 1 : 3, gS, g_hat, G, G_hat, A, nbr, calpha, dDp, stream);
+        e = launch_dd_kspace(d, direct, signed_form ? 1 : 3, gS, g_hat, G, G_hat, A, nbr, calpha, dDp, stream);
         if (e != hipSuccess) return e;
     }
-    if (dDm) return launch_dd_kspace(d, 2, gS, g_hat, G, G_hat, A, nbr, calpha, dDm, stream);
+    if (dDm) return launch_dd_kspace(d, direct, 2, gS, g_hat, G, G_hat, A, nbr, calpha, dDm, stream);
     return hipSuccess;
 }
 

@@ -35,14 +35,13 @@ struct DhTile {
 };
 
 struct DhArgs {
-    const double *g, *G;
-    int64_t g_atom, g_kst, g_est, G_atom, G_kst, G_est;
+    ks::Blocks g, G;  // dSigma and G, or their transforms
     bool by_energy;
 };
 
 }  // namespace
 
-template <int GSRC, int BSRC, bool TWO>
+template <int GSRC, int BSRC, bool DIRECT, bool TWO>
 __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p, const double* __restrict__ Dp,
                                                                 const double* __restrict__ Dm, const double* __restrict__ A,
                                                                 const int32_t* __restrict__ nbr, cd alpha, DhTile t,
@@ -73,9 +72,10 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
     if (b < 0 || b >= d.na) return;  // the reduction writes zero
     const int m_lo = p.by_energy ? 0 : share, m_hi = p.by_energy ? nkz : share + 1;
     const int e_lo = p.by_energy ? 32 * share : 0, e_hi = p.by_energy ? (e_lo + 32 < ne ? e_lo + 32 : ne) : ne;
-    ks::stage_twiddles(tw, table, nkz, tid, kThreads);
+    if constexpr (!DIRECT) ks::stage_twiddles(tw, table, nkz, tid, kThreads);
     ks::stage_factor<kThreads>(A, edge, nn, sA, tid);
-    const ks::Source gs{p.g + 2 * a * p.g_atom, p.g_kst, p.g_est}, bs{p.G + 2 * b * p.G_atom, p.G_kst, p.G_est};
+    const ks::Source gs = ks::source(p.g, a);
+    const ks::Source bs = ks::source(p.G, b);
     const int kk = lane >> 4, j16 = lane & 15;
     const int nt = (2 * n + 15) / 16;
 
@@ -91,14 +91,18 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
             f64x4 sum[kNT];
 #pragma unroll
             for (int c = 0; c < kNT; ++c) sum[c] = f64x4{0.0, 0.0, 0.0, 0.0};
-            for (int m = m_lo; m < m_hi; ++m) {
-                const int kt = SECOND && m > 0 ? nkz - m : m;
+            // the coefficients of transformed momentum, or (DIRECT) of phonon momentum, q
+            auto coeff = [&](int q) {
                 __syncthreads();
                 if (tid == 0) *bad = 0;
                 __syncthreads();
-                ks::stage_coeff<kThreads, true, !SECOND, SECOND>(Dm, tw, nkz, kt, nw, ne, edges, edge, sD, bad, tid);
+                ks::stage_coeff<kThreads, DIRECT, !SECOND, SECOND>(Dm, tw, nkz, q, nw, ne, edges, edge, sD, bad, tid);
                 if constexpr (TWO)
-                    ks::stage_coeff<kThreads, true, !SECOND, SECOND>(Dp, tw, nkz, kt, nw, ne, edges, edge, sDm, bad, tid);
+                    ks::stage_coeff<kThreads, DIRECT, !SECOND, SECOND>(Dp, tw, nkz, q, nw, ne, edges, edge, sDm, bad, tid);
+            };
+            for (int m = m_lo; m < m_hi; ++m) {
+                const int kt = !DIRECT && SECOND && m > 0 ? nkz - m : m;
+                if constexpr (!DIRECT) coeff(kt);
                 for (int e0 = e_lo; e0 < e_hi; e0 += eb) {
                     const int e_n = e_hi - e0 < eb ? e_hi - e0 : eb, ewin = eb + 2 * nw;
                     cd acc[3][ks::kEBlk];
@@ -106,23 +110,29 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
                     for (int i = 0; i < 3; ++i)
 #pragma unroll
                         for (int e = 0; e < ks::kEBlk; ++e) acc[i][e] = cd{0.0, 0.0};
-                    __syncthreads();
-                    ks::load_rows<kThreads, GSRC, SECOND>(gs, tw, nkz, kt, e0 - nw, ewin, ne, r0, rc, n, by_row, t.by_n, sG, tid);
-                    __syncthreads();
-                    const bool finite = *bad == 0;
-                    for (int j = 0; j < 3; ++j) {
-                        ks::right_product<kWaves, 2, kCB, false>(sG, sA + j * nn, ewin * rc, n, t.ncb, t.by_ncb,
-                                                                 (wave + j) % kWaves, lane, [&](int row) { return sX + row * np; });
+                    for (int kp = 0; kp < (DIRECT ? nkz : 1); ++kp) {
+                        // dSigma at k' + q meets B at k' = m with the coefficient of q
+                        if constexpr (DIRECT) coeff(kp - m < 0 ? kp - m + nkz : kp - m);
                         __syncthreads();
-                        if (f_lane) {
-                            const cd* Dl = sD + 3 * j * nw;
-                            const cd* Dh = (TWO ? sDm : sD) + 3 * j * nw;
-                            if (finite)
-                                ks::filter<TWO>(acc, sX + f_off, rc * np, nw, Dl, Dh);
-                            else
-                                ks::filter_masked<TWO>(acc, sX + f_off, rc * np, nw, Dl, Dh, e0 + eq * ks::kEBlk, ne);
+                        ks::load_rows<kThreads, GSRC, SECOND>(gs, tw, nkz, DIRECT ? kp : kt, e0 - nw, ewin, r0, rc, n,
+                                                              by_row, t.by_n, sG, tid);
+                        __syncthreads();
+                        const bool finite = *bad == 0;
+                        for (int j = 0; j < 3; ++j) {
+                            ks::right_product<kWaves, 2, kCB, false>(sG, sA + j * nn, ewin * rc, n, t.ncb, t.by_ncb,
+                                                                     (wave + j) % kWaves, lane,
+                                                                     [&](int row) { return sX + row * np; });
+                            __syncthreads();
+                            if (f_lane) {
+                                const cd* Dl = sD + 3 * j * nw;
+                                const cd* Dh = (TWO ? sDm : sD) + 3 * j * nw;
+                                if (finite)
+                                    ks::filter<TWO>(acc, sX + f_off, rc * np, nw, Dl, Dh);
+                                else
+                                    ks::filter_masked<TWO>(acc, sX + f_off, rc * np, nw, Dl, Dh, e0 + eq * ks::kEBlk, ne);
+                            }
+                            __syncthreads();
                         }
-                        __syncthreads();
                     }
                     if (f_lane) {
 #pragma unroll
@@ -130,7 +140,7 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
 #pragma unroll
                             for (int i = 0; i < 3; ++i) ks::st(sU + ((eq * ks::kEBlk + e) * 3 + i) * nel + el, acc[i][e]);
                     }
-                    ks::load_rows<kThreads, BSRC, SECOND>(bs, tw, nkz, kt, e0, e_n, ne, 0, n, n, t.by_nn, t.by_n, sB, tid);
+                    ks::load_rows<kThreads, BSRC, SECOND>(bs, tw, nkz, kt, e0, e_n, 0, n, n, t.by_nn, t.by_n, sB, tid);
                     __syncthreads();
                     // C[(i,r)][(t,re/im)] += sum over (e, c, re/im): K index kk = (c parity, re/im)
                     const bool row_ok = j16 < nrow;
@@ -253,11 +263,11 @@ static bool dh_tile(const Dims& d, bool two, DhTile* best) {
 
 bool dh_kspace_supported(const Dims& d) { return dh_fits(d, true); }
 
-template <int GSRC, int BSRC, bool TWO>
+template <int GSRC, int BSRC, bool DIRECT, bool TWO>
 static hipError_t launch_dh(const Dims& d, const DhArgs& p, const double* Dp, const double* Dm, const double* A,
                             const int32_t* nbr, cd alpha, const DhTile& t, int64_t nshare, double* shares,
                             hipStream_t stream) {
-    auto kern = dh_kspace_kernel<GSRC, BSRC, TWO>;
+    auto kern = dh_kspace_kernel<GSRC, BSRC, DIRECT, TWO>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds);
     if (e != hipSuccess) return e;
     if (d.nb * nshare > INT32_MAX) return hipErrorInvalidValue;
@@ -268,33 +278,23 @@ static hipError_t launch_dh(const Dims& d, const DhArgs& p, const double* Dp, co
     return hipGetLastError();
 }
 
-hipError_t launch_dh_kspace(const Dims& d, const double* g, const double* g_hat, const double* G, const double* G_hat,
-                            const double* Dp, const double* Dm, const double* A, const int32_t* nbr, cd alpha,
-                            bool by_energy, double* shares, hipStream_t stream) {
+hipError_t launch_dh_kspace(const Dims& d, bool direct, const double* g, const double* g_hat, const double* G,
+                            const double* G_hat, const double* Dp, const double* Dm, const double* A, const int32_t* nbr,
+                            cd alpha, bool by_energy, double* shares, hipStream_t stream) {
     const bool two = Dm != Dp;
     DhTile t;
     if (!dh_tile(d, two, &t)) return hipErrorInvalidValue;
-    const int64_t nn = d.norb * d.norb, ne = d.ne, na = d.na, G_atom = d.gs * nn;
-    DhArgs p{g, G, nn, ne * na * nn, na * nn, G_atom, ne * na * G_atom, na * G_atom, by_energy};
-    if (g_hat) {
-        p.g = g_hat;
-        p.g_atom = ne * nn;
-        p.g_kst = na * ne * nn;
-        p.g_est = nn;
-    }
-    if (G_hat) {
-        p.G = G_hat;
-        p.G_atom = ne * nn;
-        p.G_kst = na * ne * nn;
-        p.G_est = nn;
-    }
+    DhArgs p{ks::array_blocks(g, d, 1), ks::array_blocks(G, d, d.gs), by_energy};
+    const int64_t nshare = by_energy ? (d.ne + 31) / 32 : d.nkz;
+#define SSE_DH(GS, BS, DIRECT, SCALE)                                                                         \
+    (two ? launch_dh<GS, BS, DIRECT, true>(d, p, Dp, Dm, A, nbr, SCALE, t, nshare, shares, stream)            \
+         : launch_dh<GS, BS, DIRECT, false>(d, p, Dp, Dm, A, nbr, SCALE, t, nshare, shares, stream))
+    if (direct) return SSE_DH(ks::kDirect, ks::kDirect, true, alpha);
+    if (g_hat) p.g = ks::hat_blocks(g_hat, d, 0, d.ne);
+    if (G_hat) p.G = ks::hat_blocks(G_hat, d, 0, d.ne);
     const cd a{alpha.re / (double)d.nkz, alpha.im / (double)d.nkz};
-    const int64_t nshare = by_energy ? (ne + 31) / 32 : d.nkz;
-#define SSE_DH(GS, BS)                                                                                    \
-    (two ? launch_dh<GS, BS, true>(d, p, Dp, Dm, A, nbr, a, t, nshare, shares, stream)                    \
-         : launch_dh<GS, BS, false>(d, p, Dp, Dm, A, nbr, a, t, nshare, shares, stream))
-    if (g_hat) return G_hat ? SSE_DH(ks::kDirect, ks::kDirect) : SSE_DH(ks::kDirect, ks::kTrans);
-    return SSE_DH(ks::kTrans, ks::kTrans);
+    if (G_hat) return SSE_DH(ks::kDirect, ks::kDirect, false, a);
+    return g_hat ? SSE_DH(ks::kDirect, ks::kTrans, false, a) : SSE_DH(ks::kTrans, ks::kTrans, false, a);
 #undef SSE_DH
 }
 

@@ -15,7 +15,7 @@
 // output back in place.
 //
 // SRC = kTrans transforms while it loads (Nkz loads per entry, the same sums): for a
-// workspace without room.  DIRECT takes the sum over source momenta as it stands
+// workspace without room.  The direct sum takes the sum over source momenta as it stands
 // (a loop over k' around the steps, Nkz times the work): every product and sum
 // is then one of Eq. 3's own, so integer-valued inputs give exact results.
 // Small problems and Nkz = 1 run it.
@@ -69,8 +69,7 @@ struct InEdges {
 
 // CB columns per pass of the products, MT passes of the left product per wave
 template <int SRC, bool DIRECT, bool TWO, int MODE, int CB, int MT>
-__global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const double* __restrict__ G, int64_t g_atom,
-                                                                 int64_t g_kst, int64_t g_est, int slab,
+__global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, ks::Blocks blocks,
                                                                  const double* __restrict__ Dp,
                                                                  const double* __restrict__ Dm,
                                                                  const double* __restrict__ A,
@@ -123,7 +122,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
         const int64_t edge = ADJ ? (int64_t)__builtin_amdgcn_readfirstlane(in.edges[m]) : a * nb + m;
         const int64_t b = ADJ ? edge / nb : (int64_t)__builtin_amdgcn_readfirstlane(nbr[edge]);
         if (b < 0 || b >= d.na) continue;
-        const ks::Source src{G + 2 * b * g_atom, g_kst, g_est};
+        const ks::Source src = ks::source(blocks, b);
         for (int r0 = 0; r0 < n; r0 += tile.rc) {
             const int rc = n - r0 < tile.rc ? n - r0 : tile.rc;
             // filter lanes: entry el = (r, c) of the chunk, energies 4 eq .. 4 eq + 3
@@ -138,22 +137,22 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, const d
 #pragma unroll
                 for (int e = 0; e < ks::kEBlk; ++e) acc[i][e] = cd{0.0, 0.0};
             for (int kp = 0; kp < (DIRECT ? nkz : 1); ++kp) {
-                const int kg = DIRECT ? kp : kt;                                      // momentum of the blocks
-                const int kd = DIRECT ? (kt - kp < 0 ? kt - kp + nkz : kt - kp) : kt;  // of the coefficients
+                const int kg = DIRECT ? kp : kt;  // momentum of the blocks
+                const int q = ADJ ? kp - kt : kt - kp, kd = !DIRECT ? kt : q < 0 ? q + nkz : q;  // of the coefficients
                 const bool coeff = DIRECT || r0 == 0;  // this step's coefficients are new ones
                 __syncthreads();                       // the buffers of the step before are read
                 if (coeff && tid == 0) *bad = 0;
-                ks::load_rows<kThreads, SRC, false>(src, tw, nkz, kg, e0 - nw - slab, ewin, ne - slab, r0, rc, n,
-                                                      by_row, tile.by_n, sG, tid);
+                ks::load_rows<kThreads, SRC, false>(src, tw, nkz, kg, e0 - nw, ewin, r0, rc, n, by_row, tile.by_n, sG,
+                                                    tid);
                 if (r0 == 0 && kp == 0) {
                     ks::stage_factor<kThreads>(A, edge, nn, sA, tid);
                     if constexpr (MODE == kStored) ks::stage_factor<kThreads>(B, edge, nn, sR, tid);
                 }
                 if (coeff) {
                     __syncthreads();  // *bad is cleared
-                    ks::stage_coeff<kThreads, !DIRECT, ADJ>(Dp, tw, nkz, kd, nw, ne, edges, edge, sD, bad, tid);
+                    ks::stage_coeff<kThreads, DIRECT, ADJ>(Dp, tw, nkz, kd, nw, ne, edges, edge, sD, bad, tid);
                     if constexpr (TWO)
-                        ks::stage_coeff<kThreads, !DIRECT, ADJ>(Dm, tw, nkz, kd, nw, ne, edges, edge, sDm, bad, tid);
+                        ks::stage_coeff<kThreads, DIRECT, ADJ>(Dm, tw, nkz, kd, nw, ne, edges, edge, sDm, bad, tid);
                 }
                 __syncthreads();
                 const bool finite = *bad == 0;
@@ -307,18 +306,17 @@ size_t fwd_kspace_workspace(const Dims& d) {
 }
 
 template <int SRC, bool DIRECT, bool TWO, int MODE, int CB, int MT>
-static hipError_t launch_cb(const Dims& d, const double* G, int64_t g_atom, int64_t g_kst, int64_t g_est, int slab,
-                            const double* Dp, const double* Dm, const double* A, const double* B, const int32_t* nbr,
-                            InEdges in, cd alpha, const Tile& t, int e_lo, int e_hi, int s_slots, double* S,
-                            hipStream_t stream) {
+static hipError_t launch_cb(const Dims& d, const ks::Blocks& blocks, const double* Dp, const double* Dm, const double* A,
+                            const double* B, const int32_t* nbr, InEdges in, cd alpha, const Tile& t, int e_lo, int e_hi,
+                            int s_slots, double* S, hipStream_t stream) {
     auto kern = fwd_kspace_kernel<SRC, DIRECT, TWO, MODE, CB, MT>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds);
     if (e != hipSuccess) return e;
     const int64_t per = d.nkz * ((e_hi - e_lo + t.eb - 1) / t.eb);
     if (per > INT32_MAX) return hipErrorInvalidValue;
     ks::launch_parts(d.na, per, kThreads, [&](ks::LaunchPart part) {
-        hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, G, g_atom, g_kst, g_est, slab, Dp, Dm, A,
-                           B, nbr, in, alpha, t, e_lo, e_hi, part, ks::twiddles(d.nkz), s_slots, S);
+        hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, blocks, Dp, Dm, A, B, nbr, in, alpha, t,
+                           e_lo, e_hi, part, ks::twiddles(d.nkz), s_slots, S);
     });
     return hipGetLastError();
 }
@@ -332,16 +330,17 @@ static hipError_t launch_shape(int cb, Args... args) {
 
 template <int SRC, bool DIRECT, class... Args>
 static hipError_t launch_tables(bool two, int mode, int cb, Args... args) {
-    if constexpr (!DIRECT) {
-        if (mode == kAdjoint)
-            return two ? launch_shape<SRC, DIRECT, true, kAdjoint>(cb, args...) : launch_shape<SRC, DIRECT, false, kAdjoint>(cb, args...);
-    }
+    if (mode == kAdjoint)
+        return two ? launch_shape<SRC, DIRECT, true, kAdjoint>(cb, args...) : launch_shape<SRC, DIRECT, false, kAdjoint>(cb, args...);
     if (two)
         return mode == kStored ? launch_shape<SRC, DIRECT, true, kStored>(cb, args...)
                                : launch_shape<SRC, DIRECT, true, kHermitian>(cb, args...);
     return mode == kStored ? launch_shape<SRC, DIRECT, false, kStored>(cb, args...)
                            : launch_shape<SRC, DIRECT, false, kHermitian>(cb, args...);
 }
+
+template <int SRC>
+using kFrom = std::integral_constant<int, SRC>;
 
 // the tile for these dims on the current device
 static hipError_t choose_tile(const Dims& d, bool two, bool stored, int* cb, Tile* t) {
@@ -354,9 +353,9 @@ static hipError_t choose_tile(const Dims& d, bool two, bool stored, int* cb, Til
     return pick_tile(d, two, stored, *cb, mt, cus, t, &cost) ? hipSuccess : hipErrorInvalidValue;
 }
 
-hipError_t launch_dg_kspace(const Dims& d, const double* g, const double* g_hat, const double* Dp, const double* Dm,
-                            const double* A, const int32_t* offset, const int32_t* edges, const int32_t* order, cd calpha,
-                            double* dG, hipStream_t stream) {
+hipError_t launch_dg_kspace(const Dims& d, bool direct, const double* g, const double* g_hat, const double* Dp,
+                            const double* Dm, const double* A, const int32_t* offset, const int32_t* edges,
+                            const int32_t* order, cd calpha, double* dG, hipStream_t stream) {
     const bool two = Dm != Dp;
     const int64_t nn = d.norb * d.norb, ne = d.ne;
     int cb;
@@ -364,35 +363,37 @@ hipError_t launch_dg_kspace(const Dims& d, const double* g, const double* g_hat,
     hipError_t e = choose_tile(d, two, false, &cb, &t);
     if (e != hipSuccess) return e;
     const InEdges in{offset, edges, order};
+    const ks::Blocks raw = ks::array_blocks(g, d, 1), hat = ks::hat_blocks(g_hat, d, 0, ne);
     const int32_t* no_nbr = nullptr;
     const double* no_b = nullptr;
     // the E - w terms of this sum come from the table of the G at E + w
-    if (g_hat)
-        e = launch_tables<ks::kDirect, false>(two, kAdjoint, cb, d, g_hat, ne * nn, d.na * ne * nn, nn, 0, Dm, Dp, A, no_b, no_nbr,
-                                              in, calpha, t, 0, (int)ne, (int)d.gs, dG, stream);
-    else
-        e = launch_tables<ks::kTrans, false>(two, kAdjoint, cb, d, g, nn, ne * d.na * nn, d.na * nn, 0, Dm, Dp, A, no_b, no_nbr, in,
-                                             calpha, t, 0, (int)ne, (int)d.gs, dG, stream);
+    auto launch = [&](auto src, auto is_direct, const ks::Blocks& blocks) {
+        return launch_tables<decltype(src)::value, decltype(is_direct)::value>(two, kAdjoint, cb, d, blocks, Dm, Dp, A, no_b, no_nbr,
+                                                                               in, calpha, t, 0, (int)ne, (int)d.gs, dG, stream);
+    };
+    if (direct) return launch(kFrom<ks::kDirect>{}, std::true_type{}, raw);
+    e = g_hat ? launch(kFrom<ks::kDirect>{}, std::false_type{}, hat) : launch(kFrom<ks::kTrans>{}, std::false_type{}, raw);
     if (e != hipSuccess) return e;
-    return launch_inverse((int)d.nkz, ne * d.na, nn, d.gs * nn, calpha, dG,
-                          stream);
+    return launch_inverse((int)d.nkz, ne * d.na, nn, d.gs * nn, calpha, dG, stream);
 }
 
 hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
                              const double* B, const int32_t* nbr, cd alpha, double* S, bool transform, void* ws,
                              size_t ws_bytes, hipStream_t stream) {
     const bool two = Dm != Dp;
-    const int mode = B ? kStored : kHermitian;
     const int64_t nn = d.norb * d.norb, ne = d.ne;
     int cb;
     Tile t{};
     hipError_t e = choose_tile(d, two, B != nullptr, &cb, &t);
     if (e != hipSuccess) return e;
     const InEdges none{};
-    const int64_t g_atom = d.gs * nn, g_est = d.na * g_atom, g_kst = ne * g_est;
-    if (!transform)
-        return launch_tables<ks::kDirect, true>(two, mode, cb, d, G, g_atom, g_kst, g_est, 0, Dp, Dm, A, B, nbr, none, alpha, t, 0,
-                                                (int)ne, 1, S, stream);
+    const ks::Blocks raw = ks::array_blocks(G, d, d.gs);
+    auto launch = [&](auto src, auto is_direct, const ks::Blocks& blocks, int64_t lo, int64_t hi) {
+        return launch_tables<decltype(src)::value, decltype(is_direct)::value>(two, B ? kStored : kHermitian, cb, d, blocks, Dp, Dm,
+                                                                               A, B, nbr, none, alpha, t, (int)lo, (int)hi, 1, S,
+                                                                               stream);
+    };
+    if (!transform) return launch(kFrom<ks::kDirect>{}, std::true_type{}, raw, 0, ne);
     const int64_t room = (int64_t)(ws_bytes / (size_t)hat_energy_bytes(d));  // energies
     if (room >= std::min(ne, (int64_t)t.eb + 2 * d.nw)) {
         // slabs of whole tiles; a slab's transform takes the 2 nw energies around it
@@ -401,15 +402,13 @@ hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, c
         for (int64_t lo = 0; lo < ne; lo += step) {
             const int64_t hi = std::min(ne, lo + step);
             const int64_t first = std::max<int64_t>(0, lo - d.nw), n_e = std::min(ne, hi + d.nw) - first;
-            e = launch_transform((int)d.nkz, first, n_e, d.na, nn, g_atom, g_est, g_kst, G, hat, stream);
+            e = launch_transform(d, first, n_e, raw, hat, stream);
             if (e != hipSuccess) return e;
-            e = launch_tables<ks::kDirect, false>(two, mode, cb, d, hat, n_e * nn, d.na * n_e * nn, nn, (int)first, Dp, Dm, A,
-                                                  B, nbr, none, alpha, t, (int)lo, (int)hi, 1, S, stream);
+            e = launch(kFrom<ks::kDirect>{}, std::false_type{}, ks::hat_blocks(hat, d, first, n_e), lo, hi);
             if (e != hipSuccess) return e;
         }
     } else {
-        e = launch_tables<ks::kTrans, false>(two, mode, cb, d, G, g_atom, g_kst, g_est, 0, Dp, Dm, A, B, nbr, none, alpha, t, 0,
-                                             (int)ne, 1, S, stream);
+        e = launch(kFrom<ks::kTrans>{}, std::false_type{}, raw, 0, ne);
         if (e != hipSuccess) return e;
     }
     return launch_inverse((int)d.nkz, ne * d.na, nn, nn, alpha, S, stream);

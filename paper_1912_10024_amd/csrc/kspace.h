@@ -90,13 +90,35 @@ __device__ __forceinline__ cd momentum_sum(int nkz, int m, const cd* tw, Load lo
     return s;
 }
 
-// Where a tile of energies x rows of a source block array is loaded from
-struct Source {
-    const double* p;   // block of the wanted atom at momentum 0, energy 0
-    int64_t kst, est;  // complex elements between momenta and energies
+// A block array, or its transform: complex elements between momenta, atoms and energies,
+// and the energies that it holds
+struct Blocks {
+    const double* p;
+    int64_t kst, atom, est;
+    int first, count;
 };
+// an array [nkz][ne][na][slots][norb][norb], its slot 0
+inline Blocks array_blocks(const double* p, const Dims& d, int64_t slots) {
+    const int64_t atom = slots * d.norb * d.norb;
+    return Blocks{p, d.ne * d.na * atom, atom, d.na * atom, 0, (int)d.ne};
+}
+// a transform of its energies [first, first + count), [nkz][na][count][norb][norb]
+inline Blocks hat_blocks(const double* p, const Dims& d, int64_t first, int64_t count) {
+    const int64_t nn = d.norb * d.norb;
+    return Blocks{p, d.na * count * nn, count * nn, nn, (int)first, (int)count};
+}
+// Where a tile of energies x rows of it is loaded from
+struct Source {
+    const double* p;   // block of the wanted atom at momentum 0, energy `first`
+    int64_t kst, est;
+    int first, count;
+};
+__device__ __forceinline__ Source source(const Blocks& b, int64_t a) {
+    return Source{b.p + 2 * a * b.atom, b.kst, b.est, b.first, b.count};
+}
 constexpr int kDirect = 0;  // blocks of one momentum as they are, from an array or from its transform
-constexpr int kTrans = 1;   // transformed over the momenta while they are loaded
+constexpr int kTrans = 1;   // transformed over the momenta while they are loaded, from an array
+
 
 // Rows r0 .. r0+rc-1 of the source blocks of energies e_first .. e_first+new_-1 into
 // LDS, entry (ew, r, u) of [ew][rc][row_len].  CT: of the conjugate transpose of
@@ -104,7 +126,7 @@ constexpr int kTrans = 1;   // transformed over the momenta while they are loade
 // kt = -m).  Energies outside the grid give zeros.  U entries per thread are
 // loaded together, which is what hides the latency.
 template <int THREADS, int SRC, bool CT>
-__device__ __forceinline__ void load_rows(const Source& s, const cd* tw, int nkz, int kt, int e_first, int new_, int ne,
+__device__ __forceinline__ void load_rows(const Source& s, const cd* tw, int nkz, int kt, int e_first, int new_,
                                           int r0, int rc, int n, Div by_row, Div by_n, cd* sG, int tid) {
     constexpr int U = SRC == kTrans ? 4 : 8;
     const int nrow = rc * n, total = new_ * nrow, np = row_len(n);
@@ -119,8 +141,8 @@ __device__ __forceinline__ void load_rows(const Source& s, const cd* tw, int nkz
             const int x = x0 + u * THREADS;
             const int xx = x < total ? x : 0;
             const int ew = by_row.quot(xx), rem = xx - ew * nrow, r = by_n.quot(rem), c = rem - r * n;
-            const int e = e_first + ew;
-            ok[u] = e >= 0 && e < ne;
+            const int e = e_first + ew - s.first;
+            ok[u] = e >= 0 && e < s.count;
             dst[u] = x < total ? (ew * rc + r) * np + c : -1;
             p[u] = base + 2 * ((ok[u] ? e : 0) * s.est + (CT ? c * n + r0 + r : r0 * n + rem));
             acc[u] = cd{0.0, 0.0};
@@ -159,10 +181,11 @@ __device__ __forceinline__ void load_rows(const Source& s, const cd* tw, int nkz
 template <int THREADS, int U, int SRC, bool CT>
 struct RowsAhead {
     cd v[U];
-    __device__ __forceinline__ cd get(const Source& s, const cd* tw, int nkz, int kt, int e, int ne, int at) const {
-        const bool ok = e >= 0 && e < ne;
+    __device__ __forceinline__ cd get(const Source& s, const cd* tw, int nkz, int kt, int e, int at) const {
+        e -= s.first;
+        const bool ok = e >= 0 && e < s.count;
         const double* p = s.p + 2 * ((SRC == kTrans ? 0 : kt * s.kst) + (ok ? e : 0) * s.est + at);
-        cd a{0.0, 0.0};
+        cd a;
         if constexpr (SRC == kTrans)
             a = momentum_sum(nkz, kt, tw, [&](int k) { return cload(p, k * s.kst); });
         else
@@ -170,17 +193,17 @@ struct RowsAhead {
         if (!ok) a = cd{0.0, 0.0};
         return CT ? cd{a.re, -a.im} : a;
     }
-    __device__ __forceinline__ void ask(const Source& s, const cd* tw, int nkz, int kt, int e_first, int new_, int ne, int r0,
+    __device__ __forceinline__ void ask(const Source& s, const cd* tw, int nkz, int kt, int e_first, int new_, int r0,
                                         int rc, int n, Div by_row, Div by_n, int tid) {
         const int nrow = rc * n, total = new_ * nrow;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int x = tid + u * THREADS < total ? tid + u * THREADS : 0;
             const int ew = by_row.quot(x), rem = x - ew * nrow, r = by_n.quot(rem), c = rem - r * n;
-            v[u] = get(s, tw, nkz, kt, e_first + ew, ne, CT ? c * n + r0 + r : r0 * n + rem);
+            v[u] = get(s, tw, nkz, kt, e_first + ew, CT ? c * n + r0 + r : r0 * n + rem);
         }
     }
-    __device__ __forceinline__ void put(const Source& s, const cd* tw, int nkz, int kt, int e_first, int new_, int ne, int r0,
+    __device__ __forceinline__ void put(const Source& s, const cd* tw, int nkz, int kt, int e_first, int new_, int r0,
                                         int rc, int n, Div by_row, Div by_n, cd* dst, int tid) const {
         const int nrow = rc * n, total = new_ * nrow, np = row_len(n);
 #pragma unroll
@@ -191,7 +214,7 @@ struct RowsAhead {
         }
         for (int x = tid + U * THREADS; x < total; x += THREADS) {
             const int ew = by_row.quot(x), rem = x - ew * nrow, r = by_n.quot(rem), c = rem - r * n;
-            st(dst + (ew * rc + r) * np + c, get(s, tw, nkz, kt, e_first + ew, ne, CT ? c * n + r0 + r : r0 * n + rem));
+            st(dst + (ew * rc + r) * np + c, get(s, tw, nkz, kt, e_first + ew, CT ? c * n + r0 + r : r0 * n + rem));
         }
     }
 };
@@ -477,20 +500,19 @@ __device__ __forceinline__ void filter_masked(cd (&acc)[3][kEBlk], const cd* X, 
 }
 
 // Coefficients of one edge into LDS, [j][w][i] (nine per frequency): the transform
-// over the phonon momenta at kt (TRANS) or those of momentum kt.  CONJ: conjugated
+// over the phonon momenta at kt, or (DIRECT) those of momentum kt.  CONJ: conjugated
 // (the adjoint).  SWAP: [i][w][j].  Sets *bad where one is not finite.
-template <int THREADS, bool TRANS, bool CONJ, bool SWAP = false>
+template <int THREADS, bool DIRECT, bool CONJ, bool SWAP = false>
 __device__ __forceinline__ void stage_coeff(const double* __restrict__ D, const cd* tw, int nkz, int kt, int nw, int ne,
                                             int64_t edges, int64_t edge, cd* sD, int* bad, int tid) {
     for (int x = tid; x < nw * 9; x += THREADS) {
         const int w = x / 9, ij = x % 9;
         cd v;
         const int64_t o = ((int64_t)w * edges + edge) * 9 + ij, qst = (int64_t)nw * edges * 9;
-        if constexpr (TRANS) {
-            v = momentum_sum(nkz, kt, tw, [&](int q) { return cload(D, o + q * qst); });
-        } else {
+        if constexpr (DIRECT)
             v = cload(D, o + kt * qst);
-        }
+        else
+            v = momentum_sum(nkz, kt, tw, [&](int q) { return cload(D, o + q * qst); });
         if (w + 1 >= ne) v = cd{0.0, 0.0};  // a frequency that no pair of energies differs by has no term
         if constexpr (CONJ) v.im = -v.im;
         if (!(fabs(v.re) <= 1.7976931348623157e308 && fabs(v.im) <= 1.7976931348623157e308)) *bad = 1;

@@ -110,12 +110,15 @@ static hipError_t launch_transform_kernel(K kern, bool any, int nkz, int64_t tot
         default: return launch_transform_kernel(KERN<0>, true, nkz, TOTAL, stream, __VA_ARGS__);      \
     }
 
-hipError_t launch_transform(int nkz, int64_t first, int64_t n_e, int64_t na, int64_t nn, int64_t atom, int64_t est,
-                            int64_t kst, const double* src, double* hat, hipStream_t stream) {
-    SSE_BY_NKZ(transform_kernel, n_e * na * nn, first, n_e, na, nn, atom, est, kst, src, hat)
+hipError_t launch_transform(const Dims& d, int64_t first, int64_t n_e, const ks::Blocks& src, double* hat,
+                            hipStream_t stream) {
+    const int nkz = (int)d.nkz;
+    const int64_t na = d.na, nn = d.norb * d.norb;
+    SSE_BY_NKZ(transform_kernel, n_e * na * nn, first, n_e, na, nn, src.atom, src.est, src.kst, src.p, hat)
 }
 
-hipError_t launch_inverse(int nkz, int64_t blocks, int64_t nn, int64_t bs, cd scale, double* X, hipStream_t stream) {
+hipError_t launch_inverse(int nkz, int64_t blocks, int64_t nn, int64_t bs, cd scale, double* X,
+                          hipStream_t stream) {
     SSE_BY_NKZ(inverse_kernel, blocks * nn, blocks, nn, bs, scale, X)
 }
 

@@ -21,8 +21,8 @@
 // of Y that the next tile still needs move to the front of the buffer.  The lanes'
 // sums are added in LDS in a fixed order at the end.
 //
-// YSRC, XSRC = kTrans transform g and B while they load; DIRECT sums over k as it stands, one
-// workgroup per (edge, q) (exact for integer-valued inputs, Nkz times the work).
+// YSRC, XSRC = kTrans transform g and B while they load; the direct sum takes k as it stands,
+// one workgroup per (edge, q) (exact for integer-valued inputs, Nkz times the work).
 #include <algorithm>
 
 #include "kspace.h"
@@ -38,12 +38,9 @@ using ks::corr_tile;
 using ks::CorrTile;
 
 struct CorrArgs {
-    const double *y, *x;                             // g (or Gs) and B (or Go), or their transforms
-    int64_t y_atom, y_kst, y_est, x_atom, x_kst, x_est;
-    int lo, hi;         // energies of X that are summed
-    int first, n_e;     // the energies that y holds
-    int x_first;        // the first energy that x holds
-    bool add;                // add to the output instead of writing it
+    ks::Blocks y, x;  // g (or Gs) and B (or Go), or their transforms
+    int lo, hi;       // energies of X that are summed
+    bool add;         // add to the output instead of writing it
 };
 
 }  // namespace
@@ -89,8 +86,8 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
         ks::stage_twiddles(tw, table, nkz, tid, kThreads);
         if (tid == 0) *bad = 0;
         ks::stage_factor<kThreads>(A, edge, nn, sA, tid);
-        const ks::Source ys{g.y + 2 * a * g.y_atom, g.y_kst, g.y_est};
-        const ks::Source xs{g.x + 2 * b * g.x_atom, g.x_kst, g.x_est};
+        const ks::Source ys = ks::source(g.y, a);
+        const ks::Source xs = ks::source(g.x, b);
         for (int kp = 0; kp < (DIRECT ? nkz : 1); ++kp) {
             const int ky = DIRECT ? (kp + kt) % nkz : kt;
             const int kx = DIRECT ? kp : CT ? (nkz - kt) % nkz : kt;
@@ -98,8 +95,8 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
                 const int rc = n - r0 < t.rc ? n - r0 : t.rc, last = rc < t.rc;
                 const int nel = rc * n, ps = 3 * nel;  // entries of a plane
                 auto load = [&](int energy, int count) {
-                    ks::load_rows<kThreads, YSRC, false>(ys, tw, nkz, ky, energy - g.first, count, g.n_e, r0, rc, n, t.by_row[last],
-                                                         t.by_n, sG, tid);
+                    ks::load_rows<kThreads, YSRC, false>(ys, tw, nkz, ky, energy, count, r0, rc, n, t.by_row[last], t.by_n,
+                                                         sG, tid);
                 };
                 // Y of the loaded rows of `count` energies into the planes from `plane` on; the first
                 // task goes to wave `from`
@@ -128,15 +125,15 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
                 ks::RowsAhead<kThreads, 4, XSRC, CT> x_next;
                 auto ask = [&](int e0) {
                     const int e_n = g.hi - e0 < eb ? g.hi - e0 : eb;
-                    y_next.ask(ys, tw, nkz, ky, e0 + t.halo_hi - g.first, eb, g.n_e, r0, rc, n, t.by_row[last], t.by_n, tid);
-                    x_next.ask(xs, tw, nkz, kx, e0 - g.x_first, e_n, ne, 0, n, n, t.by_nn, t.by_n, tid);
+                    y_next.ask(ys, tw, nkz, ky, e0 + t.halo_hi, eb, r0, rc, n, t.by_row[last], t.by_n, tid);
+                    x_next.ask(xs, tw, nkz, kx, e0, e_n, 0, n, n, t.by_nn, t.by_n, tid);
                 };
                 ask(g.lo);
                 for (int e0 = g.lo; e0 < g.hi; e0 += eb) {
                     const int e_n = g.hi - e0 < eb ? g.hi - e0 : eb;
                     __syncthreads();
-                    y_next.put(ys, tw, nkz, ky, e0 + t.halo_hi - g.first, eb, g.n_e, r0, rc, n, t.by_row[last], t.by_n, sG, tid);
-                    x_next.put(xs, tw, nkz, kx, e0 - g.x_first, e_n, ne, 0, n, n, t.by_nn, t.by_n, sB, tid);
+                    y_next.put(ys, tw, nkz, ky, e0 + t.halo_hi, eb, r0, rc, n, t.by_row[last], t.by_n, sG, tid);
+                    x_next.put(xs, tw, nkz, kx, e0, e_n, 0, n, n, t.by_nn, t.by_n, sB, tid);
                     __syncthreads();
                     // X_i[e][r][c] = sum_t A_i[r0 + r][t] B[e][t][c]; two columns (e, c) per lane
                     const int ncol = e_n * n, nout = 3 * rc, nob = (nout + kXB - 1) / kXB;
@@ -340,15 +337,16 @@ static hipError_t launch_corr_shape(int wb, Args... args) {
         case 2: return launch_corr_wb<YSRC, XSRC, DIRECT, HI, LO, CT, 2>(args...);
         case 3: return launch_corr_wb<YSRC, XSRC, DIRECT, HI, LO, CT, 3>(args...);
         case 4: return launch_corr_wb<YSRC, XSRC, DIRECT, HI, LO, CT, 4>(args...);
-        default: return launch_corr_wb<YSRC, XSRC, DIRECT, HI, LO, CT, 5>(args...);
     }
+    if constexpr (!(HI && LO)) return launch_corr_wb<YSRC, XSRC, DIRECT, HI, LO, CT, 5>(args...);  // corr_max_wb
+    return hipErrorInvalidValue;
 }
 
-template <int YSRC, int XSRC, class... Args>
+template <int YSRC, int XSRC, bool DIRECT, class... Args>
 static hipError_t launch_dd(int branches, int wb, Args... args) {
-    if (branches == 3) return launch_corr_shape<YSRC, XSRC, false, true, true, false>(wb, args...);
-    if (branches == 1) return launch_corr_shape<YSRC, XSRC, false, true, false, false>(wb, args...);
-    return launch_corr_shape<YSRC, XSRC, false, false, true, false>(wb, args...);
+    if (branches == 3) return launch_corr_shape<YSRC, XSRC, DIRECT, true, true, false>(wb, args...);
+    if (branches == 1) return launch_corr_shape<YSRC, XSRC, DIRECT, true, false, false>(wb, args...);
+    return launch_corr_shape<YSRC, XSRC, DIRECT, false, true, false>(wb, args...);
 }
 
 template <int SRC, bool DIRECT, class... Args>
@@ -356,66 +354,55 @@ static hipError_t launch_pi_corr(int wb, Args... args) {
     return launch_corr_shape<SRC, SRC, DIRECT, true, false, true>(wb, args...);
 }
 
-hipError_t launch_dd_kspace(const Dims& d, int branches, const double* g, const double* g_hat, const double* G,
+hipError_t launch_dd_kspace(const Dims& d, bool direct, int branches, const double* g, const double* g_hat, const double* G,
                             const double* G_hat, const double* A, const int32_t* nbr, cd calpha, double* dD,
                             hipStream_t stream) {
     CorrTile t;
     if (!corr_tile(d, (branches & 1) != 0, (branches & 2) != 0, &t)) return hipErrorInvalidValue;
-        const int64_t nn = d.norb * d.norb, ne = d.ne, na = d.na, x_atom = d.gs * nn;
-    CorrArgs a{g, G, nn, ne * na * nn, na * nn, x_atom, ne * na * x_atom, na * x_atom, 0, (int)ne, 0, (int)ne, 0, false};
-    if (g_hat) {
-        a.y = g_hat;
-        a.y_atom = ne * nn;
-        a.y_kst = na * ne * nn;
-        a.y_est = nn;
-    }
-    if (G_hat) {
-        a.x = G_hat;
-        a.x_atom = ne * nn;
-        a.x_kst = na * ne * nn;
-        a.x_est = nn;
-    }
+    CorrArgs a{ks::array_blocks(g, d, 1), ks::array_blocks(G, d, d.gs), 0, (int)d.ne, false};
+    if (direct) return launch_dd<ks::kDirect, ks::kDirect, true>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
+    if (g_hat) a.y = ks::hat_blocks(g_hat, d, 0, d.ne);
+    if (G_hat) a.x = ks::hat_blocks(G_hat, d, 0, d.ne);
     hipError_t e;
     if (G_hat)
-        e = launch_dd<ks::kDirect, ks::kDirect>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
+        e = launch_dd<ks::kDirect, ks::kDirect, false>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
     else if (g_hat)
-        e = launch_dd<ks::kDirect, ks::kTrans>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
+        e = launch_dd<ks::kDirect, ks::kTrans, false>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
     else
-        e = launch_dd<ks::kTrans, ks::kTrans>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
+        e = launch_dd<ks::kTrans, ks::kTrans, false>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
     if (e != hipSuccess) return e;
-    return launch_inverse((int)d.nkz, d.nw * na * d.nb, 9, 9, calpha, dD, stream);
+    return launch_inverse((int)d.nkz, d.nw * d.na * d.nb, 9, 9, calpha, dD, stream);
 }
 
 hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, const double* A, const int32_t* nbr, cd beta,
                             double* Pi, bool transform, void* ws, size_t ws_bytes, hipStream_t stream) {
     CorrTile t;
     if (!corr_tile(d, true, false, &t)) return hipErrorInvalidValue;
-    const int nkz = (int)d.nkz;
-    const int64_t nn = d.norb * d.norb, ne = d.ne, na = d.na, atom = d.gs * nn, est = na * atom;
-    CorrArgs g{Gs, Go, atom, ne * est, est, atom, ne * est, est, 0, (int)ne, 0, (int)ne, 0, false};
+    const int64_t ne = d.ne;
+    const ks::Blocks y = ks::array_blocks(Gs, d, d.gs), x = ks::array_blocks(Go, d, d.gs);
+    CorrArgs g{y, x, 0, (int)ne, false};
     if (!transform) return launch_pi_corr<ks::kDirect, true>(t.wb, d, g, A, nbr, beta, t, Pi, stream);
     // room for energies of a transform: both arrays whole, or slabs of whole tiles of
     // energies of both (with the nw energies above for Gs), or neither
     hipError_t e = hipSuccess;
-    const int64_t per = 16 * d.nkz * na * nn, room = (int64_t)(ws_bytes / (size_t)per);
+    const int64_t per = 16 * d.nkz * d.na * d.norb * d.norb, room = (int64_t)(ws_bytes / (size_t)per);
     const int64_t step = room >= 2 * ne ? ne : (room - d.nw) / 2 / t.eb * t.eb;
     if (step >= std::min<int64_t>(ne, t.eb)) {
         double* hy = static_cast<double*>(ws);
         for (int64_t lo = 0; lo < ne && e == hipSuccess; lo += step) {
             const int64_t hi = std::min(ne, lo + step), n_y = std::min(ne, hi + d.nw) - lo, n_x = hi - lo;
             double* hx = hy + per / 8 * n_y;
-            e = launch_transform(nkz, lo, n_y, na, nn, atom, est, ne * est, Gs, hy, stream);
-            if (e == hipSuccess) e = launch_transform(nkz, lo, n_x, na, nn, atom, est, ne * est, Go, hx, stream);
+            e = launch_transform(d, lo, n_y, y, hy, stream);
+            if (e == hipSuccess) e = launch_transform(d, lo, n_x, x, hx, stream);
             if (e != hipSuccess) return e;
-            g = CorrArgs{hy, hx, n_y * nn, na * n_y * nn, nn, n_x * nn, na * n_x * nn, nn,
-                         (int)lo, (int)hi, (int)lo, (int)n_y, (int)lo, lo > 0};
+            g = CorrArgs{ks::hat_blocks(hy, d, lo, n_y), ks::hat_blocks(hx, d, lo, n_x), (int)lo, (int)hi, lo > 0};
             e = launch_pi_corr<ks::kDirect, false>(t.wb, d, g, A, nbr, beta, t, Pi, stream);
         }
     } else {
         e = launch_pi_corr<ks::kTrans, false>(t.wb, d, g, A, nbr, beta, t, Pi, stream);
     }
     if (e != hipSuccess) return e;
-    return launch_inverse(nkz, d.nw * na * d.nb, 9, 9, beta, Pi, stream);
+    return launch_inverse((int)d.nkz, d.nw * d.na * d.nb, 9, 9, beta, Pi, stream);
 }
 
 // both transforms, or slabs of at most 32 GiB of them (a slab costs a prologue and a

@@ -361,3 +361,26 @@ def test_more_workgroups_than_one_launch_takes_in_half_precision():
     for a in (0, 1055000, 2097151, 2097152, d.na - 1):
         err = (S[:, :, a] - ref[:, :, a]).abs().norm() / ref[:, :, a].abs().norm()
         assert float(err) <= 1e-5, (a, float(err))   # fp16x2 carries about 22 bits; unwritten is NaN
+
+
+@pytest.mark.parametrize("dims", [(4, 32, 3, 8, 2, 6), (3, 16, 2, 16, 4, 4), (1, 200, 4, 7, 3, 5), (7, 13, 10, 5, 4, 10)],
+                         ids=lambda v: "x".join(map(str, v)))
+def test_gradients_of_a_thousand_blocks_keep_exact_sums(dims):
+    """At most 1024 blocks: integer-valued inputs give integer gradients exactly, for one
+    coefficient table and for two."""
+    nkz, ne, nw, na, nb, norb = dims
+    d = Dims(nkz=nkz, ne=ne, nqz=nkz, nw=nw, na=na, nb=nb, norb=norb, g_slots=2)
+    print(f"[gpu] kspace exact gradients dims={d.as_tuple()}", flush=True)
+    rng = np.random.default_rng(9)
+    ints = lambda shape: (rng.integers(-3, 4, shape) + 1j * rng.integers(-3, 4, shape)).astype(np.complex128)
+    x = dict(G=ints(d.g_shape), D=ints(d.d_shape), Dm=ints(d.d_shape), dH=ints(d.dh_shape), gS=ints(d.sigma_shape),
+             nbr=make_nbr(rng, d.na, d.nb))
+    t = _gpu(x)
+    got = sse.backward(t["G"], t["D"], t["dH"], t["nbr"], t["gS"], alpha=1.0)
+    ref = oracle.sse_backward(d, x["G"], x["D"], x["dH"], x["nbr"], x["gS"], alpha=1.0)
+    for name, g, r in zip(("dG", "dD", "ddH"), got, ref):
+        assert np.array_equal(g.cpu().numpy(), r), name
+    got = sse.backward_signed(t["G"], t["D"], t["Dm"], t["dH"], t["nbr"], t["gS"], alpha=1.0)
+    ref = oracle.sse_backward_signed(d, x["G"], x["D"], x["Dm"], x["dH"], x["nbr"], x["gS"], alpha=1.0)
+    for name, g, r in zip(("dG", "dDp", "dDm", "ddH"), got, ref):
+        assert np.array_equal(g.cpu().numpy(), r), name
