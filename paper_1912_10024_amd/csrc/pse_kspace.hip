@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
         for (int u = 0; u < WB; ++u) acc[i][u] = cd{0.0, 0.0};
 
     if (valid) {
-        ks::stage_twiddles(tw, table, nkz, tid, kThreads);
+        if constexpr (YSRC == ks::kTrans || XSRC == ks::kTrans) ks::stage_twiddles(tw, table, nkz, tid, kThreads);
         if (tid == 0) *bad = 0;
         ks::stage_factor<kThreads>(A, edge, nn, sA, tid);
         const ks::Source ys = ks::source(g.y, a);
