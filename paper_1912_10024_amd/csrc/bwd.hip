@@ -33,7 +33,8 @@ constexpr int kYHalf = kBwdThreads / 2;   // first thread of the second Y group
 }
 
 // ---------------------------------------------------------------- reverse adjacency
-// ws layout (int32): count[na] | offset[na+1] | cursor[na] | edges[na*nb]
+// ws layout (int32): count[na] | offset[na+1] | cursor[na] | edges[na*nb] | order[na]; once it is
+// built, the first word holds what spread_kernel found
 __global__ void rcsr_count_kernel(int64_t na, int64_t nb, const int32_t* __restrict__ nbr, int32_t* count) {
     for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < na * nb; x += (int64_t)gridDim.x * blockDim.x) {
         const int32_t b = nbr[x];
@@ -553,35 +554,50 @@ bool bwd_supported(const Dims& d) {
 }
 
 // the kernels of kspace.h: every gradient from the transforms of g and G (room for
-// them, or for that of g, permitting)
+// them, or for that of g, permitting), or as the sum over the momenta stands
 static hipError_t launch_bwd_kspace(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
                                     const int32_t* nbr, cd alpha, const double* gS, double* dG, double* dDp, double* dDm,
-                                    double* dA, char* ws, size_t ws_bytes, const int32_t* offset, const int32_t* edges,
-                                    const int32_t* order, hipStream_t stream, bool signed_form) {
+                                    double* dA, char* ws, size_t ws_bytes, int* word, const int32_t* offset,
+                                    const int32_t* edges, const int32_t* order, hipStream_t stream, bool signed_form) {
     const cd calpha{alpha.re, -alpha.im};
+    const int nkz = (int)d.nkz;
     const int64_t nn = d.norb * d.norb;
-    // the sum over the momenta as it stands under the same line as the forward
-    const bool direct = d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks;
+    const bool d_part = dDp || dDm;
     const size_t hat = bwd_hat_bytes(d), used = bwd_csr_bytes(d) + (dA ? bwd_dh_bytes(d, signed_form) : 0);
     double *g_hat = nullptr, *G_hat = nullptr;
+    // the direct sum under the same line as the forward (the gate stays open for it), or where
+    // the arrays under a gradient's sum ask for it: g and D for dG, G too for d gradH, g and G for dD
+    auto gate = [&, small = d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks](int mask) {
+        return ks::Gate{small ? nullptr : word, mask | ks::kSpreadSigma};
+    };
     hipError_t e = hipSuccess;
-    if (!direct && ws_bytes >= used + hat) {
-        g_hat = reinterpret_cast<double*>(ws + used);
-        e = launch_transform(d, 0, d.ne, ks::array_blocks(gS, d, 1), g_hat, stream);
-        if (e != hipSuccess) return e;
-        if ((dA || dDp || dDm) && ws_bytes >= used + 2 * hat) {
-            G_hat = reinterpret_cast<double*>(ws + used + hat);
-            e = launch_transform(d, 0, d.ne, ks::array_blocks(G, d, d.gs), G_hat, stream);
-            if (e != hipSuccess) return e;
+    if (gate(0).word) {
+        if (ws_bytes >= used + hat) {
+            g_hat = reinterpret_cast<double*>(ws + used);
+            e = launch_transform(d, 0, d.ne, ks::array_blocks(gS, d, 1), g_hat, word, stream);
+            if (e == hipSuccess && (dA || d_part) && ws_bytes >= used + 2 * hat) {
+                G_hat = reinterpret_cast<double*>(ws + used + hat);
+                e = launch_transform(d, 0, d.ne, ks::array_blocks(G, d, d.gs), G_hat, nullptr, stream);
+            }
+        } else {
+            e = launch_clear_word(word, stream);
         }
+        if (e == hipSuccess)
+            e = launch_spread(nkz, ks::Gate{}, d.ne * d.na, nn, nn, gS, nullptr, ks::kSpreadSigma, word, stream);
+        if (e == hipSuccess && (dG || dA))
+            e = launch_spread(nkz, gate(0), d.nw * d.na * d.nb, 9, 9, Dp, Dm != Dp ? Dm : nullptr, ks::kSpreadD, word, stream);
+        if (e == hipSuccess && (dA || d_part))
+            e = launch_spread(nkz, gate(0), d.ne * d.na, nn, d.gs * nn, G, nullptr, ks::kSpreadG, word, stream);
+        if (e != hipSuccess) return e;
     }
     if (dG) {
-        e = launch_dg_kspace(d, direct, gS, g_hat, Dp, Dm, A, offset, edges, order, calpha, dG, stream);
+        e = launch_dg_kspace(d, gate(ks::kSpreadD), gS, g_hat, Dp, Dm, A, offset, edges, order, calpha, dG, stream);
         if (e != hipSuccess) return e;
     }
     if (dA) {
         double* shares = reinterpret_cast<double*>(ws + bwd_csr_bytes(d));
-        e = launch_dh_kspace(d, direct, gS, g_hat, G, G_hat, Dp, Dm, A, nbr, alpha, bwd_by_energy(d, signed_form), shares, stream);
+        e = launch_dh_kspace(d, gate(ks::kSpreadD | ks::kSpreadG), gS, g_hat, G, G_hat, Dp, Dm, A, nbr, alpha,
+                             bwd_by_energy(d, signed_form), shares, stream);
         if (e != hipSuccess) return e;
         const int64_t n = d.na * d.nb * 3 * nn;
         hipLaunchKernelGGL(bwd_dh_reduce_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 65536)), dim3(256), 0, stream,
@@ -590,10 +606,10 @@ static hipError_t launch_bwd_kspace(const Dims& d, const double* G, const double
         if (e != hipSuccess) return e;
     }
     if (dDp) {
-        e = launch_dd_kspace(d, direct, signed_form ? 1 : 3, gS, g_hat, G, G_hat, A, nbr, calpha, dDp, stream);
+        e = launch_dd_kspace(d, gate(ks::kSpreadG), signed_form ? 1 : 3, gS, g_hat, G, G_hat, A, nbr, calpha, dDp, stream);
         if (e != hipSuccess) return e;
     }
-    if (dDm) return launch_dd_kspace(d, direct, 2, gS, g_hat, G, G_hat, A, nbr, calpha, dDm, stream);
+    if (dDm) return launch_dd_kspace(d, gate(ks::kSpreadG), 2, gS, g_hat, G, G_hat, A, nbr, calpha, dDm, stream);
     return hipSuccess;
 }
 
@@ -645,8 +661,8 @@ hipError_t launch_bwd(const Dims& d, const double* G, const double* Dp, const do
         if (e != hipSuccess) return e;
     }
     if (kspace)
-        return launch_bwd_kspace(d, G, Dp, Dm, A, nbr, alpha, gS, dG, dDp, dDm, dA, static_cast<char*>(ws), ws_bytes, offset,
-                                 edges, order, stream, signed_form);
+        return launch_bwd_kspace(d, G, Dp, Dm, A, nbr, alpha, gS, dG, dDp, dDm, dA, static_cast<char*>(ws), ws_bytes, count,
+                                 offset, edges, order, stream, signed_form);
     if (dG || dA) {
         double* shares = dA ? reinterpret_cast<double*>(reinterpret_cast<char*>(ws) + bwd_csr_bytes(d)) : nullptr;
         const int64_t groups = (d.na + 7) / 8 * 8 * d.nkz;

@@ -41,12 +41,12 @@ struct DhArgs {
 
 }  // namespace
 
+// One (edge, share): block x of a launch's part
 template <int GSRC, int BSRC, bool DIRECT, bool TWO>
-__global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p, const double* __restrict__ Dp,
-                                                                const double* __restrict__ Dm, const double* __restrict__ A,
-                                                                const int32_t* __restrict__ nbr, cd alpha, DhTile t,
-                                                                int nshare, ks::LaunchPart part, ks::Twiddles table,
-                                                                double* __restrict__ out) {
+__device__ __forceinline__ void dh_block(int block, const Dims& d, const DhArgs& p, const double* __restrict__ Dp,
+                                         const double* __restrict__ Dm, const double* __restrict__ A,
+                                         const int32_t* __restrict__ nbr, cd alpha, const DhTile& t, int nshare,
+                                         const ks::LaunchPart& part, const ks::Twiddles& table, double* __restrict__ out) {
     extern __shared__ __align__(16) double smem[];
     const int n = (int)d.norb, nkz = (int)d.nkz, nw = (int)d.nw, ne = (int)d.ne, nb = (int)d.nb;
     const int nn = n * n, np = ks::row_len(n), eb = t.eb;
@@ -63,8 +63,8 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the workgroups of an atom on one XCD
-    const int s = blockIdx.x >> 3;
-    const int64_t a = part.a0 + s / part.n * 8 + (blockIdx.x & 7);
+    const int s = block >> 3;
+    const int64_t a = part.a0 + s / part.n * 8 + (block & 7);
     if (a >= d.na) return;  // uniform, before any barrier
     const int rem = part.first + s % part.n, share = rem % nshare;
     const int64_t edge = a * nb + rem / nshare, edges = d.na * nb;
@@ -206,6 +206,26 @@ __global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, DhArgs p
     }
 }
 
+template <int GSRC, int BSRC, bool DIRECT, bool TWO>
+__global__ __launch_bounds__(kThreads, 2) void dh_kspace_kernel(Dims d, ks::Gate gate, DhArgs p, const double* __restrict__ Dp,
+                                                                const double* __restrict__ Dm, const double* __restrict__ A,
+                                                                const int32_t* __restrict__ nbr, cd alpha, DhTile t,
+                                                                int nshare, ks::LaunchPart part, ks::Twiddles table,
+                                                                double* __restrict__ out) {
+    if (ks::shut<DIRECT>(gate)) return;
+    auto run = [&](int block) {
+        dh_block<GSRC, BSRC, DIRECT, TWO>(block, d, p, Dp, Dm, A, nbr, alpha, t, nshare, part, table, out);
+    };
+    if constexpr (DIRECT) {
+        for (unsigned block = blockIdx.x; block < part.groups; block += gridDim.x) {
+            __syncthreads();  // the LDS of the block before
+            run((int)block);
+        }
+    } else {
+        run((int)blockIdx.x);
+    }
+}
+
 // LDS entries of a tile: its buffers, then everything
 static int64_t dh_body(const Dims& d, int rc, int eb) {
     const int64_t n = d.norb, np = ks::row_len((int)n), rows = (eb + 2 * d.nw) * rc * np;
@@ -264,7 +284,7 @@ static bool dh_tile(const Dims& d, bool two, DhTile* best) {
 bool dh_kspace_supported(const Dims& d) { return dh_fits(d, true); }
 
 template <int GSRC, int BSRC, bool DIRECT, bool TWO>
-static hipError_t launch_dh(const Dims& d, const DhArgs& p, const double* Dp, const double* Dm, const double* A,
+static hipError_t launch_dh(const Dims& d, ks::Gate gate, const DhArgs& p, const double* Dp, const double* Dm, const double* A,
                             const int32_t* nbr, cd alpha, const DhTile& t, int64_t nshare, double* shares,
                             hipStream_t stream) {
     auto kern = dh_kspace_kernel<GSRC, BSRC, DIRECT, TWO>;
@@ -272,29 +292,35 @@ static hipError_t launch_dh(const Dims& d, const DhArgs& p, const double* Dp, co
     if (e != hipSuccess) return e;
     if (d.nb * nshare > INT32_MAX) return hipErrorInvalidValue;
     ks::launch_parts(d.na, d.nb * nshare, kThreads, [&](ks::LaunchPart part) {
-        hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, p, Dp, Dm, A, nbr, alpha, t, (int)nshare,
+        const unsigned groups = DIRECT && gate.word ? std::min(part.groups, ks::kGatedGroups) : part.groups;
+        hipLaunchKernelGGL(kern, dim3(groups), dim3(kThreads), t.lds, stream, d, gate, p, Dp, Dm, A, nbr, alpha, t, (int)nshare,
                            part, ks::twiddles(d.nkz), shares);
     });
     return hipGetLastError();
 }
 
-hipError_t launch_dh_kspace(const Dims& d, bool direct, const double* g, const double* g_hat, const double* G,
+hipError_t launch_dh_kspace(const Dims& d, ks::Gate gate, const double* g, const double* g_hat, const double* G,
                             const double* G_hat, const double* Dp, const double* Dm, const double* A, const int32_t* nbr,
                             cd alpha, bool by_energy, double* shares, hipStream_t stream) {
     const bool two = Dm != Dp;
     DhTile t;
     if (!dh_tile(d, two, &t)) return hipErrorInvalidValue;
-    DhArgs p{ks::array_blocks(g, d, 1), ks::array_blocks(G, d, d.gs), by_energy};
+    const DhArgs raw{ks::array_blocks(g, d, 1), ks::array_blocks(G, d, d.gs), by_energy};
     const int64_t nshare = by_energy ? (d.ne + 31) / 32 : d.nkz;
-#define SSE_DH(GS, BS, DIRECT, SCALE)                                                                         \
-    (two ? launch_dh<GS, BS, DIRECT, true>(d, p, Dp, Dm, A, nbr, SCALE, t, nshare, shares, stream)            \
-         : launch_dh<GS, BS, DIRECT, false>(d, p, Dp, Dm, A, nbr, SCALE, t, nshare, shares, stream))
-    if (direct) return SSE_DH(ks::kDirect, ks::kDirect, true, alpha);
-    if (g_hat) p.g = ks::hat_blocks(g_hat, d, 0, d.ne);
-    if (G_hat) p.G = ks::hat_blocks(G_hat, d, 0, d.ne);
-    const cd a{alpha.re / (double)d.nkz, alpha.im / (double)d.nkz};
-    if (G_hat) return SSE_DH(ks::kDirect, ks::kDirect, false, a);
-    return g_hat ? SSE_DH(ks::kDirect, ks::kTrans, false, a) : SSE_DH(ks::kTrans, ks::kTrans, false, a);
+#define SSE_DH(GS, BS, DIRECT, ARGS, SCALE)                                                                             \
+    (two ? launch_dh<GS, BS, DIRECT, true>(d, gate, ARGS, Dp, Dm, A, nbr, SCALE, t, nshare, shares, stream)             \
+         : launch_dh<GS, BS, DIRECT, false>(d, gate, ARGS, Dp, Dm, A, nbr, SCALE, t, nshare, shares, stream))
+    if (gate.word) {
+        DhArgs p = raw;
+        if (g_hat) p.g = ks::hat_blocks(g_hat, d, 0, d.ne);
+        if (G_hat) p.G = ks::hat_blocks(G_hat, d, 0, d.ne);
+        const cd a{alpha.re / (double)d.nkz, alpha.im / (double)d.nkz};
+        const hipError_t e = G_hat   ? SSE_DH(ks::kDirect, ks::kDirect, false, p, a)
+                             : g_hat ? SSE_DH(ks::kDirect, ks::kTrans, false, p, a)
+                                     : SSE_DH(ks::kTrans, ks::kTrans, false, p, a);
+        if (e != hipSuccess) return e;
+    }
+    return SSE_DH(ks::kDirect, ks::kDirect, true, raw, alpha);
 #undef SSE_DH
 }
 

@@ -68,16 +68,13 @@ struct InEdges {
 };
 
 // CB columns per pass of the products, MT passes of the left product per wave
+// One tile: block x of a launch's part
 template <int SRC, bool DIRECT, bool TWO, int MODE, int CB, int MT>
-__global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, ks::Blocks blocks,
-                                                                 const double* __restrict__ Dp,
-                                                                 const double* __restrict__ Dm,
-                                                                 const double* __restrict__ A,
-                                                                 const double* __restrict__ B,
-                                                                 const int32_t* __restrict__ nbr, InEdges in, cd alpha,
-                                                                 Tile tile, int e_lo, int e_hi, ks::LaunchPart part,
-                                                                 ks::Twiddles table, int s_slots,
-                                                                 double* __restrict__ S) {
+__device__ __forceinline__ void fwd_tile(int block, const Dims& d, const ks::Blocks& blocks, const double* __restrict__ Dp,
+                                         const double* __restrict__ Dm, const double* __restrict__ A,
+                                         const double* __restrict__ B, const int32_t* __restrict__ nbr, const InEdges& in,
+                                         cd alpha, const Tile& tile, int e_lo, int e_hi, const ks::LaunchPart& part,
+                                         const ks::Twiddles& table, int s_slots, double* __restrict__ S) {
     constexpr bool ADJ = MODE == kAdjoint;
     extern __shared__ __align__(16) double smem[];
     const int n = (int)d.norb, nkz = (int)d.nkz, nw = (int)d.nw, ne = (int)d.ne, nb = (int)d.nb;
@@ -96,8 +93,8 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, ks::Blo
     // the workgroups of an atom get ids on one XCD, the tiles of a momentum next to
     // each other: their windows of energies overlap
     const int ntile = (e_hi - e_lo + eb - 1) / eb;
-    const int s = blockIdx.x >> 3;
-    const int64_t pos = part.a0 + s / part.n * 8 + (blockIdx.x & 7);
+    const int s = block >> 3;
+    const int64_t pos = part.a0 + s / part.n * 8 + (block & 7);
     if (pos >= d.na) return;  // uniform, before any barrier
     const int64_t a = ADJ ? __builtin_amdgcn_readfirstlane(in.order[pos]) : pos;
     const int rem = part.first + s % part.n, kt = rem / ntile, e0 = e_lo + (rem - kt * ntile) * eb;
@@ -250,6 +247,31 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, ks::Blo
     }
 }
 
+template <int SRC, bool DIRECT, bool TWO, int MODE, int CB, int MT>
+__global__ __launch_bounds__(kThreads, 2) void fwd_kspace_kernel(Dims d, ks::Gate gate, ks::Blocks blocks,
+                                                                 const double* __restrict__ Dp,
+                                                                 const double* __restrict__ Dm,
+                                                                 const double* __restrict__ A,
+                                                                 const double* __restrict__ B,
+                                                                 const int32_t* __restrict__ nbr, InEdges in, cd alpha,
+                                                                 Tile tile, int e_lo, int e_hi, ks::LaunchPart part,
+                                                                 ks::Twiddles table, int s_slots,
+                                                                 double* __restrict__ S) {
+    if (ks::shut<DIRECT>(gate)) return;
+    auto run = [&](int block) {
+        fwd_tile<SRC, DIRECT, TWO, MODE, CB, MT>(block, d, blocks, Dp, Dm, A, B, nbr, in, alpha, tile, e_lo, e_hi, part, table,
+                                                 s_slots, S);
+    };
+    if constexpr (DIRECT) {
+        for (unsigned block = blockIdx.x; block < part.groups; block += gridDim.x) {
+            __syncthreads();  // the LDS of the tile before
+            run((int)block);
+        }
+    } else {
+        run((int)blockIdx.x);
+    }
+}
+
 // The tile with the least time per energy under the quantisation of each step:
 // cycles of the busiest wave, 16 per complex multiply-add, and the number of
 // rounds of workgroups on the chip.
@@ -302,11 +324,11 @@ size_t fwd_kspace_workspace(const Dims& d) {
     constexpr int64_t kSlabBytes = int64_t(4) << 30;
     if (d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks || !fwd_kspace_supported(d, true)) return 0;
     const int64_t per = hat_energy_bytes(d), want = std::max(kSlabBytes / per, 64 + 4 * d.nw);
-    return (size_t)(per * std::min(d.ne, want));
+    return (size_t)(per * std::min(d.ne, want)) + 2 * ks::kWordBytes;
 }
 
 template <int SRC, bool DIRECT, bool TWO, int MODE, int CB, int MT>
-static hipError_t launch_cb(const Dims& d, const ks::Blocks& blocks, const double* Dp, const double* Dm, const double* A,
+static hipError_t launch_cb(const Dims& d, ks::Gate gate, const ks::Blocks& blocks, const double* Dp, const double* Dm, const double* A,
                             const double* B, const int32_t* nbr, InEdges in, cd alpha, const Tile& t, int e_lo, int e_hi,
                             int s_slots, double* S, hipStream_t stream) {
     auto kern = fwd_kspace_kernel<SRC, DIRECT, TWO, MODE, CB, MT>;
@@ -315,7 +337,8 @@ static hipError_t launch_cb(const Dims& d, const ks::Blocks& blocks, const doubl
     const int64_t per = d.nkz * ((e_hi - e_lo + t.eb - 1) / t.eb);
     if (per > INT32_MAX) return hipErrorInvalidValue;
     ks::launch_parts(d.na, per, kThreads, [&](ks::LaunchPart part) {
-        hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, blocks, Dp, Dm, A, B, nbr, in, alpha, t,
+        const unsigned groups = DIRECT && gate.word ? std::min(part.groups, ks::kGatedGroups) : part.groups;
+        hipLaunchKernelGGL(kern, dim3(groups), dim3(kThreads), t.lds, stream, d, gate, blocks, Dp, Dm, A, B, nbr, in, alpha, t,
                            e_lo, e_hi, part, ks::twiddles(d.nkz), s_slots, S);
     });
     return hipGetLastError();
@@ -353,7 +376,7 @@ static hipError_t choose_tile(const Dims& d, bool two, bool stored, int* cb, Til
     return pick_tile(d, two, stored, *cb, mt, cus, t, &cost) ? hipSuccess : hipErrorInvalidValue;
 }
 
-hipError_t launch_dg_kspace(const Dims& d, bool direct, const double* g, const double* g_hat, const double* Dp,
+hipError_t launch_dg_kspace(const Dims& d, ks::Gate gate, const double* g, const double* g_hat, const double* Dp,
                             const double* Dm, const double* A, const int32_t* offset, const int32_t* edges,
                             const int32_t* order, cd calpha, double* dG, hipStream_t stream) {
     const bool two = Dm != Dp;
@@ -367,14 +390,17 @@ hipError_t launch_dg_kspace(const Dims& d, bool direct, const double* g, const d
     const int32_t* no_nbr = nullptr;
     const double* no_b = nullptr;
     // the E - w terms of this sum come from the table of the G at E + w
-    auto launch = [&](auto src, auto is_direct, const ks::Blocks& blocks) {
-        return launch_tables<decltype(src)::value, decltype(is_direct)::value>(two, kAdjoint, cb, d, blocks, Dm, Dp, A, no_b, no_nbr,
-                                                                               in, calpha, t, 0, (int)ne, (int)d.gs, dG, stream);
+    auto launch = [&](auto src, auto direct, const ks::Blocks& blocks) {
+        return launch_tables<decltype(src)::value, decltype(direct)::value>(two, kAdjoint, cb, d, gate, blocks, Dm, Dp, A, no_b,
+                                                                            no_nbr, in, calpha, t, 0, (int)ne, (int)d.gs, dG,
+                                                                            stream);
     };
-    if (direct) return launch(kFrom<ks::kDirect>{}, std::true_type{}, raw);
-    e = g_hat ? launch(kFrom<ks::kDirect>{}, std::false_type{}, hat) : launch(kFrom<ks::kTrans>{}, std::false_type{}, raw);
-    if (e != hipSuccess) return e;
-    return launch_inverse((int)d.nkz, ne * d.na, nn, d.gs * nn, calpha, dG, stream);
+    if (gate.word) {
+        e = g_hat ? launch(kFrom<ks::kDirect>{}, std::false_type{}, hat) : launch(kFrom<ks::kTrans>{}, std::false_type{}, raw);
+        if (e == hipSuccess) e = launch_inverse((int)d.nkz, gate, 0, ne * d.na, nn, d.gs * nn, calpha, dG, stream);
+        if (e != hipSuccess) return e;
+    }
+    return launch(kFrom<ks::kDirect>{}, std::true_type{}, raw);
 }
 
 hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
@@ -382,36 +408,51 @@ hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, c
                              size_t ws_bytes, hipStream_t stream) {
     const bool two = Dm != Dp;
     const int64_t nn = d.norb * d.norb, ne = d.ne;
+    const int nkz = (int)d.nkz;
     int cb;
     Tile t{};
     hipError_t e = choose_tile(d, two, B != nullptr, &cb, &t);
     if (e != hipSuccess) return e;
     const InEdges none{};
     const ks::Blocks raw = ks::array_blocks(G, d, d.gs);
-    auto launch = [&](auto src, auto is_direct, const ks::Blocks& blocks, int64_t lo, int64_t hi) {
-        return launch_tables<decltype(src)::value, decltype(is_direct)::value>(two, B ? kStored : kHermitian, cb, d, blocks, Dp, Dm,
-                                                                               A, B, nbr, none, alpha, t, (int)lo, (int)hi, 1, S,
-                                                                               stream);
+    ks::Gate gate{nullptr, ks::kSpreadD | ks::kSpreadG};
+    auto launch = [&](auto src, auto direct, const ks::Blocks& blocks, int64_t lo, int64_t hi) {
+        return launch_tables<decltype(src)::value, decltype(direct)::value>(two, B ? kStored : kHermitian, cb, d, gate, blocks, Dp,
+                                                                            Dm, A, B, nbr, none, alpha, t, (int)lo, (int)hi, 1, S,
+                                                                            stream);
     };
     if (!transform) return launch(kFrom<ks::kDirect>{}, std::true_type{}, raw, 0, ne);
-    const int64_t room = (int64_t)(ws_bytes / (size_t)hat_energy_bytes(d));  // energies
-    if (room >= std::min(ne, (int64_t)t.eb + 2 * d.nw)) {
+    // the word of the checks, then hat G, both aligned
+    int* word = reinterpret_cast<int*>(ks::aligned(ws));
+    double* hat = reinterpret_cast<double*>(reinterpret_cast<char*>(word) + ks::kWordBytes);
+    const int64_t left = static_cast<char*>(ws) + ws_bytes - reinterpret_cast<char*>(hat);
+    const int64_t room = left / hat_energy_bytes(d);  // energies
+    const bool slabs = room >= std::min(ne, (int64_t)t.eb + 2 * d.nw);
+    auto check = [&] {
+        gate.word = word;
+        hipError_t c = launch_spread(nkz, ks::Gate{}, d.nw * d.na * d.nb, 9, 9, Dp, two ? Dm : nullptr, ks::kSpreadD, word, stream);
+        if (c != hipSuccess) return c;
+        return launch_spread(nkz, ks::Gate{word, ks::kSpreadD}, ne * d.na, nn, d.gs * nn, G, nullptr, ks::kSpreadG, word, stream);
+    };
+    if (slabs) {
         // slabs of whole tiles; a slab's transform takes the 2 nw energies around it
         const int64_t step = room >= ne ? ne : (room - 2 * d.nw) / t.eb * t.eb;
-        double* hat = static_cast<double*>(ws);
         for (int64_t lo = 0; lo < ne; lo += step) {
             const int64_t hi = std::min(ne, lo + step);
             const int64_t first = std::max<int64_t>(0, lo - d.nw), n_e = std::min(ne, hi + d.nw) - first;
-            e = launch_transform(d, first, n_e, raw, hat, stream);
-            if (e != hipSuccess) return e;
-            e = launch(kFrom<ks::kDirect>{}, std::false_type{}, ks::hat_blocks(hat, d, first, n_e), lo, hi);
+            e = launch_transform(d, first, n_e, raw, hat, lo == 0 ? word : nullptr, stream);
+            if (e == hipSuccess && lo == 0) e = check();
+            if (e == hipSuccess) e = launch(kFrom<ks::kDirect>{}, std::false_type{}, ks::hat_blocks(hat, d, first, n_e), lo, hi);
             if (e != hipSuccess) return e;
         }
     } else {
-        e = launch(kFrom<ks::kTrans>{}, std::false_type{}, raw, 0, ne);
+        e = launch_clear_word(word, stream);
+        if (e == hipSuccess) e = check();
+        if (e == hipSuccess) e = launch(kFrom<ks::kTrans>{}, std::false_type{}, raw, 0, ne);
         if (e != hipSuccess) return e;
     }
-    return launch_inverse((int)d.nkz, ne * d.na, nn, nn, alpha, S, stream);
+    e = launch_inverse(nkz, gate, 0, ne * d.na, nn, nn, alpha, S, stream);
+    return e != hipSuccess ? e : launch(kFrom<ks::kDirect>{}, std::true_type{}, raw, 0, ne);
 }
 
 }  // namespace sse

@@ -116,6 +116,69 @@ struct Source {
 __device__ __forceinline__ Source source(const Blocks& b, int64_t a) {
     return Source{b.p + 2 * a * b.atom, b.kst, b.est, b.first, b.count};
 }
+
+// Transform or direct sum.  The transform rounds every value of a cyclic sum relative to the
+// largest of its Nkz values, the direct sum each relative to its own terms.  The two are
+// alike (within about kSpread) as soon as one of the arrays under the sum has blocks of like
+// size at all momenta, whatever the others hold: spread_kernel finds out for every block of
+// one array, and of a second and third only where those before are not like that, and sets a
+// bit per array in a word of the workspace.  Where all the bits of a sum are set, the kernels of
+// the transform leave at once and the direct ones run; else the other way round.
+constexpr double kSpread = 32.0;
+constexpr int kSpreadD = 1, kSpreadG = 2, kSpreadSigma = 4;  // bits: coefficients, G (or Go), dSigma (or Gs)
+constexpr int64_t kWordBytes = 16;  // of the workspace, so that what follows stays aligned
+inline void* aligned(void* p) { return reinterpret_cast<void*>((reinterpret_cast<uintptr_t>(p) + 15) & ~uintptr_t(15)); }
+struct Gate {
+    const int* word;  // NULL: open, whatever the kernel
+    int mask;
+};
+__device__ __forceinline__ bool all_spread(const Gate& g) { return (__builtin_amdgcn_readfirstlane(*g.word) & g.mask) == g.mask; }
+template <bool DIRECT>
+__device__ __forceinline__ bool shut(const Gate& g) {
+    return g.word && all_spread(g) != DIRECT;
+}
+// workgroups of a direct launch behind a gate: few, since they mostly find it shut, each
+// with several tiles if not
+constexpr unsigned kGatedGroups = 2048;
+
+// The blocks of one energy and atom at the nkz momenta, nn entries each, are of like size: the
+// largest part of the largest is at most kSpread times that of the smallest, and finite.
+// L lanes (a power of two, aligned in the wave) work on one block, l the lane's number.
+__device__ __forceinline__ bool like_blocks(const double* p, int64_t kst, int nkz, int nn, int l, int L) {
+    double least = __builtin_inf(), most = 0.0;
+    auto part = [](double v) { return fabs(v) <= 1.7976931348623157e308 ? fabs(v) : __builtin_inf(); };
+    for (int k0 = 0; k0 < nkz; k0 += 4) {
+        double m[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int x = l; x < nn; x += L) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const cd v = cload(p, (k0 + u < nkz ? k0 + u : k0) * kst + x);
+                m[u] = fmax(m[u], fmax(part(v.re), part(v.im)));
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            for (int o = 1; o < L; o <<= 1) m[u] = fmax(m[u], __shfl_xor(m[u], o));
+            least = fmin(least, m[u]);
+            most = fmax(most, m[u]);
+        }
+    }
+    return most <= 1.7976931348623157e308 && most <= kSpread * least;
+}
+// lanes for blocks of nn entries
+inline int block_lanes(int64_t nn) {
+    int l = 1;
+    while (l < 64 && l < nn) l *= 2;
+    return l;
+}
+
+// Without a workspace Pi keeps the finding in its output: a workgroup's first output holds
+// kMarker until the direct kernel writes it.  A signalling NaN, which no operation returns.
+constexpr unsigned long long kMarker = 0x7ff4535345306b73ull;
+__device__ __forceinline__ bool marked(const double* out, int64_t entry) {
+    return *reinterpret_cast<const unsigned long long*>(out + 2 * entry) == kMarker;
+}
+
 constexpr int kDirect = 0;  // blocks of one momentum as they are, from an array or from its transform
 constexpr int kTrans = 1;   // transformed over the momenta while they are loaded, from an array
 

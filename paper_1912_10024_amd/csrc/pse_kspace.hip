@@ -46,10 +46,11 @@ struct CorrArgs {
 }  // namespace
 
 // HI, LO: the branches; CT: B is the conjugate transpose of the array's blocks
+// One (edge, momentum, group of frequencies): block x of a launch's part
 template <int YSRC, int XSRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
-__global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs g, const double* __restrict__ A,
-                                                                  const int32_t* __restrict__ nbr, cd scale, CorrTile t,
-                                                                  ks::LaunchPart part, ks::Twiddles table, double* __restrict__ out) {
+__device__ __forceinline__ void corr_block(int block, const Dims& d, bool marks, const CorrArgs& g, const double* __restrict__ A,
+                                           const int32_t* __restrict__ nbr, cd scale, const CorrTile& t,
+                                           const ks::LaunchPart& part, const ks::Twiddles& table, double* __restrict__ out) {
     extern __shared__ __align__(16) double smem[];
     const int n = (int)d.norb, nkz = (int)d.nkz, nw = (int)d.nw, ne = (int)d.ne, nb = (int)d.nb;
     const int nn = n * n, np = ks::row_len(n), eb = t.eb;
@@ -63,8 +64,8 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the workgroups of an atom on one XCD: they read the same blocks of g
-    const int s = blockIdx.x >> 3;
-    const int64_t a = part.a0 + s / part.n * 8 + (blockIdx.x & 7);
+    const int s = block >> 3;
+    const int64_t a = part.a0 + s / part.n * 8 + (block & 7);
     if (a >= d.na) return;  // uniform, before any barrier
     int rem = part.first + s % part.n;
     const int wg = rem % t.nwg;
@@ -73,6 +74,8 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
     const int64_t edge = a * nb + m, edges = d.na * nb;
     const int32_t b = __builtin_amdgcn_readfirstlane(nbr[edge]);
     const bool valid = b >= 0 && b < d.na;
+    // an edge marked for the direct kernel (uniform, and only this workgroup writes the entry)
+    if (marks && ks::marked(out, (((int64_t)kt * nw + wg * t.nwb * WB) * edges + edge) * 9) != DIRECT) return;
 
     const ks::CorrLane own = ks::corr_lane(t, tid, wg);
     const int el = own.el, j = own.j, es = own.es, w0 = own.w0;
@@ -314,10 +317,29 @@ __global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, CorrArgs 
     }
 }
 
+template <int YSRC, int XSRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
+__global__ __launch_bounds__(kThreads) void corr_kspace_kernel(Dims d, ks::Gate gate, bool marks, CorrArgs g,
+                                                               const double* __restrict__ A, const int32_t* __restrict__ nbr,
+                                                               cd scale, CorrTile t, ks::LaunchPart part, ks::Twiddles table,
+                                                               double* __restrict__ out) {
+    if (ks::shut<DIRECT>(gate)) return;
+    auto run = [&](int block) {
+        corr_block<YSRC, XSRC, DIRECT, HI, LO, CT, WB>(block, d, marks, g, A, nbr, scale, t, part, table, out);
+    };
+    if constexpr (DIRECT) {
+        for (unsigned block = blockIdx.x; block < part.groups; block += gridDim.x) {
+            __syncthreads();  // the LDS of the block before
+            run((int)block);
+        }
+    } else {
+        run((int)blockIdx.x);
+    }
+}
+
 bool corr_kspace_supported(const Dims& d, bool both) { return ks::corr_fits(d, true, both); }
 
 template <int YSRC, int XSRC, bool DIRECT, bool HI, bool LO, bool CT, int WB>
-static hipError_t launch_corr_wb(const Dims& d, const CorrArgs& g, const double* A, const int32_t* nbr, cd scale,
+static hipError_t launch_corr_wb(const Dims& d, ks::Gate gate, bool marks, const CorrArgs& g, const double* A, const int32_t* nbr, cd scale,
                                  const CorrTile& t, double* out, hipStream_t stream) {
     auto kern = corr_kspace_kernel<YSRC, XSRC, DIRECT, HI, LO, CT, WB>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds);
@@ -325,7 +347,8 @@ static hipError_t launch_corr_wb(const Dims& d, const CorrArgs& g, const double*
     const int64_t per = d.nb * d.nkz * t.nwg;
     if (per > INT32_MAX) return hipErrorInvalidValue;
     ks::launch_parts(d.na, per, kThreads, [&](ks::LaunchPart part) {
-        hipLaunchKernelGGL(kern, dim3(part.groups), dim3(kThreads), t.lds, stream, d, g, A, nbr, scale, t, part,
+        const unsigned groups = DIRECT && (gate.word || marks) ? std::min(part.groups, ks::kGatedGroups) : part.groups;
+        hipLaunchKernelGGL(kern, dim3(groups), dim3(kThreads), t.lds, stream, d, gate, marks, g, A, nbr, scale, t, part,
                            ks::twiddles(d.nkz), out);
     });
     return hipGetLastError();
@@ -354,55 +377,79 @@ static hipError_t launch_pi_corr(int wb, Args... args) {
     return launch_corr_shape<SRC, SRC, DIRECT, true, false, true>(wb, args...);
 }
 
-hipError_t launch_dd_kspace(const Dims& d, bool direct, int branches, const double* g, const double* g_hat, const double* G,
+hipError_t launch_dd_kspace(const Dims& d, ks::Gate gate, int branches, const double* g, const double* g_hat, const double* G,
                             const double* G_hat, const double* A, const int32_t* nbr, cd calpha, double* dD,
                             hipStream_t stream) {
     CorrTile t;
     if (!corr_tile(d, (branches & 1) != 0, (branches & 2) != 0, &t)) return hipErrorInvalidValue;
-    CorrArgs a{ks::array_blocks(g, d, 1), ks::array_blocks(G, d, d.gs), 0, (int)d.ne, false};
-    if (direct) return launch_dd<ks::kDirect, ks::kDirect, true>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
-    if (g_hat) a.y = ks::hat_blocks(g_hat, d, 0, d.ne);
-    if (G_hat) a.x = ks::hat_blocks(G_hat, d, 0, d.ne);
-    hipError_t e;
-    if (G_hat)
-        e = launch_dd<ks::kDirect, ks::kDirect, false>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
-    else if (g_hat)
-        e = launch_dd<ks::kDirect, ks::kTrans, false>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
-    else
-        e = launch_dd<ks::kTrans, ks::kTrans, false>(branches, t.wb, d, a, A, nbr, calpha, t, dD, stream);
-    if (e != hipSuccess) return e;
-    return launch_inverse((int)d.nkz, d.nw * d.na * d.nb, 9, 9, calpha, dD, stream);
+    const CorrArgs raw{ks::array_blocks(g, d, 1), ks::array_blocks(G, d, d.gs), 0, (int)d.ne, false};
+    if (gate.word) {
+        CorrArgs a = raw;
+        if (g_hat) a.y = ks::hat_blocks(g_hat, d, 0, d.ne);
+        if (G_hat) a.x = ks::hat_blocks(G_hat, d, 0, d.ne);
+        hipError_t e;
+        if (G_hat)
+            e = launch_dd<ks::kDirect, ks::kDirect, false>(branches, t.wb, d, gate, false, a, A, nbr, calpha, t, dD, stream);
+        else if (g_hat)
+            e = launch_dd<ks::kDirect, ks::kTrans, false>(branches, t.wb, d, gate, false, a, A, nbr, calpha, t, dD, stream);
+        else
+            e = launch_dd<ks::kTrans, ks::kTrans, false>(branches, t.wb, d, gate, false, a, A, nbr, calpha, t, dD, stream);
+        if (e == hipSuccess) e = launch_inverse((int)d.nkz, gate, 0, d.nw * d.na * d.nb, 9, 9, calpha, dD, stream);
+        if (e != hipSuccess) return e;
+    }
+    return launch_dd<ks::kDirect, ks::kDirect, true>(branches, t.wb, d, gate, false, raw, A, nbr, calpha, t, dD, stream);
 }
 
 hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, const double* A, const int32_t* nbr, cd beta,
                             double* Pi, bool transform, void* ws, size_t ws_bytes, hipStream_t stream) {
     CorrTile t;
     if (!corr_tile(d, true, false, &t)) return hipErrorInvalidValue;
-    const int64_t ne = d.ne;
+    const int64_t ne = d.ne, nn = d.norb * d.norb, edges = d.na * d.nb;
+    const int nkz = (int)d.nkz;
     const ks::Blocks y = ks::array_blocks(Gs, d, d.gs), x = ks::array_blocks(Go, d, d.gs);
-    CorrArgs g{y, x, 0, (int)ne, false};
-    if (!transform) return launch_pi_corr<ks::kDirect, true>(t.wb, d, g, A, nbr, beta, t, Pi, stream);
-    // room for energies of a transform: both arrays whole, or slabs of whole tiles of
-    // energies of both (with the nw energies above for Gs), or neither
+    const CorrArgs raw{y, x, 0, (int)ne, false};
+    ks::Gate gate{nullptr, ks::kSpreadG | ks::kSpreadSigma};
+    bool marks = false;
+    auto direct = [&] { return launch_pi_corr<ks::kDirect, true>(t.wb, d, gate, marks, raw, A, nbr, beta, t, Pi, stream); };
+    if (!transform) return direct();
+    // The word of the checks, then the transforms: both whole, or slabs of whole tiles of energies
+    // of both, or neither.  A slab of Go meets the energies of Gs above its first, up to nw
+    // more than its own: one fewer than the two arrays have, which leaves the word its room.
+    int* word = reinterpret_cast<int*>(ks::aligned(ws));
+    double* hy = reinterpret_cast<double*>(reinterpret_cast<char*>(word) + ks::kWordBytes);
+    const int64_t left = static_cast<char*>(ws) + ws_bytes - reinterpret_cast<char*>(hy);
+    const int64_t per = 16 * d.nkz * d.na * nn, room = left > 0 ? left / per : 0;  // energies
+    const int64_t step = room >= 2 * ne - 1 ? ne : (room - d.nw + 1) / 2 / t.eb * t.eb;
     hipError_t e = hipSuccess;
-    const int64_t per = 16 * d.nkz * d.na * d.norb * d.norb, room = (int64_t)(ws_bytes / (size_t)per);
-    const int64_t step = room >= 2 * ne ? ne : (room - d.nw) / 2 / t.eb * t.eb;
-    if (step >= std::min<int64_t>(ne, t.eb)) {
-        double* hy = static_cast<double*>(ws);
+    auto check = [&] {
+        gate.word = word;
+        hipError_t c = launch_spread(nkz, ks::Gate{}, ne * d.na, nn, d.gs * nn, Go, nullptr, ks::kSpreadG, word, stream);
+        if (c != hipSuccess) return c;
+        return launch_spread(nkz, ks::Gate{word, ks::kSpreadG}, ne * d.na, nn, d.gs * nn, Gs, nullptr, ks::kSpreadSigma, word, stream);
+    };
+    if (ws && step >= std::min<int64_t>(ne, t.eb)) {
         for (int64_t lo = 0; lo < ne && e == hipSuccess; lo += step) {
-            const int64_t hi = std::min(ne, lo + step), n_y = std::min(ne, hi + d.nw) - lo, n_x = hi - lo;
+            const int64_t hi = std::min(ne, lo + step), n_x = hi - lo, n_y = std::min(ne, hi + d.nw) - (lo + 1);
             double* hx = hy + per / 8 * n_y;
-            e = launch_transform(d, lo, n_y, y, hy, stream);
-            if (e == hipSuccess) e = launch_transform(d, lo, n_x, x, hx, stream);
+            e = launch_transform(d, lo, n_x, x, hx, lo == 0 ? word : nullptr, stream);
+            if (e == hipSuccess && n_y > 0) e = launch_transform(d, lo + 1, n_y, y, hy, nullptr, stream);
+            if (e == hipSuccess && lo == 0) e = check();
             if (e != hipSuccess) return e;
-            g = CorrArgs{ks::hat_blocks(hy, d, lo, n_y), ks::hat_blocks(hx, d, lo, n_x), (int)lo, (int)hi, lo > 0};
-            e = launch_pi_corr<ks::kDirect, false>(t.wb, d, g, A, nbr, beta, t, Pi, stream);
+            const CorrArgs g{ks::hat_blocks(hy, d, lo + 1, n_y), ks::hat_blocks(hx, d, lo, n_x), (int)lo, (int)hi, lo > 0};
+            e = launch_pi_corr<ks::kDirect, false>(t.wb, d, gate, marks, g, A, nbr, beta, t, Pi, stream);
         }
     } else {
-        e = launch_pi_corr<ks::kTrans, false>(t.wb, d, g, A, nbr, beta, t, Pi, stream);
+        if (ws && left >= 0) {
+            e = launch_clear_word(word, stream);
+            if (e == hipSuccess) e = check();
+        } else {
+            marks = true;
+            e = launch_mark_pi(d, y, x, t.nwb * t.wb, nbr, Pi, stream);
+        }
+        if (e == hipSuccess) e = launch_pi_corr<ks::kTrans, false>(t.wb, d, gate, marks, raw, A, nbr, beta, t, Pi, stream);
     }
-    if (e != hipSuccess) return e;
-    return launch_inverse((int)d.nkz, d.nw * d.na * d.nb, 9, 9, beta, Pi, stream);
+    if (e == hipSuccess) e = launch_inverse(nkz, gate, marks ? edges : 0, d.nw * edges, 9, 9, beta, Pi, stream);
+    return e != hipSuccess ? e : direct();
 }
 
 // both transforms, or slabs of at most 32 GiB of them (a slab costs a prologue and a

@@ -21,14 +21,25 @@ hipError_t launch_fwd_generic(const Dims& d, const double* G, const double* Dp, 
 
 namespace ks {
 struct Blocks;  // kspace.h
+struct Gate;
 }
 
 // the momentum transform of a block array into hat[m][atom][energy][nn] for the
-// energies [first, first + n_e), and its inverse in place over the leading axis of
-// [nkz][blocks][bs] (the first nn entries of every block), times scale / nkz
-hipError_t launch_transform(const Dims& d, int64_t first, int64_t n_e, const ks::Blocks& src, double* hat,
+// energies [first, first + n_e) (clear: a word that is set to zero, or NULL), and its inverse in
+// place over the leading axis of [nkz][blocks][bs] (the first nn entries of every block), times
+// scale / nkz; edges: 0, or those of Pi (marked ones are left)
+hipError_t launch_transform(const Dims& d, int64_t first, int64_t n_e, const ks::Blocks& src, double* hat, int* clear,
                             hipStream_t stream);
-hipError_t launch_inverse(int nkz, int64_t blocks, int64_t nn, int64_t bs, cd scale, double* X,
+hipError_t launch_inverse(int nkz, ks::Gate gate, int64_t edges, int64_t blocks, int64_t nn, int64_t bs, cd scale, double* X,
+                          hipStream_t stream);
+
+// the choice between transform and direct sum (ks::Gate): sets a bit of *word where blocks of
+// p (or q, unless NULL) differ in size over the momenta, if all bits of `only` are set; or
+// marks edges of Pi
+hipError_t launch_spread(int nkz, ks::Gate only, int64_t blocks, int64_t nn, int64_t bs, const double* p, const double* q, int bit,
+                         int* word, hipStream_t stream);
+hipError_t launch_clear_word(int* word, hipStream_t stream);
+hipError_t launch_mark_pi(const Dims& d, const ks::Blocks& y, const ks::Blocks& x, int step, const int32_t* nbr, double* Pi,
                           hipStream_t stream);
 
 // fp64 forward in the momentum transform (kspace.h), any shape whose tile fits the
@@ -56,17 +67,17 @@ hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, c
 // of g = dL/dSigma and G (launch_transform), or NULL: every workgroup transforms what
 // it loads (the same sums, bit for bit).
 // dG from the in-edges of every atom; the one-table form passes Dm = Dp
-hipError_t launch_dg_kspace(const Dims& d, bool direct, const double* g, const double* g_hat, const double* Dp,
+hipError_t launch_dg_kspace(const Dims& d, ks::Gate gate, const double* g, const double* g_hat, const double* Dp,
                             const double* Dm, const double* A, const int32_t* offset, const int32_t* edges,
                             const int32_t* order, cd calpha, double* dG, hipStream_t stream);
 // d gradH: one share per edge and part of the (momenta, energies), added by the caller;
 // by_energy: a share holds all momenta of 32 energies, else all energies of a momentum
 bool dh_kspace_supported(const Dims& d);
-hipError_t launch_dh_kspace(const Dims& d, bool direct, const double* g, const double* g_hat, const double* G,
+hipError_t launch_dh_kspace(const Dims& d, ks::Gate gate, const double* g, const double* g_hat, const double* G,
                             const double* G_hat, const double* Dp, const double* Dm, const double* A, const int32_t* nbr,
                             cd alpha, bool by_energy, double* shares, hipStream_t stream);
 // dD; branches: 1 the terms with G at E - w (coefficients at +w), 2 those with G at E + w, 3 both
-hipError_t launch_dd_kspace(const Dims& d, bool direct, int branches, const double* g, const double* g_hat, const double* G,
+hipError_t launch_dd_kspace(const Dims& d, ks::Gate gate, int branches, const double* g, const double* g_hat, const double* G,
                             const double* G_hat, const double* A, const int32_t* nbr, cd calpha, double* dD,
                             hipStream_t stream);
 

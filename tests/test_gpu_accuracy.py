@@ -67,3 +67,109 @@ def test_dg_rounds_as_its_terms_do(d):
     err = float(np.sqrt((abs(got - ref) ** 2).sum() / (abs(ref) ** 2).sum()))
     print(f"  error {err:.3e}, bound {bound:.3e}", flush=True)
     assert err <= bound
+
+
+# ------------------------------------------------------------------ blocks that differ over the momenta
+DIMS = Dims(nkz=5, ne=50, nqz=5, nw=4, na=6, nb=2, norb=5, g_slots=2)   # above 1024 blocks
+
+
+def _peaked(x, at, low):
+    """The array with all momenta but one scaled down."""
+    s = np.full(x.shape[0], low)
+    s[at] = 1.0
+    return x * s.reshape(-1, *([1] * (x.ndim - 1)))
+
+
+def _worst(got, ref):
+    """The largest error of a momentum relative to its own values."""
+    return max(np.linalg.norm(g - r) / np.linalg.norm(r) for g, r in zip(got, ref))
+
+
+def _sets(d, low, **at):
+    x = _inputs(d, 17)
+    for k, m in at.items():
+        x[k] = _peaked(x[k], m, low)
+    return x, _gpu(x)
+
+
+# peaked by 1e8 the direct sum is taken; by 16 the transform, whose errors grow by less than
+# that.  A sum of at most 2 * nkz * nw * nb * 9 products of norb^3 terms rounds below 1e-14.
+PEAKS = pytest.mark.parametrize("low,bound", [(1e-8, 1e-13), (1.0 / 16, 2e-13)], ids=["far", "near"])
+
+
+@PEAKS
+def test_sigma_of_peaked_arrays(low, bound):
+    print(f"[gpu] peaked sigma {low}", flush=True)
+    from oracle import oracle
+    d = DIMS
+    x, t = _sets(d, low, G=1, D=2, Dm=3)
+    ref = oracle.sse_forward(d, x["G"], x["D"], x["dH"], x["nbr"])
+    per = 16 * d.nkz * d.na * d.norb ** 2
+    for ws in (None, torch.empty(256, dtype=torch.uint8, device="cuda"), torch.empty(40 * per + 77, dtype=torch.uint8, device="cuda")[13:]):
+        assert _worst(sse.forward(t["G"], t["D"], t["dH"], t["nbr"], ws=ws).cpu().numpy(), ref) <= bound
+    ref = oracle.sse_forward_signed(d, x["G"], x["D"], x["Dm"], x["dH"], x["nbr"])
+    assert _worst(sse.forward_signed(t["G"], t["D"], t["Dm"], t["dH"], t["nbr"]).cpu().numpy(), ref) <= bound
+    # the second table alone: the first is of like size everywhere
+    x, t = _sets(d, low, G=1, Dm=3)
+    x["D"] *= 1e-20
+    t["D"] *= 1e-20
+    ref = oracle.sse_forward_signed(d, x["G"], x["D"], x["Dm"], x["dH"], x["nbr"])
+    assert _worst(sse.forward_signed(t["G"], t["D"], t["Dm"], t["dH"], t["nbr"]).cpu().numpy(), ref) <= bound
+
+
+@PEAKS
+def test_pi_of_peaked_arrays(low, bound):
+    import ctypes
+
+    from oracle import oracle
+    from paper_1912_10024_amd import _lib
+    print(f"[gpu] peaked pi {low}", flush=True)
+    d = DIMS.replace(ne=60)
+    x, t = _sets(d, low, G=1, Go=3)
+    x["nbr"][2, 1] = -1
+    t["nbr"][2, 1] = -1
+    ok = np.ones((d.na, d.nb), bool)
+    ok[2, 1] = False
+    ref = oracle.pse_forward(d, x["G"], x["Go"], x["dH"], np.where(x["nbr"] < 0, 0, x["nbr"]).astype(np.int32))[:, :, ok]
+    per = 16 * d.nkz * d.na * d.norb ** 2
+    for nbytes in (0, 40, per * 2 * d.ne, per * 50):
+        out = torch.full(d.d_shape, complex(float("nan"), float("nan")), dtype=torch.complex128, device="cuda")
+        ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device="cuda")
+        P = lambda v: ctypes.c_void_p(v.data_ptr())
+        rc = _lib.load().sse_phonon_forward_ws(ctypes.byref(_lib.SSEDims.of(d)), P(t["G"]), P(t["Go"]), P(t["dH"]), P(t["nbr"]),
+                                               0.0, -1.0, P(out), P(ws), nbytes, ctypes.c_void_p(0))
+        assert rc == 0
+        got = out.cpu().numpy()
+        assert np.array_equal(got[:, :, 2, 1], np.zeros_like(got[:, :, 2, 1]))
+        assert _worst(got[:, :, ok], ref) <= bound, nbytes
+
+
+@PEAKS
+@pytest.mark.parametrize("signed", [False, True], ids=["one_table", "two_tables"])
+def test_gradients_of_peaked_arrays(low, bound, signed):
+    """All three arrays peaked, so that every gradient's sum has a large and small values;
+    d grad H has one value per edge, here one without a product of three peaks."""
+    from oracle import oracle
+    print(f"[gpu] peaked gradients {low} signed={signed}", flush=True)
+    d = DIMS
+    x, t = _sets(d, low, G=1, D=2, Dm=2, gS=1)
+    if signed:
+        got = sse.backward_signed(t["G"], t["D"], t["Dm"], t["dH"], t["nbr"], t["gS"])
+        ref = oracle.sse_backward_signed(d, x["G"], x["D"], x["Dm"], x["dH"], x["nbr"], x["gS"])
+    else:
+        got = sse.backward(t["G"], t["D"], t["dH"], t["nbr"], t["gS"])
+        ref = oracle.sse_backward(d, x["G"], x["D"], x["dH"], x["nbr"], x["gS"])
+    assert _worst(got[0].cpu().numpy(), ref[0]) <= bound
+    for g, r in zip(got[1:-1], ref[1:-1]):
+        assert _worst(g.cpu().numpy(), r) <= bound
+    assert _worst(got[-1].cpu().numpy(), ref[-1]) <= bound
+
+
+def test_zeros_by_momentum_selection_stay_zero():
+    """D at one q and G at one k: Sigma at every momentum but their sum is exactly zero."""
+    print("[gpu] momentum selection", flush=True)
+    d = DIMS
+    x, t = _sets(d, 0.0, G=1, D=2)
+    S = sse.forward(t["G"], t["D"], t["dH"], t["nbr"])
+    for k in range(d.nkz):
+        assert bool((S[k] != 0).any()) == (k == 3)
