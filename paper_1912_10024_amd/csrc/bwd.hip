@@ -553,6 +553,7 @@ bool bwd_supported(const Dims& d) {
            bwd_lds_dd(d) <= 160 * 1024 && d.na * d.nb <= INT32_MAX && (d.na + 7) / 8 * 8 * d.nkz <= INT32_MAX;
 }
 
+static bool bwd_small(const Dims& d) { return d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks; }
 // the kernels of kspace.h: every gradient from the transforms of g and G (room for
 // them, or for that of g, permitting), or as the sum over the momenta stands
 static hipError_t launch_bwd_kspace(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
@@ -567,50 +568,54 @@ static hipError_t launch_bwd_kspace(const Dims& d, const double* G, const double
     double *g_hat = nullptr, *G_hat = nullptr;
     // the direct sum under the same line as the forward (the gate stays open for it), or where
     // the arrays under a gradient's sum ask for it: g and D for dG, G too for d gradH, g and G for dD
-    auto gate = [&, small = d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks](int mask) {
-        return ks::Gate{small ? nullptr : word, mask | ks::kSpreadSigma};
-    };
+    const bool small = bwd_small(d);
+    auto gate = [&](int mask) { return ks::Gate{small ? nullptr : word, mask | ks::kSpreadSigma}; };
     hipError_t e = hipSuccess;
     if (gate(0).word) {
-        if (ws_bytes >= used + hat) {
-            g_hat = reinterpret_cast<double*>(ws + used);
-            e = launch_transform(d, 0, d.ne, ks::array_blocks(gS, d, 1), g_hat, word, stream);
-            if (e == hipSuccess && (dA || d_part) && ws_bytes >= used + 2 * hat) {
-                G_hat = reinterpret_cast<double*>(ws + used + hat);
-                e = launch_transform(d, 0, d.ne, ks::array_blocks(G, d, d.gs), G_hat, nullptr, stream);
-            }
-        } else {
-            e = launch_clear_word(word, stream);
-        }
+        // Room for one transform: that of g if dG is wanted, whose array then holds that of G until
+        // its own turn comes (d gradH and dD go first); else that of G, which they read more often
+        // than that of g.  Without room, dG's array for that of G all the same.
+        const size_t room = ws_bytes >= used ? (ws_bytes - used) / hat : 0;
+        const bool want_G = dA || d_part;
+        double* first = reinterpret_cast<double*>(ws + used);
+        if (room >= 1 && (dG || room >= 2)) g_hat = first;
+        if (want_G && room >= 2)
+            G_hat = reinterpret_cast<double*>(ws + used + hat);
+        else if (want_G && dG)
+            G_hat = dG;
+        else if (want_G && room >= 1)
+            G_hat = first;
+        if (g_hat) e = launch_transform(d, 0, d.ne, ks::array_blocks(gS, d, 1), g_hat, nullptr, stream);
+        if (e == hipSuccess && G_hat) e = launch_transform(d, 0, d.ne, ks::array_blocks(G, d, d.gs), G_hat, nullptr, stream);
+        if (e == hipSuccess) e = launch_clear_word(word, stream);
         if (e == hipSuccess)
             e = launch_spread(nkz, ks::Gate{}, d.ne * d.na, nn, nn, gS, nullptr, ks::kSpreadSigma, word, stream);
         if (e == hipSuccess && (dG || dA))
             e = launch_spread(nkz, gate(0), d.nw * d.na * d.nb, 9, 9, Dp, Dm != Dp ? Dm : nullptr, ks::kSpreadD, word, stream);
-        if (e == hipSuccess && (dA || d_part))
+        if (e == hipSuccess && want_G)
             e = launch_spread(nkz, gate(0), d.ne * d.na, nn, d.gs * nn, G, nullptr, ks::kSpreadG, word, stream);
         if (e != hipSuccess) return e;
     }
-    if (dG) {
-        e = launch_dg_kspace(d, gate(ks::kSpreadD), gS, g_hat, Dp, Dm, A, offset, edges, order, calpha, dG, stream);
-        if (e != hipSuccess) return e;
+    double* shares = dA ? reinterpret_cast<double*>(ws + bwd_csr_bytes(d)) : nullptr;
+    const ks::Gate dg_gate = gate(ks::kSpreadD), dh_gate = gate(ks::kSpreadD | ks::kSpreadG), dd_gate = gate(ks::kSpreadG);
+    if (dA)
+        e = launch_dh_kspace(d, dh_gate, true, gS, g_hat, G, G_hat, Dp, Dm, A, nbr, alpha, bwd_by_energy(d, signed_form), shares,
+                             stream);
+    for (int branch = 1; branch <= 2; ++branch) {
+        double* dD = branch == 1 ? dDp : dDm;
+        if (!dD || e != hipSuccess) continue;
+        const int branches = signed_form ? branch : 3;
+        e = launch_dd_kspace(d, dd_gate, true, branches, gS, g_hat, G, G_hat, A, nbr, calpha, dD, stream);
     }
-    if (dA) {
-        double* shares = reinterpret_cast<double*>(ws + bwd_csr_bytes(d));
-        e = launch_dh_kspace(d, gate(ks::kSpreadD | ks::kSpreadG), gS, g_hat, G, G_hat, Dp, Dm, A, nbr, alpha,
-                             bwd_by_energy(d, signed_form), shares, stream);
-        if (e != hipSuccess) return e;
+    if (dG && e == hipSuccess)
+        e = launch_dg_kspace(d, dg_gate, true, gS, g_hat, Dp, Dm, A, offset, edges, order, calpha, dG, stream);
+    if (dA && e == hipSuccess) {
         const int64_t n = d.na * d.nb * 3 * nn;
         hipLaunchKernelGGL(bwd_dh_reduce_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 65536)), dim3(256), 0, stream,
                            d, nbr, shares, bwd_shares(d, signed_form), dA);
         e = hipGetLastError();
-        if (e != hipSuccess) return e;
     }
-    if (dDp) {
-        e = launch_dd_kspace(d, gate(ks::kSpreadG), signed_form ? 1 : 3, gS, g_hat, G, G_hat, A, nbr, calpha, dDp, stream);
-        if (e != hipSuccess) return e;
-    }
-    if (dDm) return launch_dd_kspace(d, gate(ks::kSpreadG), 2, gS, g_hat, G, G_hat, A, nbr, calpha, dDm, stream);
-    return hipSuccess;
+    return e;
 }
 
 // dD (or dDp / dDm) for the given energy branches

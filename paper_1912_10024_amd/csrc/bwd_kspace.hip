@@ -299,9 +299,10 @@ static hipError_t launch_dh(const Dims& d, ks::Gate gate, const DhArgs& p, const
     return hipGetLastError();
 }
 
-hipError_t launch_dh_kspace(const Dims& d, ks::Gate gate, const double* g, const double* g_hat, const double* G,
+hipError_t launch_dh_kspace(const Dims& d, ks::Gate gate, bool with_direct, const double* g, const double* g_hat, const double* G,
                             const double* G_hat, const double* Dp, const double* Dm, const double* A, const int32_t* nbr,
                             cd alpha, bool by_energy, double* shares, hipStream_t stream) {
+    if (!gate.word && !with_direct) return hipSuccess;
     const bool two = Dm != Dp;
     DhTile t;
     if (!dh_tile(d, two, &t)) return hipErrorInvalidValue;
@@ -312,14 +313,15 @@ hipError_t launch_dh_kspace(const Dims& d, ks::Gate gate, const double* g, const
          : launch_dh<GS, BS, DIRECT, false>(d, gate, ARGS, Dp, Dm, A, nbr, SCALE, t, nshare, shares, stream))
     if (gate.word) {
         DhArgs p = raw;
-        if (g_hat) p.g = ks::hat_blocks(g_hat, d, 0, d.ne);
+        if (G_hat && g_hat) p.g = ks::hat_blocks(g_hat, d, 0, d.ne);
         if (G_hat) p.G = ks::hat_blocks(G_hat, d, 0, d.ne);
         const cd a{alpha.re / (double)d.nkz, alpha.im / (double)d.nkz};
-        const hipError_t e = G_hat   ? SSE_DH(ks::kDirect, ks::kDirect, false, p, a)
-                             : g_hat ? SSE_DH(ks::kDirect, ks::kTrans, false, p, a)
-                                     : SSE_DH(ks::kTrans, ks::kTrans, false, p, a);
+        const hipError_t e = G_hat && g_hat ? SSE_DH(ks::kDirect, ks::kDirect, false, p, a)
+                             : G_hat        ? SSE_DH(ks::kTrans, ks::kDirect, false, p, a)
+                                            : SSE_DH(ks::kTrans, ks::kTrans, false, p, a);
         if (e != hipSuccess) return e;
     }
+    if (!with_direct) return hipSuccess;
     return SSE_DH(ks::kDirect, ks::kDirect, true, raw, alpha);
 #undef SSE_DH
 }

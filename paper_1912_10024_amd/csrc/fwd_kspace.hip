@@ -376,9 +376,10 @@ static hipError_t choose_tile(const Dims& d, bool two, bool stored, int* cb, Til
     return pick_tile(d, two, stored, *cb, mt, cus, t, &cost) ? hipSuccess : hipErrorInvalidValue;
 }
 
-hipError_t launch_dg_kspace(const Dims& d, ks::Gate gate, const double* g, const double* g_hat, const double* Dp,
+hipError_t launch_dg_kspace(const Dims& d, ks::Gate gate, bool with_direct, const double* g, const double* g_hat, const double* Dp,
                             const double* Dm, const double* A, const int32_t* offset, const int32_t* edges,
                             const int32_t* order, cd calpha, double* dG, hipStream_t stream) {
+    if (!gate.word && !with_direct) return hipSuccess;
     const bool two = Dm != Dp;
     const int64_t nn = d.norb * d.norb, ne = d.ne;
     int cb;
@@ -400,6 +401,7 @@ hipError_t launch_dg_kspace(const Dims& d, ks::Gate gate, const double* g, const
         if (e == hipSuccess) e = launch_inverse((int)d.nkz, gate, 0, ne * d.na, nn, d.gs * nn, calpha, dG, stream);
         if (e != hipSuccess) return e;
     }
+    if (!with_direct) return hipSuccess;
     return launch(kFrom<ks::kDirect>{}, std::true_type{}, raw);
 }
 

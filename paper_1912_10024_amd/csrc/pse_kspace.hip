@@ -377,26 +377,28 @@ static hipError_t launch_pi_corr(int wb, Args... args) {
     return launch_corr_shape<SRC, SRC, DIRECT, true, false, true>(wb, args...);
 }
 
-hipError_t launch_dd_kspace(const Dims& d, ks::Gate gate, int branches, const double* g, const double* g_hat, const double* G,
+hipError_t launch_dd_kspace(const Dims& d, ks::Gate gate, bool with_direct, int branches, const double* g, const double* g_hat, const double* G,
                             const double* G_hat, const double* A, const int32_t* nbr, cd calpha, double* dD,
                             hipStream_t stream) {
+    if (!gate.word && !with_direct) return hipSuccess;
     CorrTile t;
     if (!corr_tile(d, (branches & 1) != 0, (branches & 2) != 0, &t)) return hipErrorInvalidValue;
     const CorrArgs raw{ks::array_blocks(g, d, 1), ks::array_blocks(G, d, d.gs), 0, (int)d.ne, false};
     if (gate.word) {
         CorrArgs a = raw;
-        if (g_hat) a.y = ks::hat_blocks(g_hat, d, 0, d.ne);
+        if (G_hat && g_hat) a.y = ks::hat_blocks(g_hat, d, 0, d.ne);
         if (G_hat) a.x = ks::hat_blocks(G_hat, d, 0, d.ne);
         hipError_t e;
-        if (G_hat)
+        if (G_hat && g_hat)
             e = launch_dd<ks::kDirect, ks::kDirect, false>(branches, t.wb, d, gate, false, a, A, nbr, calpha, t, dD, stream);
-        else if (g_hat)
-            e = launch_dd<ks::kDirect, ks::kTrans, false>(branches, t.wb, d, gate, false, a, A, nbr, calpha, t, dD, stream);
+        else if (G_hat)
+            e = launch_dd<ks::kTrans, ks::kDirect, false>(branches, t.wb, d, gate, false, a, A, nbr, calpha, t, dD, stream);
         else
             e = launch_dd<ks::kTrans, ks::kTrans, false>(branches, t.wb, d, gate, false, a, A, nbr, calpha, t, dD, stream);
         if (e == hipSuccess) e = launch_inverse((int)d.nkz, gate, 0, d.nw * d.na * d.nb, 9, 9, calpha, dD, stream);
         if (e != hipSuccess) return e;
     }
+    if (!with_direct) return hipSuccess;
     return launch_dd<ks::kDirect, ks::kDirect, true>(branches, t.wb, d, gate, false, raw, A, nbr, calpha, t, dD, stream);
 }
 

@@ -67,17 +67,17 @@ hipError_t launch_pi_kspace(const Dims& d, const double* Gs, const double* Go, c
 // of g = dL/dSigma and G (launch_transform), or NULL: every workgroup transforms what
 // it loads (the same sums, bit for bit).
 // dG from the in-edges of every atom; the one-table form passes Dm = Dp
-hipError_t launch_dg_kspace(const Dims& d, ks::Gate gate, const double* g, const double* g_hat, const double* Dp,
+hipError_t launch_dg_kspace(const Dims& d, ks::Gate gate, bool with_direct, const double* g, const double* g_hat, const double* Dp,
                             const double* Dm, const double* A, const int32_t* offset, const int32_t* edges,
                             const int32_t* order, cd calpha, double* dG, hipStream_t stream);
 // d gradH: one share per edge and part of the (momenta, energies), added by the caller;
 // by_energy: a share holds all momenta of 32 energies, else all energies of a momentum
 bool dh_kspace_supported(const Dims& d);
-hipError_t launch_dh_kspace(const Dims& d, ks::Gate gate, const double* g, const double* g_hat, const double* G,
+hipError_t launch_dh_kspace(const Dims& d, ks::Gate gate, bool with_direct, const double* g, const double* g_hat, const double* G,
                             const double* G_hat, const double* Dp, const double* Dm, const double* A, const int32_t* nbr,
                             cd alpha, bool by_energy, double* shares, hipStream_t stream);
 // dD; branches: 1 the terms with G at E - w (coefficients at +w), 2 those with G at E + w, 3 both
-hipError_t launch_dd_kspace(const Dims& d, ks::Gate gate, int branches, const double* g, const double* g_hat, const double* G,
+hipError_t launch_dd_kspace(const Dims& d, ks::Gate gate, bool with_direct, int branches, const double* g, const double* g_hat, const double* G,
                             const double* G_hat, const double* A, const int32_t* nbr, cd calpha, double* dD,
                             hipStream_t stream);
 
