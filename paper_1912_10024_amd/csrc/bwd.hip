@@ -554,6 +554,16 @@ bool bwd_supported(const Dims& d) {
 }
 
 static bool bwd_small(const Dims& d) { return d.nkz == 1 || d.nkz * d.ne * d.na <= kDirectBlocks; }
+// Direct sums on the matrix cores where they have an instance.  dG and d gradH: 2.2 against 3.5 ms
+// with dD (13 energies of 5 atoms), 69 against 268 ms (128 energies of 512).  dD: its matrix-core
+// kernel has a workgroup per atom that takes 12.6 us per source point, the other one per (edge, q)
+// that takes about 0.53 ms for few energies: by their rounds on 256 compute units.
+static bool bwd_direct_mfma(const Dims& d, bool signed_form) { return !signed_form && bwd_mfma_specialised(d); }
+static bool dd_direct_mfma(const Dims& d) {
+    const int64_t cus = 256, rounds = (d.na + cus - 1) / cus, other = (d.na * d.nb * d.nkz + cus - 1) / cus;
+    return pse_mfma_specialised(d) && (!bwd_small(d) || d.nkz * d.ne * rounds < 42 * other);
+}
+
 // the kernels of kspace.h: every gradient from the transforms of g and G (room for
 // them, or for that of g, permitting), or as the sum over the momenta stands
 static hipError_t launch_bwd_kspace(const Dims& d, const double* G, const double* Dp, const double* Dm, const double* A,
@@ -570,6 +580,7 @@ static hipError_t launch_bwd_kspace(const Dims& d, const double* G, const double
     // the arrays under a gradient's sum ask for it: g and D for dG, G too for d gradH, g and G for dD
     const bool small = bwd_small(d);
     auto gate = [&](int mask) { return ks::Gate{small ? nullptr : word, mask | ks::kSpreadSigma}; };
+    const bool mfma = bwd_direct_mfma(d, signed_form), dd_mfma = dd_direct_mfma(d);
     hipError_t e = hipSuccess;
     if (gate(0).word) {
         // Room for one transform: that of g if dG is wanted, whose array then holds that of G until
@@ -599,16 +610,19 @@ static hipError_t launch_bwd_kspace(const Dims& d, const double* G, const double
     double* shares = dA ? reinterpret_cast<double*>(ws + bwd_csr_bytes(d)) : nullptr;
     const ks::Gate dg_gate = gate(ks::kSpreadD), dh_gate = gate(ks::kSpreadD | ks::kSpreadG), dd_gate = gate(ks::kSpreadG);
     if (dA)
-        e = launch_dh_kspace(d, dh_gate, true, gS, g_hat, G, G_hat, Dp, Dm, A, nbr, alpha, bwd_by_energy(d, signed_form), shares,
+        e = launch_dh_kspace(d, dh_gate, !mfma, gS, g_hat, G, G_hat, Dp, Dm, A, nbr, alpha, bwd_by_energy(d, signed_form), shares,
                              stream);
     for (int branch = 1; branch <= 2; ++branch) {
         double* dD = branch == 1 ? dDp : dDm;
         if (!dD || e != hipSuccess) continue;
         const int branches = signed_form ? branch : 3;
-        e = launch_dd_kspace(d, dd_gate, true, branches, gS, g_hat, G, G_hat, A, nbr, calpha, dD, stream);
+        e = launch_dd_kspace(d, dd_gate, !dd_mfma, branches, gS, g_hat, G, G_hat, A, nbr, calpha, dD, stream);
+        if (e == hipSuccess && dd_mfma) e = launch_dd_mfma(d, dd_gate, branches, gS, G, A, nbr, calpha, dD, stream);
     }
     if (dG && e == hipSuccess)
-        e = launch_dg_kspace(d, dg_gate, true, gS, g_hat, Dp, Dm, A, offset, edges, order, calpha, dG, stream);
+        e = launch_dg_kspace(d, dg_gate, !mfma, gS, g_hat, Dp, Dm, A, offset, edges, order, calpha, dG, stream);
+    if (mfma && (dG || dA) && e == hipSuccess)
+        e = launch_bwd_mfma(d, dg_gate, dh_gate, G, Dp, A, gS, calpha, offset, edges, order, dG, shares, stream);
     if (dA && e == hipSuccess) {
         const int64_t n = d.na * d.nb * 3 * nn;
         hipLaunchKernelGGL(bwd_dh_reduce_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 65536)), dim3(256), 0, stream,
@@ -649,7 +663,7 @@ hipError_t launch_bwd(const Dims& d, const double* G, const double* Dp, const do
     int32_t* cursor = offset + d.na + 1;
     int32_t* edges = cursor + d.na;
     int32_t* order = edges + d.na * d.nb;
-    if (dG || (dA && !kspace)) {
+    if (dG || (dA && (!kspace || bwd_direct_mfma(d, signed_form)))) {
         if (d.na <= kSmallAtoms && d.na * d.nb <= kSmallEdges) {
             hipLaunchKernelGGL(rcsr_small_kernel, dim3(1), dim3(1024), 0, stream, (int)d.na, (int)d.nb, nbr, offset, edges, order);
         } else {

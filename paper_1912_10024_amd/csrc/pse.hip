@@ -119,13 +119,24 @@ __device__ __forceinline__ void pse_sum_row_tile(const Dims& d, const double* re
     }
 }
 
-template <int N, int NK, int NW, int NB>
+// MODE = 0: Pi (Eq. 4) with Gs, Go as documented above.
+// MODE != 0: the D part of the adjoint of Eq. 3 for dL/dSigma = g,
+//   dD[q, w-1, a, n][i][j] = conj(alpha) sum_{k', E'} sum_{s in S} [0 <= E' + s w < NE]
+//                            sum_{r,c} conj((A_i G[k', E', b] A_j^H)[r][c]) g[k'+q, E'+s w, a][r][c],
+// which is the same contraction with Gs := g (no slot axis), the energy
+// branches of S summed into each A row, and T_ij = A_j . G^H . A_i^H (the Go
+// block is staged conjugate-transposed); beta = conj(alpha).  MODE is the set
+// S: bit 0 the branch s = +1 (g at E' + w: the terms whose G sits at E - w,
+// i.e. the coefficients at +w), bit 1 the branch s = -1 (coefficients at -w);
+// the one-table form of Eq. 3 takes both.
+template <int N, int NK, int NW, int NB, int MODE>
 __global__ __launch_bounds__(64 * (8 + NB)) void pse_mfma_kernel(
     Dims d, const double* __restrict__ Gs, const double* __restrict__ Go, const double* __restrict__ Ag,
     const int32_t* __restrict__ nbr, cd beta, ks::Gate gate, double* __restrict__ Pi) {
     if (ks::shut<true>(gate)) return;  // behind the check of the momenta
     using C = PseCfg<N, NK, NW, NB>;
     static_assert(C::THREADS == 64 * (8 + NB), "launch bounds");
+    constexpr bool ADJ = MODE != 0, LO = ADJ && (MODE & 2) != 0, UP = !ADJ || (MODE & 1) != 0;
     constexpr int NN = C::NN;
     extern __shared__ __align__(16) double smem[];
     double* sA = smem;           // [NB][3][N][N] complex
@@ -140,6 +151,8 @@ __global__ __launch_bounds__(64 * (8 + NB)) void pse_mfma_kernel(
     const int64_t slot = 2 * d.gs * NN;   // doubles between atoms at one (k, E)
     const int64_t e_step = slot * NA;      // doubles between energies
     const int64_t k_step = e_step * NE;    // doubles between momenta
+    // the shifted operand: Gs (laid out like G) or, for the adjoint, g (one block per atom)
+    const int64_t rs_slot = ADJ ? 2 * NN : slot, rs_e = rs_slot * NA, rs_k = rs_e * NE;
     const int nsrc = NK * NE;
 
     for (int x = tid; x < NB * 3 * NN; x += C::THREADS) {
@@ -178,7 +191,10 @@ __global__ __launch_bounds__(64 * (8 + NB)) void pse_mfma_kernel(
             for (int u = 0; u < C::GO_PER_LANE; ++u) {
                 const int x = lane + 64 * u;
                 if (x < NN) {
-                    *reinterpret_cast<double2*>(myGo + 2 * x) = make_double2(gv[u].re, gv[u].im);
+                    if constexpr (ADJ)   // G^H: element (r, c) of G goes to (c, r), conjugated
+                        *reinterpret_cast<double2*>(myGo + 2 * ((x % N) * N + x / N)) = make_double2(gv[u].re, -gv[u].im);
+                    else
+                        *reinterpret_cast<double2*>(myGo + 2 * x) = make_double2(gv[u].re, gv[u].im);
                 }
             }
             if (src + 1 < nsrc) load_go(src + 1);
@@ -299,8 +315,10 @@ __global__ __launch_bounds__(64 * (8 + NB)) void pse_mfma_kernel(
 #pragma unroll
         for (int s = 0; s < C::SL; ++s) acc[s] = pse_f64x4{0.0, 0.0, 0.0, 0.0};
 
-        // A rows of a source point: the wave's first k-step and the lane's K index folded in
+        // A rows of a source point: the wave's first k-step and the lane's K index folded
+        // in; the adjoint adds the row of the lower energy branch (ap2)
         const double* ap[C::ML];
+        const double* ap2[C::ML];
         auto a_rows = [&](int src) {
             const int E = src / NK, k = src % NK;
 #pragma unroll
@@ -309,11 +327,22 @@ __global__ __launch_bounds__(64 * (8 + NB)) void pse_mfma_kernel(
                 const int w = r % NW + 1, es = E + w;
                 const bool ok = r < C::MROWS && es < NE;
                 const int kq = (k + r / NW) % NK;
-                const double* base = Gs + kq * k_step + slot * a;
-                ap[ml] = (ok ? base + (int64_t)es * e_step : pse_zero_block) + 4 * kg + kk;
+                const double* base = Gs + kq * rs_k + rs_slot * a;
+                ap[ml] = (ok ? base + (int64_t)es * rs_e : pse_zero_block) + 4 * kg + kk;
+                if constexpr (LO) {
+                    const bool ok2 = r < C::MROWS && E - w >= 0;
+                    ap2[ml] = (ok2 ? base + (int64_t)(E - w) * rs_e : pse_zero_block) + 4 * kg + kk;
+                }
             }
         };
-        auto a_load = [&](int ml, int off) { return ap[ml][off]; };
+        auto a_load = [&](int ml, int off) {
+            if constexpr (UP && LO)
+                return ap[ml][off] + ap2[ml][off];
+            else if constexpr (LO)
+                return ap2[ml][off];
+            else
+                return ap[ml][off];
+        };
         double an[C::ML];
         a_rows(0);
 #pragma unroll
@@ -452,11 +481,11 @@ bool pse_mfma_specialised(const Dims& d) {
     return d.norb == 10 && d.nkz == 7 && d.nqz == 7 && d.nw == 10 && (d.nb == 4 || d.nb == 3) && d.ne < (1 << 28);
 }
 
-template <int NB>
+template <int NB, int MODE = 0>
 static hipError_t launch_pse_mfma(const Dims& d, const double* Rs, const double* Go, const double* A,
                                   const int32_t* nbr, cd beta, ks::Gate gate, double* out, hipStream_t stream) {
     using C = PseCfg<10, 7, 10, NB>;
-    auto kern = pse_mfma_kernel<10, 7, 10, NB>;
+    auto kern = pse_mfma_kernel<10, 7, 10, NB, MODE>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)C::LDS_BYTES);
     if (e != hipSuccess) return e;
@@ -483,6 +512,23 @@ hipError_t launch_pse(const Dims& d, const double* Gs, const double* Go, const d
         hipLaunchKernelGGL(pse_generic_kernel, dim3((unsigned)std::min(step, edges - first)), dim3(kPseThreads), lds, stream, d,
                            Gs, Go, A, nbr, beta, first, Pi);
     return hipGetLastError();
+}
+
+template <int NB>
+static hipError_t launch_dd_mode(int branches, const Dims& d, const double* G, const double* A, const int32_t* nbr, const double* gS,
+                                 cd calpha, ks::Gate gate, double* dD, hipStream_t stream) {
+    switch (branches) {
+        case 1: return launch_pse_mfma<NB, 1>(d, gS, G, A, nbr, calpha, gate, dD, stream);
+        case 2: return launch_pse_mfma<NB, 2>(d, gS, G, A, nbr, calpha, gate, dD, stream);
+        case 3: return launch_pse_mfma<NB, 3>(d, gS, G, A, nbr, calpha, gate, dD, stream);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_dd_mfma(const Dims& d, ks::Gate gate, int branches, const double* g, const double* G, const double* A,
+                          const int32_t* nbr, cd calpha, double* dD, hipStream_t stream) {
+    return d.nb == 4 ? launch_dd_mode<4>(branches, d, G, A, nbr, g, calpha, gate, dD, stream)
+                     : launch_dd_mode<3>(branches, d, G, A, nbr, g, calpha, gate, dD, stream);
 }
 
 }  // namespace sse

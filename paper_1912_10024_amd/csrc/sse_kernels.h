@@ -81,6 +81,15 @@ hipError_t launch_dd_kspace(const Dims& d, ks::Gate gate, bool with_direct, int 
                             const double* G_hat, const double* A, const int32_t* nbr, cd calpha, double* dD,
                             hipStream_t stream);
 
+// the direct sums of the adjoint on the matrix cores: dG and the d gradH shares of the one-table
+// form (one per 32 energies), each behind its own check, and dD
+bool bwd_mfma_specialised(const Dims& d);
+hipError_t launch_bwd_mfma(const Dims& d, ks::Gate gate, ks::Gate gate_dh, const double* G, const double* D, const double* A,
+                           const double* gS, cd calpha, const int32_t* offset, const int32_t* edges, const int32_t* order,
+                           double* dG, double* shares, hipStream_t stream);
+hipError_t launch_dd_mfma(const Dims& d, ks::Gate gate, int branches, const double* g, const double* G, const double* A,
+                          const int32_t* nbr, cd calpha, double* dD, hipStream_t stream);
+
 // matrix-core forward (fp64 or fp32 operands; the split 16-bit forms go to
 // launch_fwd_h16) for the shapes it is
 // instantiated for; flags selects the energy branches (kBranchMinus,

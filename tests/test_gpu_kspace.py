@@ -363,7 +363,8 @@ def test_more_workgroups_than_one_launch_takes_in_half_precision():
         assert float(err) <= 1e-5, (a, float(err))   # fp16x2 carries about 22 bits; unwritten is NaN
 
 
-@pytest.mark.parametrize("dims", [(4, 32, 3, 8, 2, 6), (3, 16, 2, 16, 4, 4), (1, 200, 4, 7, 3, 5), (7, 13, 10, 5, 4, 10)],
+@pytest.mark.parametrize("dims", [(4, 32, 3, 8, 2, 6), (3, 16, 2, 16, 4, 4), (1, 200, 4, 7, 3, 5), (7, 13, 10, 5, 4, 10),
+                                  (7, 4, 10, 36, 4, 10)],
                          ids=lambda v: "x".join(map(str, v)))
 def test_gradients_of_a_thousand_blocks_keep_exact_sums(dims):
     """At most 1024 blocks: integer-valued inputs give integer gradients exactly, for one
