@@ -84,13 +84,28 @@ def _fast_workspace(cd, op: int, device, least: int = 1 << 26):
     out = ctypes.c_size_t(0)
     _raise(_lib.load().sse_fast_workspace_bytes(ctypes.byref(cd), op, ctypes.byref(out)), "sse_fast_workspace_bytes")
     nbytes = int(out.value)
-    least = min(least, nbytes)
+    return _empty_or_less(nbytes, min(least, nbytes), device)
+
+
+def _empty_or_less(nbytes: int, least: int, device):
+    """nbytes of device memory, or as much less (by halves) as the device has room for, or
+    None below `least` bytes."""
     while nbytes > 0 and nbytes >= least:
         try:
             return torch.empty(nbytes, dtype=torch.uint8, device=device)
         except torch.OutOfMemoryError:
             nbytes //= 2
     return None
+
+
+def _forward_workspace(d: Dims, precision: str, device) -> torch.Tensor:
+    """The workspace of a forward call: with less than sse_workspace_bytes it transforms G in
+    slabs of energies that fit, down to the 256 bytes that it requires."""
+    out = ctypes.c_size_t(0)
+    _raise(_lib.load().sse_workspace_bytes(ctypes.byref(_lib.SSEDims.of(d)), PRECISIONS[precision], 0, ctypes.byref(out)),
+           "sse_workspace_bytes")
+    ws = _empty_or_less(int(out.value), 1 << 20, device) if out.value > 256 else None
+    return ws if ws is not None else torch.empty(256, dtype=torch.uint8, device=device)
 
 
 def effective_flops(d: Dims) -> float:
@@ -199,10 +214,7 @@ def _forward(G, D, Dm, dH, dHba, nbr, alpha, precision, out, ws) -> torch.Tensor
         if tuple(out.shape) != d.sigma_shape:
             raise ValueError(f"out must be {d.sigma_shape}")
     if ws is None:
-        try:
-            ws = workspace(d, precision, device=G.device)
-        except torch.OutOfMemoryError:  # the least a call takes: slower, the same results
-            ws = torch.empty(256, dtype=torch.uint8, device=G.device)
+        ws = _forward_workspace(d, precision, G.device)
     lib = _lib.load()
     cd = _lib.SSEDims.of(d)
     a = complex(alpha)

@@ -43,3 +43,29 @@ def test_pi_asks_for_a_workspace_wherever_its_one_window_fits(norb, nw):
     the LDS still run in the transform."""
     d = Dims(nkz=2, ne=130, nqz=2, nw=nw, na=5, nb=2, norb=norb, g_slots=1)
     assert _fast(d, 3) >= 16 * d.nkz * d.na * norb ** 2 * (2 * d.ne - 1)
+
+
+@pytest.mark.parametrize("room", [1 << 40, 3 << 30, 100 << 20, 1000])
+def test_a_forward_call_takes_the_room_there_is(monkeypatch, room):
+    """Out of memory, the forward asks for half as much until it fits instead of falling to the
+    least at once."""
+    import torch
+
+    from paper_1912_10024_amd import sse
+    d = Dims(nkz=7, ne=256, nqz=7, nw=10, na=1024, nb=4, norb=10, g_slots=1)
+    real, asked = torch.empty, []
+
+    def empty(n, **kw):
+        asked.append(n)
+        if n > room:
+            raise torch.OutOfMemoryError("no room")
+        return real(min(n, 256), dtype=torch.uint8)
+
+    monkeypatch.setattr(torch, "empty", empty)
+    sse._forward_workspace(d, "fp64", "cpu")
+    want = _bytes(d, 0)
+    if room < 1 << 20:
+        assert asked[-1] == 256
+    else:
+        assert asked[-1] <= room and (asked[-1] == want or 2 * asked[-1] > room // 2)
+        assert asked[-1] > 256
