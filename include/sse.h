@@ -44,6 +44,18 @@
  *   stream).  Outputs are overwritten, never accumulated.  Inputs are only
  *   read.  Calls that use distinct outputs and workspaces may run
  *   concurrently.
+ * - The sums over the momenta in fp64 (SSE_FP64, the gradients, Pi) are cyclic
+ *   convolutions or correlations, taken in their discrete Fourier transform, which
+ *   rounds each value relative to the largest of its nkz values.  It is used
+ *   where one of the arrays under the sum (D and G for Sigma; Gs and Go; dSigma
+ *   and D for dG; dSigma and G for dD; all three for ddH) has finite blocks whose largest
+ *   entries, over the momenta, are within a factor of 32 of one another at every
+ *   energy (or frequency), which bounds that value's error by about that factor times
+ *   that of its own terms.  Otherwise, for problems of at most 1024 blocks
+ *   (nkz * ne * na) and for nkz = 1 the terms are summed as they stand: up to nkz times
+ *   slower, every element rounded relative to its own terms, exact for small
+ *   integers, and zero where no term is left.  The arrays decide on the device, the
+ *   same for every workspace; nothing is copied to the host.
  * - Status codes (no exceptions cross this boundary; on an argument error --
  *   every code but SSE_ERR_HIP -- no kernel has been launched and no output has
  *   been touched; an SSE_ERR_HIP from a call that launches several kernels may
@@ -68,7 +80,7 @@
 extern "C" {
 #endif
 
-#define SSE_ABI_VERSION 6
+#define SSE_ABI_VERSION 7
 
 typedef struct sse_dims {
     int64_t nkz;     /* electron momentum points kz (periodic grid)              */
@@ -82,7 +94,7 @@ typedef struct sse_dims {
 } sse_dims;
 
 enum sse_precision {
-    SSE_FP64 = 0,    /* fp64 products on matrix cores, fp64 reduction                  */
+    SSE_FP64 = 0,    /* fp64 throughout                                                */
     SSE_FP32 = 1,    /* operands of the dense products rounded to fp32 after the fp64
                         gather, fp32 matrix cores, each 36-term K chunk accumulated in
                         fp32 then added in fp64; fp64 (qz, w, +/-) reduction            */
@@ -175,8 +187,10 @@ int sse_effective_flops(const sse_dims* dims, double* f_eff);
  * SSE_ERR_PRECISION).  SSE_FP64 sums over the momenta in their discrete Fourier
  * transform on every shape, except for problems of at most 1024 output blocks
  * (nkz * ne * na) and nkz = 1, which sum the terms as they stand (integer-valued
- * inputs then give exact integers), and for shapes whose window of 2 nw energies
- * does not fit the LDS, which take a slow direct kernel.
+ * inputs then give exact integers), for arrays that both differ in size over the
+ * momenta (above), and for shapes whose window of 2 nw energies does not fit the LDS,
+ * which take a slow direct kernel.  The workspace's first bytes, aligned to 16, hold what
+ * the check of the arrays found.
  */
 int sse_forward(const sse_dims* dims, const double* G, const double* D, const double* dH,
                 const int32_t* nbr, double alpha_re, double alpha_im, int precision,
@@ -245,8 +259,9 @@ int sse_forward_ex(const sse_dims* dims, const double* G, const double* Dp, cons
  * of 32 energies) on the shape (norb = 10, nkz = nqz = 7, nw = 10), S = nkz (one
  * per momentum) otherwise and in sse_backward_signed.  Room beyond these holds the
  * momentum transforms of dSigma and of G (16 * na * nkz * ne * norb^2 bytes each),
- * whichever fit (sse_fast_workspace_bytes); without them every kernel transforms what it
- * reads, slower and with the same results bit for bit.  On the shapes (norb = 10,
+ * whichever fit (sse_fast_workspace_bytes); dG's array, written last, holds that of G where the
+ * workspace has no room for both.  Without either a kernel transforms what it reads, slower and
+ * with the same results bit for bit.  Outputs must not overlap inputs or one another.  On the shapes (norb = 10,
  * nkz = nqz = 7, nw = 10, nb = 4 or 3) a call of sse_backward that wants dD requires
  * room for the transform of dSigma.  A smaller workspace than this call requires is
  * refused with SSE_ERR_WORKSPACE.  An entry of nbr outside [0, na) has no
@@ -340,7 +355,8 @@ int sse_combine_d(const sse_dims* dims, const double* Dfull, const int32_t* nbr,
  * phonon frequency w sits on the electron energy grid, w = 1..Nw; the momentum
  * grids coincide (Nqz = Nkz) and kz + qz wraps around.
  * Output Pi [nqz][nw][na][nb][3][3] complex (the layout of D), fully
- * overwritten.  fp64 throughout; no workspace (sse_phonon_forward_ws with one is faster).  Gs and Go may alias.
+ * overwritten (until then it may hold marks of the edges that are summed as they
+ * stand).  fp64 throughout; no workspace (sse_phonon_forward_ws with one is faster).  Gs and Go may alias.
  * Errors as for sse_forward (SSE_ERR_DIMS also when no kernel covers the
  * shape: norb^2 > 640 or nqz * nw > 512 outside the matrix-core shape).
  */
@@ -351,7 +367,8 @@ int sse_phonon_forward(const sse_dims* dims, const double* Gs, const double* Go,
  * sse_phonon_forward with a workspace (NULL: none) of any size, used for the
  * momentum transforms of Gs and Go: all of them with
  * sse_fast_workspace_bytes(dims, 3) bytes, slabs of energies with less (whose sums
- * are added in order: equal to the other sizes' up to rounding).
+ * are added in order: equal to the other sizes' up to rounding).  Its first 16 to 31 bytes
+ * hold what the check of the arrays found.
  */
 int sse_phonon_forward_ws(const sse_dims* dims, const double* Gs, const double* Go, const double* dH,
                           const int32_t* nbr, double beta_re, double beta_im, double* Pi, void* workspace,

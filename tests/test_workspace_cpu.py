@@ -69,3 +69,11 @@ def test_a_forward_call_takes_the_room_there_is(monkeypatch, room):
     else:
         assert asked[-1] <= room and (asked[-1] == want or 2 * asked[-1] > room // 2)
         assert asked[-1] > 256
+
+
+def test_the_interface_of_the_workspaces_has_its_own_version():
+    """sse_fast_workspace_bytes and sse_phonon_forward_ws, and the size that
+    sse_workspace_bytes gives for the forward, came after version 6."""
+    lib = _lib.load()
+    assert {"sse_fast_workspace_bytes", "sse_phonon_forward_ws"} <= set(_lib.EXPORTS)
+    assert lib.sse_abi_version() >= 7
