@@ -168,10 +168,11 @@ def kernel_source_hash(sources) -> str:
     return h.hexdigest()
 
 
-FWD_SOURCES = ("fwd_kspace.hip", "kspace.hip", "kspace.h", "sse_common.h")
+FWD_SOURCES = ("fwd_kspace.hip", "fwd_kspace.h", "kspace.hip", "kspace.h", "kspace_plan.h", "sse_common.h")
 H16_SOURCES = ("fwd_h16.hip", "fwd_common.h", "sse_common.h")
-PSE_SOURCES = ("pse_kspace.hip", "kspace.h", "sse_common.h")
-BWD_SOURCES = ("bwd_kspace.hip", "fwd_kspace.hip", "kspace.h", "sse_common.h")
+PSE_SOURCES = ("pse_kspace.hip", "corr_kspace.h", "kspace.hip", "kspace.h", "kspace_plan.h", "sse_common.h")
+BWD_SOURCES = ("bwd_kspace.hip", "bwd_dg_kspace.hip", "bwd_dd_kspace.hip", "fwd_kspace.h", "corr_kspace.h", "kspace.hip", "kspace.h",
+               "kspace_plan.h", "sse_common.h")
 
 
 def recorded_traffic(record, sources):
@@ -462,10 +463,13 @@ def main():
         "kernel_ms": round(res[head]["kernel_ms"], 3),
         "f_eff": f_eff,
         "roofline": res[head]["roofline"],
-        "executed_flops_per_launch": flops.pd_executed_flops(d),
+        # what the head form executes: fp64 its useful flops in the transform (padding and the
+        # products in the overlap of tiles not counted), the others the P.D form with its padding
+        "executed_flops_per_launch": flops.kspace_flops(d) if head == "fp64" else flops.pd_executed_flops(d),
         "input_gen_s": round(t_gen, 2),
         "forms": {f: {"value": round(r["value"], 3), "kernel_ms": round(r["kernel_ms"], 3),
-                      "kernel_ms_all": r["kernel_ms_all"], "mfma_frac": r["roofline"]["frac"],
+                      "kernel_ms_all": r["kernel_ms_all"],
+                      ("alu_frac" if r["roofline"]["bound"] == "alu" else "mfma_frac"): r["roofline"]["frac"],
                       "speedup_vs_" + head: round(res[head]["kernel_ms"] / r["kernel_ms"], 3)}
                   for f, r in res.items()},
     }

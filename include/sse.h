@@ -50,12 +50,13 @@
  *   where one of the arrays under the sum (D and G for Sigma; Gs and Go; dSigma
  *   and D for dG; dSigma and G for dD; all three for ddH) has finite blocks whose largest
  *   entries, over the momenta, are within a factor of 32 of one another at every
- *   energy (or frequency), which bounds that value's error by about that factor times
- *   that of its own terms.  Otherwise, for problems of at most 1024 blocks
- *   (nkz * ne * na) and for nkz = 1 the terms are summed as they stand: up to nkz times
- *   slower, every element rounded relative to its own terms, exact for small
- *   integers, and zero where no term is left.  The arrays decide on the device, the
- *   same for every workspace; nothing is copied to the host.
+ *   energy (or frequency): an element's error is then at most 32 nkz times, and
+ *   for random blocks about, that of the sum of its own terms.  Otherwise, for
+ *   problems of at most 1024 blocks (nkz * ne * na) and for nkz = 1 the terms are
+ *   summed as they stand: up to nkz times slower, every element rounded relative to
+ *   its own terms, exact for small integers, and zero where no term is left.  The
+ *   arrays decide on the device, the same for every workspace; nothing is copied to
+ *   the host.
  * - Status codes (no exceptions cross this boundary; on an argument error --
  *   every code but SSE_ERR_HIP -- no kernel has been launched and no output has
  *   been touched; an SSE_ERR_HIP from a call that launches several kernels may

@@ -1,6 +1,6 @@
 // Adjoint of the scattering self-energy (fp64): the workspace and the dispatch, and the
 // kernels for shapes whose window of 2 nw energies does not fit the LDS of those in
-// fwd_kspace.hip (dG), bwd_kspace.hip (d gradH) and pse_kspace.hip (dD).
+// bwd_dg_kspace.hip (dG), bwd_kspace.hip (d gradH) and bwd_dd_kspace.hip (dD).
 //
 // With g = dL/dSigma (PyTorch's complex-gradient convention) define, for an
 // edge (a, n) with neighbour b = nbr[a,n] and a source point (k', E'):

@@ -1,4 +1,6 @@
-// Matrix-core adjoint of the scattering self-energy (Eq. 3): dG and d gradH in fp64.
+// Matrix-core adjoint of the scattering self-energy (Eq. 3): dG and d gradH in fp64, summed over
+// the momenta as they stand.  It runs for small problems and behind the check of the momenta
+// (ks::Gate); other calls go through the transform (bwd_dg_kspace.hip, bwd_kspace.hip).
 //
 // With g = dL/dSigma (PyTorch's complex-gradient convention) and, for an edge
 // (a, n) with neighbour b = nbr[a,n] and A_i = grad_i H_{a,n},

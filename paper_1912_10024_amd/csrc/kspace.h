@@ -139,7 +139,7 @@ __device__ __forceinline__ bool shut(const Gate& g) {
 }
 // workgroups of a direct launch behind a gate: few, since they mostly find it shut, each
 // with several tiles if not
-constexpr unsigned kGatedGroups = 2048;
+constexpr unsigned kGatedGroups = 1024;
 
 // The blocks of one energy and atom at the nkz momenta, nn entries each, are of like size: the
 // largest part of the largest is at most kSpread times that of the smallest, and finite.

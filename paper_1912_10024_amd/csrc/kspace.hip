@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256) void spread_kernel(int nkz, ks::Gate only, int
 hipError_t launch_spread(int nkz, ks::Gate only, int64_t blocks, int64_t nn, int64_t bs, const double* p, const double* q, int bit,
                          int* word, hipStream_t stream) {
     const int L = ks::block_lanes(nn);
-    const int64_t groups = (blocks + 256 / L - 1) / (256 / L), most = only.word ? ks::kGatedGroups : 4 * ks::kGatedGroups;
+    const int64_t groups = (blocks + 256 / L - 1) / (256 / L), most = only.word ? 512 : 8192;
     hipLaunchKernelGGL(spread_kernel, dim3((unsigned)std::min(groups, most)), dim3(256), 0, stream, nkz, only, blocks, (int)nn, bs,
                        blocks * bs, L, p, q, bit, word);
     return hipGetLastError();
