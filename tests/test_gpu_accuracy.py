@@ -198,3 +198,34 @@ def test_zeros_by_momentum_selection_stay_zero():
     S = sse.forward(t["G"], t["D"], t["dH"], t["nbr"])
     for k in range(d.nkz):
         assert bool((S[k] != 0).any()) == (k == 3)
+
+
+def test_a_captured_call_decides_by_what_it_finds_at_replay():
+    """Sigma, Pi and the gradients in a graph: replayed on arrays of like size, on peaked
+    ones and on the first again, each against the eager calls."""
+    print("[gpu] captured calls", flush=True)
+    d = DIMS
+    sets = [_sets(d, low, G=1, Go=2, D=2, gS=1)[1] for low in (1.0, 1e-8, 0.25)]
+    t = {k: v.clone() for k, v in sets[0].items()}
+
+    def calls():
+        S = sse.forward(t["G"], t["D"], t["dH"], t["nbr"])
+        P = sse.phonon_forward(t["G"], t["Go"], t["dH"], t["nbr"], d.nqz, d.nw)
+        return (S, P) + sse.backward(t["G"], t["D"], t["dH"], t["nbr"], t["gS"])
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        calls()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = calls()
+    for i in (0, 1, 2, 1, 0):
+        for k, v in sets[i].items():
+            t[k].copy_(v)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [o.clone() for o in out]
+        for g, r in zip(got, calls()):
+            assert torch.equal(g, r), i
